@@ -24,7 +24,8 @@ HIPCC_FLAGS = [
 
 
 def sources():
-    return [os.path.join(CSRC, "gla_decode.hip")]
+    """Translation units of the library (compiled side by side)."""
+    return [os.path.join(CSRC, f) for f in ("gla_decode.hip", "tuned_256.hip", "tuned_512.hip", "tuned_128.hip", "wide.hip")]
 
 
 def needs_build() -> bool:
@@ -39,10 +40,20 @@ def needs_build() -> bool:
 def build(verbose: bool = True, extra_flags=()) -> str:
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     tmp = LIB + f".tmp{os.getpid()}"
-    cmd = [hipcc] + HIPCC_FLAGS + list(extra_flags) + ["-o", tmp] + sources()
-    if verbose:
-        print(" ".join(cmd), flush=True)
-    subprocess.check_call(cmd)
+    flags = HIPCC_FLAGS + list(extra_flags)
+    with tempfile.TemporaryDirectory() as objdir:
+        jobs, objs = [], []
+        for src in sources():
+            obj = os.path.join(objdir, os.path.basename(src) + ".o")
+            cmd = [hipcc] + [f for f in flags if f != "-shared"] + ["-c", "-o", obj, src]
+            if verbose:
+                print(" ".join(cmd), flush=True)
+            jobs.append((cmd, subprocess.Popen(cmd)))
+            objs.append(obj)
+        failed = [cmd for cmd, job in jobs if job.wait() != 0]
+        if failed:
+            raise subprocess.CalledProcessError(1, failed[0])
+        subprocess.check_call([hipcc, "--offload-arch=gfx950", "-fPIC", "-shared", "-o", tmp] + objs)
     os.replace(tmp, LIB)
     return LIB
 

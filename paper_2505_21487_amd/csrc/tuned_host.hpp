@@ -1,11 +1,10 @@
 // Host side of the tuned decode-attention path: shape check and plan, workspace
-// size, and the launches of the main and merge kernels.
+// size, and the choice of the launch function (tuned_launch.hpp).
 #pragma once
 
 #include <algorithm>
 
 #include "../../include/gla_decode.h"
-#include "tuned_combine_kernel.hpp"
 #include "tuned_main_kernel.hpp"
 
 namespace gla {
@@ -22,6 +21,7 @@ struct TunedPlan {
   int num_chunks;  // chunks of the tile list; the main-kernel grid is num_chunks * mb
   int chunk_tiles; // fixed tiles per chunk, 0: derived on the device
   size_t slot_floats;
+  bool wide;       // the eight-wave kernel (wide_main_kernel.hpp): wpg slabs per workgroup, ks waves per slab's output
   bool stream;     // fetch the cache with the streaming hint
 };
 
@@ -41,6 +41,30 @@ inline int device_cu_count() {
 inline bool aligned16(const void* ptr) { return ((uintptr_t)ptr & 15u) == 0; }
 
 constexpr int kMinChunkTiles = 4;
+
+// Does the eight-wave kernel (128 query rows per workgroup with 256 dims, 64 with 512) take this problem?  It
+// wins where the matrix pipe sets the pace and chunks are long; it starts a chunk and a sequence more slowly (twice
+// the tokens per tile, queries loaded by twice the waves), so short chunks stay with the four-wave kernel.
+// Measured, four waves -> eight waves, in us per call:
+//   512 dims, 128 rows per group, chunks of 110 tiles (of 64 tokens), pages of 64 / 8 / 1: 393 -> 356 / 467 -> 357 / 471 -> 371;
+//     chunks of 8 tiles 43.5 -> 42.1, of 3 tiles 32.2 -> 40.4
+//   256 dims, 256 rows per group, chunks of 128 tiles inside one sequence each, pages of 64 / 1: 328 -> 305 / 369 -> 315; chunks of
+//     55 tiles over 1.75 sequences each 183 -> 196, of 4 tiles 33.6 -> 37.4; with 128 rows per group (no second row
+//     block to share the tiles with, the kernel is half bound by HBM) 117 -> 123
+// Lengths are known on the device only: the host goes by the table's row length.
+inline bool wide_pays(const gla_decode_params* p, int rows_group) {
+  const int64_t tiles_seq = ((int64_t)p->max_pages_per_seq * p->page_size + 63) / 64;
+  if (p->d_v == 512 && rows_group > 32) {
+    const int64_t chunks = std::max<int64_t>(1, device_cu_count() / ((rows_group + 63) / 64));
+    return (int64_t)p->batch * p->num_groups * tiles_seq >= 12 * chunks;
+  }
+  if (p->d_v == 256 && rows_group > 128) {
+    const int64_t chunks = std::max<int64_t>(1, device_cu_count() / ((rows_group + 127) / 128));
+    const int64_t units = (int64_t)p->batch * p->num_groups;
+    return units * tiles_seq >= 64 * chunks && (2 * units <= chunks || p->page_size < 16);
+  }
+  return false;
+}
 
 inline bool tuned_plan(const gla_decode_params* p, int is_gta, TunedPlan* plan) {
   const int ps = p->page_size;
@@ -66,9 +90,10 @@ inline bool tuned_plan(const gla_decode_params* p, int is_gta, TunedPlan* plan) 
   // as four waves allow (they share one RoPE-key tile)
   // A latent of 512 dims needs two waves per row slab: 32 rows x 512 fp32
   // output accumulators alone would fill a wave's accumulation registers.
-  const int ks = p->d_v > 256 ? 2 : 1;
-  const int wpg = rows_group <= 32 ? 1 : ((rows_group <= 64 || ks == 2) ? 2 : 4);
-  int ng = 4 / (wpg * ks);
+  plan->wide = wide_pays(p, rows_group);
+  const int ks = plan->wide ? p->d_v / 128 : p->d_v > 256 ? 2 : 1;
+  const int wpg = plan->wide ? 8 / ks : rows_group <= 32 ? 1 : ((rows_group <= 64 || ks == 2) ? 2 : 4);
+  int ng = plan->wide ? 1 : 4 / (wpg * ks);
   while (ng > 1 && (p->num_groups % ng || 4 * (ng * 32 * p->d_v * 2 + 32 * 128) > 160 * 1024)) ng >>= 1;
   plan->dv = p->d_v;
   plan->dn = p->d_nope;
@@ -80,12 +105,12 @@ inline bool tuned_plan(const gla_decode_params* p, int is_gta, TunedPlan* plan) 
   plan->units = p->batch * (p->num_groups / ng) * plan->mb;
   // (small pages: page-id windows in LDS where tiles and mailboxes leave room for them, else in registers)
   const bool lds_windows = lane && tuned_windows_fit(p->d_v, ng, wpg, ks);
-  const int tok = kTok, stages = tuned_stages(p->d_v, ng, wpg, ks, lds_windows);
+  const int tok = plan->wide ? 2 * kTok : kTok, stages = tuned_stages(p->d_v, ng, wpg, ks, lds_windows);
   // co-resident workgroups per CU: one wave per SIMD, 160 KiB of LDS
   const int smem = stages * (ng * tok * p->d_v * 2 + tok * 128) + (ks > 1 ? ng * wpg * ks * 4096 : 0) +
                    (lds_windows ? ng * wpg * ks * 2 * kPageWindow * 4 : 0);
-  if (smem > 160 * 1024) return false;
-  const int per_cu = std::max(1, std::min((160 * 1024) / smem, 4 / (ng * wpg * ks)));
+  if (!plan->wide && smem > 160 * 1024) return false;
+  const int per_cu = plan->wide ? 1 : std::max(1, std::min((160 * 1024) / smem, 4 / (ng * wpg * ks)));
   plan->tok = tok;
   plan->stages = stages;
   // the tile list holds each (sequence, group block) once; every chunk of it is
@@ -102,7 +127,7 @@ inline bool tuned_plan(const gla_decode_params* p, int is_gta, TunedPlan* plan) 
     // (by the upper bound on the list length): a partial costs as much memory
     // traffic as three or four tiles, and every extra chunk is one more to merge
     const int64_t resident = std::max<int64_t>(1, (int64_t)device_cu_count() * per_cu / plan->mb);
-    const int64_t by_length = std::max<int64_t>(1, bound / kMinChunkTiles);
+    const int64_t by_length = std::max<int64_t>(1, bound * tok / (kMinChunkTiles * kTok));
     plan->num_chunks = (int)std::max<int64_t>(1, std::min<int64_t>(by_length, resident));
   }
   plan->slot_floats = (size_t)plan->rows * p->d_v + (size_t)32 * ng * wpg * ks;
@@ -128,75 +153,12 @@ inline size_t tuned_workspace(const gla_decode_params* p, int is_gta) {
   return tuned_slots_bytes(plan) + (size_t)plan.units * 2 * sizeof(int32_t);
 }
 
-template <int DV, int DN, int NG, int WPG, int KS, int TOK, bool STREAM>
-inline int launch_tuned_main(const DevParams& d, dim3 mgrid, dim3 mblock, hipStream_t st) {
-  constexpr int STAGES = tuned_stages(DV, NG, WPG, KS), STAGES_LANE = tuned_stages(DV, NG, WPG, KS, true);
-  constexpr bool kLaneFits = tuned_windows_fit(DV, NG, WPG, KS);
-  if (d.lg_page == 6) {
-    hipLaunchKernelGGL((tuned_main_kernel<DV, DN, 64, NG, WPG, KS, TOK, STAGES, 0, STREAM>), mgrid, mblock, 0, st, d);
-  } else if (d.lg_page >= 4) {
-    hipLaunchKernelGGL((tuned_main_kernel<DV, DN, 64, NG, WPG, KS, TOK, STAGES, 1, STREAM>), mgrid, mblock, 0, st, d);
-  } else {
-    if constexpr (kLaneFits)
-      hipLaunchKernelGGL((tuned_main_kernel<DV, DN, 64, NG, WPG, KS, TOK, STAGES_LANE, 2, STREAM>), mgrid, mblock, 0, st, d);
-    else  // (no LDS left for the page-id windows: kept in registers)
-      hipLaunchKernelGGL((tuned_main_kernel<DV, DN, 64, NG, WPG, KS, TOK, STAGES, 3, STREAM>), mgrid, mblock, 0, st, d);
-  }
-  return GLA_OK;
-}
-
-template <int DV, int DN, int NG, int WPG, int KS, int TOK>
-inline int launch_tuned_variant(const TunedPlan& plan, DevParams& d, hipStream_t st, hipEvent_t* ev) {
-  if (ev) (void)hipEventRecord(ev[0], st);
-  const dim3 mgrid(plan.num_chunks * plan.mb), mblock(64 * NG * WPG * KS);
-  // (plan.stream: the cache of this batch can be larger than the last-level cache: fetch it with the streaming hint)
-  const int lrc = plan.stream ? launch_tuned_main<DV, DN, NG, WPG, KS, TOK, true>(d, mgrid, mblock, st)
-                              : launch_tuned_main<DV, DN, NG, WPG, KS, TOK, false>(d, mgrid, mblock, st);
-  if (lrc != GLA_OK) return lrc;
-  if (hipGetLastError() != hipSuccess) return GLA_ERR_LAUNCH;
-  if (ev) (void)hipEventRecord(ev[1], st);
-  // waves per merge task from the expected number of chunks per unit
-  const int64_t span_est = (plan.num_chunks + std::max(1, plan.units / plan.mb) - 1) / std::max(1, plan.units / plan.mb) + 1;
-  const dim3 cgrid(plan.units, NG * WPG * (DV / 32));
-  if (span_est <= 2)
-    hipLaunchKernelGGL((tuned_combine_kernel<DV, NG, WPG, KS, TOK, 1, 1, 2>), cgrid, dim3(64), 0, st, d);
-  else if (span_est <= 6)  // (one wave with four chunks in flight: a fourth of the waves to launch, no merge through LDS)
-    hipLaunchKernelGGL((tuned_combine_kernel<DV, NG, WPG, KS, TOK, 1, 1, 4>), cgrid, dim3(64), 0, st, d);
-  else if (span_est <= 12)
-    hipLaunchKernelGGL((tuned_combine_kernel<DV, NG, WPG, KS, TOK, 4, 1, 2>), cgrid, dim3(256), 0, st, d);
-  else if (span_est <= 64)  // (a wave folds eight chunks per round trip: four waves do for fairly long lists)
-    hipLaunchKernelGGL((tuned_combine_kernel<DV, NG, WPG, KS, TOK, 4, 1, 8>), cgrid, dim3(256), 0, st, d);
-  else if ((int64_t)cgrid.x * cgrid.y * 4 > 4 * device_cu_count())
-    hipLaunchKernelGGL((tuned_combine_kernel<DV, NG, WPG, KS, TOK, 16, 1, 4>), cgrid, dim3(1024), 0, st, d);
-  else  // few tasks: each cut into quarters (see the kernel)
-    hipLaunchKernelGGL((tuned_combine_kernel<DV, NG, WPG, KS, TOK, 16, 4, 4>), dim3(cgrid.x, cgrid.y * 4), dim3(1024), 0, st, d);
-  if (hipGetLastError() != hipSuccess) return GLA_ERR_LAUNCH;
-  if (ev) (void)hipEventRecord(ev[2], st);
-  return GLA_OK;
-}
-
-template <int DV, int DN>
-inline int launch_tuned_shape(const TunedPlan& plan, DevParams& d, hipStream_t st, hipEvent_t* ev) {
-  if constexpr (DV > 256) {
-    switch (plan.ng * 100 + plan.wpg * 10 + plan.ks) {
-      case 112: return launch_tuned_variant<DV, DN, 1, 1, 2, kTok>(plan, d, st, ev);
-      case 122: return launch_tuned_variant<DV, DN, 1, 2, 2, kTok>(plan, d, st, ev);
-      default: return GLA_ERR_UNSUPPORTED_SHAPE;
-    }
-  } else {
-    switch (plan.ng * 100 + plan.wpg * 10 + plan.ks) {
-      case 111: return launch_tuned_variant<DV, DN, 1, 1, 1, kTok>(plan, d, st, ev);
-      case 121: return launch_tuned_variant<DV, DN, 1, 2, 1, kTok>(plan, d, st, ev);
-      case 141: return launch_tuned_variant<DV, DN, 1, 4, 1, kTok>(plan, d, st, ev);
-      case 211: return launch_tuned_variant<DV, DN, 2, 1, 1, kTok>(plan, d, st, ev);
-      case 221: return launch_tuned_variant<DV, DN, 2, 2, 1, kTok>(plan, d, st, ev);
-      case 411:
-        if constexpr (DV <= 128) return launch_tuned_variant<DV, DN, 4, 1, 1, kTok>(plan, d, st, ev);
-        else return GLA_ERR_UNSUPPORTED_SHAPE;
-      default: return GLA_ERR_UNSUPPORTED_SHAPE;
-    }
-  }
-}
+// Main and merge kernel of a plan, per state shape (tuned_256.hip, tuned_512.hip, tuned_128.hip) and of a plan
+// with `wide` set (wide.hip): translation units of their own, compiled side by side.
+int tuned_launch_256(const TunedPlan& plan, const DevParams& d, hipStream_t st, hipEvent_t* ev);
+int tuned_launch_512(const TunedPlan& plan, const DevParams& d, hipStream_t st, hipEvent_t* ev);
+int tuned_launch_128(const TunedPlan& plan, const DevParams& d, hipStream_t st, hipEvent_t* ev);
+int wide_launch(const TunedPlan& plan, const DevParams& d, hipStream_t st, hipEvent_t* ev);
 
 inline int tuned_launch(const gla_decode_params* p, int is_gta, DevParams& d, hipStream_t st,
                         hipEvent_t* ev) {
@@ -225,9 +187,10 @@ inline int tuned_launch(const gla_decode_params* p, int is_gta, DevParams& d, hi
     d.fd_units_full = make_fastdiv((uint32_t)(d.upb * d.tiles_full));
     d.fd_upb_mb = make_fastdiv((uint32_t)(d.upb * plan.mb));
   }
-  if (plan.dv == 256 && plan.dn == 256) return launch_tuned_shape<256, 256>(plan, d, st, ev);
-  if (plan.dv == 128 && plan.dn == 64) return launch_tuned_shape<128, 64>(plan, d, st, ev);
-  if (plan.dv == 512 && plan.dn == 512) return launch_tuned_shape<512, 512>(plan, d, st, ev);
+  if (plan.wide) return wide_launch(plan, d, st, ev);
+  if (plan.dv == 256 && plan.dn == 256) return tuned_launch_256(plan, d, st, ev);
+  if (plan.dv == 128 && plan.dn == 64) return tuned_launch_128(plan, d, st, ev);
+  if (plan.dv == 512 && plan.dn == 512) return tuned_launch_512(plan, d, st, ev);
   return GLA_ERR_UNSUPPORTED_SHAPE;
 }
 
