@@ -58,6 +58,9 @@ struct DevParams {
   float scale;
   // generic kernel: uniform split of every sequence's page range
   int32_t splits, pages_per_split;
+  // generic MFMA kernel: the split in tokens, divisors (page size, 16-byte chunks of a cache row)
+  int32_t split_tokens;
+  FastDiv fd_page, fd_cpr;
   int64_t stream_min_bytes; // second MFMA kernel: a batch with more cache bytes than this is fetched with the streaming hint
   int32_t flex_rb;          // flex kernel: blocks of 16 query rows per group
   int32_t* flex_rng;        // flex kernel: per (sequence, strand) the first chunk holding a piece of it (x 2 + its slot) and the last

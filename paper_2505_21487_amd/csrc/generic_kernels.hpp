@@ -122,6 +122,47 @@ __global__ __launch_bounds__(64) void generic_combine_kernel(DevParams p) {
   const int t = (row / p.h_q) % p.T;
   const int b = row / (p.h_q * p.T);
   const int64_t rows = (int64_t)p.B * p.T * p.h_q;
+  const int64_t base = b * p.out_s[0] + t * p.out_s[1] + h * p.out_s[2];
+  // Up to 64 ranges: lane s holds the log-sum-exp, then the weight of range s, and four consecutive dims per lane are
+  // summed with eight ranges in flight (bound by the latency of these loads; the loop below, for longer lists, goes
+  // through the ranges one by one).
+  if (p.splits <= 64 && p.d_v % 4 == 0) {
+    const float ls = lane < p.splits ? p.ws_lse[(int64_t)lane * rows + row] : -INFINITY;
+    float m = ls;
+#pragma unroll
+    for (int sh = 32; sh > 0; sh >>= 1) m = fmaxf(m, __shfl_xor(m, sh, 64));
+    const float e = ls != -INFINITY ? expf(ls - m) : 0.f;
+    const float z = wave_sum(e);
+    if (lane == 0) p.lse[row] = m == -INFINITY ? -INFINITY : m + logf(z);
+    const float w = z > 0.f ? e / z : 0.f;
+    for (int d0 = 0; d0 < p.d_v; d0 += 256) {  // (every lane stays in the loop: the weights are read across lanes)
+      const bool mine = d0 + 4 * lane < p.d_v;
+      const int d = mine ? d0 + 4 * lane : 0;
+      float acc[4] = {0.f, 0.f, 0.f, 0.f};
+      const float* src = p.ws_out + (int64_t)row * p.d_v + d;
+      for (int s = 0; s < p.splits; s += 8) {
+        float4 v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = *(const float4*)(src + (int64_t)min(s + u, p.splits - 1) * rows * p.d_v);
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+          // (a range without keys left zeros)
+          const float ws = s + u < p.splits ? __shfl(w, s + u, 64) : 0.f;
+          acc[0] += ws * v[u].x;
+          acc[1] += ws * v[u].y;
+          acc[2] += ws * v[u].z;
+          acc[3] += ws * v[u].w;
+        }
+      }
+      if (!mine) continue;
+#pragma unroll
+      for (int e2 = 0; e2 < 4; ++e2) {
+        if (p.out_fp32) ((float*)p.out)[base + d + e2] = acc[e2];
+        else ((uint16_t*)p.out)[base + d + e2] = f32_to_bf16_bits(acc[e2]);
+      }
+    }
+    return;
+  }
   float m = -INFINITY;
   for (int s = 0; s < p.splits; ++s) m = fmaxf(m, p.ws_lse[(int64_t)s * rows + row]);
   float z = 0.f;
@@ -129,7 +170,6 @@ __global__ __launch_bounds__(64) void generic_combine_kernel(DevParams p) {
     for (int s = 0; s < p.splits; ++s) z += expf(p.ws_lse[(int64_t)s * rows + row] - m);
   const float lse = (m == -INFINITY) ? -INFINITY : m + logf(z);
   if (lane == 0) p.lse[row] = lse;
-  const int64_t base = b * p.out_s[0] + t * p.out_s[1] + h * p.out_s[2];
   for (int d = lane; d < p.d_v; d += 64) {
     float acc = 0.f;
     if (m != -INFINITY) {

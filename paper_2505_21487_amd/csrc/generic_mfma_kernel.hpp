@@ -1,0 +1,255 @@
+// Generic decode-attention kernel on bf16 MFMA: any page size, any strides and any dims in steps of eight (sixteen
+// for the value), as long as rows of cache, query and output are 16-byte aligned; what is not aligned stays with the
+// scalar kernel (generic_kernels.hpp).  Same operation, same partials, same merge, and the same precision: products
+// of bf16 are exact in fp32, and each fp32 softmax weight enters the value product as a sum of three bf16 (24
+// significant bits, three MFMAs), never rounded to 16 bits.
+//
+// One workgroup of WR waves takes one (sequence, group, block of 16 * WR query rows, range of tokens); the waves
+// share tiles of 32 tokens in LDS, double-buffered and filled by direct-to-LDS loads, and own 16 query rows each
+// (transposed form, S^T = K . Q^T and O^T += V^T . P^T, on 16x16x32 MFMAs; row statistics in the four lanes of a
+// row).  A cache row lies in LDS as its 16-byte chunks [value | RoPE key] or [value | key], rotated by the row
+// number so that reads of one column spread over the banks.  The page ids of a tile's 32 tokens sit in the lanes of
+// one register, fetched a tile ahead.
+//
+// Bound by latency and vector work (address arithmetic with run-time dims, the three-way split).  Two latent heads of
+// 256 dims, 128 heads, 9 sequences of up to 4500 tokens at 128 tokens per page: 1923 us with the scalar kernel, whose
+// waves each read the whole cache for one row, 39 us here (one latent head of 512 dims: 3135 -> 62; four tied states
+// of 128: 374 -> 39).  With one contraction step of operand reads in flight instead of four: 47 us.
+#pragma once
+
+#include "common.hpp"
+#include "tuned_device.hpp"
+
+namespace gla {
+
+template <int DVB, int WR, bool SEPK>
+__global__ __launch_bounds__(64 * WR) void generic_mfma_kernel(DevParams p) {
+  constexpr int kMaxChunks = SEPK ? 2 * DVB / 8 : (DVB + 128) / 8;  // chunks per cache row (RoPE keys of up to 128 dims)
+  constexpr int kTile = 32 * kMaxChunks * 16;
+  constexpr int NDB = DVB / 16, NKN = DVB / 32, NKR = SEPK ? 0 : 4;
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[2 * kTile];
+  const unsigned lds_base = (unsigned)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem;
+  const int lane = threadIdx.x & 63, wave = uniform((int)threadIdx.x >> 6);
+  const int r16 = lane & 15, q = lane >> 4;
+
+  const int rows_group = p.g_q * p.T;
+  const int blocks = (rows_group + 16 * WR - 1) / (16 * WR);
+  const int unit = (int)blockIdx.x / blocks, rb = (int)blockIdx.x - unit * blocks;
+  const int b = unit / p.h_c, g = unit - b * p.h_c;
+  const int split = blockIdx.y;
+  const int R = (rb * WR + wave) * 16 + r16;
+  const bool row_valid = R < rows_group;
+  const int Rc = row_valid ? R : rows_group - 1;
+  const int t = Rc / p.g_q, h = g * p.g_q + (Rc - t * p.g_q);
+  const int row = (b * p.T + t) * p.h_q + h;
+
+  const int L = p.seq_lens[b];
+  const int n_vis = p.causal ? L - p.T + 1 + t : L;  // visible keys of this lane's row
+  const int j_begin = (int)min((int64_t)split * p.split_tokens, (int64_t)max(L, 0));
+  const int j_end = (int)min((int64_t)j_begin + p.split_tokens, (int64_t)max(L, 0));
+
+  // ---- chunks of a cache row in LDS: value first, then RoPE key or key
+  const int cv = p.d_v >> 3, ck = p.d_n >> 3, cr = p.d_r >> 3;
+  const int cpr = cv + (SEPK ? ck : cr);
+  auto slot_of = [&](int row_i, int row_mod, int chunk) {  // byte offset of a chunk inside a tile
+    int s = chunk + row_mod;
+    s -= s >= cpr ? cpr : 0;
+    return (unsigned)((row_i * cpr + s) * 16);
+  };
+  auto mod_cpr = [&](int x) { return x - (int)fast_div((unsigned)x, p.fd_cpr) * cpr; };
+
+  // ---- queries (B operand): dims beyond the real ones are zero, whatever the key operand holds there
+  u32x4_t qn[NKN], qr[NKR > 0 ? NKR : 1];
+  {
+    const uint16_t* src = p.q_nope + b * p.qn_s[0] + t * p.qn_s[1] + h * p.qn_s[2];
+#pragma unroll
+    for (int ks = 0; ks < NKN; ++ks) qn[ks] = 4 * ks + q < ck ? *(const u32x4_t*)(src + (4 * ks + q) * 8) : u32x4_t{0, 0, 0, 0};
+    if constexpr (!SEPK) {
+      const uint16_t* srcr = p.q_rope + b * p.qr_s[0] + t * p.qr_s[1] + h * p.qr_s[2];
+#pragma unroll
+      for (int ks = 0; ks < NKR; ++ks) qr[ks] = 4 * ks + q < cr ? *(const u32x4_t*)(srcr + (4 * ks + q) * 8) : u32x4_t{0, 0, 0, 0};
+    }
+  }
+  f32x4_t o[NDB];
+#pragma unroll
+  for (int d = 0; d < NDB; ++d) o[d] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  float m = -INFINITY, l = 0.f;
+  const float sc2 = p.scale * 1.4426950408889634f;
+
+  // ---- tile loads.  ids / tips: page and slot of token lane % 32 of the tile to fetch (rows past the end of the
+  //      sequence repeat its last token: valid memory, masked and zeroed below)
+  int ids = 0, tips = 0;
+  auto fetch_ids = [&](int tok0) {
+    const int tok = min(tok0 + (lane & 31), L - 1);
+    const int pg = (int)fast_div((unsigned)tok, p.fd_page);
+    tips = tok - pg * p.P;
+    ids = p.page_table[(int64_t)b * p.max_pages + pg];
+  };
+  const int n_slots = 32 * cpr, n_inst = (n_slots + 63) >> 6;
+  auto load_tile = [&](int buf) {
+    for (int i = wave; i < n_inst; i += WR) {
+      const int n = i * 64 + lane;
+      const int row_i = min((int)fast_div((unsigned)n, p.fd_cpr), 31);
+      int chunk = n - row_i * cpr - mod_cpr(row_i);
+      chunk += chunk < 0 ? cpr : 0;
+      const int64_t page = __builtin_amdgcn_ds_bpermute(row_i << 2, ids);
+      const int64_t tip = __builtin_amdgcn_ds_bpermute(row_i << 2, tips);
+      const uint16_t* src;
+      if (chunk < cv) src = p.state + page * p.st_s[0] + g * p.st_s[1] + tip * p.st_s[2] + chunk * 8;
+      else if constexpr (SEPK) src = p.kstate + page * p.k_s[0] + g * p.k_s[1] + tip * p.k_s[2] + (chunk - cv) * 8;
+      else src = p.rope + page * p.rp_s[0] + tip * p.rp_s[1] + (chunk - cv) * 8;
+      if (n < n_slots) __builtin_amdgcn_global_load_lds((global_cvoid_t*)src, (lds_void_t*)(smem + buf * kTile + i * 1024), 16, 0, 0);
+    }
+  };
+
+  const int mod_k[2] = {mod_cpr(r16), mod_cpr(16 + r16)};
+  const int tr_r = r16 >> 2, tr_c = r16 & 3;
+  const int mod_v[2] = {mod_cpr(4 * q + tr_r), mod_cpr(16 + 4 * q + tr_r)};
+  const int k0 = SEPK ? cv : 0;  // first chunk of the key (RoPE part apart)
+
+  if (j_begin < j_end) {
+    fetch_ids(j_begin);
+    load_tile(0);
+    fetch_ids(min(j_begin + 32, j_end - 1));
+    int buf = 0;
+    for (int j = j_begin; j < j_end; j += 32, buf ^= 1) {
+      wait_vmcnt<0>();  // this wave's part of the tile (and the ids of the next) ...
+      lds_barrier();    // ... and everybody's; the other buffer is free
+      if (j + 32 < j_end) {
+        load_tile(buf ^ 1);
+        fetch_ids(min(j + 64, j_end - 1));
+      }
+      const unsigned base = lds_base + (unsigned)(buf * kTile);
+      if (j + 32 > L) {  // rows past the end may hold anything: 0 x NaN must not leak (uniform over the workgroup)
+        for (int off = (L - j) * cpr * 16 + (int)threadIdx.x * 16; off < n_slots * 16; off += 64 * WR * 16)
+          lds_write_b128<0>(base + (unsigned)off, u32x4_t{0, 0, 0, 0});
+        lds_barrier();
+      }
+      // ---- scores of 2 x 16 tokens: S^T[token 16 tb + 4 q + e][row r16]
+      f32x4_t s[2] = {f32x4_t{0.f, 0.f, 0.f, 0.f}, f32x4_t{0.f, 0.f, 0.f, 0.f}};
+      // (four steps at a time, their eight reads in flight together; a step beyond the key's dims reads its last
+      // chunk again, against zeros of the query)
+      auto score_steps = [&](auto nc, const auto& qf, int first, int chunks) {
+        static_for<0, decltype(nc)::value / 4>([&](auto gc) {
+          constexpr int k4 = 4 * decltype(gc)::value;
+          if (4 * k4 < chunks) {
+            u32x4_t kf[4][2];
+            static_for<0, 4>([&](auto kc) {
+              constexpr int ks = decltype(kc)::value;
+              const int c = first + min(4 * (k4 + ks) + q, chunks - 1);
+              lds_read_b128<0>(kf[ks][0], base + slot_of(r16, mod_k[0], c));
+              lds_read_b128<0>(kf[ks][1], base + slot_of(16 + r16, mod_k[1], c));
+            });
+            static_for<0, 4>([&](auto kc) {
+              constexpr int ks = decltype(kc)::value;
+              pin_arch(kf[ks][0]);
+              lds_wait<2 * (3 - ks)>(kf[ks][1]);
+              pin_arch(kf[ks][0]);
+              static_for<0, 2>([&](auto tc) {
+                constexpr int tb = decltype(tc)::value;
+                s[tb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, kf[ks][tb]), __builtin_bit_cast(bf16x8_t, qf[k4 + ks]), s[tb], 0, 0, 0);
+              });
+            });
+          }
+        });
+      };
+      score_steps(std::integral_constant<int, NKN>{}, qn, k0, ck);
+      if constexpr (!SEPK) score_steps(std::integral_constant<int, NKR>{}, qr, cv, cr);
+      // ---- online softmax (base 2), masked by select
+      float mx = -INFINITY;
+      bool visible[8];
+#pragma unroll
+      for (int tb = 0; tb < 2; ++tb)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int tok = j + 16 * tb + 4 * q + e;
+          visible[4 * tb + e] = tok < n_vis && tok < j_end;
+          mx = fmaxf(mx, visible[4 * tb + e] ? s[tb][e] * sc2 : -INFINITY);
+        }
+      mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
+      mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+      const float m_new = fmaxf(m, mx);
+      if (__ballot(m_new != m) != 0) {
+        const float alpha = m_new != m ? __builtin_amdgcn_exp2f(m - m_new) : 1.f;  // (m = -inf on the first key: 0)
+        l *= alpha;
+#pragma unroll
+        for (int d = 0; d < NDB; ++d) o[d] *= alpha;
+        m = m_new;
+      }
+      const float ref = m == -INFINITY ? 0.f : m;
+      uint32_t w[3][4];  // the weights as sums of three bf16, in B operand order
+#pragma unroll
+      for (int e2 = 0; e2 < 4; ++e2) {
+        // (one rounding between the score and the exponential)
+        float a0 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[e2 >> 1][2 * (e2 & 1)], sc2, -ref));
+        float a1 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[e2 >> 1][2 * (e2 & 1) + 1], sc2, -ref));
+        a0 = visible[2 * e2] ? a0 : 0.f;
+        a1 = visible[2 * e2 + 1] ? a1 : 0.f;
+        l += a0 + a1;
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+          w[i][e2] = cvt_pk_bf16(a0, a1);
+          a0 -= __builtin_bit_cast(float, w[i][e2] << 16);
+          a1 -= __builtin_bit_cast(float, w[i][e2] & 0xffff0000u);
+        }
+      }
+      // ---- values
+      static_for<0, NDB / 4>([&](auto gc) {
+        constexpr int d4 = 4 * decltype(gc)::value;
+        if (2 * d4 < cv) {
+          u32x2_t v0[4], v1[4];
+          static_for<0, 4>([&](auto dc) {
+            constexpr int d = decltype(dc)::value;
+            const int c = min(2 * (d4 + d) + (tr_c >> 1), cv - 1);  // (blocks past the value's dims: accumulated, never stored)
+            lds_read_tr16_b64<0>(v0[d], base + slot_of(4 * q + tr_r, mod_v[0], c) + (unsigned)((tr_c & 1) * 8));
+            lds_read_tr16_b64<0>(v1[d], base + slot_of(16 + 4 * q + tr_r, mod_v[1], c) + (unsigned)((tr_c & 1) * 8));
+          });
+          static_for<0, 4>([&](auto dc) {
+            constexpr int d = decltype(dc)::value;
+            lds_wait2<2 * (3 - d)>(v0[d], v1[d]);
+            const u32x4_t a4 = {v0[d][0], v0[d][1], v1[d][0], v1[d][1]};
+#pragma unroll
+            for (int i = 0; i < 3; ++i) {
+              const u32x4_t b4 = {w[i][0], w[i][1], w[i][2], w[i][3]};
+              o[d4 + d] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a4), __builtin_bit_cast(bf16x8_t, b4), o[d4 + d], 0, 0, 0);
+            }
+          });
+        }
+      });
+    }
+  }
+
+  l += __shfl_xor(l, 16, 64);
+  l += __shfl_xor(l, 32, 64);
+  const bool empty = !(m > -INFINITY) && l == 0.f;  // no visible key in this range
+  const float inv = empty ? 0.f : 1.f / l;
+  const float lse = empty ? -INFINITY : (m + log2f(l)) * 0.6931471805599453f;
+  if (!row_valid) return;
+  if (p.splits == 1) {
+    if (q == 0) p.lse[row] = lse;
+    const int64_t ob = b * p.out_s[0] + t * p.out_s[1] + h * p.out_s[2];
+#pragma unroll
+    for (int d = 0; d < NDB; ++d) {
+      const int dim = 16 * d + 4 * q;
+      if (16 * d >= p.d_v) continue;
+      const f32x4_t v = o[d] * inv;
+      if (p.out_fp32) {
+        *(f32x4_t*)((float*)p.out + ob + dim) = v;
+      } else {
+        u32x2_t pk;
+        pk[0] = (uint32_t)f32_to_bf16_bits(v[0]) | ((uint32_t)f32_to_bf16_bits(v[1]) << 16);
+        pk[1] = (uint32_t)f32_to_bf16_bits(v[2]) | ((uint32_t)f32_to_bf16_bits(v[3]) << 16);
+        *(u32x2_t*)((uint16_t*)p.out + ob + dim) = pk;
+      }
+    }
+  } else {
+    const int64_t rows = (int64_t)p.B * p.T * p.h_q;
+    if (q == 0) p.ws_lse[(int64_t)split * rows + row] = lse;
+    float* dst = p.ws_out + ((int64_t)split * rows + row) * p.d_v;
+#pragma unroll
+    for (int d = 0; d < NDB; ++d)
+      if (16 * d < p.d_v) *(f32x4_t*)(dst + 16 * d + 4 * q) = o[d] * inv;
+  }
+}
+
+}  // namespace gla

@@ -12,6 +12,7 @@
 #include "common.hpp"
 #include "flex_kernels.hpp"
 #include "generic_kernels.hpp"
+#include "generic_mfma_kernel.hpp"
 #include "proj_kernels.hpp"
 #include "tuned_kernels.hpp"
 
@@ -131,6 +132,18 @@ int generic_splits(const gla_decode_params* p) {
   const int64_t rows = std::max<int64_t>(1, (int64_t)p->batch * p->q_len * p->num_q_heads);
   int64_t s = p->num_splits > 0 ? p->num_splits : (4096 + rows - 1) / rows;
   s = std::min<int64_t>(s, p->max_pages_per_seq);
+  if (p->num_splits <= 0) {
+    // The MFMA variant works on 64 rows at once: ranges for two workgroups per compute unit, of at least 256 tokens
+    // (a partial costs as much as a few tiles of 32: 18 units of up to 4500 tokens take 39 us in 17 ranges, 46 in 28),
+    // of at least 64 while the grid is small (2 units of 256 tokens: 19 us in four ranges, 49 in one), within 64
+    // ranges and 64 MB of partials.
+    const int64_t units = std::max<int64_t>(1, (int64_t)p->batch * p->num_groups * (((int64_t)p->num_q_heads / p->num_groups * p->q_len + 63) / 64));
+    const int64_t tokens = (int64_t)p->max_pages_per_seq * p->page_size;
+    int64_t want = (2 * (int64_t)device_cu_count() + units - 1) / units;
+    want = std::min(want, std::max((tokens + 255) / 256, std::min((tokens + 63) / 64, 64 / units)));
+    want = std::min<int64_t>(want, (64ll << 20) / std::max<int64_t>(1, rows * (p->d_v + 1) * 4));
+    s = std::max<int64_t>(s, std::min<int64_t>(want, 64));
+  }
   s = std::min<int64_t>(s, 65535);
   return (int)std::max<int64_t>(s, 1);
 }
@@ -254,7 +267,54 @@ void fill_dev(const gla_decode_params* p, DevParams* d) {
   d->stream_min_bytes = kLastLevelCacheBytes;
 }
 
-int launch_generic(const gla_decode_params* p, DevParams& d, hipStream_t st, hipEvent_t* ev) {
+// Does the MFMA variant of the generic kernel take this call?  Every 16-byte piece it loads or stores must be
+// aligned: dims in steps of eight (value: sixteen), strides likewise, aligned bases.  (It computes what the scalar
+// kernel computes, to the same precision: no size at which the scalar one is the better choice.)
+bool generic_mfma_ok(const gla_decode_params* p, const KeyCache* kc) {
+  if (p->d_v % 16 || p->d_nope % 8 || p->d_rope % 8 || std::max(p->d_v, p->d_nope) > 512) return false;
+  if ((int64_t)p->max_pages_per_seq * p->page_size > (1ll << 30)) return false;  // (token indices and divisions in 32 bits)
+  for (int i = 0; i < 3; ++i) {
+    if (p->q_nope_stride[i] % 8 || p->state_stride[i] % 8 || p->out_stride[i] % 4) return false;
+    if (p->d_rope > 0 && (p->q_rope_stride[i] % 8 || (i < 2 && p->rope_stride[i] % 8))) return false;
+    if (kc && kc->stride[i] % 8) return false;
+  }
+  uintptr_t bases = (uintptr_t)p->q_nope | (uintptr_t)p->state_cache | (uintptr_t)p->out;
+  if (p->d_rope > 0) bases |= (uintptr_t)p->q_rope | (uintptr_t)p->rope_cache;
+  if (kc) bases |= (uintptr_t)kc->ptr;
+  return (bases & 15u) == 0;
+}
+
+template <int DVB, bool SEPK>
+void launch_generic_mfma_waves(int rows_group, int64_t units, int splits, hipStream_t st, const DevParams& d) {
+  // waves per workgroup (16 rows each): as many as the rows of a group fill, at most four
+  const int wr = rows_group <= 16 ? 1 : rows_group <= 32 ? 2 : 4;
+  const dim3 grid((unsigned)(units * ((rows_group + 16 * wr - 1) / (16 * wr))), (unsigned)splits);
+  if (wr == 1) hipLaunchKernelGGL((generic_mfma_kernel<DVB, 1, SEPK>), grid, dim3(64), 0, st, d);
+  else if (wr == 2) hipLaunchKernelGGL((generic_mfma_kernel<DVB, 2, SEPK>), grid, dim3(128), 0, st, d);
+  else hipLaunchKernelGGL((generic_mfma_kernel<DVB, 4, SEPK>), grid, dim3(256), 0, st, d);
+}
+
+void launch_generic_mfma(const gla_decode_params* p, DevParams& d, hipStream_t st) {
+  const int64_t tokens = (int64_t)p->max_pages_per_seq * p->page_size;
+  d.split_tokens = (int32_t)(((tokens + d.splits - 1) / d.splits + 31) / 32 * 32);
+  d.fd_page = make_fastdiv((uint32_t)p->page_size);
+  const bool sepk = d.kstate != nullptr;
+  d.fd_cpr = make_fastdiv((uint32_t)(p->d_v / 8 + (sepk ? p->d_nope : p->d_rope) / 8));
+  const int rows_group = p->num_q_heads / p->num_groups * p->q_len;
+  const int64_t units = (int64_t)p->batch * p->num_groups;
+  const int dmax = std::max(p->d_v, p->d_nope);
+  if (sepk) {
+    if (dmax <= 128) launch_generic_mfma_waves<128, true>(rows_group, units, d.splits, st, d);
+    else if (dmax <= 256) launch_generic_mfma_waves<256, true>(rows_group, units, d.splits, st, d);
+    else launch_generic_mfma_waves<512, true>(rows_group, units, d.splits, st, d);
+  } else {
+    if (dmax <= 128) launch_generic_mfma_waves<128, false>(rows_group, units, d.splits, st, d);
+    else if (dmax <= 256) launch_generic_mfma_waves<256, false>(rows_group, units, d.splits, st, d);
+    else launch_generic_mfma_waves<512, false>(rows_group, units, d.splits, st, d);
+  }
+}
+
+int launch_generic(const gla_decode_params* p, const KeyCache* kc, DevParams& d, hipStream_t st, hipEvent_t* ev) {
   const int s = generic_splits(p);
   d.splits = s;
   d.pages_per_split = (p->max_pages_per_seq + s - 1) / s;
@@ -266,7 +326,8 @@ int launch_generic(const gla_decode_params* p, DevParams& d, hipStream_t st, hip
   dim3 grid((unsigned)rows, (unsigned)s), block(64);
   const int nv = (std::max(p->d_v, p->d_nope) + 63) / 64;
   if (ev) (void)hipEventRecord(ev[0], st);
-  if (nv <= 2) hipLaunchKernelGGL(generic_main_kernel<2>, grid, block, 0, st, d);
+  if (generic_mfma_ok(p, kc)) launch_generic_mfma(p, d, st);
+  else if (nv <= 2) hipLaunchKernelGGL(generic_main_kernel<2>, grid, block, 0, st, d);
   else if (nv <= 4) hipLaunchKernelGGL(generic_main_kernel<4>, grid, block, 0, st, d);
   else if (nv <= 8) hipLaunchKernelGGL(generic_main_kernel<8>, grid, block, 0, st, d);
   else hipLaunchKernelGGL(generic_main_kernel<16>, grid, block, 0, st, d);
@@ -312,7 +373,7 @@ int run(const gla_decode_params* p, int is_gta, hipEvent_t* ev, const KeyCache* 
     if (!flex_plan(p, is_gta, kc, &fp)) return GLA_ERR_UNSUPPORTED_SHAPE;
     return launch_flex(p, fp, d, st, ev);
   }
-  return launch_generic(p, d, st, ev);
+  return launch_generic(p, kc, d, st, ev);
 }
 
 // ---- fixed scratch buffer of the allocation-free entry point -------------------

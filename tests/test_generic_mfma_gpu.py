@@ -1,0 +1,70 @@
+"""The generic kernel's MFMA variant against the oracle where its general indexing can go wrong: page sizes that are
+not powers of two or larger than 64, dims that are no multiple of a contraction step, an odd number of 16-byte chunks
+per cache row, row counts around its 16-row waves, ranges that end inside a tile, strided and misaligned tensors (the
+scalar variant then runs, same bounds), separate key caches.
+
+fp32 results are held to 2e-5: products of bf16 are exact, weights keep 24 bits, and the largest term left is the
+rounding of a score before its exponential, |score| 2^-24 relative to a weight (scores here stay below 20 in base 2,
+values below 5: 20 * 0.7 * 6e-8 * 2 * 5 < 1e-5), beside sums of at most 1300 terms of total weight one."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2505_21487_amd as gla
+from paper_2505_21487_amd.harness import DeviceProblem
+from workloads import make_problem
+
+from gpu_util import run_gpu
+
+pytestmark = pytest.mark.gpu
+
+LENS = [0, 1, 31, 32, 33, 300, 1, 1300]
+CASES = {
+    # name: (kind, h_q, h_c, d_v, d_r, T, page, splits)
+    "gla2_page128": ("gla", 128, 2, 256, 64, 1, 128, 0),
+    "gla2_page256_q4": ("gla", 32, 2, 256, 64, 4, 256, 3),
+    "mla_page128": ("gla", 40, 1, 512, 64, 2, 128, 0),
+    "page48_rope40": ("gla", 12, 3, 96, 40, 3, 48, 5),
+    "page3_dv80": ("gla", 4, 1, 80, 24, 1, 3, 1),
+    "page100_rope0": ("gla", 17, 1, 128, 0, 1, 100, 2),
+    "gta_page7": ("gta", 18, 2, 112, 56, 1, 7, 0),
+    "gqa_page24": ("gqa", 10, 2, 80, 0, 4, 24, 0),
+    "gqa_dv256": ("gqa", 33, 1, 256, 0, 1, 5, 4),
+    "gqa_dv512_rows1": ("gqa", 1, 1, 512, 0, 1, 64, 2),
+    "rope128": ("gla", 16, 1, 64, 128, 1, 16, 0),
+}
+
+
+def _close(p, dp, **kw):
+    out, lse = run_gpu(p, dp=dp, impl=gla.GLA_IMPL_GENERIC, out_dtype=torch.float32, **kw)
+    ref_out, ref_lse = oracle.decode_problem(p)
+    none = np.isneginf(ref_lse)
+    assert np.array_equal(np.isneginf(lse), none) and (out[none] == 0).all()
+    assert np.abs(out - ref_out).max() <= 2e-5
+    assert np.abs(lse[~none] - ref_lse[~none]).max() <= 2e-5
+
+
+@pytest.mark.parametrize("name", sorted(CASES))
+def test_generic_mfma(name):
+    kind, h_q, h_c, d_v, d_r, T, page, splits = CASES[name]
+    p = make_problem(name, kind=kind, seq_lens=LENS, T=T, h_q=h_q, h_c=h_c, d_v=d_v, d_r=d_r, page_size=page, seed=8100 + len(name),
+                     num_pages=sum(n // page + 1 for n in LENS) + 9, poison_tail=True, extra_table_cols=2, causal=0 if page == 7 else 1)
+    _close(p, DeviceProblem(p, poison_unused=True), num_splits=splits)
+
+
+@pytest.mark.parametrize("offset", [8, 4, 1])
+def test_generic_strided_queries(offset):
+    """Queries inside a wider buffer: 16-byte aligned (MFMA variant), 8-byte and 2-byte aligned (scalar variant)."""
+    p = make_problem("strided", seq_lens=LENS, T=2, h_q=6, h_c=3, d_v=96, d_r=32, page_size=48, seed=8200, num_pages=64, poison_tail=True)
+    dp = DeviceProblem(p, poison_unused=True)
+    wide = torch.zeros(p.B, p.T, p.h_q, p.d_n + 40, dtype=torch.bfloat16, device="cuda")
+    wide[..., offset:offset + p.d_n] = dp.q_nope
+    dp.q_nope = wide[..., offset:offset + p.d_n]
+    _close(p, dp)
+
+
+def test_merge_of_more_ranges_than_lanes():
+    p = make_problem("many_ranges", seq_lens=[1300, 0, 70], T=1, h_q=5, h_c=1, d_v=112, d_r=40, page_size=5, seed=8300, num_pages=512)
+    for splits in (63, 64, 65, 200):
+        _close(p, DeviceProblem(p, poison_unused=True), num_splits=splits)
