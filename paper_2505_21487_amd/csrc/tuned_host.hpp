@@ -51,12 +51,14 @@ constexpr int kMinChunkTiles = 4;
 //   256 dims, 256 rows per group, chunks of 128 tiles inside one sequence each, pages of 64 / 1: 328 -> 305 / 369 -> 315; chunks of
 //     55 tiles over 1.75 sequences each 183 -> 196, of 4 tiles 33.6 -> 37.4; with 128 rows per group (no second row
 //     block to share the tiles with, the kernel is half bound by HBM) 117 -> 123
-// Lengths are known on the device only: the host goes by the table's row length.
+// Lengths are known on the device only: the host goes by the table's row length, and asks for a wide margin where the
+// gain is small (pages of 16 tokens or more): with one long sequence among short ones the real chunks are a tenth of
+// what the table allows (fifteen of 1024 tokens beside one of 65536, 512 dims: 74.3 -> 76.9).
 inline bool wide_pays(const gla_decode_params* p, int rows_group) {
   const int64_t tiles_seq = ((int64_t)p->max_pages_per_seq * p->page_size + 63) / 64;
   if (p->d_v == 512 && rows_group > 32) {
     const int64_t chunks = std::max<int64_t>(1, device_cu_count() / ((rows_group + 63) / 64));
-    return (int64_t)p->batch * p->num_groups * tiles_seq >= 12 * chunks;
+    return (int64_t)p->batch * p->num_groups * tiles_seq >= (p->page_size < 16 ? 24 : 192) * chunks;
   }
   if (p->d_v == 256 && rows_group > 128) {
     const int64_t chunks = std::max<int64_t>(1, device_cu_count() / ((rows_group + 127) / 128));
@@ -127,7 +129,13 @@ inline bool tuned_plan(const gla_decode_params* p, int is_gta, TunedPlan* plan) 
     // (by the upper bound on the list length): a partial costs as much memory
     // traffic as three or four tiles, and every extra chunk is one more to merge
     const int64_t resident = std::max<int64_t>(1, (int64_t)device_cu_count() * per_cu / plan->mb);
-    const int64_t by_length = std::max<int64_t>(1, bound * tok / (kMinChunkTiles * kTok));
+    int64_t by_length = std::max<int64_t>(1, bound * tok / (kMinChunkTiles * kTok));
+    // While the grid is small the chip is idle and a tile more in the serial chain of a chunk costs more than a
+    // partial: chunks of two tiles up to a quarter of the compute units, of one up to an eighth.  Measured, us per
+    // call: 16 heads x 256 tokens 17.8 -> 14.6, batch 1 x 100 tokens 21.5 -> 16.4, x 512 20.4 -> 17.8, x 2048
+    // 21.9 -> 20.4; further (one tile up to a quarter) loses again, 22.8 at 2048; with the grid full (batch 64 x 300)
+    // two tiles take 36.6 against 34.2 with four.
+    if (!plan->wide) by_length = std::max({by_length, std::min(bound / 2, resident / 4), std::min(bound, resident / 8)});
     plan->num_chunks = (int)std::max<int64_t>(1, std::min<int64_t>(by_length, resident));
   }
   plan->slot_floats = (size_t)plan->rows * p->d_v + (size_t)32 * ng * wpg * ks;

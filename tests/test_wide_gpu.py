@@ -37,8 +37,8 @@ def test_eight_wave_kernel(name):
     shape, lens, T, page, kw = CASES[name]
     kw = dict(kw)
     h_q = kw.pop("h_q", 128)
-    # (a row length for which the plan picks the kernel: chunks of at least 12 / 64 tiles if every row were full)
-    want_tokens = (12 if shape == "mla" else 64) * 64 * 256 // len(lens) + 64
+    # (a row length for which the plan picks the kernel: chunks of at least 24 / 192 / 64 tiles if every row were full)
+    want_tokens = ((24 if page < 16 else 192) if shape == "mla" else 64) * 64 * 256 // len(lens) + 64
     pages = max((n + page - 1) // page for n in lens)
     p = make_problem(name, seq_lens=lens, T=T, h_q=h_q, h_c=1 if shape == "mla" else 2, d_v=512 if shape == "mla" else 256,
                      page_size=page, seed=7000 + len(name), num_pages=sum((n + page - 1) // page for n in lens) + 64,
@@ -51,7 +51,7 @@ def test_eight_wave_kernel(name):
 def test_eight_wave_kernel_repeats_bit_for_bit():
     """Many segments, moved references and residual passes: the same call gives the same bits."""
     p = make_problem("repeat", seq_lens=[70, 300, 64, 1, 513] * 8, T=1, h_q=128, h_c=1, d_v=512, page_size=64, seed=71,
-                     num_pages=4096, q_gain=3.0, poison_tail=True, extra_table_cols=600)
+                     num_pages=4096, q_gain=3.0, poison_tail=True, extra_table_cols=1300)
     dp = DeviceProblem(p, poison_unused=True)
     first = None
     for _ in range(20):
