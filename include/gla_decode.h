@@ -33,8 +33,9 @@
  * (512, 512), (128, 64) and RoPE dims 64, 48 or 32.  A second, simpler MFMA
  * kernel covers GTA states of 64 and 96 dims (RoPE key d_v / 2), latent heads of
  * 128 dims with a RoPE key of 32, and gqa_decode, at any power-of-two
- * page_size.  Everything else takes the generic kernel.  GLA_IMPL_TUNED means
- * "one of the MFMA kernels".
+ * page_size.  Everything else takes the generic kernel (itself on MFMA where rows
+ * are 16-byte aligned, dims multiples of 8 and the value's of 16, up to 512).
+ * GLA_IMPL_TUNED means "one of the MFMA kernels made for a shape".
  *
  * Ownership and execution.  Every pointer in the struct is a DEVICE pointer
  * owned by the caller unless stated otherwise; the library allocates no device
@@ -67,7 +68,7 @@ enum {
 
 enum {
   GLA_IMPL_AUTO = 0,     /* tuned MFMA kernel when the shape has one, else the generic kernel */
-  GLA_IMPL_GENERIC = 1,  /* shape-agnostic scalar kernel (any dims, any page size)            */
+  GLA_IMPL_GENERIC = 1,  /* shape-agnostic kernel (any dims, page size, strides); fp32 weights  */
   GLA_IMPL_TUNED = 2     /* tuned kernel or GLA_ERR_UNSUPPORTED_SHAPE                          */
 };
 

@@ -1,8 +1,8 @@
 // Shape-agnostic decode-attention kernels: one wave64 per (sequence, query row,
 // head, key split), scalar fp32 FMAs, online softmax one key at a time.  Slow
 // (every head re-reads its group's cache) but valid for any dims, page size and
-// strides; it serves shapes without a tuned kernel and cross-checks the tuned
-// one.  Same operation as the tuned path: score = scale * (q_nope . state[:d_n]
+// strides; it serves what the MFMA variant (generic_mfma_kernel.hpp) does not take:
+// rows that are not 16-byte aligned, dims beyond 512.  Same operation as the tuned path: score = scale * (q_nope . state[:d_n]
 // + q_rope . rope_key), softmax over visible keys, output = weights . state
 // (paper Sections 2.1, 3.3.1, 3.3.2).
 #pragma once
