@@ -117,10 +117,10 @@ bool flex_plan(const gla_decode_params* p, int mode, const KeyCache* kc, FlexPla
     int64_t by_length = bound / 8;
     // ... but while most of the chip is idle a shorter serial chain pays: chunks of four tiles up to one wave per
     // compute unit, of two up to half of that.  us per call: GTA-4 d_h 64, batch 1 x 200 12.9 -> 11.0, 4 x 100 to 900
-    // 16.5 -> 12.5; GQA-4 batch 2 x 300 18.1 -> 11.9, 32 x 300 20.7 -> 15.7.  Not quite twice as many chunks as
-    // sequences would cut most of these in two for little (64 x 200: 14.1 us, 15.9 with 112 chunks): one each then.
-    by_length = std::max({by_length, std::min(bound / 4, waves / plan->strands), std::min(bound / 2, waves / 2 / plan->strands)});
-    if (by_length > p->batch && by_length < 2 * (int64_t)p->batch) by_length = std::max<int64_t>(bound / 8, p->batch);
+    // 16.5 -> 12.5; GQA-4 batch 2 x 300 18.1 -> 11.9.  Few sequences only: a batch of many short ones has its
+    // parallelism already, and cut further it pays in merges (64 x 200: 14.1 us, 15.9 with 112 chunks).
+    if (p->batch <= 4)
+      by_length = std::max({by_length, std::min(bound / 4, waves / plan->strands), std::min(bound / 2, waves / 2 / plan->strands)});
     chunks = std::min<int64_t>((4 * waves + plan->strands - 1) / plan->strands, by_length);
   }
   chunks = std::max<int64_t>(1, chunks);

@@ -135,7 +135,8 @@ inline bool tuned_plan(const gla_decode_params* p, int is_gta, TunedPlan* plan) 
     // call: 16 heads x 256 tokens 17.8 -> 14.6, batch 1 x 100 tokens 21.5 -> 16.4, x 512 20.4 -> 17.8, x 2048
     // 21.9 -> 20.4; further (one tile up to a quarter) loses again, 22.8 at 2048; with the grid full (batch 64 x 300)
     // two tiles take 36.6 against 34.2 with four.
-    if (!plan->wide) by_length = std::max({by_length, std::min(bound / 2, resident / 4), std::min(bound, resident / 8)});
+    // (Few sequences only: a batch of many short ones has its parallelism already, and cut further it pays in merges.)
+    if (!plan->wide && p->batch <= 4) by_length = std::max({by_length, std::min(bound / 2, resident / 4), std::min(bound, resident / 8)});
     plan->num_chunks = (int)std::max<int64_t>(1, std::min<int64_t>(by_length, resident));
   }
   plan->slot_floats = (size_t)plan->rows * p->d_v + (size_t)32 * ng * wpg * ks;
