@@ -133,7 +133,8 @@ __global__ __launch_bounds__(64) void generic_combine_kernel(DevParams p) {
     for (int sh = 32; sh > 0; sh >>= 1) m = fmaxf(m, __shfl_xor(m, sh, 64));
     const float e = ls != -INFINITY ? expf(ls - m) : 0.f;
     const float z = wave_sum(e);
-    if (lane == 0) p.lse[row] = m == -INFINITY ? -INFINITY : m + logf(z);
+    // (z == 0: no key in any range; NaN where every range that has keys is NaN)
+    if (lane == 0) p.lse[row] = z == 0.f ? -INFINITY : m + logf(z);
     const float w = z > 0.f ? e / z : 0.f;
     for (int d0 = 0; d0 < p.d_v; d0 += 256) {  // (every lane stays in the loop: the weights are read across lanes)
       const bool mine = d0 + 4 * lane < p.d_v;
@@ -146,12 +147,13 @@ __global__ __launch_bounds__(64) void generic_combine_kernel(DevParams p) {
         for (int u = 0; u < 8; ++u) v[u] = *(const float4*)(src + (int64_t)min(s + u, p.splits - 1) * rows * p.d_v);
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
-          // (a range without keys left zeros)
-          const float ws = s + u < p.splits ? __shfl(w, s + u, 64) : 0.f;
-          acc[0] += ws * v[u].x;
-          acc[1] += ws * v[u].y;
-          acc[2] += ws * v[u].z;
-          acc[3] += ws * v[u].w;
+          // (a range without keys left zeros; past the last range its values once more, dropped: not multiplied by zero)
+          const bool live = s + u < p.splits;
+          const float ws = __shfl(w, live ? s + u : 0, 64);
+          acc[0] += live ? ws * v[u].x : 0.f;
+          acc[1] += live ? ws * v[u].y : 0.f;
+          acc[2] += live ? ws * v[u].z : 0.f;
+          acc[3] += live ? ws * v[u].w : 0.f;
         }
       }
       if (!mine) continue;

@@ -68,3 +68,44 @@ def test_merge_of_more_ranges_than_lanes():
     p = make_problem("many_ranges", seq_lens=[1300, 0, 70], T=1, h_q=5, h_c=1, d_v=112, d_r=40, page_size=5, seed=8300, num_pages=512)
     for splits in (63, 64, 65, 200):
         _close(p, DeviceProblem(p, poison_unused=True), num_splits=splits)
+
+
+# ---- values a cache is not meant to hold.  A row's result depends on the keys it sees and on nothing else, and is what
+# the definition gives for them (the oracle reads visible keys alone): NaN where it sees a NaN, infinite where the
+# only such value it sees is an infinity of one sign.
+def _set_tokens(p, b, tokens, value, dims=slice(None)):
+    """Write `value` into cached tokens of sequence b: state (or value) rows, and keys where they are kept apart."""
+    for tok in tokens:
+        page = int(p.table_compact[b, tok // p.page_size])
+        p.state_pages[page, :, tok % p.page_size, dims] = value
+        if p.key_pages is not None and dims == slice(None):
+            p.key_pages[page, :, tok % p.page_size] = value
+
+
+def _same_with_special_values(p, **kw):
+    out, lse = run_gpu(p, impl=gla.GLA_IMPL_GENERIC, out_dtype=torch.float32, **kw)
+    ref_out, ref_lse = oracle.decode_problem(p)
+    for got, ref in ((out, ref_out), (lse, ref_lse)):
+        assert np.array_equal(np.isnan(got), np.isnan(ref))
+        assert np.array_equal(np.where(np.isinf(got), got, 0), np.where(np.isinf(ref), ref, 0))
+        fin = np.isfinite(ref)
+        assert (np.abs(got[fin] - ref[fin]) <= 2e-5).all()
+
+
+@pytest.mark.parametrize("d_v,splits,aligned", [(80, 3, False), (256, 2, False)])
+def test_infinite_values(d_v, splits, aligned):
+    """Infinities in values whose keys, kept apart, are ordinary numbers.  (Misaligned queries: the scalar kernel.)"""
+    p = make_problem("infinite", kind="gqa", seq_lens=[33, 300, 64], T=2, h_q=12, h_c=2, d_v=d_v, page_size=128, seed=8500, num_pages=16)
+    inf = float("inf")
+    _set_tokens(p, 0, [5], inf, d_v - 1)
+    _set_tokens(p, 1, [0, 299], inf, d_v - 2)
+    _set_tokens(p, 1, [140], -inf, d_v - 3)
+    _set_tokens(p, 2, [63], -inf, d_v - 4)
+    ref_out, _ = oracle.decode_problem(p)
+    assert np.isposinf(ref_out).any() and np.isneginf(ref_out).any() and not np.isnan(ref_out).any()
+    dp = DeviceProblem(p, poison_unused=True)
+    if not aligned:
+        wide = torch.zeros(p.B, p.T, p.h_q, p.d_n + 2, dtype=torch.bfloat16, device="cuda")
+        wide[..., 1:1 + p.d_n] = dp.q_nope
+        dp.q_nope = wide[..., 1:1 + p.d_n]
+    _same_with_special_values(p, dp=dp, num_splits=splits)
