@@ -17,24 +17,13 @@ __device__ __forceinline__ float wave_sum(float v) {
   return v;
 }
 
-// NV = ceil(d_v / 64): state elements owned by one lane.
+// One query row over keys [j0, j1) by one wave: running maximum m, sum of weights l, weighted values o (element
+// lane + 64 i of the value at o[i]).  NV = ceil(d_v / 64): state elements owned by one lane.
 template <int NV>
-__global__ __launch_bounds__(64) void generic_main_kernel(DevParams p) {
-  const int row = blockIdx.x;
-  const int s = blockIdx.y;
-  const int lane = threadIdx.x;
-  const int h = row % p.h_q;
-  const int t = (row / p.h_q) % p.T;
-  const int b = row / (p.h_q * p.T);
+__device__ __forceinline__ void scalar_row(const DevParams& p, int b, int t, int h, int lane, int64_t j0, int64_t j1,
+                                           float (&o)[NV], float& m, float& l) {
   const int g = h / p.g_q;
-
-  const int64_t L = p.seq_lens[b];
-  const int64_t n_vis = p.causal ? L - p.T + 1 + t : L;
-  const int64_t span = (int64_t)p.pages_per_split * p.P;
-  const int64_t j0 = (int64_t)s * span;
-  const int64_t j1 = (j0 + span < n_vis) ? j0 + span : n_vis;
-
-  float qn[NV], qr[2], o[NV];
+  float qn[NV], qr[2];
   const uint16_t* qn_ptr = p.q_nope + b * p.qn_s[0] + t * p.qn_s[1] + h * p.qn_s[2];
 #pragma unroll
   for (int i = 0; i < NV; ++i) {
@@ -53,7 +42,8 @@ __global__ __launch_bounds__(64) void generic_main_kernel(DevParams p) {
     qr[0] = qr[1] = 0.f;
   }
 
-  float m = -INFINITY, l = 0.f;
+  m = -INFINITY;
+  l = 0.f;
   int64_t page = 0;
   for (int64_t j = j0; j < j1; ++j) {
     const int off = (int)(j % p.P);
@@ -86,8 +76,13 @@ __global__ __launch_bounds__(64) void generic_main_kernel(DevParams p) {
     for (int i = 0; i < NV; ++i) o[i] = o[i] * alpha + pj * cv[i];
     m = m_new;
   }
+}
 
-  const bool empty = j1 <= j0;
+// What scalar_row() found for output row `row`: the result, or range s's partial of it.
+template <int NV>
+__device__ __forceinline__ void store_scalar_row(const DevParams& p, int b, int t, int h, int s, int lane, bool empty,
+                                                 const float (&o)[NV], float m, float l) {
+  const int row = (b * p.T + t) * p.h_q + h;
   const float inv = empty ? 0.f : 1.f / l;
   const float lse = empty ? -INFINITY : m + logf(l);
   if (p.splits == 1) {
@@ -111,6 +106,26 @@ __global__ __launch_bounds__(64) void generic_main_kernel(DevParams p) {
       if (d < p.d_v) dst[d] = o[i] * inv;
     }
   }
+}
+
+template <int NV>
+__global__ __launch_bounds__(64) void generic_main_kernel(DevParams p) {
+  const int row = blockIdx.x;
+  const int s = blockIdx.y;
+  const int lane = threadIdx.x;
+  const int h = row % p.h_q;
+  const int t = (row / p.h_q) % p.T;
+  const int b = row / (p.h_q * p.T);
+
+  const int64_t L = p.seq_lens[b];
+  const int64_t n_vis = p.causal ? L - p.T + 1 + t : L;
+  const int64_t span = (int64_t)p.pages_per_split * p.P;
+  const int64_t j0 = (int64_t)s * span;
+  const int64_t j1 = (j0 + span < n_vis) ? j0 + span : n_vis;
+
+  float o[NV], m, l;
+  scalar_row(p, b, t, h, lane, j0, j1, o, m, l);
+  store_scalar_row(p, b, t, h, s, lane, j1 <= j0, o, m, l);
 }
 
 // Merge of the per-split partial results: lse = ln sum_s exp(lse_s),

@@ -18,6 +18,7 @@
 #pragma once
 
 #include "common.hpp"
+#include "generic_kernels.hpp"
 #include "tuned_device.hpp"
 
 namespace gla {
@@ -221,34 +222,66 @@ __global__ __launch_bounds__(64 * WR) void generic_mfma_kernel(DevParams p) {
 
   l += __shfl_xor(l, 16, 64);
   l += __shfl_xor(l, 32, 64);
-  const bool empty = !(m > -INFINITY) && l == 0.f;  // no visible key in this range
+  const bool empty = j_begin >= min(j_end, n_vis);  // no visible key in this range
   const float inv = empty ? 0.f : 1.f / l;
   const float lse = empty ? -INFINITY : (m + log2f(l)) * 0.6931471805599453f;
-  if (!row_valid) return;
-  if (p.splits == 1) {
-    if (q == 0) p.lse[row] = lse;
-    const int64_t ob = b * p.out_s[0] + t * p.out_s[1] + h * p.out_s[2];
+
+  // Is every number of this row finite?  If not, the scalar loop works the row out again below: with NaN or infinities in
+  // the cache the products above give too much NaN.  They multiply keys a row does not see (hidden by causality, seen by
+  // later rows of the tile) by a weight of zero, and an infinite value by each of the three parts of its weight, zero and
+  // negative ones among them.  (The look costs 0.4 us of the 39 above.)
+  f32x4_t probes = {l, 0.f, 0.f, 0.f};  // (blocks past the value's dims repeat the last one's numbers)
 #pragma unroll
-    for (int d = 0; d < NDB; ++d) {
-      const int dim = 16 * d + 4 * q;
-      if (16 * d >= p.d_v) continue;
-      const f32x4_t v = o[d] * inv;
-      if (p.out_fp32) {
-        *(f32x4_t*)((float*)p.out + ob + dim) = v;
-      } else {
-        u32x2_t pk;
-        pk[0] = (uint32_t)f32_to_bf16_bits(v[0]) | ((uint32_t)f32_to_bf16_bits(v[1]) << 16);
-        pk[1] = (uint32_t)f32_to_bf16_bits(v[2]) | ((uint32_t)f32_to_bf16_bits(v[3]) << 16);
-        *(u32x2_t*)((uint16_t*)p.out + ob + dim) = pk;
+  for (int d = 0; d < NDB; ++d)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) probes[e] = __builtin_fmaf(o[d][e], 0.f, probes[e]);
+  const float probe = (probes[0] + probes[1]) + (probes[2] + probes[3]);
+  const bool odd = empty ? probe != 0.f : !(probe > 0.f && probe < INFINITY);
+  uint64_t odd_rows = __ballot(odd && row_valid);
+  odd_rows |= odd_rows >> 32;
+  odd_rows = (odd_rows | odd_rows >> 16) & 0xffff;
+
+  if (row_valid && !((odd_rows >> r16) & 1)) {
+    if (p.splits == 1) {
+      if (q == 0) p.lse[row] = lse;
+      const int64_t ob = b * p.out_s[0] + t * p.out_s[1] + h * p.out_s[2];
+#pragma unroll
+      for (int d = 0; d < NDB; ++d) {
+        const int dim = 16 * d + 4 * q;
+        if (16 * d >= p.d_v) continue;
+        const f32x4_t v = o[d] * inv;
+        if (p.out_fp32) {
+          *(f32x4_t*)((float*)p.out + ob + dim) = v;
+        } else {
+          u32x2_t pk;
+          pk[0] = (uint32_t)f32_to_bf16_bits(v[0]) | ((uint32_t)f32_to_bf16_bits(v[1]) << 16);
+          pk[1] = (uint32_t)f32_to_bf16_bits(v[2]) | ((uint32_t)f32_to_bf16_bits(v[3]) << 16);
+          *(u32x2_t*)((uint16_t*)p.out + ob + dim) = pk;
+        }
       }
-    }
-  } else {
-    const int64_t rows = (int64_t)p.B * p.T * p.h_q;
-    if (q == 0) p.ws_lse[(int64_t)split * rows + row] = lse;
-    float* dst = p.ws_out + ((int64_t)split * rows + row) * p.d_v;
+    } else {
+      const int64_t rows = (int64_t)p.B * p.T * p.h_q;
+      if (q == 0) p.ws_lse[(int64_t)split * rows + row] = lse;
+      float* dst = p.ws_out + ((int64_t)split * rows + row) * p.d_v;
 #pragma unroll
-    for (int d = 0; d < NDB; ++d)
-      if (16 * d < p.d_v) *(f32x4_t*)(dst + 16 * d + 4 * q) = o[d] * inv;
+      for (int d = 0; d < NDB; ++d)
+        if (16 * d < p.d_v) *(f32x4_t*)(dst + 16 * d + 4 * q) = o[d] * inv;
+    }
+  }
+  if (odd_rows) {
+    // (the arguments once more, through a pointer the compiler cannot see through: what only this loop needs is loaded
+    // here and not kept, or spilled, across the kernel)
+    auto* kernarg = (__attribute__((address_space(4))) const void*)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(kernarg));
+    const DevParams& pk = *(const DevParams*)kernarg;
+    for (; odd_rows; odd_rows &= odd_rows - 1) {
+      const int R1 = (rb * WR + wave) * 16 + __ffsll((unsigned long long)odd_rows) - 1;
+      const int t1 = R1 / pk.g_q, h1 = g * pk.g_q + (R1 - t1 * pk.g_q);
+      const int j1 = min(j_end, pk.causal ? L - pk.T + 1 + t1 : L);
+      float o1[DVB / 64], m1, l1;
+      scalar_row(pk, b, t1, h1, lane, j_begin, j1, o1, m1, l1);
+      store_scalar_row(pk, b, t1, h1, split, lane, j1 <= j_begin, o1, m1, l1);
+    }
   }
 }
 

@@ -92,7 +92,24 @@ def _same_with_special_values(p, **kw):
         assert (np.abs(got[fin] - ref[fin]) <= 2e-5).all()
 
 
-@pytest.mark.parametrize("d_v,splits,aligned", [(80, 3, False), (256, 2, False)])
+HIDDEN_LENS = [1, 2, 4, 32, 33, 34, 35, 36, 63, 66, 300]
+
+
+@pytest.mark.parametrize("value", [float("nan"), float("inf")])
+@pytest.mark.parametrize("kind,d_v,T,splits", [("gla", 256, 4, 1), ("gla", 96, 2, 0), ("gta", 128, 3, 4), ("gqa", 80, 4, 3), ("gla", 512, 3, 2)])
+def test_causally_hidden_keys_do_not_reach_earlier_rows(kind, d_v, T, splits, value):
+    """The last T - 1 tokens are hidden from the first row and seen by later ones: on tile and range boundaries too."""
+    for hidden in sorted({1, T - 1}):
+        p = make_problem("hidden", kind=kind, seq_lens=HIDDEN_LENS, T=T, h_q=24, h_c=2, d_v=d_v, d_r=32 if kind == "gla" else d_v // 2,
+                         page_size=128, seed=8400 + T, num_pages=40, poison_tail=True)
+        for b, n in enumerate(HIDDEN_LENS):
+            _set_tokens(p, b, range(max(0, n - hidden), n), value)
+        ref_out, _ = oracle.decode_problem(p)
+        assert np.isfinite(ref_out[:, :T - hidden]).all() and np.isnan(ref_out).any()
+        _same_with_special_values(p, num_splits=splits)
+
+
+@pytest.mark.parametrize("d_v,splits,aligned", [(80, 1, True), (256, 3, True), (512, 0, True), (80, 3, False), (256, 2, False)])
 def test_infinite_values(d_v, splits, aligned):
     """Infinities in values whose keys, kept apart, are ordinary numbers.  (Misaligned queries: the scalar kernel.)"""
     p = make_problem("infinite", kind="gqa", seq_lens=[33, 300, 64], T=2, h_q=12, h_c=2, d_v=d_v, page_size=128, seed=8500, num_pages=16)
