@@ -24,8 +24,7 @@ HIPCC_FLAGS = [
 
 
 def sources():
-    """Translation units of the library (compiled side by side)."""
-    return [os.path.join(CSRC, f) for f in ("gla_decode.hip", "tuned_256.hip", "tuned_512.hip", "tuned_128.hip", "wide.hip")]
+    return [os.path.join(CSRC, "library.hip")]  # (one unit: see there)
 
 
 def needs_build() -> bool:
@@ -40,20 +39,10 @@ def needs_build() -> bool:
 def build(verbose: bool = True, extra_flags=()) -> str:
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     tmp = LIB + f".tmp{os.getpid()}"
-    flags = HIPCC_FLAGS + list(extra_flags)
-    with tempfile.TemporaryDirectory() as objdir:
-        jobs, objs = [], []
-        for src in sources():
-            obj = os.path.join(objdir, os.path.basename(src) + ".o")
-            cmd = [hipcc] + [f for f in flags if f != "-shared"] + ["-c", "-o", obj, src]
-            if verbose:
-                print(" ".join(cmd), flush=True)
-            jobs.append((cmd, subprocess.Popen(cmd)))
-            objs.append(obj)
-        failed = [cmd for cmd, job in jobs if job.wait() != 0]
-        if failed:
-            raise subprocess.CalledProcessError(1, failed[0])
-        subprocess.check_call([hipcc, "--offload-arch=gfx950", "-fPIC", "-shared", "-o", tmp] + objs)
+    cmd = [hipcc] + HIPCC_FLAGS + list(extra_flags) + ["-o", tmp] + sources()
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.check_call(cmd)
     os.replace(tmp, LIB)
     return LIB
 

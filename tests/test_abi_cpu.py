@@ -27,6 +27,12 @@ def test_library_exports_every_declared_symbol():
         assert getattr(lib, n) is not None
 
 
+def test_library_is_one_device_code_object():
+    """Several would each have memory of their own on the GPU, which costs programs that change kernels all the time."""
+    with open(gla.binding.LIB_PATH, "rb") as f:
+        assert f.read().count(b"__CLANG_OFFLOAD_BUNDLE__") == 1
+
+
 def test_version_and_status_strings():
     assert gla.gla_decode_version() >= 100
     seen = {gla.gla_status_string(c) for c in (0, -1, -2, -3, -4)}
