@@ -156,7 +156,10 @@ int gla_decode_noalloc(const gla_decode_params* p, int is_gta);
  * fields are ignored).  is_gta: 0 for gla_decode, 1 for gta_decode, 2 for
  * gqa_decode (the helpers below take the same values; they have no passage of
  * the paper to cite: they describe this library's own kernels).  Returns 0 for
- * an invalid parameter set. */
+ * an invalid parameter set.  On the MFMA kernels made for a shape the size for a
+ * batch serves every smaller batch of otherwise equal parameters.  A call whose
+ * workspace is smaller than this may still run, on a plan with fewer chunks
+ * (slower, other roundings), where that plan fits. */
 size_t gla_decode_workspace_size(const gla_decode_params* p, int is_gta);
 
 /* ---- the two projections around the attention -----------------------------------

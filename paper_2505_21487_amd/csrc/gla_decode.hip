@@ -81,7 +81,7 @@ int flex_variant(const gla_decode_params* p, int mode) {
   return -1;
 }
 
-bool flex_plan(const gla_decode_params* p, int mode, const KeyCache* kc, FlexPlan* plan) {
+bool flex_plan(const gla_decode_params* p, int mode, const KeyCache* kc, bool lean, FlexPlan* plan) {  // (lean: as in tuned_plan)
   plan->id = flex_variant(p, mode);
   if (plan->id < 0) return false;
   const int ps = p->page_size;
@@ -119,7 +119,7 @@ bool flex_plan(const gla_decode_params* p, int mode, const KeyCache* kc, FlexPla
     // compute unit, of two up to half of that.  us per call: GTA-4 d_h 64, batch 1 x 200 12.9 -> 11.0, 4 x 100 to 900
     // 16.5 -> 12.5; GQA-4 batch 2 x 300 18.1 -> 11.9.  Few sequences only: a batch of many short ones has its
     // parallelism already, and cut further it pays in merges (64 x 200: 14.1 us, 15.9 with 112 chunks).
-    if (p->batch <= 4)
+    if (!lean && p->batch <= 4)
       by_length = std::max({by_length, std::min(bound / 4, waves / plan->strands), std::min(bound / 2, waves / 2 / plan->strands)});
     chunks = std::min<int64_t>((4 * waves + plan->strands - 1) / plan->strands, by_length);
   }
@@ -136,11 +136,11 @@ size_t flex_workspace(const gla_decode_params* p, const FlexPlan& plan) {
          align_up((size_t)p->batch * plan.strands * 2 * sizeof(int32_t), 256);
 }
 
-int generic_splits(const gla_decode_params* p) {
+int generic_splits(const gla_decode_params* p, bool lean) {
   const int64_t rows = std::max<int64_t>(1, (int64_t)p->batch * p->q_len * p->num_q_heads);
   int64_t s = p->num_splits > 0 ? p->num_splits : (4096 + rows - 1) / rows;
   s = std::min<int64_t>(s, p->max_pages_per_seq);
-  if (p->num_splits <= 0) {
+  if (p->num_splits <= 0 && !lean) {
     // The MFMA variant works on 64 rows at once: ranges for two workgroups per compute unit, of at least 256 tokens
     // (a partial costs as much as a few tiles of 32: 18 units of up to 4500 tokens take 39 us in 17 ranges, 46 in 28),
     // of at least 64 while the grid is small (2 units of 256 tokens: 19 us in four ranges, 49 in one), within 64
@@ -164,7 +164,7 @@ int select_kernel(const gla_decode_params* p, int is_gta, const KeyCache* kc) {
   if (rc != GLA_OK) return rc;
   const bool tuned_ok = is_gta != kModeGqa && tuned_supported(p, is_gta);
   FlexPlan fp;
-  const bool flex_ok = !tuned_ok && flex_plan(p, is_gta, kc, &fp);
+  const bool flex_ok = !tuned_ok && flex_plan(p, is_gta, kc, false, &fp);
   if (p->impl != GLA_IMPL_GENERIC) {
     if (tuned_ok) return GLA_IMPL_TUNED;
     if (flex_ok) return kImplFlex;
@@ -177,8 +177,8 @@ int select_impl(const gla_decode_params* p, int is_gta) {
   return k == kImplFlex ? GLA_IMPL_TUNED : k;
 }
 
-size_t generic_workspace(const gla_decode_params* p) {
-  const int s = generic_splits(p);
+size_t generic_workspace(const gla_decode_params* p, bool lean) {
+  const int s = generic_splits(p, lean);
   if (s == 1) return 0;
   const size_t rows = (size_t)p->batch * p->q_len * p->num_q_heads;
   return align_up((size_t)s * rows * p->d_v * sizeof(float), 256) +
@@ -322,8 +322,8 @@ void launch_generic_mfma(const gla_decode_params* p, DevParams& d, hipStream_t s
   }
 }
 
-int launch_generic(const gla_decode_params* p, const KeyCache* kc, DevParams& d, hipStream_t st, hipEvent_t* ev) {
-  const int s = generic_splits(p);
+int launch_generic(const gla_decode_params* p, const KeyCache* kc, bool lean, DevParams& d, hipStream_t st, hipEvent_t* ev) {
+  const int s = generic_splits(p, lean);
   d.splits = s;
   d.pages_per_split = (p->max_pages_per_seq + s - 1) / s;
   const size_t rows = (size_t)p->batch * p->q_len * p->num_q_heads;
@@ -349,13 +349,26 @@ int launch_generic(const gla_decode_params* p, const KeyCache* kc, DevParams& d,
   return GLA_OK;
 }
 
-size_t workspace_need(const gla_decode_params* p, int is_gta, int kernel, const KeyCache* kc) {
-  if (kernel == GLA_IMPL_TUNED) return tuned_workspace(p, is_gta);
+size_t workspace_need(const gla_decode_params* p, int is_gta, int kernel, const KeyCache* kc, bool lean) {
+  if (kernel == GLA_IMPL_TUNED) return tuned_workspace(p, is_gta, lean);
   if (kernel == kImplFlex) {
     FlexPlan fp;
-    return flex_plan(p, is_gta, kc, &fp) ? flex_workspace(p, fp) : 0;
+    return flex_plan(p, is_gta, kc, lean, &fp) ? flex_workspace(p, fp) : 0;
   }
-  return generic_workspace(p);
+  return generic_workspace(p, lean);
+}
+
+// What gla_decode_workspace_size() reports: never less than for a smaller batch on the MFMA kernels, so that a program
+// may size its workspace once, for its largest batch.  (Batches of up to four may be cut into more chunks than larger
+// ones, see tuned_plan and flex_plan; among themselves, and beyond four, the need grows with the batch.)
+size_t workspace_reported(const gla_decode_params* p, int is_gta, int kernel) {
+  size_t need = workspace_need(p, is_gta, kernel, nullptr, false);
+  if (p->batch > 4 && kernel != GLA_IMPL_GENERIC) {
+    gla_decode_params four = *p;
+    four.batch = 4;
+    need = std::max(need, workspace_need(&four, is_gta, kernel, nullptr, false));
+  }
+  return need;
 }
 
 int run(const gla_decode_params* p, int is_gta, hipEvent_t* ev, const KeyCache* kc = nullptr) {
@@ -365,7 +378,11 @@ int run(const gla_decode_params* p, int is_gta, hipEvent_t* ev, const KeyCache* 
   if (rc != GLA_OK) return rc;
   if (is_gta == kModeGqa && p->batch > 0 && (!kc || !kc->ptr)) return GLA_ERR_INVALID_ARG;
   if (p->batch == 0) return GLA_OK;
-  const size_t need = workspace_need(p, is_gta, impl, kc);
+  // A workspace that is too small for the plan of this call may do for the lean one: the call then runs on that (more
+  // slowly, and with the roundings of its chunks) and is not refused.
+  size_t need = workspace_need(p, is_gta, impl, kc, false);
+  const bool lean = need > p->workspace_bytes;
+  if (lean) need = workspace_need(p, is_gta, impl, kc, true);
   if (need > 0 && (!p->workspace || p->workspace_bytes < need)) return GLA_ERR_WORKSPACE_TOO_SMALL;
   if (need > 0 && ((uintptr_t)p->workspace & 255u)) return GLA_ERR_INVALID_ARG;
   DevParams d;
@@ -375,13 +392,13 @@ int run(const gla_decode_params* p, int is_gta, hipEvent_t* ev, const KeyCache* 
     for (int i = 0; i < 3; ++i) d.k_s[i] = kc->stride[i];
   }
   hipStream_t st = (hipStream_t)p->stream;
-  if (impl == GLA_IMPL_TUNED) return tuned_launch(p, is_gta, d, st, ev);
+  if (impl == GLA_IMPL_TUNED) return tuned_launch(p, is_gta, lean, d, st, ev);
   if (impl == kImplFlex) {
     FlexPlan fp;
-    if (!flex_plan(p, is_gta, kc, &fp)) return GLA_ERR_UNSUPPORTED_SHAPE;
+    if (!flex_plan(p, is_gta, kc, lean, &fp)) return GLA_ERR_UNSUPPORTED_SHAPE;
     return launch_flex(p, fp, d, st, ev);
   }
-  return launch_generic(p, kc, d, st, ev);
+  return launch_generic(p, kc, lean, d, st, ev);
 }
 
 // ---- fixed scratch buffer of the allocation-free entry point -------------------
@@ -414,8 +431,8 @@ int scratch_of_current_device(void** out) {
 int run_noalloc(const gla_decode_params* p, int is_gta) {
   const int impl = select_impl(p, is_gta);
   if (impl < 0) return impl;
-  const size_t need = workspace_need(p, is_gta, select_kernel(p, is_gta, nullptr), nullptr);
-  if (need > kScratchBytes) return GLA_ERR_WORKSPACE_TOO_SMALL;  // beyond the fixed buffer: use gla_decode / gta_decode
+  const int kernel = select_kernel(p, is_gta, nullptr);
+  if (std::min(workspace_need(p, is_gta, kernel, nullptr, false), workspace_need(p, is_gta, kernel, nullptr, true)) > kScratchBytes) return GLA_ERR_WORKSPACE_TOO_SMALL;  // beyond the fixed buffer: use gla_decode / gta_decode
   gla_decode_params q = *p;
   void* ptr = nullptr;
   if (p->batch > 0) {
@@ -607,7 +624,7 @@ size_t gla_decode_workspace_size(const gla_decode_params* p, int is_gta) {
   const int impl = gla::select_kernel(p, is_gta, nullptr);
   if (impl < 0) return 0;
   // A little more than nothing, so callers can always pass a real buffer.
-  return std::max<size_t>(gla::workspace_need(p, is_gta, impl, nullptr), 256);
+  return std::max<size_t>(gla::workspace_reported(p, is_gta, impl), 256);
 }
 
 int gqa_decode(const gla_decode_params* p, const void* key_cache, const int64_t* key_stride) {

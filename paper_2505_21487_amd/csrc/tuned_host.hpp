@@ -68,7 +68,9 @@ inline bool wide_pays(const gla_decode_params* p, int rows_group) {
   return false;
 }
 
-inline bool tuned_plan(const gla_decode_params* p, int is_gta, TunedPlan* plan) {
+// lean: the plan a call gets whose workspace is too small for the one it would get otherwise (see run() in
+// gla_decode.hip): no chunks of fewer than kMinChunkTiles tiles, no eight-wave kernel.
+inline bool tuned_plan(const gla_decode_params* p, int is_gta, bool lean, TunedPlan* plan) {
   const int ps = p->page_size;
   if (ps < 1 || ps > 64 || (ps & (ps - 1))) return false;  // 64, 32, ..., 1 tokens
   if (p->d_rope != 64 && p->d_rope != 48 && p->d_rope != 32) return false;  // (fewer than 64: padded inside the kernel)
@@ -92,7 +94,7 @@ inline bool tuned_plan(const gla_decode_params* p, int is_gta, TunedPlan* plan) 
   // as four waves allow (they share one RoPE-key tile)
   // A latent of 512 dims needs two waves per row slab: 32 rows x 512 fp32
   // output accumulators alone would fill a wave's accumulation registers.
-  plan->wide = wide_pays(p, rows_group);
+  plan->wide = !lean && wide_pays(p, rows_group);
   const int ks = plan->wide ? p->d_v / 128 : p->d_v > 256 ? 2 : 1;
   const int wpg = plan->wide ? 8 / ks : rows_group <= 32 ? 1 : ((rows_group <= 64 || ks == 2) ? 2 : 4);
   int ng = plan->wide ? 1 : 4 / (wpg * ks);
@@ -136,10 +138,10 @@ inline bool tuned_plan(const gla_decode_params* p, int is_gta, TunedPlan* plan) 
     // 21.9 -> 20.4; further (one tile up to a quarter) loses again, 22.8 at 2048; with the grid full (batch 64 x 300)
     // two tiles take 36.6 against 34.2 with four.
     // (Few sequences only: a batch of many short ones has its parallelism already, and cut further it pays in merges.)
-    if (!plan->wide && p->batch <= 4) by_length = std::max({by_length, std::min(bound / 2, resident / 4), std::min(bound, resident / 8)});
+    if (!lean && !plan->wide && p->batch <= 4) by_length = std::max({by_length, std::min(bound / 2, resident / 4), std::min(bound, resident / 8)});
     plan->num_chunks = (int)std::max<int64_t>(1, std::min<int64_t>(by_length, resident));
   }
-  plan->slot_floats = (size_t)plan->rows * p->d_v + (size_t)32 * ng * wpg * ks;
+  plan->slot_floats = (size_t)plan->rows * p->d_v + (size_t)32 * ng * wpg * (plan->wide ? ks / 2 : ks);
   // upper bound of the batch's cache bytes (the lengths are known on the device only) against the chip's
   // last-level cache
   plan->stream = bound * tok * 2 * ((int64_t)ng * p->d_v + p->d_rope) > kLastLevelCacheBytes;
@@ -148,7 +150,7 @@ inline bool tuned_plan(const gla_decode_params* p, int is_gta, TunedPlan* plan) 
 
 inline bool tuned_supported(const gla_decode_params* p, int is_gta) {
   TunedPlan plan;
-  return tuned_plan(p, is_gta, &plan);
+  return tuned_plan(p, is_gta, false, &plan);
 }
 
 // Workspace: two partial slots per chunk, then per unit the chunk range holding it.
@@ -156,9 +158,9 @@ inline size_t tuned_slots_bytes(const TunedPlan& plan) {
   return (((size_t)plan.num_chunks * plan.mb * 2 * plan.slot_floats * sizeof(float)) + 255) & ~(size_t)255;
 }
 
-inline size_t tuned_workspace(const gla_decode_params* p, int is_gta) {
+inline size_t tuned_workspace(const gla_decode_params* p, int is_gta, bool lean) {
   TunedPlan plan;
-  if (!tuned_plan(p, is_gta, &plan)) return 0;
+  if (!tuned_plan(p, is_gta, lean, &plan)) return 0;
   return tuned_slots_bytes(plan) + (size_t)plan.units * 2 * sizeof(int32_t);
 }
 
@@ -169,10 +171,10 @@ int tuned_launch_512(const TunedPlan& plan, const DevParams& d, hipStream_t st, 
 int tuned_launch_128(const TunedPlan& plan, const DevParams& d, hipStream_t st, hipEvent_t* ev);
 int wide_launch(const TunedPlan& plan, const DevParams& d, hipStream_t st, hipEvent_t* ev);
 
-inline int tuned_launch(const gla_decode_params* p, int is_gta, DevParams& d, hipStream_t st,
+inline int tuned_launch(const gla_decode_params* p, int is_gta, bool lean, DevParams& d, hipStream_t st,
                         hipEvent_t* ev) {
   TunedPlan plan;
-  if (!tuned_plan(p, is_gta, &plan)) return GLA_ERR_UNSUPPORTED_SHAPE;
+  if (!tuned_plan(p, is_gta, lean, &plan)) return GLA_ERR_UNSUPPORTED_SHAPE;
   d.ws_out = (float*)p->workspace;
   d.ws_lse = (float*)((char*)p->workspace + tuned_slots_bytes(plan));  // per-unit chunk ranges (int32 pairs)
   d.num_chunks = plan.num_chunks;

@@ -19,7 +19,7 @@ static int launch_wide(const TunedPlan& plan, const DevParams& d, hipStream_t st
   }
   if (hipGetLastError() != hipSuccess) return GLA_ERR_LAUNCH;
   if (ev) (void)hipEventRecord(ev[1], st);
-  return launch_tuned_combine<DV, 1, W::NSL, W::E, W::TT>(plan, d, st, ev);
+  return launch_tuned_combine<DV, 1, W::NSL, W::E / 2, kTok>(plan, d, st, ev);  // (the four-wave kernel's: the same partials)
 }
 
 int wide_launch(const TunedPlan& plan, const DevParams& d, hipStream_t st, hipEvent_t* ev) {

@@ -63,7 +63,8 @@ struct WideTraits {
   static constexpr int OFF_FLAG = OFF_MREF + NSL * 64 * 4;                  // one word per wave
   static constexpr int OFF_WIN = OFF_FLAG + 64;                             // page ids: two windows of 64 per wave
   static constexpr int kSmem = OFF_WIN + 8 * 2 * 256;
-  static constexpr size_t kSlotFloats = (size_t)kRows * DV + 32 * 8;
+  // partials as the four-wave kernel leaves them: the same block order, a log-sum-exp for every second wave
+  static constexpr size_t kSlotFloats = (size_t)kRows * DV + 32 * 4;
   static_assert(DV == 256 || DV == 512, "state dims");
   static_assert(!PP || NST == 3, "half a tile apart a tile is in use for three half-steps: two stages are too few");
   static_assert(kSmem <= 160 * 1024, "LDS capacity");
@@ -703,8 +704,8 @@ __global__ __launch_bounds__(512) void wide_main_kernel(DevParams p) {
         span.y = (c0 + (k - seg_n) + cur.tiles_b - 1) / chunk;
         ((int2*)p.ws_lse)[(cur.b * UPB + cur.ub) * MB + mb_wg] = span;
       }
-      if (hi == 0) {
-        if (!complete) slot[(size_t)TT::kRows * DV + wave * 32 + col] = lse;
+      if (hi == 0 && (pe & 1) == 0) {
+        if (!complete) slot[(size_t)TT::kRows * DV + (wave >> 1) * 32 + col] = lse;
         else if (row_valid && pe == 0) p.lse[((int64_t)cur.b * p.T + t) * p.h_q + h] = lse;
       }
 #pragma unroll
