@@ -151,26 +151,31 @@ __global__ __launch_bounds__(64) void generic_combine_kernel(DevParams p) {
     // (z == 0: no key in any range; NaN where every range that has keys is NaN)
     if (lane == 0) p.lse[row] = z == 0.f ? -INFINITY : m + logf(z);
     const float w = z > 0.f ? e / z : 0.f;
+    const uint64_t with_keys = __ballot(ls != -INFINITY);
+    const int n = 64 - __clzll((long long)with_keys);  // ranges up to the last one with a key
     for (int d0 = 0; d0 < p.d_v; d0 += 256) {  // (every lane stays in the loop: the weights are read across lanes)
       const bool mine = d0 + 4 * lane < p.d_v;
       const int d = mine ? d0 + 4 * lane : 0;
       float acc[4] = {0.f, 0.f, 0.f, 0.f};
       const float* src = p.ws_out + (int64_t)row * p.d_v + d;
-      for (int s = 0; s < p.splits; s += 8) {
+      int s = 0;
+      do {  // (the first loads need not wait for the log-sum-exps)
         float4 v[8];
 #pragma unroll
         for (int u = 0; u < 8; ++u) v[u] = *(const float4*)(src + (int64_t)min(s + u, p.splits - 1) * rows * p.d_v);
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
-          // (a range without keys left zeros; past the last range its values once more, dropped: not multiplied by zero)
-          const bool live = s + u < p.splits;
-          const float ws = __shfl(w, live ? s + u : 0, 64);
-          acc[0] += live ? ws * v[u].x : 0.f;
-          acc[1] += live ? ws * v[u].y : 0.f;
-          acc[2] += live ? ws * v[u].z : 0.f;
-          acc[3] += live ? ws * v[u].w : 0.f;
+          // (where there was no key, or is no range, there may be anything: left out, not multiplied by zero)
+          if ((with_keys >> (s + u)) & 1) {
+            const float ws = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, w), s + u));
+            acc[0] += ws * v[u].x;
+            acc[1] += ws * v[u].y;
+            acc[2] += ws * v[u].z;
+            acc[3] += ws * v[u].w;
+          }
         }
-      }
+        s += 8;
+      } while (s < n);
       if (!mine) continue;
 #pragma unroll
       for (int e2 = 0; e2 < 4; ++e2) {

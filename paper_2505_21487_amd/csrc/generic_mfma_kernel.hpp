@@ -23,6 +23,21 @@
 
 namespace gla {
 
+// Tokens per range, for every sequence the same: the caller's, else the batch's longest sequence in ranges of at least
+// 256 tokens (a partial costs as much as a few tiles: 18 units of up to 4500 tokens take 39 us in 17 ranges, 46 in 28),
+// of at least 64 while the grid is small (2 units of 256 tokens: 19 us in four ranges, 49 in one).  By the lengths
+// and not by the page table's row length, which is all the host knows: in a table for the longest context every sequence
+// would lie in its first range (nine sequences of up to 4500 tokens, table for 72000: 213 us, 41 this way).
+// (len: the length of sequence `lane`, loaded ahead)
+__device__ __forceinline__ int range_tokens(const DevParams& p, int lane, int len) {
+  if (p.split_tokens > 0) return p.split_tokens;
+  int longest = len;
+  for (int i = lane + 64; i < p.B; i += 64) longest = max(longest, p.seq_lens[i]);
+  longest = wave_max(max(longest, 1));
+  const int n = max(1, min(p.splits, max((longest + 255) >> 8, min((longest + 63) >> 6, p.small_ranges))));
+  return ((longest + n - 1) / n + 31) & ~31;
+}
+
 template <int DVB, int WR, bool SEPK>
 __global__ __launch_bounds__(64 * WR) void generic_mfma_kernel(DevParams p) {
   constexpr int kMaxChunks = SEPK ? 2 * DVB / 8 : (DVB + 128) / 8;  // chunks per cache row (RoPE keys of up to 128 dims)
@@ -44,10 +59,8 @@ __global__ __launch_bounds__(64 * WR) void generic_mfma_kernel(DevParams p) {
   const int t = Rc / p.g_q, h = g * p.g_q + (Rc - t * p.g_q);
   const int row = (b * p.T + t) * p.h_q + h;
 
-  const int L = p.seq_lens[b];
+  const int L = p.seq_lens[b], len_lane = lane < p.B ? p.seq_lens[lane] : 0;
   const int n_vis = p.causal ? L - p.T + 1 + t : L;  // visible keys of this lane's row
-  const int j_begin = (int)min((int64_t)split * p.split_tokens, (int64_t)max(L, 0));
-  const int j_end = (int)min((int64_t)j_begin + p.split_tokens, (int64_t)max(L, 0));
 
   // ---- chunks of a cache row in LDS: value first, then RoPE key or key
   const int cv = p.d_v >> 3, ck = p.d_n >> 3, cr = p.d_r >> 3;
@@ -71,6 +84,15 @@ __global__ __launch_bounds__(64 * WR) void generic_mfma_kernel(DevParams p) {
       for (int ks = 0; ks < NKR; ++ks) qr[ks] = 4 * ks + q < cr ? *(const u32x4_t*)(srcr + (4 * ks + q) * 8) : u32x4_t{0, 0, 0, 0};
     }
   }
+  // ---- this range (behind the loads of the queries, which need no lengths)
+  const int span = p.splits == 1 ? 1 << 30 : range_tokens(p, lane, len_lane);
+  const int j_begin = (int)min((int64_t)split * span, (int64_t)max(L, 0));
+  const int j_end = (int)min((int64_t)j_begin + span, (int64_t)max(L, 0));
+  if (p.splits > 1 && j_begin >= j_end) {  // nothing here: the merge needs no values
+    if (q == 0 && row_valid) p.ws_lse[(int64_t)split * p.B * p.T * p.h_q + row] = -INFINITY;
+    return;
+  }
+
   f32x4_t o[NDB];
 #pragma unroll
   for (int d = 0; d < NDB; ++d) o[d] = f32x4_t{0.f, 0.f, 0.f, 0.f};
@@ -226,22 +248,7 @@ __global__ __launch_bounds__(64 * WR) void generic_mfma_kernel(DevParams p) {
   const float inv = empty ? 0.f : 1.f / l;
   const float lse = empty ? -INFINITY : (m + log2f(l)) * 0.6931471805599453f;
 
-  // Is every number of this row finite?  If not, the scalar loop works the row out again below: with NaN or infinities in
-  // the cache the products above give too much NaN.  They multiply keys a row does not see (hidden by causality, seen by
-  // later rows of the tile) by a weight of zero, and an infinite value by each of the three parts of its weight, zero and
-  // negative ones among them.  (The look costs 0.4 us of the 39 above.)
-  f32x4_t probes = {l, 0.f, 0.f, 0.f};  // (blocks past the value's dims repeat the last one's numbers)
-#pragma unroll
-  for (int d = 0; d < NDB; ++d)
-#pragma unroll
-    for (int e = 0; e < 4; ++e) probes[e] = __builtin_fmaf(o[d][e], 0.f, probes[e]);
-  const float probe = (probes[0] + probes[1]) + (probes[2] + probes[3]);
-  const bool odd = empty ? probe != 0.f : !(probe > 0.f && probe < INFINITY);
-  uint64_t odd_rows = __ballot(odd && row_valid);
-  odd_rows |= odd_rows >> 32;
-  odd_rows = (odd_rows | odd_rows >> 16) & 0xffff;
-
-  if (row_valid && !((odd_rows >> r16) & 1)) {
+  if (row_valid) {
     if (p.splits == 1) {
       if (q == 0) p.lse[row] = lse;
       const int64_t ob = b * p.out_s[0] + t * p.out_s[1] + h * p.out_s[2];
@@ -268,7 +275,23 @@ __global__ __launch_bounds__(64 * WR) void generic_mfma_kernel(DevParams p) {
         if (16 * d < p.d_v) *(f32x4_t*)(dst + 16 * d + 4 * q) = o[d] * inv;
     }
   }
+
+  // Was every number of this row finite?  If not, the scalar loop works the row out again: with NaN or infinities in
+  // the cache the products above give too much NaN.  They multiply keys a row does not see (hidden by causality, seen by
+  // later rows of the tile) by a weight of zero, and an infinite value by each of the three parts of its weight, zero and
+  // negative ones among them.
+  f32x4_t probes = {l, 0.f, 0.f, 0.f};  // (blocks past the value's dims repeat the last one's numbers)
+#pragma unroll
+  for (int d = 0; d < NDB; ++d)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) probes[e] = __builtin_fmaf(o[d][e], 0.f, probes[e]);
+  const float probe = (probes[0] + probes[1]) + (probes[2] + probes[3]);
+  const bool odd = empty ? probe != 0.f : !(probe > 0.f && probe < INFINITY);
+  uint64_t odd_rows = __ballot(odd && row_valid);
+  odd_rows |= odd_rows >> 32;
+  odd_rows = (odd_rows | odd_rows >> 16) & 0xffff;
   if (odd_rows) {
+    wait_vmcnt<0>();  // (what was stored above is stored)
     // (the arguments once more, through a pointer the compiler cannot see through: what only this loop needs is loaded
     // here and not kept, or spilled, across the kernel)
     auto* kernarg = (__attribute__((address_space(4))) const void*)__builtin_amdgcn_kernarg_segment_ptr();

@@ -136,16 +136,19 @@ size_t flex_workspace(const gla_decode_params* p, const FlexPlan& plan) {
          align_up((size_t)p->batch * plan.strands * 2 * sizeof(int32_t), 256);
 }
 
+// Workgroups of the generic MFMA kernel per range of tokens, about (64 rows each).
+int64_t generic_units(const gla_decode_params* p) {
+  return std::max<int64_t>(1, (int64_t)p->batch * p->num_groups * (((int64_t)p->num_q_heads / p->num_groups * p->q_len + 63) / 64));
+}
+
 int generic_splits(const gla_decode_params* p, bool lean) {
   const int64_t rows = std::max<int64_t>(1, (int64_t)p->batch * p->q_len * p->num_q_heads);
   int64_t s = p->num_splits > 0 ? p->num_splits : (4096 + rows - 1) / rows;
   s = std::min<int64_t>(s, p->max_pages_per_seq);
   if (p->num_splits <= 0 && !lean) {
-    // The MFMA variant works on 64 rows at once: ranges for two workgroups per compute unit, of at least 256 tokens
-    // (a partial costs as much as a few tiles of 32: 18 units of up to 4500 tokens take 39 us in 17 ranges, 46 in 28),
-    // of at least 64 while the grid is small (2 units of 256 tokens: 19 us in four ranges, 49 in one), within 64
-    // ranges and 64 MB of partials.
-    const int64_t units = std::max<int64_t>(1, (int64_t)p->batch * p->num_groups * (((int64_t)p->num_q_heads / p->num_groups * p->q_len + 63) / 64));
+    // The MFMA variant works on 64 rows at once: ranges for two workgroups per compute unit, no more than the longest
+    // sequence the table can hold is cut into (range_tokens), within 64 ranges and 64 MB of partials.
+    const int64_t units = generic_units(p);
     const int64_t tokens = (int64_t)p->max_pages_per_seq * p->page_size;
     int64_t want = (2 * (int64_t)device_cu_count() + units - 1) / units;
     want = std::min(want, std::max((tokens + 255) / 256, std::min((tokens + 63) / 64, 64 / units)));
@@ -304,7 +307,8 @@ void launch_generic_mfma_waves(int rows_group, int64_t units, int splits, hipStr
 
 void launch_generic_mfma(const gla_decode_params* p, DevParams& d, hipStream_t st) {
   const int64_t tokens = (int64_t)p->max_pages_per_seq * p->page_size;
-  d.split_tokens = (int32_t)(((tokens + d.splits - 1) / d.splits + 31) / 32 * 32);
+  if (p->num_splits > 0) d.split_tokens = (int32_t)(((tokens + d.splits - 1) / d.splits + 31) / 32 * 32);
+  else d.small_ranges = (int32_t)(64 / generic_units(p));
   d.fd_page = make_fastdiv((uint32_t)p->page_size);
   const bool sepk = d.kstate != nullptr;
   d.fd_cpr = make_fastdiv((uint32_t)(p->d_v / 8 + (sepk ? p->d_nope : p->d_rope) / 8));

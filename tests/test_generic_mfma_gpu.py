@@ -126,3 +126,31 @@ def test_infinite_values(d_v, splits, aligned):
         wide[..., 1:1 + p.d_n] = dp.q_nope
         dp.q_nope = wide[..., 1:1 + p.d_n]
     _same_with_special_values(p, dp=dp, num_splits=splits)
+
+
+def _partial_lse(p, **kw):
+    """Log-sum-exps [range][batch, position, head] a call leaves in its workspace (NaN: not written), after the check of
+    its result."""
+    dp = DeviceProblem(p, poison_unused=True)
+    out = torch.empty(p.B, p.T, p.h_q, p.d_v, dtype=torch.float32, device="cuda")
+    lse = torch.empty(p.B, p.T, p.h_q, dtype=torch.float32, device="cuda")
+    prm = gla.make_params(*dp.args()[:6], p.scale, out=out, lse=lse, workspace=None, impl=gla.GLA_IMPL_GENERIC, **kw)
+    need = gla.gla_decode_workspace_size(prm, p.kind == "gta")
+    ws = torch.full((need,), 0xFF, dtype=torch.uint8, device="cuda")
+    _close(p, dp, workspace=ws, **kw)
+    rows = p.B * p.T * p.h_q
+    up = lambda n: (n + 255) // 256 * 256
+    splits = next(s for s in range(1, 4097) if up(s * rows * p.d_v * 4) + up(s * rows * 4) == need)
+    part = ws[up(splits * rows * p.d_v * 4):][:splits * rows * 4].view(torch.float32)
+    return part.view(splits, p.B, p.T, p.h_q).cpu().numpy()
+
+
+@pytest.mark.parametrize("extra_cols", [0, 1000])
+def test_ranges_go_by_the_longest_sequence(extra_cols):
+    """However wide the page table: the longest sequence is cut into ranges of 256 tokens or a little more."""
+    lens = [4500, 300, 1, 0, 2100]
+    p = make_problem("ranges", seq_lens=lens, T=1, h_q=128, h_c=2, d_v=256, page_size=128, seed=8700, num_pages=64, poison_tail=True,
+                     extra_table_cols=extra_cols)
+    used = np.isfinite(_partial_lse(p)).sum(axis=0)[:, 0]
+    for b, n in enumerate(lens):
+        assert (used[b] == used[b, 0]).all() and -(-n // 320) <= used[b, 0] <= -(-n // 256), (b, used[b, 0])
