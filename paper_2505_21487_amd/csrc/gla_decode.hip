@@ -141,22 +141,26 @@ int64_t generic_units(const gla_decode_params* p) {
   return std::max<int64_t>(1, (int64_t)p->batch * p->num_groups * (((int64_t)p->num_q_heads / p->num_groups * p->q_len + 63) / 64));
 }
 
-int generic_splits(const gla_decode_params* p, bool lean) {
+// Ranges of the generic route.  The scalar kernel has one wave per row and range: about 4096 of them.
+int scalar_splits(const gla_decode_params* p) {
   const int64_t rows = std::max<int64_t>(1, (int64_t)p->batch * p->q_len * p->num_q_heads);
   int64_t s = p->num_splits > 0 ? p->num_splits : (4096 + rows - 1) / rows;
   s = std::min<int64_t>(s, p->max_pages_per_seq);
-  if (p->num_splits <= 0 && !lean) {
-    // The MFMA variant works on 64 rows at once: ranges for two workgroups per compute unit, no more than the longest
-    // sequence the table can hold is cut into (range_tokens), within 64 ranges and 64 MB of partials.
-    const int64_t units = generic_units(p);
-    const int64_t tokens = (int64_t)p->max_pages_per_seq * p->page_size;
-    int64_t want = (2 * (int64_t)device_cu_count() + units - 1) / units;
-    want = std::min(want, std::max((tokens + 255) / 256, std::min((tokens + 63) / 64, 64 / units)));
-    want = std::min<int64_t>(want, (64ll << 20) / std::max<int64_t>(1, rows * (p->d_v + 1) * 4));
-    s = std::max<int64_t>(s, std::min<int64_t>(want, 64));
-  }
-  s = std::min<int64_t>(s, 65535);
-  return (int)std::max<int64_t>(s, 1);
+  return (int)std::max<int64_t>(std::min<int64_t>(s, 65535), 1);
+}
+
+// The MFMA variant works on 64 rows at once: ranges for two workgroups per compute unit, no more than the longest
+// sequence the table can hold is cut into (range_tokens), within 64 ranges (one per lane of the merge; beyond them it
+// goes through the ranges one by one) and 64 MB of partials.  16 heads, one sequence of 30000 tokens: 93 us in 64
+// ranges, 340 in the 235 that the scalar kernel's rule makes of it.
+int mfma_splits(const gla_decode_params* p) {
+  if (p->num_splits > 0) return scalar_splits(p);
+  const int64_t rows = std::max<int64_t>(1, (int64_t)p->batch * p->q_len * p->num_q_heads);
+  const int64_t units = generic_units(p), tokens = (int64_t)p->max_pages_per_seq * p->page_size;
+  int64_t want = (2 * (int64_t)device_cu_count() + units - 1) / units;
+  want = std::min(want, std::max((tokens + 255) / 256, std::min((tokens + 63) / 64, 64 / units)));
+  want = std::min<int64_t>(want, (64ll << 20) / std::max<int64_t>(1, rows * (p->d_v + 1) * 4));
+  return (int)std::max<int64_t>(std::min<int64_t>(want, 64), 1);
 }
 
 // Internal choice: GLA_IMPL_TUNED (the tuned kernel), kImplFlex (the second MFMA kernel, reported to
@@ -180,12 +184,36 @@ int select_impl(const gla_decode_params* p, int is_gta) {
   return k == kImplFlex ? GLA_IMPL_TUNED : k;
 }
 
-size_t generic_workspace(const gla_decode_params* p, bool lean) {
-  const int s = generic_splits(p, lean);
-  if (s == 1) return 0;
+// Does the MFMA variant of the generic kernel take this call?  Every 16-byte piece it loads or stores must be
+// aligned: dims in steps of eight (value: sixteen), strides likewise, aligned bases.  (It computes what the scalar
+// kernel computes, to the same precision: no size at which the scalar one is the better choice.)
+bool generic_mfma_dims(const gla_decode_params* p) {
+  if (p->d_v % 16 || p->d_nope % 8 || p->d_rope % 8 || std::max(p->d_v, p->d_nope) > 512) return false;
+  return (int64_t)p->max_pages_per_seq * p->page_size <= (1ll << 30);  // (token indices and divisions in 32 bits)
+}
+bool generic_mfma_ok(const gla_decode_params* p, const KeyCache* kc) {
+  if (!generic_mfma_dims(p)) return false;
+  for (int i = 0; i < 3; ++i) {
+    if (p->q_nope_stride[i] % 8 || p->state_stride[i] % 8 || p->out_stride[i] % 4) return false;
+    if (p->d_rope > 0 && (p->q_rope_stride[i] % 8 || (i < 2 && p->rope_stride[i] % 8))) return false;
+    if (kc && kc->stride[i] % 8) return false;
+  }
+  uintptr_t bases = (uintptr_t)p->q_nope | (uintptr_t)p->state_cache | (uintptr_t)p->out;
+  if (p->d_rope > 0) bases |= (uintptr_t)p->q_rope | (uintptr_t)p->rope_cache;
+  if (kc) bases |= (uintptr_t)kc->ptr;
+  return (bases & 15u) == 0;
+}
+
+size_t generic_bytes(const gla_decode_params* p, int splits) {
+  if (splits == 1) return 0;
   const size_t rows = (size_t)p->batch * p->q_len * p->num_q_heads;
-  return align_up((size_t)s * rows * p->d_v * sizeof(float), 256) +
-         align_up((size_t)s * rows * sizeof(float), 256);
+  return align_up((size_t)splits * rows * p->d_v * sizeof(float), 256) + align_up((size_t)splits * rows * sizeof(float), 256);
+}
+
+// (lean: what the scalar kernel's ranges need; else enough for either kernel, as strides and pointers may not be known yet)
+size_t generic_workspace(const gla_decode_params* p, bool lean) {
+  const size_t scalar = generic_bytes(p, scalar_splits(p));
+  return lean || !generic_mfma_dims(p) ? scalar : std::max(scalar, generic_bytes(p, mfma_splits(p)));
 }
 
 int check_pointers(const gla_decode_params* p) {
@@ -278,23 +306,6 @@ void fill_dev(const gla_decode_params* p, DevParams* d) {
   d->stream_min_bytes = kLastLevelCacheBytes;
 }
 
-// Does the MFMA variant of the generic kernel take this call?  Every 16-byte piece it loads or stores must be
-// aligned: dims in steps of eight (value: sixteen), strides likewise, aligned bases.  (It computes what the scalar
-// kernel computes, to the same precision: no size at which the scalar one is the better choice.)
-bool generic_mfma_ok(const gla_decode_params* p, const KeyCache* kc) {
-  if (p->d_v % 16 || p->d_nope % 8 || p->d_rope % 8 || std::max(p->d_v, p->d_nope) > 512) return false;
-  if ((int64_t)p->max_pages_per_seq * p->page_size > (1ll << 30)) return false;  // (token indices and divisions in 32 bits)
-  for (int i = 0; i < 3; ++i) {
-    if (p->q_nope_stride[i] % 8 || p->state_stride[i] % 8 || p->out_stride[i] % 4) return false;
-    if (p->d_rope > 0 && (p->q_rope_stride[i] % 8 || (i < 2 && p->rope_stride[i] % 8))) return false;
-    if (kc && kc->stride[i] % 8) return false;
-  }
-  uintptr_t bases = (uintptr_t)p->q_nope | (uintptr_t)p->state_cache | (uintptr_t)p->out;
-  if (p->d_rope > 0) bases |= (uintptr_t)p->q_rope | (uintptr_t)p->rope_cache;
-  if (kc) bases |= (uintptr_t)kc->ptr;
-  return (bases & 15u) == 0;
-}
-
 template <int DVB, bool SEPK>
 void launch_generic_mfma_waves(int rows_group, int64_t units, int splits, hipStream_t st, const DevParams& d) {
   // waves per workgroup (16 rows each): as many as the rows of a group fill, at most four
@@ -327,7 +338,8 @@ void launch_generic_mfma(const gla_decode_params* p, DevParams& d, hipStream_t s
 }
 
 int launch_generic(const gla_decode_params* p, const KeyCache* kc, bool lean, DevParams& d, hipStream_t st, hipEvent_t* ev) {
-  const int s = generic_splits(p, lean);
+  const bool mfma = generic_mfma_ok(p, kc);
+  const int s = mfma && !lean ? mfma_splits(p) : scalar_splits(p);
   d.splits = s;
   d.pages_per_split = (p->max_pages_per_seq + s - 1) / s;
   const size_t rows = (size_t)p->batch * p->q_len * p->num_q_heads;
@@ -338,7 +350,7 @@ int launch_generic(const gla_decode_params* p, const KeyCache* kc, bool lean, De
   dim3 grid((unsigned)rows, (unsigned)s), block(64);
   const int nv = (std::max(p->d_v, p->d_nope) + 63) / 64;
   if (ev) (void)hipEventRecord(ev[0], st);
-  if (generic_mfma_ok(p, kc)) launch_generic_mfma(p, d, st);
+  if (mfma) launch_generic_mfma(p, d, st);
   else if (nv <= 2) hipLaunchKernelGGL(generic_main_kernel<2>, grid, block, 0, st, d);
   else if (nv <= 4) hipLaunchKernelGGL(generic_main_kernel<4>, grid, block, 0, st, d);
   else if (nv <= 8) hipLaunchKernelGGL(generic_main_kernel<8>, grid, block, 0, st, d);

@@ -154,3 +154,16 @@ def test_ranges_go_by_the_longest_sequence(extra_cols):
     used = np.isfinite(_partial_lse(p)).sum(axis=0)[:, 0]
     for b, n in enumerate(lens):
         assert (used[b] == used[b, 0]).all() and -(-n // 320) <= used[b, 0] <= -(-n // 256), (b, used[b, 0])
+
+
+@pytest.mark.parametrize("page", [128, 3])
+def test_small_batches_are_not_cut_too_finely(page):
+    """A few output rows: no more ranges than the merge takes in one go (the scalar kernel's rule alone would cut the
+    first of these into 235, the second into 256), so the rest of the workspace is left alone."""
+    p = make_problem("fine", seq_lens=[30000 if page == 128 else 2600], T=1, h_q=16, h_c=1, d_v=96, d_r=32, page_size=page, seed=8800, num_pages=1200)
+    dp = DeviceProblem(p, poison_unused=True)
+    out = torch.empty(1, 1, 16, 96, dtype=torch.float32, device="cuda")
+    prm = gla.make_params(*dp.args()[:6], p.scale, out=out, lse=torch.empty(1, 1, 16, device="cuda"), workspace=None)
+    ws = torch.full((gla.gla_decode_workspace_size(prm),), 0xFF, dtype=torch.uint8, device="cuda")
+    _close(p, dp, workspace=ws)
+    assert (ws[64 * 16 * (96 + 1) * 4:] == 0xFF).all() and (ws[:4] != 0xFF).any()
