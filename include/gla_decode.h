@@ -85,7 +85,7 @@ typedef struct gla_decode_params {
   int32_t page_size;          /* tokens per page                                               */
   int32_t max_pages_per_seq;  /* row length of page_table                                      */
   int32_t causal;             /* 1: row t sees j <= L_b - q_len + t ; 0: every j < L_b         */
-  int64_t num_pages;          /* pool size (used for argument checks only)                     */
+  int64_t num_pages;          /* pool size (argument checks; where > 0, also the kernel choice) */
 
   /* Strides are in ELEMENTS; the last dimension is always contiguous. */
   const void* q_nope;         /* bf16 [B, T, h_q, d_nope]                                      */
@@ -219,6 +219,14 @@ size_t gla_proj_workspace_size(const gla_proj_params* p, int sum_groups);
 /* Which implementation a call would run: GLA_IMPL_GENERIC or GLA_IMPL_TUNED,
  * or a negative error code.  Host only; pointer fields are ignored. */
 int gla_decode_select_impl(const gla_decode_params* p, int is_gta);
+
+/* Name of the kernel that does the main work of a call (static string; "" for a
+ * call that would be refused): "four-wave kernel", "eight-wave kernel",
+ * "second MFMA kernel", "generic MFMA kernel" or "scalar kernel".  Between the
+ * first two the device chooses by the batch's lengths: tiles32 is the sum over
+ * the sequences of ceil(length / 32) (ignored for the others).  Strides and, where
+ * set, pointers take part; a separate key cache counts as aligned.  Host only. */
+const char* gla_decode_kernel_name(const gla_decode_params* p, int is_gta, int64_t tiles32);
 
 /* Benchmark helper: enqueue `iters` calls (1..256) bracketed by HIP events on
  * p->stream, wait for them, and report the mean duration in microseconds of

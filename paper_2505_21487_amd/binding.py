@@ -27,7 +27,7 @@ GLA_DECODE_NOALLOC_SCRATCH_BYTES = 72 << 20
 
 EXPORTS = ("gla_decode", "gta_decode", "gqa_decode", "gla_decode_noalloc", "gla_absorb_query", "gla_output_proj",
            "gla_proj_workspace_size", "gla_decode_workspace_size", "gla_decode_select_impl",
-           "gla_decode_profile", "gla_decode_check_contents", "gla_status_string", "gla_decode_version")
+           "gla_decode_kernel_name", "gla_decode_profile", "gla_decode_check_contents", "gla_status_string", "gla_decode_version")
 
 
 class GlaDecodeParams(ctypes.Structure):
@@ -101,6 +101,8 @@ def load_library() -> ctypes.CDLL:
         lib.gla_decode_workspace_size.restype = ctypes.c_size_t
         lib.gla_decode_select_impl.argtypes = [P, ctypes.c_int]
         lib.gla_decode_select_impl.restype = ctypes.c_int
+        lib.gla_decode_kernel_name.argtypes = [P, ctypes.c_int, ctypes.c_int64]
+        lib.gla_decode_kernel_name.restype = ctypes.c_char_p
         lib.gla_decode_profile.argtypes = [P, ctypes.c_int, ctypes.c_int,
                                            ctypes.POINTER(ctypes.c_float),
                                            ctypes.POINTER(ctypes.c_float)]
@@ -141,6 +143,12 @@ def gla_decode_workspace_size(p: GlaDecodeParams, is_gta: bool = False) -> int:
 
 def gla_decode_select_impl(p: GlaDecodeParams, is_gta: bool = False) -> int:
     return int(load_library().gla_decode_select_impl(ctypes.byref(p), int(is_gta)))
+
+
+def gla_decode_kernel_name(p: GlaDecodeParams, is_gta: bool, seq_lens) -> str:
+    """Kernel that does the main work of a call with these lengths (a host sequence of ints); "" if it would be refused."""
+    tiles32 = sum((max(int(n), 0) + 31) // 32 for n in seq_lens)
+    return load_library().gla_decode_kernel_name(ctypes.byref(p), int(is_gta), tiles32).decode()
 
 
 def _strides(t: torch.Tensor, n: int):

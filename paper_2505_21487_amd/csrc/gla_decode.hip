@@ -19,7 +19,7 @@
 namespace gla {
 namespace {
 
-constexpr int kVersion = 104;  // 1.04: gqa_decode; second MFMA kernel for small head shapes
+constexpr int kVersion = 105;  // 1.05: gla_decode_kernel_name
 
 inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
@@ -417,6 +417,17 @@ int run(const gla_decode_params* p, int is_gta, hipEvent_t* ev, const KeyCache* 
   return launch_generic(p, kc, lean, d, st, ev);
 }
 
+// Name of the kernel that does a call's main work; tiles32: sum over the sequences of ceil(length / 32).
+const char* kernel_name(const gla_decode_params* p, int is_gta, int64_t tiles32) {
+  const int impl = select_kernel(p, is_gta, nullptr);
+  if (impl < 0) return "";
+  if (impl == kImplFlex) return "second MFMA kernel";
+  if (impl == GLA_IMPL_GENERIC) return generic_mfma_ok(p, nullptr) ? "generic MFMA kernel" : "scalar kernel";
+  TunedPlan plan;
+  tuned_plan(p, is_gta, false, &plan);
+  return plan.wide_tiles > 0 && tiles32 * (p->num_groups / plan.ng) >= plan.wide_tiles ? "eight-wave kernel" : "four-wave kernel";
+}
+
 // ---- fixed scratch buffer of the allocation-free entry point -------------------
 // One array per GPU the library runs on, in that GPU's memory for the lifetime
 // of the process.  In host code the array's name is only a handle: the device
@@ -661,6 +672,10 @@ size_t gla_proj_workspace_size(const gla_proj_params* p, int sum_groups) {
 
 int gla_decode_select_impl(const gla_decode_params* p, int is_gta) {
   return gla::select_impl(p, is_gta);
+}
+
+const char* gla_decode_kernel_name(const gla_decode_params* p, int is_gta, int64_t tiles32) {
+  return gla::kernel_name(p, is_gta, tiles32);
 }
 
 int gla_decode_profile(const gla_decode_params* p, int is_gta, int iters, float* main_us,

@@ -21,7 +21,8 @@ struct TunedPlan {
   int num_chunks;  // chunks of the tile list; the main-kernel grid is num_chunks * mb
   int chunk_tiles; // fixed tiles per chunk, 0: derived on the device
   size_t slot_floats;
-  bool wide;       // the eight-wave kernel (wide_main_kernel.hpp): wpg slabs per workgroup, ks waves per slab's output
+  int wide_tiles;  // > 0: the eight-wave kernel is launched too and runs, instead, on lists of that many tiles or more
+  int wide_chunks; // its chunks, of twice the tokens per tile
   bool stream;     // fetch the cache with the streaming hint
 };
 
@@ -42,30 +43,38 @@ inline bool aligned16(const void* ptr) { return ((uintptr_t)ptr & 15u) == 0; }
 
 constexpr int kMinChunkTiles = 4;
 
-// Does the eight-wave kernel (128 query rows per workgroup with 256 dims, 64 with 512) take this problem?  It
-// wins where the matrix pipe sets the pace and chunks are long; it starts a chunk and a sequence more slowly (twice
-// the tokens per tile, queries loaded by twice the waves), so short chunks stay with the four-wave kernel.
-// Measured, four waves -> eight waves, in us per call:
-//   512 dims, 128 rows per group, chunks of 110 tiles (of 64 tokens), pages of 64 / 8 / 1: 393 -> 356 / 467 -> 357 / 471 -> 371;
-//     chunks of 8 tiles 43.5 -> 42.1, of 3 tiles 32.2 -> 40.4
-//   256 dims, 256 rows per group, chunks of 128 tiles inside one sequence each, pages of 64 / 1: 328 -> 305 / 369 -> 315; chunks of
-//     55 tiles over 1.75 sequences each 183 -> 196, of 4 tiles 33.6 -> 37.4; with 128 rows per group (no second row
-//     block to share the tiles with, the kernel is half bound by HBM) 117 -> 123
-// Lengths are known on the device only: the host goes by the table's row length, and asks for a wide margin where the
-// gain is small (pages of 16 tokens or more): with one long sequence among short ones the real chunks are a tenth of
-// what the table allows (fifteen of 1024 tokens beside one of 65536, 512 dims: 74.3 -> 76.9).
-inline bool wide_pays(const gla_decode_params* p, int rows_group) {
-  const int64_t tiles_seq = ((int64_t)p->max_pages_per_seq * p->page_size + 63) / 64;
-  if (p->d_v == 512 && rows_group > 32) {
-    const int64_t chunks = std::max<int64_t>(1, device_cu_count() / ((rows_group + 63) / 64));
-    return (int64_t)p->batch * p->num_groups * tiles_seq >= (p->page_size < 16 ? 24 : 192) * chunks;
+// From how many tiles of 32 tokens on (of the whole list) does the eight-wave kernel take a batch?  0: never, it is not
+// launched.  It wins where the matrix pipe sets the pace and chunks are long; it starts a chunk and a sequence more slowly
+// (twice the tokens per tile, queries loaded by twice the waves).  What counts is therefore the real number of tiles per
+// chunk t and of sequences' parts per chunk, 1 + u, which only the device knows: both kernels are launched, both count,
+// and the one that is not meant leaves (0.1 to 1 us per call).  Measured, four waves -> eight waves, us per call, tiles of
+// 64 tokens (t, u):
+//   512 dims, 128 rows, pages of 64: (63, 1) 206 -> 185, (75, 2.3) 269 -> 259, (32, 1) 118 -> 108, (31, 0.1) 116 -> 115,
+//     (16, 0) 65 -> 63, (16, 0.1) 73 -> 76, (64, 4) 243 -> 245, (16, 4) 104 -> 120, (32, 8) 207 -> 225, (4, 0) 35 -> 39
+//   ... pages of 1: (16, 0.5) 91 -> 71, (16, 1) 79 -> 66, (8, 0.5) 53 -> 51, (4, 1) 35 -> 35, (16, 8) 190 -> 187
+//   256 dims, 256 rows, pages of 64: (128, 0.5) 339 -> 316, (125, 0.3) 329 -> 310, (126, 2) 348 -> 334, (128, 0.1) 337 -> 316,
+//     (63, 1) 176 -> 171, (63, 0.5) 178 -> 184, (31, 0.3) 103 -> 110, (64, 2) 185 -> 186, (117, 4.7) 369 -> 381
+//   ... pages of 1: (32, 1) 108 -> 96, (32, 2) 123 -> 114, (31, 0.3) 116 -> 112, (16, 0.3) 75 -> 78, (16, 8) 178 -> 183
+// With 128 rows and 256 dims (no second row block to share the tiles with) it loses, 117 -> 123.
+inline int wide_tiles_of(const gla_decode_params* p, const TunedPlan& plan) {
+  if (!eight_wave_shape(p->d_v, plan.ng, plan.wpg, plan.ks) || (p->d_v == 256 && plan.mb == 1)) return 0;
+  const bool small_pages = p->page_size < 16;
+  // tiles wanted per chunk, and more per unit of the list
+  const int64_t a = p->d_v == 512 ? (small_pages ? 8 : 32) : (small_pages ? 36 : 160);
+  const int64_t b = p->d_v == 512 ? (small_pages ? 8 : 32) : (small_pages ? 12 : 40);
+  const int64_t units = (int64_t)p->batch * p->num_groups;
+  int64_t need;
+  if (plan.chunk_tiles > 0) {  // (chunks of a given length, as many as the list has: need = a need / length + b units)
+    if (plan.chunk_tiles <= a) return 0;
+    need = (b * units * plan.chunk_tiles + plan.chunk_tiles - a - 1) / (plan.chunk_tiles - a);
+  } else {
+    need = a * plan.num_chunks + b * units;
   }
-  if (p->d_v == 256 && rows_group > 128) {
-    const int64_t chunks = std::max<int64_t>(1, device_cu_count() / ((rows_group + 127) / 128));
-    const int64_t units = (int64_t)p->batch * p->num_groups;
-    return units * tiles_seq >= 64 * chunks && (2 * units <= chunks || p->page_size < 16);
-  }
-  return false;
+  // What the list can hold at most, by the page table's row length and, where its size is given, by the pool (pages shared
+  // by several sequences may hold more: such a batch stays with the four-wave kernel).
+  int64_t most = units * (((int64_t)p->max_pages_per_seq * p->page_size + kTok - 1) / kTok);
+  if (p->num_pages > 0) most = std::min(most, p->num_groups * ((p->num_pages * p->page_size + kTok - 1) / kTok + p->batch));
+  return need <= most ? (int)std::max<int64_t>(need, 1) : 0;
 }
 
 // lean: the plan a call gets whose workspace is too small for the one it would get otherwise (see run() in
@@ -94,10 +103,9 @@ inline bool tuned_plan(const gla_decode_params* p, int is_gta, bool lean, TunedP
   // as four waves allow (they share one RoPE-key tile)
   // A latent of 512 dims needs two waves per row slab: 32 rows x 512 fp32
   // output accumulators alone would fill a wave's accumulation registers.
-  plan->wide = !lean && wide_pays(p, rows_group);
-  const int ks = plan->wide ? p->d_v / 128 : p->d_v > 256 ? 2 : 1;
-  const int wpg = plan->wide ? 8 / ks : rows_group <= 32 ? 1 : ((rows_group <= 64 || ks == 2) ? 2 : 4);
-  int ng = plan->wide ? 1 : 4 / (wpg * ks);
+  const int ks = p->d_v > 256 ? 2 : 1;
+  const int wpg = rows_group <= 32 ? 1 : ((rows_group <= 64 || ks == 2) ? 2 : 4);
+  int ng = 4 / (wpg * ks);
   while (ng > 1 && (p->num_groups % ng || 4 * (ng * 32 * p->d_v * 2 + 32 * 128) > 160 * 1024)) ng >>= 1;
   plan->dv = p->d_v;
   plan->dn = p->d_nope;
@@ -109,12 +117,12 @@ inline bool tuned_plan(const gla_decode_params* p, int is_gta, bool lean, TunedP
   plan->units = p->batch * (p->num_groups / ng) * plan->mb;
   // (small pages: page-id windows in LDS where tiles and mailboxes leave room for them, else in registers)
   const bool lds_windows = lane && tuned_windows_fit(p->d_v, ng, wpg, ks);
-  const int tok = plan->wide ? 2 * kTok : kTok, stages = tuned_stages(p->d_v, ng, wpg, ks, lds_windows);
+  const int tok = kTok, stages = tuned_stages(p->d_v, ng, wpg, ks, lds_windows);
   // co-resident workgroups per CU: one wave per SIMD, 160 KiB of LDS
   const int smem = stages * (ng * tok * p->d_v * 2 + tok * 128) + (ks > 1 ? ng * wpg * ks * 4096 : 0) +
                    (lds_windows ? ng * wpg * ks * 2 * kPageWindow * 4 : 0);
-  if (!plan->wide && smem > 160 * 1024) return false;
-  const int per_cu = plan->wide ? 1 : std::max(1, std::min((160 * 1024) / smem, 4 / (ng * wpg * ks)));
+  if (smem > 160 * 1024) return false;
+  const int per_cu = std::max(1, std::min((160 * 1024) / smem, 4 / (ng * wpg * ks)));
   plan->tok = tok;
   plan->stages = stages;
   // the tile list holds each (sequence, group block) once; every chunk of it is
@@ -131,17 +139,23 @@ inline bool tuned_plan(const gla_decode_params* p, int is_gta, bool lean, TunedP
     // (by the upper bound on the list length): a partial costs as much memory
     // traffic as three or four tiles, and every extra chunk is one more to merge
     const int64_t resident = std::max<int64_t>(1, (int64_t)device_cu_count() * per_cu / plan->mb);
-    int64_t by_length = std::max<int64_t>(1, bound * tok / (kMinChunkTiles * kTok));
+    int64_t by_length = std::max<int64_t>(1, bound / kMinChunkTiles);
     // While the grid is small the chip is idle and a tile more in the serial chain of a chunk costs more than a
     // partial: chunks of two tiles up to a quarter of the compute units, of one up to an eighth.  Measured, us per
     // call: 16 heads x 256 tokens 17.8 -> 14.6, batch 1 x 100 tokens 21.5 -> 16.4, x 512 20.4 -> 17.8, x 2048
     // 21.9 -> 20.4; further (one tile up to a quarter) loses again, 22.8 at 2048; with the grid full (batch 64 x 300)
     // two tiles take 36.6 against 34.2 with four.
     // (Few sequences only: a batch of many short ones has its parallelism already, and cut further it pays in merges.)
-    if (!lean && !plan->wide && p->batch <= 4) by_length = std::max({by_length, std::min(bound / 2, resident / 4), std::min(bound, resident / 8)});
+    if (!lean && p->batch <= 4) by_length = std::max({by_length, std::min(bound / 2, resident / 4), std::min(bound, resident / 8)});
     plan->num_chunks = (int)std::max<int64_t>(1, std::min<int64_t>(by_length, resident));
   }
-  plan->slot_floats = (size_t)plan->rows * p->d_v + (size_t)32 * ng * wpg * (plan->wide ? ks / 2 : ks);
+  plan->slot_floats = (size_t)plan->rows * p->d_v + (size_t)32 * ng * wpg * ks;
+  plan->wide_tiles = lean ? 0 : wide_tiles_of(p, *plan);
+  plan->wide_chunks = plan->num_chunks;
+  if (plan->wide_tiles > 0 && plan->chunk_tiles > 0) {
+    const int64_t ct = (plan->chunk_tiles + 1) / 2, max64 = (max_tiles + 1) / 2;
+    plan->wide_chunks = (int)(((int64_t)(plan->units / plan->mb) * max64 + ct - 1) / ct);
+  }
   // upper bound of the batch's cache bytes (the lengths are known on the device only) against the chip's
   // last-level cache
   plan->stream = bound * tok * 2 * ((int64_t)ng * p->d_v + p->d_rope) > kLastLevelCacheBytes;
@@ -155,7 +169,7 @@ inline bool tuned_supported(const gla_decode_params* p, int is_gta) {
 
 // Workspace: two partial slots per chunk, then per unit the chunk range holding it.
 inline size_t tuned_slots_bytes(const TunedPlan& plan) {
-  return (((size_t)plan.num_chunks * plan.mb * 2 * plan.slot_floats * sizeof(float)) + 255) & ~(size_t)255;
+  return (((size_t)std::max(plan.num_chunks, plan.wide_chunks) * plan.mb * 2 * plan.slot_floats * sizeof(float)) + 255) & ~(size_t)255;
 }
 
 inline size_t tuned_workspace(const gla_decode_params* p, int is_gta, bool lean) {
@@ -164,12 +178,12 @@ inline size_t tuned_workspace(const gla_decode_params* p, int is_gta, bool lean)
   return tuned_slots_bytes(plan) + (size_t)plan.units * 2 * sizeof(int32_t);
 }
 
-// Main and merge kernel of a plan, per state shape (tuned_256.hip, tuned_512.hip, tuned_128.hip) and of a plan
-// with `wide` set (wide.hip): translation units of their own, compiled side by side.
+// Main and merge kernel of a plan, per state shape (tuned_256.hip, tuned_512.hip, tuned_128.hip), and the eight-wave
+// main kernel that shares its merge (wide.hip).
 int tuned_launch_256(const TunedPlan& plan, const DevParams& d, hipStream_t st, hipEvent_t* ev);
 int tuned_launch_512(const TunedPlan& plan, const DevParams& d, hipStream_t st, hipEvent_t* ev);
 int tuned_launch_128(const TunedPlan& plan, const DevParams& d, hipStream_t st, hipEvent_t* ev);
-int wide_launch(const TunedPlan& plan, const DevParams& d, hipStream_t st, hipEvent_t* ev);
+int wide_launch(const TunedPlan& plan, const DevParams& d, hipStream_t st);
 
 inline int tuned_launch(const gla_decode_params* p, int is_gta, bool lean, DevParams& d, hipStream_t st,
                         hipEvent_t* ev) {
@@ -198,7 +212,7 @@ inline int tuned_launch(const gla_decode_params* p, int is_gta, bool lean, DevPa
     d.fd_units_full = make_fastdiv((uint32_t)(d.upb * d.tiles_full));
     d.fd_upb_mb = make_fastdiv((uint32_t)(d.upb * plan.mb));
   }
-  if (plan.wide) return wide_launch(plan, d, st, ev);
+  d.wide_tiles = plan.wide_tiles;
   if (plan.dv == 256 && plan.dn == 256) return tuned_launch_256(plan, d, st, ev);
   if (plan.dv == 128 && plan.dn == 64) return tuned_launch_128(plan, d, st, ev);
   if (plan.dv == 512 && plan.dn == 512) return tuned_launch_512(plan, d, st, ev);

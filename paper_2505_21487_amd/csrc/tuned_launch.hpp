@@ -54,6 +54,12 @@ inline int launch_tuned_variant(const TunedPlan& plan, const DevParams& d, hipSt
                               : launch_tuned_main<DV, DN, NG, WPG, KS, TOK, false>(d, mgrid, mblock, st);
   if (lrc != GLA_OK) return lrc;
   if (hipGetLastError() != hipSuccess) return GLA_ERR_LAUNCH;
+  if constexpr (eight_wave_shape(DV, NG, WPG, KS)) {
+    if (plan.wide_tiles > 0) {  // (one of the two kernels finds that the batch is the other's, and leaves)
+      const int wrc = wide_launch(plan, d, st);
+      if (wrc != GLA_OK) return wrc;
+    }
+  }
   if (ev) (void)hipEventRecord(ev[1], st);
   return launch_tuned_combine<DV, NG, WPG, KS, TOK>(plan, d, st, ev);
 }

@@ -79,6 +79,11 @@ constexpr bool tuned_windows_fit(int dv, int ng, int wpg, int ks) {
              ng * wpg * ks * 2 * kPageWindow * 4 <= 160 * 1024;
 }
 
+// Four-wave variants beside which an eight-wave kernel exists: many query rows (wide_main_kernel.hpp).
+constexpr bool eight_wave_shape(int dv, int ng, int wpg, int ks) {
+  return ng == 1 && ((dv == 256 && wpg == 4 && ks == 1) || (dv == 512 && wpg == 2 && ks == 2));
+}
+
 template <int DV, int DN, int DR, int NG, int WPG, int KS, int TOK, int STAGES, int PM, bool STREAM>
 __global__ __launch_bounds__(64 * NG * WPG * KS) void tuned_main_kernel(DevParams p) {
   using TT = TunedTraits<DV, DN, DR, NG, WPG, KS, TOK, STAGES>;
@@ -174,6 +179,9 @@ __global__ __launch_bounds__(64 * NG * WPG * KS) void tuned_main_kernel(DevParam
   const int incl0 = wave_incl_scan(tiles_of<TOK>(L_first) * UPB);
   const int n_total = total_tiles<TOK>(p, UPB, lane, incl0);
   if (n_total <= 0) return;
+  if constexpr (eight_wave_shape(DV, NG, WPG, KS)) {
+    if (p.wide_tiles > 0 && n_total >= p.wide_tiles) return;  // the eight-wave kernel, launched next, takes this batch
+  }
   // Chunk i covers tiles [i * chunk, (i + 1) * chunk): a fixed length if the
   // caller chose a split count, else an equal share of the list.
   const int chunk = p.chunk_tiles > 0 ? p.chunk_tiles : (int)fast_div((unsigned)(n_total + n_chunks - 1), p.fd_chunks);

@@ -1,15 +1,14 @@
-// Launches of the eight-wave decode-attention kernel (its own translation unit: built beside the others).
-#include "tuned_launch.hpp"
+// Launch of the eight-wave decode-attention kernel.
+#include "tuned_host.hpp"
 #include "wide_main_kernel.hpp"
 
 namespace gla {
 
 template <int DV, bool PP>
-static int launch_wide(const TunedPlan& plan, const DevParams& d, hipStream_t st, hipEvent_t* ev) {
+static int launch_wide(const TunedPlan& plan, const DevParams& d, hipStream_t st) {
   using W = WideTraits<DV, PP>;
-  if (plan.wpg != W::NSL || plan.ks != W::E || plan.tok != W::TT || plan.slot_floats != W::kSlotFloats) return GLA_ERR_LAUNCH;
-  if (ev) (void)hipEventRecord(ev[0], st);
-  const dim3 grid(plan.num_chunks * plan.mb), block(512);
+  if (plan.rows != W::kRows || plan.slot_floats != W::kSlotFloats) return GLA_ERR_LAUNCH;
+  const dim3 grid(plan.wide_chunks * plan.mb), block(512);
   if (d.lg_page >= 3) {
     if (plan.stream) hipLaunchKernelGGL((wide_main_kernel<DV, PP, 0, true>), grid, block, 0, st, d);
     else hipLaunchKernelGGL((wide_main_kernel<DV, PP, 0, false>), grid, block, 0, st, d);
@@ -17,13 +16,16 @@ static int launch_wide(const TunedPlan& plan, const DevParams& d, hipStream_t st
     if (plan.stream) hipLaunchKernelGGL((wide_main_kernel<DV, PP, 1, true>), grid, block, 0, st, d);
     else hipLaunchKernelGGL((wide_main_kernel<DV, PP, 1, false>), grid, block, 0, st, d);
   }
-  if (hipGetLastError() != hipSuccess) return GLA_ERR_LAUNCH;
-  if (ev) (void)hipEventRecord(ev[1], st);
-  return launch_tuned_combine<DV, 1, W::NSL, W::E / 2, kTok>(plan, d, st, ev);  // (the four-wave kernel's: the same partials)
+  return hipGetLastError() == hipSuccess ? GLA_OK : GLA_ERR_LAUNCH;
 }
 
-int wide_launch(const TunedPlan& plan, const DevParams& d, hipStream_t st, hipEvent_t* ev) {
-  return plan.dv == 256 ? launch_wide<256, true>(plan, d, st, ev) : launch_wide<512, false>(plan, d, st, ev);
+int wide_launch(const TunedPlan& plan, const DevParams& four, hipStream_t st) {
+  DevParams d = four;  // (tiles of twice as many tokens)
+  d.num_chunks = plan.wide_chunks;
+  d.chunk_tiles = (plan.chunk_tiles + 1) / 2;
+  d.fd_chunks = make_fastdiv((uint32_t)plan.wide_chunks);
+  d.xcd_map = plan.wide_chunks % 8 == 0 ? 1 : 0;
+  return plan.dv == 256 ? launch_wide<256, true>(plan, d, st) : launch_wide<512, false>(plan, d, st);
 }
 
 }  // namespace gla

@@ -153,6 +153,9 @@ __global__ __launch_bounds__(512) void wide_main_kernel(DevParams p) {
 
   // ---- this workgroup's chunk of the flat tile list
   const int L_first = lane < p.B ? load_i32_sync(p.seq_lens + lane) : 0;
+  if (p.wide_tiles > 0 &&  // (counted as the four-wave kernel counts them: one of the two runs)
+      total_tiles<kTok>(p, UPB, lane, wave_incl_scan(tiles_of<kTok>(L_first) * UPB)) < p.wide_tiles)
+    return;
   const int incl0 = wave_incl_scan(tiles_of<TOK>(L_first) * UPB);
   const int n_total = total_tiles<TOK>(p, UPB, lane, incl0);
   if (n_total <= 0) return;

@@ -1,7 +1,7 @@
 """The eight-wave kernel against the oracle at the sizes where it can go wrong: remainders of its 64-token tiles,
 many sequences inside one chunk, more than 64 sequences, page-id windows crossed (64 tiles at pages of 8 tokens or
 more, 8 tiles below), row blocks that are not full, RoPE keys of fewer than 64 dims, moved references and heavy
-weights (peaky softmax).  Tables are long enough that the plan takes that kernel."""
+weights (peaky softmax).  Every batch holds one sequence long enough for the library to take that kernel."""
 import numpy as np
 import pytest
 import torch
@@ -17,45 +17,69 @@ pytestmark = pytest.mark.gpu
 EDGES = [0, 1, 63, 64, 65, 127, 129, 700, 2, 4]
 CASES = {
     # name: (shape, lengths, T, page, other)
-    "mla_edges": ("mla", EDGES, 1, 64, {}),
-    "mla_peaky": ("mla", EDGES + [1500], 1, 16, dict(q_gain=6.0)),
-    "mla_rows33": ("mla", [300, 65, 31, 0, 128], 3, 32, dict(h_q=11)),
+    "mla_edges": ("mla", EDGES + [17000], 1, 64, {}),
+    "mla_peaky": ("mla", EDGES + [18001], 1, 16, dict(q_gain=6.0)),
+    "mla_rows33": ("mla", [300, 65, 31, 0, 128, 9100], 3, 32, dict(h_q=11)),
     "mla_windows_page8": ("mla", [5000, 4097, 64], 1, 8, {}),
-    "mla_windows_page1": ("mla", [1100, 513, 70], 2, 1, {}),
-    "mla_page4_rope32": ("mla", [700, 130, 9], 1, 4, dict(d_r=32)),
-    "mla_many": ("mla", [17] * 70 + [0, 200, 64], 1, 64, {}),
-    "gla_edges_page8": ("gla", EDGES, 4, 8, {}),
-    "gla_peaky_page2": ("gla", [900, 77, 300], 3, 2, dict(q_gain=6.0)),
-    "gla_long": ("gla", [9000, 4100], 4, 64, {}),
-    "gla_rope48_page1": ("gla", [640, 1, 63], 4, 1, dict(d_r=48)),
-    "gla_many_page4": ("gla", [5] * 66 + [129, 0, 3], 3, 4, {}),
+    "mla_windows_page1": ("mla", [1100, 2513, 70], 2, 1, {}),
+    "mla_page4_rope32": ("mla", [700, 1930, 9], 1, 4, dict(d_r=32)),
+    "mla_many": ("mla", [17] * 12 + [0, 200, 64, 23000], 1, 64, {}),
+    "mla_many_page8": ("mla", [17] * 70 + [0, 20100, 64], 1, 8, dict(h_q=64)),
+    "gla_edges_page8": ("gla", EDGES + [10000], 4, 8, {}),
+    "gla_edges": ("gla", EDGES + [32100], 3, 64, dict(h_q=96)),
+    "gla_peaky_page2": ("gla", [900, 77, 4300], 3, 2, dict(q_gain=6.0)),
+    "gla_long": ("gla", [19000, 8100], 4, 64, {}),
+    "gla_rope48_page1": ("gla", [640, 1, 63, 5000], 4, 1, dict(d_r=48)),
+    "gla_many_page4": ("gla", [5] * 66 + [129, 0, 3, 32000], 3, 4, dict(h_q=96)),
 }
+
+
+def _problem(name, lens, **kw):
+    page = kw["page_size"]
+    return make_problem(name, seq_lens=lens, num_pages=sum((n + page - 1) // page for n in lens) + 64, poison_tail=True, **kw)
+
+
+def _kernel(p, num_splits=0):
+    dp = DeviceProblem(p)
+    out = torch.empty(p.B, p.T, p.h_q, p.d_v, dtype=torch.float32, device="cuda")
+    prm = gla.make_params(*dp.args()[:6], p.scale, out=out, lse=torch.empty(p.B, p.T, p.h_q, device="cuda"), workspace=None, num_splits=num_splits)
+    return gla.gla_decode_kernel_name(prm, 0, p.seq_lens)
 
 
 @pytest.mark.parametrize("name", sorted(CASES))
 def test_eight_wave_kernel(name):
     shape, lens, T, page, kw = CASES[name]
     kw = dict(kw)
-    h_q = kw.pop("h_q", 128)
-    # (a row length for which the plan picks the kernel: chunks of at least 24 / 192 / 64 tiles if every row were full)
-    want_tokens = ((24 if page < 16 else 192) if shape == "mla" else 64) * 64 * 256 // len(lens) + 64
-    pages = max((n + page - 1) // page for n in lens)
-    p = make_problem(name, seq_lens=lens, T=T, h_q=h_q, h_c=1 if shape == "mla" else 2, d_v=512 if shape == "mla" else 256,
-                     page_size=page, seed=7000 + len(name), num_pages=sum((n + page - 1) // page for n in lens) + 64,
-                     poison_tail=True, extra_table_cols=max(1, want_tokens // page - pages), **kw)
-    for splits in (0, 3):
+    p = _problem(name, lens, T=T, h_q=kw.pop("h_q", 128), h_c=1 if shape == "mla" else 2, d_v=512 if shape == "mla" else 256,
+                 page_size=page, seed=7000 + len(name), **kw)
+    # few chunks per sequence: several sequences in one, and sequences over several
+    for splits in (1, 2):
+        assert _kernel(p, splits) == "eight-wave kernel"
         check_problem(p, impl=gla.GLA_IMPL_TUNED, num_splits=splits, what=f"{name} splits={splits}")
-    check_problem(p, impl=gla.GLA_IMPL_TUNED, num_splits=p.max_pages, what=f"{name} one tile per chunk or little more")
+    # short chunks: the four-wave kernel, launched alone
+    assert _kernel(p, p.max_pages if page > 1 else 400) == "four-wave kernel"
+
+
+@pytest.mark.parametrize("shape,lens,T,page,h_q", [("mla", [4000, 3900, 2100] * 20 + [0, 77], 1, 64, 128), ("mla", [2600] * 16 + [0, 77], 1, 4, 128),
+                                                  ("gla", [2900] * 32 + [0, 77], 3, 8, 96)])
+def test_automatic_chunks(shape, lens, T, page, h_q):
+    """The library's own cut, on lists on either side of the line between the two kernels (all rows of some sequences)."""
+    for keep, want in ((len(lens), "eight-wave kernel"), (4, "four-wave kernel")):
+        p = _problem("auto", lens[-keep:], T=T, h_q=h_q, h_c=1 if shape == "mla" else 2, d_v=512 if shape == "mla" else 256, page_size=page,
+                     seed=7100 + page, extra_table_cols=131072 // page)
+        assert _kernel(p) == want
+        sel = [(b, t, h) for b in (0, p.B // 2, p.B - 3, p.B - 2, p.B - 1) for t in range(T) for h in range(0, h_q, 3)]
+        check_problem(p, sel=sel, impl=gla.GLA_IMPL_TUNED, what=f"{shape} {want}")
 
 
 def test_eight_wave_kernel_repeats_bit_for_bit():
     """Many segments, moved references and residual passes: the same call gives the same bits."""
-    p = make_problem("repeat", seq_lens=[70, 300, 64, 1, 513] * 8, T=1, h_q=128, h_c=1, d_v=512, page_size=64, seed=71,
-                     num_pages=4096, q_gain=3.0, poison_tail=True, extra_table_cols=1300)
+    p = _problem("repeat", [70, 300, 64, 1, 513] * 4 + [30000], T=1, h_q=128, h_c=1, d_v=512, page_size=64, seed=71, q_gain=3.0)
+    assert _kernel(p, 1) == "eight-wave kernel"
     dp = DeviceProblem(p, poison_unused=True)
     first = None
     for _ in range(20):
-        out, lse = gla.gla_decode(*dp.args(), out_dtype=torch.float32)
+        out, lse = gla.gla_decode(*dp.args(), out_dtype=torch.float32, num_splits=1)
         torch.cuda.synchronize()
         if first is None:
             first = (out.clone(), lse.clone())

@@ -1,5 +1,6 @@
-"""Workspace sizes (host only): a program may size its workspace once, for its largest batch, and keep it as requests
-come and go."""
+"""What the host decides from shapes alone.  Workspace sizes: a program may size its workspace once, for its largest
+batch, and keep it as requests come and go.  The eight-wave kernel: taken by the real lengths, not by how long the page
+table's rows are."""
 import pytest
 
 import paper_2505_21487_amd as gla
@@ -38,3 +39,41 @@ def test_a_larger_batch_never_needs_less(shape, q_len):
                 need = gla.gla_decode_workspace_size(p, mode)
                 assert need >= last, (page, tokens, batch)
                 last = need
+
+
+def kernel(shape, lens, *, q_len, page, tokens, num_splits=0, num_pages=10**6):
+    p, mode = params(shape, batch=len(lens), q_len=q_len, page=page, tokens=tokens)
+    p.num_splits, p.num_pages = num_splits, num_pages
+    return gla.gla_decode_kernel_name(p, mode, lens)
+
+
+@pytest.mark.parametrize("shape,q_len,page", [("mla", 1, 64), ("mla", 1, 16), ("mla", 2, 1), ("mla_h40", 1, 8), ("gla2", 4, 64), ("gla2", 3, 1)])
+def test_short_sequences_in_a_long_table_stay_with_the_four_wave_kernel(shape, q_len, page):
+    for batch, length in ((1, 4096), (16, 200), (64, 200), (64, 400), (1024, 50)):
+        assert kernel(shape, [length] * batch, q_len=q_len, page=page, tokens=131072) == "four-wave kernel"
+    for batch, length in ((64, 16384), (128, 8192), (32, 16384)):
+        assert kernel(shape, [length] * batch, q_len=q_len, page=page, tokens=131072) == "eight-wave kernel"
+    # one line between them, the same however long the table
+    lines = []
+    for tokens in (16384, 131072):
+        names = [kernel(shape, [n] * 64, q_len=q_len, page=page, tokens=tokens) for n in range(32, 16385, 32)]
+        line = names.index("eight-wave kernel")
+        assert names == ["four-wave kernel"] * line + ["eight-wave kernel"] * (len(names) - line)
+        lines.append(line)
+    assert lines[0] == lines[1]
+    # not launched at all where the pool cannot hold such a batch, nor in chunks too short for it
+    assert kernel(shape, [16384] * 64, q_len=q_len, page=page, tokens=131072, num_pages=4096 // page) == "four-wave kernel"
+    assert kernel(shape, [16384] * 64, q_len=q_len, page=page, tokens=16384, num_splits=100) == "four-wave kernel"
+    assert kernel(shape, [16384] * 64, q_len=q_len, page=page, tokens=16384, num_splits=1) == "eight-wave kernel"
+
+
+def test_kernel_names():
+    assert kernel("gla2", [100000] * 64, q_len=2, page=64, tokens=131072) == "four-wave kernel"   # 128 rows per group
+    assert kernel("gta4_d128", [100000] * 64, q_len=4, page=64, tokens=131072) == "four-wave kernel"
+    assert kernel("gta4_d64", [10], q_len=1, page=64, tokens=64) == kernel("gqa4_d128", [10], q_len=1, page=64, tokens=64) == "second MFMA kernel"
+    assert kernel("gla2", [10], q_len=1, page=128, tokens=128) == "generic MFMA kernel"
+    p, _ = params("gla2", batch=1, q_len=1, page=128, tokens=128)
+    p.q_nope_stride[2] += 1
+    assert gla.gla_decode_kernel_name(p, 0, [10]) == "scalar kernel"
+    p.q_len = 5
+    assert gla.gla_decode_kernel_name(p, 0, [10]) == ""
