@@ -1,7 +1,8 @@
-"""The generic kernel's MFMA variant against the oracle where its general indexing can go wrong: page sizes that are
+"""The generic route against the oracle.  Its MFMA kernel where general indexing can go wrong: page sizes that are
 not powers of two or larger than 64, dims that are no multiple of a contraction step, an odd number of 16-byte chunks
-per cache row, row counts around its 16-row waves, ranges that end inside a tile, strided and misaligned tensors (the
-scalar variant then runs, same bounds), separate key caches.
+per cache row, row counts around its 16-row waves, ranges that end inside a tile, strided tensors, separate key caches.
+Its scalar kernel at every instantiation (value dims up to 128, 256, 512, 1024): odd dims, dims beyond 512, misaligned
+tensors.  Both where the cache holds what it is not meant to.
 
 fp32 results are held to 2e-5: products of bf16 are exact, weights keep 24 bits, and the largest term left is the
 rounding of a score before its exponential, |score| 2^-24 relative to a weight (scores here stay below 20 in base 2,
@@ -50,7 +51,50 @@ def test_generic_mfma(name):
     kind, h_q, h_c, d_v, d_r, T, page, splits = CASES[name]
     p = make_problem(name, kind=kind, seq_lens=LENS, T=T, h_q=h_q, h_c=h_c, d_v=d_v, d_r=d_r, page_size=page, seed=8100 + len(name),
                      num_pages=sum(n // page + 1 for n in LENS) + 9, poison_tail=True, extra_table_cols=2, causal=0 if page == 7 else 1)
-    _close(p, DeviceProblem(p, poison_unused=True), num_splits=splits)
+    dp = DeviceProblem(p, poison_unused=True)
+    assert _name(p, dp) == "generic MFMA kernel"
+    _close(p, dp, num_splits=splits)
+
+
+def _shifted(t, by):
+    """The same values in a wider buffer, each row `by` elements in."""
+    wide = torch.zeros(*t.shape[:-1], t.shape[-1] + 40, dtype=t.dtype, device=t.device)
+    wide[..., by:by + t.shape[-1]] = t
+    return wide[..., by:by + t.shape[-1]]
+
+
+def _name(p, dp):
+    out = torch.empty(p.B, p.T, p.h_q, p.d_v, dtype=torch.float32, device="cuda")
+    prm = gla.make_params(*dp.args()[:6], p.scale, out=out, lse=torch.empty(p.B, p.T, p.h_q, device="cuda"), workspace=None, impl=gla.GLA_IMPL_GENERIC)
+    return gla.gla_decode_kernel_name(prm, {"gla": 0, "gta": 1, "gqa": 2}[p.kind], p.seq_lens)
+
+
+SCALAR = {
+    # name: (kind, h_q, h_c, d_v, d_r, T, page, what is shifted by one element)
+    "odd_dims_90": ("gla", 6, 2, 90, 32, 2, 48, None),
+    "odd_dims_201": ("gla", 3, 1, 201, 40, 1, 3, None),
+    "dims_328_misaligned": ("gla", 4, 1, 328, 64, 1, 128, "q_nope"),
+    "dims_520": ("gla", 4, 2, 520, 24, 3, 64, None),
+    "dims_1024": ("gla", 2, 1, 1024, 128, 1, 100, None),
+    "gta_68": ("gta", 8, 4, 68, 34, 1, 7, None),
+    "gta_256_misaligned": ("gta", 4, 2, 256, 128, 4, 64, "q_rope"),
+    "gqa_80_misaligned_keys": ("gqa", 6, 3, 80, 0, 2, 24, "key_cache"),
+    "gqa_256_misaligned_values": ("gqa", 2, 2, 256, 0, 1, 128, "state_cache"),
+}
+
+
+@pytest.mark.parametrize("splits", [0, 1, 3, 70])
+@pytest.mark.parametrize("name", sorted(SCALAR))
+def test_scalar_kernel(name, splits):
+    kind, h_q, h_c, d_v, d_r, T, page, shifted = SCALAR[name]
+    p = make_problem(name, kind=kind, seq_lens=[0, 1, 33, 300], T=T, h_q=h_q, h_c=h_c, d_v=d_v, d_r=d_r, page_size=page, seed=8250 + len(name),
+                     num_pages=200, poison_tail=True, extra_table_cols=2)
+    dp = DeviceProblem(p, poison_unused=True)
+    if shifted is not None:
+        setattr(dp, shifted, _shifted(getattr(dp, shifted), 1))
+    if shifted != "key_cache":  # (not among what the query sees)
+        assert _name(p, dp) == "scalar kernel"
+    _close(p, dp, num_splits=splits)
 
 
 @pytest.mark.parametrize("offset", [8, 4, 1])
@@ -58,9 +102,8 @@ def test_generic_strided_queries(offset):
     """Queries inside a wider buffer: 16-byte aligned (MFMA variant), 8-byte and 2-byte aligned (scalar variant)."""
     p = make_problem("strided", seq_lens=LENS, T=2, h_q=6, h_c=3, d_v=96, d_r=32, page_size=48, seed=8200, num_pages=64, poison_tail=True)
     dp = DeviceProblem(p, poison_unused=True)
-    wide = torch.zeros(p.B, p.T, p.h_q, p.d_n + 40, dtype=torch.bfloat16, device="cuda")
-    wide[..., offset:offset + p.d_n] = dp.q_nope
-    dp.q_nope = wide[..., offset:offset + p.d_n]
+    dp.q_nope = _shifted(dp.q_nope, offset)
+    assert _name(p, dp) == ("generic MFMA kernel" if offset == 8 else "scalar kernel")
     _close(p, dp)
 
 
@@ -122,9 +165,7 @@ def test_infinite_values(d_v, splits, aligned):
     assert np.isposinf(ref_out).any() and np.isneginf(ref_out).any() and not np.isnan(ref_out).any()
     dp = DeviceProblem(p, poison_unused=True)
     if not aligned:
-        wide = torch.zeros(p.B, p.T, p.h_q, p.d_n + 2, dtype=torch.bfloat16, device="cuda")
-        wide[..., 1:1 + p.d_n] = dp.q_nope
-        dp.q_nope = wide[..., 1:1 + p.d_n]
+        dp.q_nope = _shifted(dp.q_nope, 1)
     _same_with_special_values(p, dp=dp, num_splits=splits)
 
 

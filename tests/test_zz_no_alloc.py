@@ -13,7 +13,7 @@ from workloads import config, make_problem
 pytestmark = pytest.mark.gpu
 
 
-def both_ways(p, **kw):
+def both_ways(p, impl=gla.GLA_IMPL_TUNED, kernel=None, **kw):
     dp = DeviceProblem(p, poison_unused=True)
     is_gta = p.kind == "gta"
     res = []
@@ -21,7 +21,8 @@ def both_ways(p, **kw):
         out = torch.full((p.B, p.T, p.h_q, p.d_v), float("nan"), dtype=torch.bfloat16, device="cuda")
         lse = torch.full((p.B, p.T, p.h_q), float("nan"), dtype=torch.float32, device="cuda")
         prm = gla.make_params(*dp.args()[:6], p.scale, out=out, lse=lse, workspace=None, causal=bool(p.causal),
-                              impl=gla.GLA_IMPL_TUNED, **kw)
+                              impl=impl, **kw)
+        assert kernel is None or gla.gla_decode_kernel_name(prm, is_gta, p.seq_lens) == kernel
         if noalloc:
             gla.gla_decode_noalloc(prm, is_gta)      # workspace fields stay null: they are ignored
         else:
@@ -44,6 +45,16 @@ def test_noalloc_matches_the_workspace_entry_points_twice_in_a_row():
                            num_pages=512, poison_tail=True))
     both_ways(make_problem("noalloc_gta", kind="gta", seq_lens=[1500, 33], T=1, h_q=32, h_c=4, d_v=128, seed=611,
                            num_pages=512, poison_tail=True))
+
+
+def test_noalloc_on_the_other_kernels():
+    """The eight-wave kernel's plan and the generic MFMA kernel's, and a small call of the first kind in between."""
+    lens = [4000, 3900, 2100] * 20 + [0, 77]
+    for lens, kernel in ((lens, "eight-wave kernel"), (lens[-3:], "four-wave kernel")):
+        both_ways(make_problem("noalloc_mla", seq_lens=lens, T=1, h_q=128, h_c=1, d_v=512, seed=612, num_pages=8192, poison_tail=True),
+                  kernel=kernel)
+    both_ways(make_problem("noalloc_page128", seq_lens=[700, 0, 4500, 3], T=2, h_q=128, h_c=2, d_v=256, page_size=128, seed=613,
+                           num_pages=64, poison_tail=True), impl=gla.GLA_IMPL_AUTO, kernel="generic MFMA kernel")
 
 
 def test_noalloc_rejects_what_does_not_fit():
