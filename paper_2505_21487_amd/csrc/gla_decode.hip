@@ -117,9 +117,8 @@ bool flex_plan(const gla_decode_params* p, int mode, const KeyCache* kc, bool le
     int64_t by_length = bound / 8;
     // ... but while most of the chip is idle a shorter serial chain pays: chunks of four tiles up to one wave per
     // compute unit, of two up to half of that.  us per call: GTA-4 d_h 64, batch 1 x 200 12.9 -> 11.0, 4 x 100 to 900
-    // 16.5 -> 12.5; GQA-4 batch 2 x 300 18.1 -> 11.9.  Few sequences only: a batch of many short ones has its
-    // parallelism already, and cut further it pays in merges (64 x 200: 14.1 us, 15.9 with 112 chunks).
-    if (!lean && p->batch <= 4)
+    // 16.5 -> 12.5; GQA-4 batch 2 x 300 18.1 -> 11.9.
+    if (!lean && p->batch <= kShortChunkBatch)
       by_length = std::max({by_length, std::min(bound / 4, waves / plan->strands), std::min(bound / 2, waves / 2 / plan->strands)});
     chunks = std::min<int64_t>((4 * waves + plan->strands - 1) / plan->strands, by_length);
   }
@@ -375,14 +374,14 @@ size_t workspace_need(const gla_decode_params* p, int is_gta, int kernel, const 
 }
 
 // What gla_decode_workspace_size() reports: never less than for a smaller batch on the MFMA kernels, so that a program
-// may size its workspace once, for its largest batch.  (Batches of up to four may be cut into more chunks than larger
-// ones, see tuned_plan and flex_plan; among themselves, and beyond four, the need grows with the batch.)
+// may size its workspace once, for its largest batch.  (Batches of up to kShortChunkBatch may be cut into more chunks
+// than larger ones; among themselves, and beyond it, the need grows with the batch.)
 size_t workspace_reported(const gla_decode_params* p, int is_gta, int kernel) {
   size_t need = workspace_need(p, is_gta, kernel, nullptr, false);
-  if (p->batch > 4 && kernel != GLA_IMPL_GENERIC) {
-    gla_decode_params four = *p;
-    four.batch = 4;
-    need = std::max(need, workspace_need(&four, is_gta, kernel, nullptr, false));
+  if (p->batch > kShortChunkBatch && kernel != GLA_IMPL_GENERIC) {
+    gla_decode_params small = *p;
+    small.batch = kShortChunkBatch;
+    need = std::max(need, workspace_need(&small, is_gta, kernel, nullptr, false));
   }
   return need;
 }
