@@ -13,8 +13,8 @@
 //
 // Bound by latency and vector work (address arithmetic with run-time dims, the three-way split).  Two latent heads of
 // 256 dims, 128 heads, 9 sequences of up to 4500 tokens at 128 tokens per page: 1923 us with the scalar kernel, whose
-// waves each read the whole cache for one row, 39 us here (one latent head of 512 dims: 3135 -> 62; four tied states
-// of 128: 374 -> 39).  With one contraction step of operand reads in flight instead of four: 47 us.
+// waves each read the whole cache for one row, 38 us here (one latent head of 512 dims: 3135 -> 60; four tied states
+// of 128: 374 -> 38).  With one contraction step of operand reads in flight instead of four: 47 us.
 #pragma once
 
 #include "common.hpp"

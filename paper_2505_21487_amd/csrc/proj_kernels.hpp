@@ -187,6 +187,13 @@ __global__ __launch_bounds__(256) void proj_kernel(ProjParams p) {
   }
 }
 
+// (Instantiated here, around the reduction: the three kernels of up to 32 rows then lie side by side in memory.  An
+// attention block alternates between them and the decode's two, about 58 KB of code together; spread over the code object
+// as they came, they displaced one another in the 64 KB instruction cache more often: a block of 24 sequences 142.5 us,
+// 141.9 this way, and between 141.4 and 144.2 with other orders of the same kernels.)
+template __global__ void proj_kernel<1, 2>(ProjParams);
+template __global__ void proj_kernel<1, 1>(ProjParams);
+
 // Sum of the partials of one output: over all grid.z slices (output projection)
 // or over the ksplit slices of each group (absorbed query).  One thread per four
 // consecutive output features, slices added in index order (deterministic).
@@ -221,5 +228,8 @@ __global__ __launch_bounds__(256) void proj_reduce_kernel(ProjParams p) {
     *reinterpret_cast<uint2*>((uint16_t*)p.c + off) = pk;
   }
 }
+
+template __global__ void proj_kernel<2, 2>(ProjParams);
+template __global__ void proj_kernel<2, 1>(ProjParams);
 
 }  // namespace gla

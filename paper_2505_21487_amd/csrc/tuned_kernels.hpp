@@ -37,7 +37,7 @@
 // softmax over the visible keys, output = weights . state[:DV].
 //
 // Files: tuned_device.hpp (device helpers), tuned_main_kernel.hpp, tuned_combine_kernel.hpp,
-// tuned_host.hpp (plan), tuned_launch.hpp (launches, one translation unit per state shape);
+// tuned_host.hpp (plan), tuned_launch.hpp (launches, one unit of library.hip per state shape);
 // wide_main_kernel.hpp is the eight-wave kernel that takes units with many query rows.
 #pragma once
 

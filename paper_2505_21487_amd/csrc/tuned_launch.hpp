@@ -1,4 +1,4 @@
-// Launches of the tuned decode-attention kernels; included by one translation unit per state shape.
+// Launches of the tuned decode-attention kernels; included by one unit (of library.hip) per state shape.
 #pragma once
 
 #include "tuned_combine_kernel.hpp"

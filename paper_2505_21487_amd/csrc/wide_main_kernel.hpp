@@ -31,7 +31,7 @@
 // rows (256 dims): 4900 cycles, of which the matrix pipe is busy for 2300, LDS for 1650, the vector pipe for about
 // 2000 in the two waves of a SIMD; without the tile loads 3900, without the value MFMAs 3800.  The four-wave kernel
 // takes 5000 cycles for the same work with one address per 64-token page, and more with small pages, whose address
-// work here hides under the other wave.  Times: see wide_pays() in tuned_host.hpp.
+// work here hides under the other wave.  Times: see wide_tiles_of() in tuned_host.hpp.
 //
 // Rare paths (a moved reference, heavy weights, tails) are written so that nothing in them costs the tile loop
 // registers or waits: LDS accesses as assembly, indices worked out on the spot.  A first version whose rare path

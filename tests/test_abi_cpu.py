@@ -28,7 +28,7 @@ def test_library_exports_every_declared_symbol():
 
 
 def test_library_is_one_device_code_object():
-    """Several would each have memory of their own on the GPU, which costs programs that change kernels all the time."""
+    """Several would lie wherever they land on the GPU, which costs programs that alternate between kernels."""
     with open(gla.binding.LIB_PATH, "rb") as f:
         assert f.read().count(b"__CLANG_OFFLOAD_BUNDLE__") == 1
 

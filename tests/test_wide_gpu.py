@@ -72,6 +72,34 @@ def test_automatic_chunks(shape, lens, T, page, h_q):
         check_problem(p, sel=sel, impl=gla.GLA_IMPL_TUNED, what=f"{shape} {want}")
 
 
+def test_captured_call_chooses_again_for_other_lengths():
+    """Replays of one captured call, the lengths changed in place between them: each takes the kernel of its lengths."""
+    p = _problem("graph", [4000, 3900, 2100] * 20 + [0, 77], T=1, h_q=128, h_c=1, d_v=512, page_size=64, seed=72)
+    dp = DeviceProblem(p, poison_unused=True)
+    out = torch.empty(p.B, p.T, p.h_q, p.d_v, dtype=torch.float32, device="cuda")
+    lse = torch.empty(p.B, p.T, p.h_q, device="cuda")
+    prm = gla.make_params(*dp.args()[:6], p.scale, out=out, lse=lse, workspace=None)
+    ws = torch.full((gla.gla_decode_workspace_size(prm),), 0xFF, dtype=torch.uint8, device="cuda")
+    prm.workspace, prm.workspace_bytes = ws.data_ptr(), ws.numel()
+    gla.decode_prepared(prm)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        prm.stream = torch.cuda.current_stream().cuda_stream
+        gla.decode_prepared(prm)
+    full = dp.seq_lens.clone()
+    for lens, kernel in ((full, "eight-wave kernel"), (full.clamp(max=150), "four-wave kernel"), (full, "eight-wave kernel"), (full // 7, "four-wave kernel")):
+        assert gla.gla_decode_kernel_name(prm, 0, lens.tolist()) == kernel
+        dp.seq_lens.copy_(lens)
+        out.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        got = out.clone(), lse.clone()
+        want = gla.gla_decode(*dp.args(), out_dtype=torch.float32)
+        torch.cuda.synchronize()
+        assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
+
+
 def test_eight_wave_kernel_repeats_bit_for_bit():
     """Many segments, moved references and residual passes: the same call gives the same bits."""
     p = _problem("repeat", [70, 300, 64, 1, 513] * 4 + [30000], T=1, h_q=128, h_c=1, d_v=512, page_size=64, seed=71, q_gain=3.0)
