@@ -57,7 +57,8 @@ struct ProjParams {
   int32_t sum_groups, c_fp32, direct;
 };
 
-template <int MT, int NT>
+// STREAM: the weights are fetched with the streaming hint (chosen by the host, see run_proj).
+template <int MT, int NT, bool STREAM>
 __global__ __launch_bounds__(256) void proj_kernel(ProjParams p) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int r = lane & 31, h = lane >> 5;
@@ -70,8 +71,8 @@ __global__ __launch_bounds__(256) void proj_kernel(ProjParams p) {
   // One ring of NST stages per workgroup; a stage holds, for 64 input features, the 32 weight rows of each
   // of the four waves (private to the wave) and the 32*MT query rows (shared: each wave fetches a quarter).
   // (NT = 1: three or four stages, 72-80 KB: two workgroups per compute unit, one streaming while the other
-  // starts up or stores.  NT = 2: three stages of up to 40 KB, one workgroup per compute unit; the host
-  // then launches about one workgroup per compute unit.  Two and four stages measured 5 % and 1 % slower.)
+  // starts up or stores.  NT = 2: three stages of up to 48 KB, one workgroup per compute unit; the host
+  // then launches about one workgroup per compute unit.  Two and four stages of 40 KB measured 5 % and 1 % slower.)
   constexpr int NST = NT > 1 ? 3 : (MT == 1 ? 4 : 3);
   constexpr int kStage = (4 * NT + MT) * 4096;
   constexpr int kAOff = 4 * NT * 4096;  // the query rows follow the weights in a stage
@@ -96,7 +97,7 @@ __global__ __launch_bounds__(256) void proj_kernel(ProjParams p) {
     unsigned char* dst = smem + stage * kStage;
 #pragma unroll
     for (int j = 0; j < 4 * NT; ++j)
-      __builtin_amdgcn_global_load_lds((global_cvoid_t*)(wsrc[j] + (int64_t)k * 2), (lds_void_t*)(dst + wave * (NT * 4096) + j * 1024), 16, 0, 0);
+      __builtin_amdgcn_global_load_lds((global_cvoid_t*)(wsrc[j] + (int64_t)k * 2), (lds_void_t*)(dst + wave * (NT * 4096) + j * 1024), 16, 0, STREAM ? 2 : 0);
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt)
       __builtin_amdgcn_global_load_lds((global_cvoid_t*)(asrc[mt] + (int64_t)k * 2), (lds_void_t*)(dst + kAOff + mt * 4096 + wave * 1024), 16, 0, 0);
@@ -143,7 +144,7 @@ __global__ __launch_bounds__(256) void proj_kernel(ProjParams p) {
         static_for<0, 4>([&](auto sc) {
           constexpr int s = decltype(sc)::value;
           constexpr int left = (3 - s) * (NT + MT);  // reads of later steps may still be in flight
-          lds_wait<left>(wf[0][s]);
+          lds_wait<(left < 15 ? left : 15)>(wf[0][s]);
           static_for<0, NT>([&](auto nc) {
             constexpr int nt = decltype(nc)::value;
             asm volatile("" : "+v"(wf[nt][s]));  // (covered by the wait above: LDS returns in order)
@@ -187,12 +188,12 @@ __global__ __launch_bounds__(256) void proj_kernel(ProjParams p) {
   }
 }
 
-// (Instantiated here, around the reduction: the three kernels of up to 32 rows then lie side by side in memory.  An
+// (Instantiated here, ahead of the reduction: the three kernels of up to 32 rows then lie side by side in memory.  An
 // attention block alternates between them and the decode's two, about 58 KB of code together; spread over the code object
 // as they came, they displaced one another in the 64 KB instruction cache more often: a block of 24 sequences 142.5 us,
 // 141.9 this way, and between 141.4 and 144.2 with other orders of the same kernels.)
-template __global__ void proj_kernel<1, 2>(ProjParams);
-template __global__ void proj_kernel<1, 1>(ProjParams);
+template __global__ void proj_kernel<1, 2, true>(ProjParams);
+template __global__ void proj_kernel<1, 1, false>(ProjParams);
 
 // Sum of the partials of one output: over all grid.z slices (output projection)
 // or over the ksplit slices of each group (absorbed query).  One thread per four
@@ -229,7 +230,5 @@ __global__ __launch_bounds__(256) void proj_reduce_kernel(ProjParams p) {
   }
 }
 
-template __global__ void proj_kernel<2, 2>(ProjParams);
-template __global__ void proj_kernel<2, 1>(ProjParams);
 
 }  // namespace gla

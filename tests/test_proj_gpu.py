@@ -70,6 +70,27 @@ def test_output_proj_against_oracle(M, G, N, K):
         check_projection(c.double().cpu().numpy(), ref, abs_prod, bf16_out=dt == torch.bfloat16, what=f"out-proj {M}x{G}x{N}x{K} {dt}")
 
 
+@pytest.mark.parametrize("M,G,N,K", [(65, 2, 1632, 6208), (97, 1, 5120, 16384), (128, 3, 1056, 12352), (129, 2, 2048, 8192)])
+def test_output_proj_of_more_than_64_rows(M, G, N, K):
+    """Long sums take up to 128 rows per workgroup: one row past 64, a last block of one row, full tiles, one row past 128;
+    (97, 1, 5120, 16384) has weights that are fetched with the streaming hint.  A workspace with room for the partials of
+    64 rows per workgroup only is still accepted."""
+    g = torch.Generator().manual_seed(820 + M)
+    a = (torch.randn(M, G, K, generator=g) * 0.05).to(torch.bfloat16)
+    w = projection_weights(G, N, K, seed=821 + M)
+    ref = oracle.project(bf16_bits(a), bf16_bits(w), sum_groups=True)
+    abs_prod = np.einsum("mgk,gnk->mn", np.abs(a.double().numpy()), np.abs(w.double().numpy()))
+    ad, wd = a.cuda(), w.cuda()
+    # 64 rows per workgroup: about one workgroup per compute unit over n blocks, row blocks, groups and ranges
+    base = (N + 255) // 256 * ((M + 63) // 64) * G
+    slices = G * max(1, torch.cuda.get_device_properties(0).multi_processor_count // base)
+    for dt, ws in ((torch.float32, None), (torch.bfloat16, None), (torch.float32, slices * M * N * 4)):
+        ws = None if ws is None else torch.empty(ws, dtype=torch.uint8, device="cuda")
+        c = gla.gla_output_proj(ad, wd, out_dtype=dt, workspace=ws)
+        torch.cuda.synchronize()
+        check_projection(c.double().cpu().numpy(), ref, abs_prod, bf16_out=dt == torch.bfloat16, what=f"out-proj {M}x{G}x{N}x{K} {dt}")
+
+
 def test_projection_argument_checks():
     a = torch.zeros(4, 2, 64, dtype=torch.bfloat16, device="cuda")
     with pytest.raises(gla.GlaError) as e:
