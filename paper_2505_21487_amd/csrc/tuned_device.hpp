@@ -247,6 +247,16 @@ __device__ __forceinline__ float half_swap_sum(float x) {
   return a + b;
 }
 
+// Results in bf16, 16 bytes per lane.  The lanes of a half-wave hold dims 0 .. 3 (lower) or 4 .. 7 (upper) of two runs of
+// eight dims, a and b; afterwards the lower half holds all eight of a, the upper half all eight of b.
+__device__ __forceinline__ u32x4_t join_halves_bf16(f32x4_t a, f32x4_t b) {
+  uint32_t a0 = cvt_pk_bf16(a[0], a[1]), a1 = cvt_pk_bf16(a[2], a[3]), b0 = cvt_pk_bf16(b[0], b[1]), b1 = cvt_pk_bf16(b[2], b[3]);
+  asm volatile("s_nop 1\n\tv_permlane32_swap_b32 %0, %2\n\tv_permlane32_swap_b32 %1, %3" : "+v"(a0), "+v"(a1), "+v"(b0), "+v"(b1));
+  return u32x4_t{a0, a1, b0, b1};
+}
+typedef u32x4_t __attribute__((aligned(8))) u32x4_a8_t;  // (rows of a strided bf16 output are aligned to 8 bytes only)
+__device__ __forceinline__ void store_b128_align8(void* dst, u32x4_t v) { *(u32x4_a8_t*)dst = v; }
+
 // Inclusive prefix sum over the 64 lanes with data-parallel-primitive moves
 // (no LDS round trips): shifts by 1, 2, 4, 8 inside each row of 16 lanes, then
 // the last lane of row 0 / 2 is broadcast into row 1 / 3 and lane 31 into the

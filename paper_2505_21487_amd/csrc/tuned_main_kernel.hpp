@@ -881,16 +881,16 @@ __global__ __launch_bounds__(64 * NG * WPG * KS) void tuned_main_kernel(DevParam
       const float m_new = bump ? mx : m_ref;
       const float alpha = bump ? __builtin_amdgcn_exp2f(m_ref - m_new) : 1.0f;  // m_ref = -inf -> 0
       l_run *= alpha;
+      if (__ballot(m_ref != -INFINITY)) {  // (a segment's first tile: all sums are zero still)
 #pragma unroll
-      for (int db = 0; db < NDB; ++db) {  // one 16-register block at a time through the vector ALU
-        f32x16_t t = o[db];
-        pin_arch(t);
+        for (int db = 0; db < NDB; ++db) {  // one 16-register block at a time through the vector ALU
+          f32x16_t t = o[db];
+          pin_arch(t);
 #pragma unroll
-        for (int i = 0; i < 16; ++i) t[i] *= alpha;
-        o[db] = t;
-        pin_acc(o[db]);
-      }
-      {
+          for (int i = 0; i < 16; ++i) t[i] *= alpha;
+          o[db] = t;
+          pin_acc(o[db]);
+        }
         f32x16_t t = o_one;
         pin_arch(t);
 #pragma unroll
@@ -1139,26 +1139,44 @@ __global__ __launch_bounds__(64 * NG * WPG * KS) void tuned_main_kernel(DevParam
         if (!complete) slot[(size_t)TT::kRows * DV + lr] = lse;
         else if (row_valid && kx == 0) p.lse[((int64_t)row_b * p.T + row_t) * p.h_q + row_h] = lse;
       }
+      // One loop per kind of result: a choice inside the loop cost a jump per store (2.1 us per segment).
+      if (!complete) {
+        // fragment order: one contiguous 1 KiB block per (wave, db, q4), lane-linear; rows that do not exist are left out
+        float* const dst = slot + (size_t)(wave * NDB * 4) * 256 + lane * 4;
+        if (row_valid) {
 #pragma unroll
-      for (int db = 0; db < NDB; ++db) {  // one 16-register block at a time
-        f32x16_t t16 = o[db];
-        pin_arch(t16);
+          for (int db = 0; db < NDB; ++db) {  // one 16-register block at a time
+            f32x16_t t = o[db];
+            pin_arch(t);
 #pragma unroll
-        for (int q4 = 0; q4 < 4; ++q4) {
-          const int dim = kx * DVW + 32 * db + 8 * q4 + 4 * hi;
-          const f32x4_t v = {t16[4 * q4] * inv, t16[4 * q4 + 1] * inv, t16[4 * q4 + 2] * inv, t16[4 * q4 + 3] * inv};
-          if (!complete) {
-            // fragment order: one contiguous 1 KiB block per (wave, db, q4), lane-linear
-            *(f32x4_t*)(slot + (size_t)((wave * NDB + db) * 4 + q4) * 256 + lane * 4) = v;
-          } else if (row_valid) {
-            if (p.out_fp32) {
-              *(f32x4_t*)((float*)p.out + ob + dim) = v;
-            } else {
-              u32x2_t pk;
-              pk[0] = (uint32_t)f32_to_bf16_bits(v[0]) | ((uint32_t)f32_to_bf16_bits(v[1]) << 16);
-              pk[1] = (uint32_t)f32_to_bf16_bits(v[2]) | ((uint32_t)f32_to_bf16_bits(v[3]) << 16);
-              *(u32x2_t*)((uint16_t*)p.out + ob + dim) = pk;
-            }
+            for (int q4 = 0; q4 < 4; ++q4)
+              *(f32x4_t*)(dst + (db * 4 + q4) * 256) = f32x4_t{t[4 * q4] * inv, t[4 * q4 + 1] * inv, t[4 * q4 + 2] * inv, t[4 * q4 + 3] * inv};
+          }
+        }
+      } else if (p.out_fp32) {
+        float* const dst = (float*)p.out + ob + kx * DVW + 4 * hi;
+        if (row_valid) {
+#pragma unroll
+          for (int db = 0; db < NDB; ++db) {
+            f32x16_t t = o[db];
+            pin_arch(t);
+#pragma unroll
+            for (int q4 = 0; q4 < 4; ++q4)
+              *(f32x4_t*)(dst + 32 * db + 8 * q4) = f32x4_t{t[4 * q4] * inv, t[4 * q4 + 1] * inv, t[4 * q4 + 2] * inv, t[4 * q4 + 3] * inv};
+          }
+        }
+      } else {
+        uint16_t* const dst = (uint16_t*)p.out + ob + kx * DVW + 8 * hi;
+#pragma unroll
+        for (int db = 0; db < NDB; ++db) {
+          f32x16_t t = o[db];
+          pin_arch(t);
+#pragma unroll
+          for (int q8 = 0; q8 < 2; ++q8) {
+            // a lane holds four dims of each eight: exchanged with the other half-wave it holds all eight of every second
+            const u32x4_t v = join_halves_bf16(f32x4_t{t[8 * q8] * inv, t[8 * q8 + 1] * inv, t[8 * q8 + 2] * inv, t[8 * q8 + 3] * inv},
+                                               f32x4_t{t[8 * q8 + 4] * inv, t[8 * q8 + 5] * inv, t[8 * q8 + 6] * inv, t[8 * q8 + 7] * inv});
+            if (row_valid) store_b128_align8(dst + 32 * db + 16 * q8, v);
           }
         }
       }
