@@ -68,6 +68,7 @@ struct DevParams {
   // tuned kernel: flat partition of all key tiles of the batch into chunks
   int32_t num_chunks;       // chunks of the tile list (the main kernel runs one workgroup per chunk and row block)
   int32_t chunk_tiles;      // > 0: fixed tiles per chunk; 0: ceil(total / num_chunks)
+  int32_t setup_tiles;      // chunks derived on the device: tiles' worth of time that a chunk's step into another unit costs (cut_list)
   // tuned kernel: constants of the plan, worked out once on the host
   int32_t mb;               // row blocks per group (workgroups per chunk)
   int32_t upb;              // units (group blocks) per sequence

@@ -156,12 +156,11 @@ __global__ __launch_bounds__(256) void flex_main_kernel(DevParams p) {
   const int rb = (int)((unsigned)strand / HB);
   const int g0 = (strand - rb * (int)HB) * GPW;  // first group of this wave
   const int L_first = lane < p.B ? p.seq_lens[lane] : 0;
-  const int incl0 = wave_incl_scan(tiles_of<32>(L_first));
-  const int total = total_tiles<32>(p, 1, lane, incl0);
-  const int C = p.chunk_tiles > 0 ? p.chunk_tiles : max(1, (int)(((unsigned)total + (unsigned)p.num_chunks - 1) / (unsigned)p.num_chunks));
-  const int pos0 = chunk * C;  // (the host keeps num_chunks * max tiles per chunk below 2^31)
-  if (pos0 >= total) return;
-  int left = min(C, total - pos0);  // tiles of this chunk not yet worked on
+  const ListCut cut = cut_list<32>(p, 1, lane, L_first);
+  const int total = cut.tiles;
+  const ChunkSpan span0 = locate_chunk<32>(p, 1, cut, chunk, lane, L_first);
+  int left = span0.n_tiles;  // tiles of this chunk not yet worked on
+  if (left <= 0) return;
   // a cache larger than the chip's last-level cache is fetched with the streaming hint (read once per call, it
   // would only push the page table, the queries and the partial results out of the caches)
   const bool stream_hint = (int64_t)total * 32 * (p.h_c * (VB + (SEPK ? KB : 0)) + RB) > p.stream_min_bytes;
@@ -214,7 +213,7 @@ __global__ __launch_bounds__(256) void flex_main_kernel(DevParams p) {
 
   // ---- two cursors over the chunk: `cur`, the tile being worked on, and `pre`, NST - 1 tiles ahead,
   //      the tile being fetched (it crosses into the next sequence without the ring running dry)
-  TileCursor cur = locate_tile<32>(p, 1, pos0, lane, L_first, incl0);
+  TileCursor cur = span0.cur;
   TileCursor pre = cur;
   int pre_left = left;
   const int lgP = p.lg_page;             // page size is a power of two (of at least 32 tokens unless LANE)

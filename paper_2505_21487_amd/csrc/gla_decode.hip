@@ -64,6 +64,7 @@ struct FlexPlan {
   int chunks;       // chunks of the tile list (one wave per chunk and strand)
   int chunk_tiles;  // > 0: fixed tiles per chunk; 0: ceil(total / chunks), worked out on the device
   bool lane;        // pages of fewer than 32 tokens: the kernel variant that forms one address per row and lane
+  int64_t list_bound; // tiles of the list at most
 };
 
 int flex_variant(const gla_decode_params* p, int mode) {
@@ -125,6 +126,7 @@ bool flex_plan(const gla_decode_params* p, int mode, const KeyCache* kc, bool le
   chunks = std::max<int64_t>(1, chunks);
   if (chunks * plan->strands > (int64_t)0x3fffffff || bound + chunks > (int64_t)0x7fffffff) return false;
   plan->chunks = (int)chunks;
+  plan->list_bound = bound;
   return true;
 }
 
@@ -233,6 +235,8 @@ int launch_flex(const gla_decode_params* p, const FlexPlan& plan, DevParams& d, 
   d.num_chunks = plan.chunks;
   d.chunk_tiles = plan.chunk_tiles;
   d.flex_rb = plan.rb;
+  d.setup_tiles = setup_tiles(kSetupTilesFlex, plan.list_bound);
+  d.fd_chunks = make_fastdiv((uint32_t)plan.chunks);
   int lg = 0;
   while ((1 << lg) < p->page_size) ++lg;
   d.lg_page = lg;

@@ -309,35 +309,106 @@ __device__ __forceinline__ int total_tiles(const DevParams& p, int UPB, int lane
   return total;
 }
 
-// Locate flat tile index `pos` (< total): which sequence / unit / tile.
-// L_first / incl0: length and inclusive tile prefix of the first 64 sequences.
+// The cut of the tile list into chunks.  A chunk that crosses from one unit into the next pays for the crossing: the
+// result of the first is stored, the queries of the second are fetched, its first tiles move the softmax reference.  So
+// every unit holds p.setup_tiles positions in front of its tiles, and chunks are equal in positions: a workgroup with
+// three short sequences gets fewer tiles than one inside a long sequence (before, the median workgroup of a decode of 24
+// ragged sequences ended after 28 us, the last one, with three segments, after 54).  Where all sequences have the same
+// number of tiles and equal chunks in tiles end with them, no chunk crosses anything and the positions are left out.
+// What it gains, and how many positions: kSetupTiles.
+struct ListCut {
+  int tiles;     // tiles of the list
+  int setup;     // positions in front of a unit's tiles
+  int positions; // tiles and set-ups
+  int chunk;     // positions per chunk
+  int incl0;     // inclusive prefix sums of the tiles (per unit) of the first 64 sequences
+};
+// L_first: lengths of the first 64 sequences.  (Every wave computes the same values.)
 template <int TOK>
-__device__ __forceinline__ TileCursor locate_tile(const DevParams& p, int UPB, int pos, int lane, int L_first,
-                                                  int incl0) {
-  TileCursor c = {0, 0, 0, 0, 0};
-  int before = 0;
+__device__ __forceinline__ ListCut cut_list(const DevParams& p, int UPB, int lane, int L_first) {
+  ListCut c;
+  const int tl0 = tiles_of<TOK>(L_first);
+  c.incl0 = wave_incl_scan(tl0);
+  int tiles = __builtin_amdgcn_readlane(c.incl0, 63);
+  unsigned long long held = __ballot(tl0 > 0);
+  int seqs = __popcll(held);
+  int same = held ? __builtin_amdgcn_readlane(tl0, __ffsll((long long)held) - 1) : 0;  // tiles of every sequence, 0: they differ
+  if (__ballot(tl0 > 0 && tl0 != same)) same = 0;
+  for (int base = 64; base < p.B; base += 64) {
+    const int idx = base + lane;
+    const int tl = idx < p.B ? tiles_of<TOK>(p.seq_lens[idx]) : 0;
+    tiles += __builtin_amdgcn_readlane(wave_incl_scan(tl), 63);
+    held = __ballot(tl > 0);
+    if (seqs == 0 && held) same = __builtin_amdgcn_readlane(tl, __ffsll((long long)held) - 1);
+    if (__ballot(tl > 0 && tl != same)) same = 0;
+    seqs += __popcll(held);
+  }
+  c.tiles = tiles * UPB;
+  c.setup = 0;
+  c.positions = c.tiles;
+  c.chunk = p.chunk_tiles;
+  if (p.chunk_tiles <= 0) {
+    c.chunk = (int)fast_div((unsigned)(c.tiles + p.num_chunks - 1), p.fd_chunks);
+    if (p.setup_tiles > 0 && c.chunk > 0 && (same == 0 || (unsigned)same % (unsigned)c.chunk != 0)) {
+      c.setup = p.setup_tiles;
+      c.positions = c.tiles + c.setup * UPB * seqs;
+      c.chunk = (int)fast_div((unsigned)(c.positions + p.num_chunks - 1), p.fd_chunks);
+    }
+  }
+  return c;
+}
+
+// What a chunk holds.
+struct ChunkSpan {
+  TileCursor cur;  // its first tile
+  int n_tiles;     // its tiles (0: none)
+  int at;          // position of the first tile of cur's unit
+};
+template <int TOK>
+__device__ __forceinline__ ChunkSpan locate_chunk(const DevParams& p, int UPB, const ListCut& c, int chunk_id, int lane, int L_first) {
+  ChunkSpan r = {{0, 0, 0, 0, 0}, 0, 0};
+  const int64_t begin64 = (int64_t)chunk_id * c.chunk;
+  if (begin64 >= c.positions) return r;
+  const int begin = (int)begin64, end = (int)min((int64_t)c.positions, begin64 + c.chunk);
+  int tile0 = 0, tile1 = end == c.positions ? c.tiles : -1;  // list indices of the first tile and of the one behind the last
+  bool found = false;
+  int tiles_before = 0, seqs_before = 0;  // (per unit)
   for (int base = 0; base < p.B; base += 64) {
     const int idx = base + lane;
     const int L = base == 0 ? L_first : (idx < p.B ? p.seq_lens[idx] : 0);
     const int tl = tiles_of<TOK>(L);
-    const int w = tl * UPB;
-    const int incl = (base == 0 ? incl0 : wave_incl_scan(w)) + before;
-    const int excl = incl - w;
-    const unsigned long long hit = __ballot(w > 0 && excl <= pos && pos < incl);
-    if (hit) {
+    const int incl = base == 0 ? c.incl0 : wave_incl_scan(tl);
+    const unsigned long long held = __ballot(tl > 0);
+    const int below = (int)__builtin_amdgcn_mbcnt_hi((unsigned)(held >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)held, 0));
+    const int tiles_x = tiles_before + incl - tl;                                  // tiles (per unit) of the sequences before
+    const int at = UPB * (tiles_x + c.setup * (seqs_before + below));              // this sequence's first position
+    const int upto = tl > 0 ? at + UPB * (tl + c.setup) : at;
+    // unit and tile of a position: the first tile of the unit for one of its set-up positions
+    auto find = [&](int pos, TileCursor& cur, int& tile, int& unit_at) -> bool {
+      const unsigned long long hit = __ballot(at <= pos && pos < upto);
+      if (!hit) return false;
       const int src = __ffsll((long long)hit) - 1;
-      const int ex = __builtin_amdgcn_readlane(excl, src);
-      c.tiles_b = __builtin_amdgcn_readlane(tl, src);
-      c.L = __builtin_amdgcn_readlane(L, src);
-      c.b = base + src;
-      const int rem = pos - ex;
-      c.ub = (int)((unsigned)rem / (unsigned)c.tiles_b);
-      c.j = rem - c.ub * c.tiles_b;
-      return c;
+      cur.tiles_b = __builtin_amdgcn_readlane(tl, src);
+      cur.L = __builtin_amdgcn_readlane(L, src);
+      cur.b = base + src;
+      const int x = __builtin_amdgcn_readlane(at, src), per = cur.tiles_b + c.setup;
+      cur.ub = UPB > 1 ? (int)((unsigned)(pos - x) / (unsigned)per) : 0;
+      unit_at = x + cur.ub * per + c.setup;
+      cur.j = max(0, pos - unit_at);
+      tile = UPB * __builtin_amdgcn_readlane(tiles_x, src) + cur.ub * cur.tiles_b + cur.j;
+      return true;
+    };
+    if (!found) found = find(begin, r.cur, tile0, r.at);
+    if (found) {
+      TileCursor last;
+      int last_at;
+      if (tile1 >= 0 || find(end, last, tile1, last_at)) break;
     }
-    before = __builtin_amdgcn_readlane(incl, 63);
+    tiles_before += __builtin_amdgcn_readlane(incl, 63);
+    seqs_before += __popcll(held);
   }
-  return c;
+  r.n_tiles = tile1 - tile0;
+  return r;
 }
 
 template <int TOK>

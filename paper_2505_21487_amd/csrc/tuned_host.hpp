@@ -24,6 +24,7 @@ struct TunedPlan {
   int wide_tiles;  // > 0: the eight-wave kernel is launched too and runs, instead, on lists of that many tiles or more
   int wide_chunks; // its chunks, of twice the tokens per tile
   bool stream;     // fetch the cache with the streaming hint
+  int64_t list_bound; // tiles of the list at most
 };
 
 inline int device_cu_count() {
@@ -42,6 +43,19 @@ inline int device_cu_count() {
 inline bool aligned16(const void* ptr) { return ((uintptr_t)ptr & 15u) == 0; }
 
 constexpr int kMinChunkTiles = 4;
+
+// What a chunk's step into another unit costs, in tiles (cut_list): on the four-wave kernel 8 to 11 us, a tile being 1.3 to
+// 1.45.  us per call with 0 / 3 / 6 / 9 / 12: absorbed query, decode of 24 ragged sequences and output projection 132.2 /
+// 121.5 / 114.9 / 113.2 / 112.6; GLA-2 16 ragged sequences 39.2 / 33.3 / 30.7 / 30.4 / 30.3, 100 60.2 / 50.0 / 47.0 / 44.8 /
+// 45.8, two query positions 37 sequences 116.0 / 107.9 / 99.8 / 97.0 / 97.2; MLA shape 15 x 1024 and 1 x 65536 73.5 / 71.4 /
+// 67.4 / 67.3 / 66.7, 100 x 50 to 600 65.5 / 52.1 / 50.9 / 48.7 / 47.0; GTA-4 d_h 128 (a smaller result to store) 128 long
+// sequences 417.5 / 414.3 / 414.2 / 415.7 / 415.6, 10 of 500 to 6000 27.1 / 23.1 / 22.9 / 22.7 / 22.5.
+// Eight-wave kernel, tiles of 64 tokens, MLA shape 128 ragged sequences, 0 / 2 / 4 / 7 / 10: 374.7 / 368.2 / 360.2 / 356.9 / 358.0.
+// Second MFMA kernel 0 / 2 / 4 / 8 / 12: GTA-4 d_h 64 48 sequences 36.3 / 34.4 / 34.4 / 34.7 / 35.4, d_h 96 30 sequences
+// 25.7 / 23.4 / 22.3 / 22.6 / 22.6, GQA-4 12 sequences 22.7 / 20.6 / 20.7 / 20.4 / 20.6.
+constexpr int kSetupTiles = 8, kSetupTiles128 = 6, kSetupTilesWide = 6, kSetupTilesFlex = 4;
+// (none where positions could leave 32 bits)
+inline int setup_tiles(int n, int64_t list_bound) { return list_bound <= 0x3fffffff / (n + 1) ? n : 0; }
 
 // Batches of up to this many sequences may be cut into chunks of fewer tiles while the grid is small (tuned_plan,
 // flex_plan).  Larger ones have their parallelism already, and a cut that falls badly costs them more than the rest
@@ -163,6 +177,7 @@ inline bool tuned_plan(const gla_decode_params* p, int is_gta, bool lean, TunedP
     const int64_t ct = (plan->chunk_tiles + 1) / 2, max64 = (max_tiles + 1) / 2;
     plan->wide_chunks = (int)(((int64_t)(plan->units / plan->mb) * max64 + ct - 1) / ct);
   }
+  plan->list_bound = bound;
   // upper bound of the batch's cache bytes (the lengths are known on the device only) against the chip's
   // last-level cache
   plan->stream = bound * tok * 2 * ((int64_t)ng * p->d_v + p->d_rope) > kLastLevelCacheBytes;
@@ -220,6 +235,7 @@ inline int tuned_launch(const gla_decode_params* p, int is_gta, bool lean, DevPa
     d.fd_upb_mb = make_fastdiv((uint32_t)(d.upb * plan.mb));
   }
   d.wide_tiles = plan.wide_tiles;
+  d.setup_tiles = setup_tiles(plan.dv == 128 ? kSetupTiles128 : kSetupTiles, plan.list_bound);
   if (plan.dv == 256 && plan.dn == 256) return tuned_launch_256(plan, d, st, ev);
   if (plan.dv == 128 && plan.dn == 64) return tuned_launch_128(plan, d, st, ev);
   if (plan.dv == 512 && plan.dn == 512) return tuned_launch_512(plan, d, st, ev);

@@ -176,22 +176,16 @@ __global__ __launch_bounds__(64 * NG * WPG * KS) void tuned_main_kernel(DevParam
   }
 
   // ---- plan: this workgroup's chunk [c0, c1) of the flat tile list
-  const int incl0 = wave_incl_scan(tiles_of<TOK>(L_first) * UPB);
-  const int n_total = total_tiles<TOK>(p, UPB, lane, incl0);
-  if (n_total <= 0) return;
+  const ListCut cut = cut_list<TOK>(p, UPB, lane, L_first);
+  if (cut.tiles <= 0) return;
   if constexpr (eight_wave_shape(DV, NG, WPG, KS)) {
-    if (p.wide_tiles > 0 && n_total >= p.wide_tiles) return;  // the eight-wave kernel, launched next, takes this batch
+    if (p.wide_tiles > 0 && cut.tiles >= p.wide_tiles) return;  // the eight-wave kernel, launched next, takes this batch
   }
-  // Chunk i covers tiles [i * chunk, (i + 1) * chunk): a fixed length if the
-  // caller chose a split count, else an equal share of the list.
-  const int chunk = p.chunk_tiles > 0 ? p.chunk_tiles : (int)fast_div((unsigned)(n_total + n_chunks - 1), p.fd_chunks);
-  auto chunk_start = [&](int i) -> int { return (int)min((int64_t)n_total, (int64_t)i * chunk); };
-  const int c0 = chunk_start(chunk_id);
-  const int c1 = chunk_start(chunk_id + 1);
-  if (c0 >= c1) return;  // only chunks past the end of the list are empty: no unit spans them
-  const int n_tiles = c1 - c0;
-
-  TileCursor cur = locate_tile<TOK>(p, UPB, c0, lane, L_first, incl0);  // compute position
+  const ChunkSpan span0 = locate_chunk<TOK>(p, UPB, cut, chunk_id, lane, L_first);
+  const int n_tiles = span0.n_tiles;
+  if (n_tiles <= 0) return;  // (past the end of the list, or all set-up of a unit that the next chunk begins: no unit spans it)
+  TileCursor cur = span0.cur;                            // compute position
+  int unit_at = span0.at;                                // list position of its unit's first tile
   TileCursor pre = cur;                                  // prefetch position
 
   // ---- tile loads, global -> LDS, 16 B per lane, 1 KiB per wave instruction.
@@ -1109,7 +1103,6 @@ __global__ __launch_bounds__(64 * NG * WPG * KS) void tuned_main_kernel(DevParam
         ++k;
       }
     }
-    for (int i = 0; i < seg_n; ++i) advance<TOK>(p, UPB, cur);
 
     // ================= end of segment: write the unit's result or its partial
     wait_states<16>();  // output accumulators: last MFMA -> vector ALU reads
@@ -1129,10 +1122,9 @@ __global__ __launch_bounds__(64 * NG * WPG * KS) void tuned_main_kernel(DevParam
       if (seg_j0 == 0 && tid == 0) {
         // tell the merge kernel which chunks hold this unit: it starts here and
         // ends in the chunk of its last tile
-        const int s_u = c0 + (k - seg_n);
         int2 span;
         span.x = chunk_id;
-        span.y = (s_u + seg_tiles_b - 1) / chunk;
+        span.y = (int)((unsigned)(unit_at + seg_tiles_b - 1) / (unsigned)cut.chunk);
         ((int2*)p.ws_lse)[seg_unit] = span;
       }
       if (hi == 0) {
@@ -1181,6 +1173,9 @@ __global__ __launch_bounds__(64 * NG * WPG * KS) void tuned_main_kernel(DevParam
         }
       }
     }
+    unit_at += seg_tiles_b + cut.setup;
+    cur.j = seg_j0 + seg_n - 1;
+    advance<TOK>(p, UPB, cur);
   }
 }
 

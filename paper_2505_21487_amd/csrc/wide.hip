@@ -23,6 +23,7 @@ int wide_launch(const TunedPlan& plan, const DevParams& four, hipStream_t st) {
   DevParams d = four;  // (tiles of twice as many tokens)
   d.num_chunks = plan.wide_chunks;
   d.chunk_tiles = (plan.chunk_tiles + 1) / 2;
+  d.setup_tiles = setup_tiles(kSetupTilesWide, plan.list_bound);
   d.fd_chunks = make_fastdiv((uint32_t)plan.wide_chunks);
   d.xcd_map = plan.wide_chunks % 8 == 0 ? 1 : 0;
   return plan.dv == 256 ? launch_wide<256, true>(plan, d, st) : launch_wide<512, false>(plan, d, st);

@@ -156,15 +156,13 @@ __global__ __launch_bounds__(512) void wide_main_kernel(DevParams p) {
   if (p.wide_tiles > 0 &&  // (counted as the four-wave kernel counts them: one of the two runs)
       total_tiles<kTok>(p, UPB, lane, wave_incl_scan(tiles_of<kTok>(L_first) * UPB)) < p.wide_tiles)
     return;
-  const int incl0 = wave_incl_scan(tiles_of<TOK>(L_first) * UPB);
-  const int n_total = total_tiles<TOK>(p, UPB, lane, incl0);
-  if (n_total <= 0) return;
-  const int chunk = p.chunk_tiles > 0 ? p.chunk_tiles : (int)fast_div((unsigned)(n_total + n_chunks - 1), p.fd_chunks);
-  const int c0 = (int)min((int64_t)n_total, (int64_t)chunk_id * chunk);
-  const int c1 = (int)min((int64_t)n_total, (int64_t)(chunk_id + 1) * chunk);
-  if (c0 >= c1) return;
-  const int n_tiles = c1 - c0;
-  TileCursor cur = locate_tile<TOK>(p, UPB, c0, lane, L_first, incl0);
+  const ListCut cut = cut_list<TOK>(p, UPB, lane, L_first);
+  if (cut.tiles <= 0) return;
+  const ChunkSpan span0 = locate_chunk<TOK>(p, UPB, cut, chunk_id, lane, L_first);
+  const int n_tiles = span0.n_tiles;
+  if (n_tiles <= 0) return;
+  TileCursor cur = span0.cur;
+  int unit_at = span0.at;  // list position of the unit's first tile
 
   auto next_unit = [&](TileCursor& c) {
     c.j = 0;
@@ -704,7 +702,7 @@ __global__ __launch_bounds__(512) void wide_main_kernel(DevParams p) {
       if (seg_j0 == 0 && tid == 0) {  // tells the merge kernel which chunks hold this unit
         int2 span;
         span.x = chunk_id;
-        span.y = (c0 + (k - seg_n) + cur.tiles_b - 1) / chunk;
+        span.y = (int)((unsigned)(unit_at + cur.tiles_b - 1) / (unsigned)cut.chunk);
         ((int2*)p.ws_lse)[(cur.b * UPB + cur.ub) * MB + mb_wg] = span;
       }
       if (hi == 0 && (pe & 1) == 0) {
@@ -731,6 +729,7 @@ __global__ __launch_bounds__(512) void wide_main_kernel(DevParams p) {
           }
         }
     }
+    unit_at += cur.tiles_b + cut.setup;
     next_unit(cur);
   }
   wait_vmcnt<0>();  // (tiles fetched again past the end of the chunk: let them land before the wave leaves)

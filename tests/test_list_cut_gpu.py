@@ -1,0 +1,37 @@
+"""The cut of a batch's tile list into chunks against the oracle, where it can go wrong: sequences on either side of the
+64 that are counted at once, empty ones first, last and between, chunks that begin in front of a sequence or hold several,
+several units per sequence, equal lengths that end with a chunk and such that do not."""
+import pytest
+
+import paper_2505_21487_amd as gla
+from workloads import make_problem
+
+from gpu_util import check_problem
+
+pytestmark = pytest.mark.gpu
+
+# kind, heads, groups, d_v, RoPE dims, query positions: every kernel that works on a cut list; with 3 positions two units
+# per sequence (groups), with 4 two row blocks too
+KERNELS = {
+    "gla2_h16": ("gla", 16, 2, 256, 64, 1), "gla2_units": ("gla", 96, 2, 256, 64, 3), "gla4_units": ("gla", 64, 4, 256, 64, 2),
+    "mla": ("gla", 40, 1, 512, 64, 1), "gta4_d128": ("gta", 32, 4, 128, 64, 1), "gta4_d64": ("gta", 32, 4, 64, 32, 1),
+    "gqa4": ("gqa", 16, 4, 128, 0, 2),
+}
+LENGTHS = {
+    "ragged": [0, 33, 700, 1, 0, 0, 95, 64, 2100, 5, 31, 32, 400, 0],
+    "empty_first_64": [0] * 64 + [70, 0, 1300, 3],
+    "around_64": [40] * 62 + [900, 0, 0, 800, 33] + [7] * 60 + [0, 500],
+    "equal_aligned": [256] * 16,
+    "equal_not_aligned": [352] * 19,
+    "one_long": [64] * 9 + [5000],
+}
+
+
+@pytest.mark.parametrize("lengths", sorted(LENGTHS))
+@pytest.mark.parametrize("kernel", sorted(KERNELS))
+def test_cut_list(kernel, lengths):
+    kind, h, g, d_v, d_r, T = KERNELS[kernel]
+    lens = LENGTHS[lengths]
+    p = make_problem(f"{kernel}_{lengths}", kind=kind, seq_lens=lens, T=T, h_q=h, h_c=g, d_v=d_v, **({"d_r": d_r} if d_r else {}), seed=8100 + len(kernel) + len(lengths),
+                     num_pages=sum((n + 63) // 64 for n in lens) + 64, poison_tail=True)
+    check_problem(p, impl=gla.GLA_IMPL_TUNED, what=f"{kernel} {lengths}")
