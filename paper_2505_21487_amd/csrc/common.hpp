@@ -77,6 +77,7 @@ struct DevParams {
   int32_t tiles_full;       // tiles of a sequence that fills its page-table row
   int32_t chunk_guess;      // chunk length if every sequence did
   FastDiv fd_mb, fd_chunks, fd_gq, fd_tiles_full, fd_units_full, fd_upb_mb;
+  int32_t merge_sets_lg, merge_span, merge_windows;  // merge kernel: log2(sets of every unit), chunks per window, windows (tuned_combine_kernel)
   int32_t wide_tiles;       // > 0: the eight-wave kernel runs if the list has that many tiles of 32 tokens, else the four-wave one
 };
 

@@ -10,164 +10,219 @@ namespace gla {
 // of units without any key:  lse = ln sum_s exp(lse_s),
 // out = sum_s exp(lse_s - lse) out_s.  The main kernel leaves, per unit, the
 // range of chunks that hold it, and stores partial outputs in the register
-// order of its waves (one contiguous 1 KiB block per wave, 32-dim block and
-// quarter), so a task here is one (32-row slab, 32-dim block) of a unit and
-// every access of a partial is a full 1 KiB line run.  The KW waves of a
-// workgroup share one task: wave j merges chunks first + j, first + j + KW, ...
-// around its own reference, and the KW results are merged once more through
-// LDS (long single sequences are cut into hundreds of chunks).  With QS = 4
-// (very few units, each spread over very many chunks: few tasks) a task is cut
-// once more into the four quarters of its 32-dim block, one workgroup each,
-// so that four times as many compute units pull the partials.
-// Grid (units, NG * WPG * DV / 32 * QS), KW waves per workgroup.
-template <int DV, int NG, int WPG, int KS, int TOK, int KW, int QS, int U>
-__global__ __launch_bounds__(64 * KW) void tuned_combine_kernel(DevParams p) {
+// order of its waves, one contiguous 1 KiB block per wave, 32-dim block and
+// quarter.
+//
+// Bound by the latency of a list's loads and by what one compute unit can pull (some 50 bytes per ns), then by the
+// 33 MB of partials that a full grid leaves.  So the work of a unit is spread by the length of its list.  A panel is
+// four 32-dim blocks of one wave of the main kernel, 16 blocks of 1 KiB per chunk.  A short list has one workgroup of
+// four waves per panel, each wave taking four blocks over the whole list.  A longer one has up to 16 workgroups per
+// panel ("sets"), each taking its share of the blocks, down to a block for one wave, two or all four; there 16 chunks
+// are in flight per wave.  How many sets a unit has only its list tells, so the workgroups beyond the first belong to
+// windows of merge_span chunks: the k-th window that lies inside a unit's list is its k-th further set, and the windows
+// that are not needed leave.  Their number is that of the chunks over merge_span, however long or short the lists turn out.
+// us per call, against four waves (or, by the mean length, one or sixteen) for every 32-dim block of every unit: GLA-2 15 x
+// 1024 and 1 x 65536 tokens 56.8 -> 41.2, MLA shape 66.1 -> 53.6, GTA-4 10 sequences of up to 6000 20.7 -> 19.1, 1 x 100000
+// 39.1 -> 35.1, GLA-2 1 x 131072 55.4 -> 53.6, 3 x 1000 19.1 -> 17.8, 64 x 8192 122.0 -> 120.6.
+//
+// Grid: (units * sets * panels, then windows * row blocks * panels), in rows where that is more than a grid's width.
+template <int DV, int NG, int WPG, int KS, int TOK, int NW>
+__global__ __launch_bounds__(64 * NW) void tuned_combine_kernel(DevParams p) {
   constexpr int NWAVES = NG * WPG * KS;
   constexpr int NDB = DV / KS / 32;  // 32-dim blocks per wave of the main kernel
   constexpr int kRows = 32 * NG * WPG;
   constexpr size_t kSlotFloats = (size_t)kRows * DV + 32 * NWAVES;
-  static_assert(KW == 1 || KW == 4 || KW == 16, "waves per task");
-  static_assert(QS == 1 || (QS == 4 && KW > 1), "workgroups per task");
-  constexpr int NQ4 = 4 / QS;  // quarters of the block per workgroup
-  __shared__ float red_m[KW][64], red_z[KW][64];
-  __shared__ f32x4_t red_a[KW][NQ4][64];
-  const int tid = threadIdx.x, lane = tid & 63, kw = tid >> 6;
+  constexpr int PANELS = NWAVES * NDB / 4;
+  constexpr int kMaxSets = 16;
+  static_assert(NDB % 4 == 0 && (PANELS & (PANELS - 1)) == 0, "panels of a unit");
+  static_assert(NW == 4 || NW == 16, "waves per workgroup");
+  __shared__ float red_m[NW][64], red_z[NW][64];
+  __shared__ f32x4_t red_a[16][64];
+  const int lane = threadIdx.x & 63, wave = uniform((int)threadIdx.x >> 6);
   const int col = lane & 31, hi = lane >> 5;
-  const int wv = blockIdx.y / QS;
-  const int q_base = QS == 1 ? 0 : (int)blockIdx.y % QS;  // first quarter this workgroup handles
-  const int w = wv / NDB, db = wv - w * NDB;  // wave of the main kernel and one of its 32-dim blocks
-  const int wpos = w % (WPG * KS), kx = wpos % KS;
-  const int rows_group = p.g_q * p.T;
   const int MB = p.mb;
   const int UPB = p.upb * MB;
-  const int unit = blockIdx.x;  // (sequence, group block, row block)
+  const unsigned block = blockIdx.y * gridDim.x + blockIdx.x, panel = block % PANELS, item = block / PANELS;
+  const unsigned base_items = ((unsigned)p.B * (unsigned)UPB) << p.merge_sets_lg;
+
+  int unit = (int)(item >> p.merge_sets_lg), set = (int)(item & ((1u << p.merge_sets_lg) - 1));  // unit: (sequence, group block, row block)
+  int2 span = {0, 0};
+  if (item >= base_items) {  // a window: whose?
+    const unsigned n = item - base_items, win = fast_div(n, p.fd_mb);
+    if (win >= (unsigned)p.merge_windows) return;  // (the grid's last row)
+    const int mb = (int)(n - win * (unsigned)MB);
+    const int w0 = (int)win * p.merge_span, w1 = w0 + p.merge_span - 1;
+    const int n_units = p.B * p.upb;  // (row blocks apart: they share their chunks)
+    unit = -1;
+    for (int base = 0; base < n_units && unit < 0; base += 256) {
+      int2 sp[4];
+      int len[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int i = min(base + 64 * u + lane, n_units - 1);
+        sp[u] = ((const int2*)p.ws_lse)[(int64_t)i * MB + mb];
+        len[u] = p.seq_lens[(int)fast_div((unsigned)i * (unsigned)MB, p.fd_upb_mb)];
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        // (the range of a unit without tiles is garbage)
+        const unsigned long long hit = __ballot(base + 64 * u + lane < n_units && len[u] > 0 && sp[u].x <= w0 && sp[u].y >= w1);
+        if (hit && unit < 0) {
+          const int src = __ffsll((long long)hit) - 1;
+          unit = (base + 64 * u + src) * MB + mb;
+          span.x = __builtin_amdgcn_readlane(sp[u].x, src);
+          span.y = __builtin_amdgcn_readlane(sp[u].y, src);
+        }
+      }
+    }
+    if (unit < 0) return;  // (several units share these chunks)
+    set = (int)win - (span.x + p.merge_span - 1) / p.merge_span + (1 << p.merge_sets_lg);
+  }
   const int b = (int)fast_div((unsigned)unit, p.fd_upb_mb);
   const int ub = unit - b * UPB;
   const int gb = (int)fast_div((unsigned)ub, p.fd_mb), mb = ub - gb * MB;
-  const int L = p.seq_lens[b];
-  const int2 span = ((const int2*)p.ws_lse)[unit];  // garbage for units without tiles: not used then
-  const bool empty = tiles_of<TOK>(L) == 0;
-  if (!empty && span.x == span.y) return;  // written directly by the main kernel (whole workgroup leaves)
+  bool empty = false;
+  if (item < base_items) {
+    const int L = p.seq_lens[b];
+    span = ((const int2*)p.ws_lse)[unit];  // garbage for units without tiles: not used then
+    empty = tiles_of<TOK>(L) == 0;
+    if (!empty && span.x == span.y) return;  // written directly by the main kernel
+  }
+  int sets = 1 << p.merge_sets_lg;
+  if (!empty && p.merge_windows > 0) {
+    const int inside = (span.y + 1) / p.merge_span - (span.x + p.merge_span - 1) / p.merge_span;
+    while (sets < kMaxSets && 2 * sets <= inside + (1 << p.merge_sets_lg)) sets *= 2;
+  }
+  if (set >= sets) return;
+
+  const int w = (int)panel * 4 / NDB, db0 = (int)panel * 4 % NDB;  // wave of the main kernel, its first 32-dim block
+  const int wpos = w % (WPG * KS), kx = wpos % KS;
+  const int rows_group = p.g_q * p.T;
   const int g = gb * NG + w / (WPG * KS);
   const int R = (mb * WPG + wpos / KS) * 32 + col;
-  const bool valid = R < rows_group;
+  const bool valid = R < rows_group;  // (what pads a slab has no partials)
+  if (__ballot(valid) == 0) return;   // (the same in every wave)
   const int Rc = valid ? R : 0;
   const int t = (int)fast_div((unsigned)Rc, p.fd_gq);
   const int h = g * p.g_q + (Rc - t * p.g_q);
-  const int r = w * 32 + col;  // this lane's entry among the slot's log-sum-exps
   // Chunk span.x holds the unit's first tile (partial slot 1); every later
   // chunk sees a unit that began before it (slot 0).
   const int k_first = empty ? 0 : span.x, k_last = empty ? -1 : span.y;
-  auto slot_of = [&](int k) { return (((size_t)k * MB + mb) * 2 + (k == k_first)) * kSlotFloats; };
-  const float* const lse0 = p.ws_out + (size_t)kRows * DV + r;
-  const float* const frag0 = p.ws_out + (size_t)((w * NDB + db) * 4) * 256 + lane * 4;
+  const float* const lse0 = p.ws_out + (size_t)kRows * DV + w * 32 + col;  // this row's entry among a slot's log-sum-exps
+  const int64_t ob = b * p.out_s[0] + t * p.out_s[1] + h * p.out_s[2] + kx * (DV / KS);
+  float* const lse_out = p.lse + ((int64_t)b * p.T + t) * p.h_q + h;
+  const bool writes_lse = hi == 0 && kx == 0 && db0 == 0;
 
-  // This wave's share, in one pass: a running (reference, sum of weights,
-  // weighted sum), the reference being the running maximum; the sums are
-  // rescaled when it moves.  Full groups of U chunks are requested together
-  // (their loads do not depend on one another: a long chunk list is bound by
-  // memory latency, not bandwidth; U is small where lists are short, since the
-  // registers it takes cost resident waves), the rest one at a time.
-  float m = -INFINITY;
-  float z = 0.f;
-  f32x4_t acc[NQ4];
+  // NQ consecutive blocks from block c0 (of the panel's 16) by kw waves, wave `share` of them taking every kw-th chunk:
+  // one pass around a running reference, U chunks requested together.
+  auto run = [&](auto nqc, auto uc, int c0, int share, int kw) {
+    constexpr int NQ = decltype(nqc)::value, U = decltype(uc)::value;
+    constexpr float kLog2e = 1.4426950408889634f;
+    const float* const frag0 = p.ws_out + (size_t)((w * NDB + db0) * 4 + c0) * 256 + lane * 4;
+    float m = -INFINITY, z = 0.f;
+    f32x4_t acc[NQ];
 #pragma unroll
-  for (int q4 = 0; q4 < NQ4; ++q4) acc[q4] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-  auto rebase = [&](float m_new) {  // m_new > -inf
-    const float keep = m == -INFINITY ? 0.f : expf(m - m_new);
-    z *= keep;
+    for (int c = 0; c < NQ; ++c) acc[c] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    // everything so far to a reference that is not below it (one rounding in front of the exponential)
+    auto rebase = [&](float m_new) {
+      const float keep = m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(__builtin_fmaf(m, kLog2e, -(m_new * kLog2e)));
+      z *= keep;
 #pragma unroll
-    for (int q4 = 0; q4 < NQ4; ++q4) acc[q4] *= keep;
-    m = m_new;
-  };
-  auto fold = [&](float ls, const f32x4_t (&v)[NQ4]) {  // m is at least ls
-    // a slot marked "no key" may hold anything: its values are dropped, not multiplied by zero
-    const bool live = ls != -INFINITY;
-    const float wgt = live ? expf(ls - m) : 0.f;
-    z += wgt;
+      for (int c = 0; c < NQ; ++c) acc[c] *= keep;
+      m = m_new;
+    };
+    if (valid) {
+      for (int k = k_first + share; k <= k_last; k += U * kw) {
+        float ls[U];
+        f32x4_t v[U][NQ];
 #pragma unroll
-    for (int q4 = 0; q4 < NQ4; ++q4) acc[q4] += wgt * (live ? v[q4] : f32x4_t{0.f, 0.f, 0.f, 0.f});
-  };
-  int k = k_first + kw;
-  for (; k + (U - 1) * KW <= k_last; k += U * KW) {
-    float ls[U];
-    f32x4_t v[U][NQ4];
+        for (int u = 0; u < U; ++u) {
+          const int ku = k + u * kw;
+          ls[u] = -INFINITY;
+          if (ku <= k_last) {
+            const size_t so = (((size_t)ku * MB + mb) * 2 + (ku == k_first)) * kSlotFloats;
+            ls[u] = lse0[so];
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const size_t so = slot_of(k + u * KW);
-      ls[u] = lse0[so];
+            for (int c = 0; c < NQ; ++c) v[u][c] = *(const f32x4_t*)(frag0 + so + c * 256);
+          } else {
 #pragma unroll
-      for (int q4 = 0; q4 < NQ4; ++q4) v[u][q4] = *(const f32x4_t*)(frag0 + so + (q_base + q4) * 256);
-    }
-    float m_new = m;
+            for (int c = 0; c < NQ; ++c) v[u][c] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+          }
+        }
+        float m_new = m;
 #pragma unroll
-    for (int u = 0; u < U; ++u) m_new = fmaxf(m_new, ls[u]);
-    if (m_new == -INFINITY) continue;
-    if (m_new != m) rebase(m_new);
+        for (int u = 0; u < U; ++u) m_new = fmaxf(m_new, ls[u]);
+        if (m_new == -INFINITY) continue;
+        if (m_new != m) rebase(m_new);
+        const float m2 = m * kLog2e;
 #pragma unroll
-    for (int u = 0; u < U; ++u) fold(ls[u], v[u]);
-  }
-  for (; k <= k_last; k += KW) {
-    const size_t so = slot_of(k);
-    const float ls = lse0[so];
-    f32x4_t v[NQ4];
+        for (int u = 0; u < U; ++u) {
+          // a slot marked "no key" may hold anything: its values are dropped, not multiplied by zero
+          const bool live = ls[u] != -INFINITY;
+          const float wgt = __builtin_amdgcn_exp2f(__builtin_fmaf(ls[u], kLog2e, -m2));
+          z += wgt;
 #pragma unroll
-    for (int q4 = 0; q4 < NQ4; ++q4) v[q4] = *(const f32x4_t*)(frag0 + so + (q_base + q4) * 256);
-    if (ls > m) rebase(ls);
-    if (m != -INFINITY) fold(ls, v);
-  }
-  // merge of the KW shares; wave q4 < 4 then finishes quarter q4 of the block
-  float lse;
-  f32x4_t res;
-  int q_mine;
-  if constexpr (KW == 1) {
-    lse = m == -INFINITY ? -INFINITY : m + logf(z);
-    const float inv = z > 0.f ? 1.0f / z : 0.f;
-#pragma unroll
-    for (int q4 = 0; q4 < NQ4; ++q4) acc[q4] *= inv;
-    q_mine = -1;  // all four quarters, below
-    res = acc[0];
-  } else {
-    red_m[kw][lane] = m;
-    red_z[kw][lane] = z;
-#pragma unroll
-    for (int q4 = 0; q4 < NQ4; ++q4) red_a[kw][q4][lane] = acc[q4];
-    __syncthreads();
-    if (kw >= NQ4) return;
-    q_mine = q_base + kw;
-    float mm = -INFINITY;
-#pragma unroll
-    for (int j = 0; j < KW; ++j) mm = fmaxf(mm, red_m[j][lane]);
-    float zz = 0.f;
-    res = f32x4_t{0.f, 0.f, 0.f, 0.f};
-    if (mm != -INFINITY) {
-#pragma unroll
-      for (int j = 0; j < KW; ++j) {
-        const float mj = red_m[j][lane];
-        const float e = mj == -INFINITY ? 0.f : expf(mj - mm);
-        zz += e * red_z[j][lane];
-        res += e * red_a[j][kw][lane];
+          for (int c = 0; c < NQ; ++c) acc[c] += wgt * (live ? v[u][c] : f32x4_t{0.f, 0.f, 0.f, 0.f});
+        }
       }
     }
-    lse = mm == -INFINITY ? -INFINITY : mm + logf(zz);
-    res *= zz > 0.f ? 1.0f / zz : 0.f;
-  }
-  if (!valid) return;
-  if (db == 0 && hi == 0 && kx == 0 && q_mine <= 0) p.lse[((int64_t)b * p.T + t) * p.h_q + h] = lse;
-  const int64_t ob = b * p.out_s[0] + t * p.out_s[1] + h * p.out_s[2];
+    if (kw > 1) {  // the waves that share the blocks meet in the first of them
+      if (share > 0) {
+        red_m[wave][lane] = m;
+        red_z[wave][lane] = z;
 #pragma unroll
-  for (int q4 = 0; q4 < 4; ++q4) {
-    if (q_mine >= 0 && q4 != q_mine) continue;
-    const f32x4_t v = q_mine >= 0 ? res : acc[q4 < NQ4 ? q4 : 0];
-    const int dim = kx * (DV / KS) + 32 * db + 8 * q4 + 4 * hi;
-    if (p.out_fp32) {
-      *(f32x4_t*)((float*)p.out + ob + dim) = v;
-    } else {
-      u32x2_t pk;
-      pk[0] = (uint32_t)f32_to_bf16_bits(v[0]) | ((uint32_t)f32_to_bf16_bits(v[1]) << 16);
-      pk[1] = (uint32_t)f32_to_bf16_bits(v[2]) | ((uint32_t)f32_to_bf16_bits(v[3]) << 16);
-      *(u32x2_t*)((uint16_t*)p.out + ob + dim) = pk;
+        for (int c = 0; c < NQ; ++c) red_a[wave * NQ + c][lane] = acc[c];
+      }
+      __syncthreads();
+      if (share > 0) return;
+      float m_new = m;
+#pragma unroll
+      for (int j = 1; j < NW; ++j)
+        if (j < kw) m_new = fmaxf(m_new, red_m[wave + j][lane]);
+      if (m_new != -INFINITY) {
+        if (m_new != m) rebase(m_new);
+        const float m2 = m * kLog2e;
+#pragma unroll
+        for (int j = 1; j < NW; ++j) {
+          if (j >= kw) continue;
+          const float wgt = __builtin_amdgcn_exp2f(__builtin_fmaf(red_m[wave + j][lane], kLog2e, -m2));  // (no key: 0, as are the sums)
+          z += wgt * red_z[wave + j][lane];
+#pragma unroll
+          for (int c = 0; c < NQ; ++c) acc[c] += wgt * red_a[(wave + j) * NQ + c][lane];
+        }
+      }
     }
+    const float inv = z > 0.f ? 1.0f / z : 0.f;
+#pragma unroll
+    for (int c = 0; c < NQ; ++c) acc[c] *= inv;
+    if (valid && writes_lse && c0 == 0) *lse_out = m == -INFINITY ? -INFINITY : m + logf(z);
+    const int dim0 = (db0 + (c0 >> 2)) * 32 + (c0 & 3) * 8;  // first of the 8 * NQ dims that the two half-waves hold
+    if (p.out_fp32) {
+      if (valid) {
+#pragma unroll
+        for (int c = 0; c < NQ; ++c) *(f32x4_t*)((float*)p.out + ob + dim0 + 8 * c + 4 * hi) = acc[c];
+      }
+    } else if constexpr (NQ == 1) {
+      if (valid) *(u32x2_t*)((uint16_t*)p.out + ob + dim0 + 4 * hi) = u32x2_t{cvt_pk_bf16(acc[0][0], acc[0][1]), cvt_pk_bf16(acc[0][2], acc[0][3])};
+    } else {
+#pragma unroll
+      for (int c = 0; c < NQ; c += 2) {
+        const u32x4_t v = join_halves_bf16(acc[c], acc[c + 1]);
+        if (valid) store_b128_align8((uint16_t*)p.out + ob + dim0 + 8 * c + 8 * hi, v);
+      }
+    }
+  };
+  using std::integral_constant;
+  constexpr integral_constant<int, 1> one{};
+  constexpr integral_constant<int, 2> two{};
+  constexpr integral_constant<int, 4> four{};
+  constexpr integral_constant<int, 8> eight{};
+  if constexpr (NW == 16) {  // (16 sets)
+    run(one, four, set, wave, 16);
+  } else {
+    if (sets <= 4) run(four, four, 4 * (set * (4 / sets) + (wave & ~(sets - 1)) / sets), wave & (sets - 1), sets);
+    else if (sets == 8) run(two, four, 2 * set, wave, 4);
+    else run(one, eight, set, wave, 4);
   }
 }
 

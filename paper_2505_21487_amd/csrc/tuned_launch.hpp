@@ -25,21 +25,27 @@ inline int launch_tuned_main(const DevParams& d, dim3 mgrid, dim3 mblock, hipStr
 
 template <int DV, int NG, int WPG, int KS, int TOK>
 inline int launch_tuned_combine(const TunedPlan& plan, const DevParams& d, hipStream_t st, hipEvent_t* ev) {
-  // waves per merge task from the expected number of chunks per unit
-  const int64_t span_est = (plan.num_chunks + std::max(1, plan.units / plan.mb) - 1) / std::max(1, plan.units / plan.mb) + 1;
-  const dim3 cgrid(plan.units, NG * WPG * (DV / 32));
-  if (span_est <= 2)
-    hipLaunchKernelGGL((tuned_combine_kernel<DV, NG, WPG, KS, TOK, 1, 1, 2>), cgrid, dim3(64), 0, st, d);
-  else if (span_est <= 6)  // (one wave with four chunks in flight: a fourth of the waves to launch, no merge through LDS)
-    hipLaunchKernelGGL((tuned_combine_kernel<DV, NG, WPG, KS, TOK, 1, 1, 4>), cgrid, dim3(64), 0, st, d);
-  else if (span_est <= 12)
-    hipLaunchKernelGGL((tuned_combine_kernel<DV, NG, WPG, KS, TOK, 4, 1, 2>), cgrid, dim3(256), 0, st, d);
-  else if (span_est <= 64)  // (a wave folds eight chunks per round trip: four waves do for fairly long lists)
-    hipLaunchKernelGGL((tuned_combine_kernel<DV, NG, WPG, KS, TOK, 4, 1, 8>), cgrid, dim3(256), 0, st, d);
-  else if ((int64_t)cgrid.x * cgrid.y * 4 > 4 * device_cu_count())
-    hipLaunchKernelGGL((tuned_combine_kernel<DV, NG, WPG, KS, TOK, 16, 1, 4>), cgrid, dim3(1024), 0, st, d);
-  else  // few tasks: each cut into quarters (see the kernel)
-    hipLaunchKernelGGL((tuned_combine_kernel<DV, NG, WPG, KS, TOK, 16, 4, 4>), dim3(cgrid.x, cgrid.y * 4), dim3(1024), 0, st, d);
+  // Sets every unit has: by the mean length of a list, while the grid is no more than two workgroups per compute unit
+  // (256 / 512 / 1024 workgroups: GLA-2 8 x 2048 tokens 24.1 / 23.5 / 23.3 us per call, 15 x 1024 and 1 x 65536 41.2 / 41.2 /
+  // 43.3, MLA shape 53.5 / 53.6 / 55.2, GTA-4 10 sequences 20.9 / 19.1 / 18.2).  Windows of eight chunks (5 / 8 / 12: MLA shape
+  // 15 x 1024 and 1 x 65536 52.5 / 53.6 / 53.4, 20 ragged sequences 33.7 / 32.8 / 33.8), at most 64; none where a unit is the
+  // only one, or looked for among thousands.
+  constexpr int kPanels = NG * WPG * KS * (DV / KS / 32) / 4;
+  DevParams c = d;
+  const int chunks = std::max(plan.num_chunks, plan.wide_chunks), seq_units = plan.units / plan.mb;
+  const int list = chunks / seq_units;
+  int lg = 0;
+  while (lg < 4 && (2 << lg) <= list && ((int64_t)plan.units * kPanels << (lg + 1)) <= 2 * device_cu_count()) ++lg;
+  c.merge_sets_lg = lg;
+  c.merge_span = std::max(8, (chunks + 63) / 64);
+  c.merge_windows = seq_units > 1 && seq_units <= 2048 && lg < 4 ? chunks / c.merge_span : 0;
+  const int64_t blocks = (((int64_t)plan.units << lg) + (int64_t)c.merge_windows * plan.mb) * kPanels, width = 1 << 20;
+  const dim3 grid((unsigned)std::min(blocks, width), (unsigned)((blocks + width - 1) / width));
+  // few panels and long lists: sixteen waves per block (one sequence of 131072 tokens: 57.5 us with four)
+  if (list >= 64 && lg == 4 && blocks <= device_cu_count())
+    hipLaunchKernelGGL((tuned_combine_kernel<DV, NG, WPG, KS, TOK, 16>), grid, dim3(1024), 0, st, c);
+  else
+    hipLaunchKernelGGL((tuned_combine_kernel<DV, NG, WPG, KS, TOK, 4>), grid, dim3(256), 0, st, c);
   if (hipGetLastError() != hipSuccess) return GLA_ERR_LAUNCH;
   if (ev) (void)hipEventRecord(ev[2], st);
   return GLA_OK;
