@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 namespace gla {
 
 // Division of a 32-bit unsigned number by a divisor fixed on the host, as one
@@ -81,16 +83,43 @@ struct DevParams {
   int32_t wide_tiles;       // > 0: the eight-wave kernel runs if the list has that many tiles of 32 tokens, else the four-wave one
 };
 
+// Over the 64 lanes with data-parallel-primitive moves (no LDS round trips): shifts by 1, 2, 4, 8 inside each row of 16
+// lanes, then the last lane of row 0 / 2 into row 1 / 3 and lane 31 into the upper half.  A lane that receives nothing
+// combines with `none`.
+template <class F>
+__device__ __forceinline__ float wave_reduce(float v, float none, F f) {
+  auto step = [&](auto ctrl, auto rows) {
+    v = f(v, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(__builtin_bit_cast(int, none), __builtin_bit_cast(int, v),
+                                                                    decltype(ctrl)::value, decltype(rows)::value, 0xf, false)));
+  };
+  step(std::integral_constant<int, 0x111>{}, std::integral_constant<int, 0xf>{});
+  step(std::integral_constant<int, 0x112>{}, std::integral_constant<int, 0xf>{});
+  step(std::integral_constant<int, 0x114>{}, std::integral_constant<int, 0xf>{});
+  step(std::integral_constant<int, 0x118>{}, std::integral_constant<int, 0xf>{});
+  step(std::integral_constant<int, 0x142>{}, std::integral_constant<int, 0xa>{});
+  step(std::integral_constant<int, 0x143>{}, std::integral_constant<int, 0xc>{});
+  return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), 63));
+}
+__device__ __forceinline__ float wave_sum(float v) {
+  return wave_reduce(v, 0.f, [](float a, float b) { return a + b; });
+}
+__device__ __forceinline__ float wave_max(float v) {
+  return wave_reduce(v, -__builtin_inff(), [](float a, float b) { return fmaxf(a, b); });
+}
+
 __device__ __forceinline__ float bf16_bits_to_f32(uint16_t v) {
   return __builtin_bit_cast(float, ((uint32_t)v) << 16);
 }
 
-// Round-to-nearest-even fp32 -> bf16 (NaN stays NaN).
-__device__ __forceinline__ uint16_t f32_to_bf16_bits(float f) {
-  uint32_t u = __builtin_bit_cast(uint32_t, f);
-  if ((u & 0x7fffffffu) > 0x7f800000u) return (uint16_t)((u >> 16) | 0x40u);
-  u += 0x7fffu + ((u >> 16) & 1u);
-  return (uint16_t)(u >> 16);
+// Two fp32 values rounded to bf16 (nearest even), `a` in the low half: one
+// v_cvt_pk_bf16_f32.  Left to the compiler (not inline asm) so that it sees the
+// instruction and provides the wait state a transcendental result needs before
+// its first use.
+typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2_t;
+typedef __attribute__((ext_vector_type(2))) float f32x2_t;
+__device__ __forceinline__ uint32_t cvt_pk_bf16(float a, float b) {
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2_t{a, b}, bf16x2_t));
 }
+__device__ __forceinline__ uint16_t f32_to_bf16_bits(float f) { return (uint16_t)cvt_pk_bf16(f, f); }
 
 }  // namespace gla

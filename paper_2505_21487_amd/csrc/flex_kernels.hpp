@@ -522,17 +522,14 @@ __global__ __launch_bounds__(256) void flex_main_kernel(DevParams p) {
       if (row_valid) {
         if (q == 0) p.lse[row_idx] = lse;
         const int64_t ob = b * p.out_s[0] + t * p.out_s[1] + h * p.out_s[2];
+        if (p.out_fp32) {
 #pragma unroll
-        for (int db = 0; db < NDB; ++db) {
-          const int dim = 16 * db + 4 * q;
-          const f32x4_t v = own(db) * inv;
-          if (p.out_fp32) {
-            *(f32x4_t*)((float*)p.out + ob + dim) = v;
-          } else {
-            u32x2_t pk;
-            pk[0] = (uint32_t)f32_to_bf16_bits(v[0]) | ((uint32_t)f32_to_bf16_bits(v[1]) << 16);
-            pk[1] = (uint32_t)f32_to_bf16_bits(v[2]) | ((uint32_t)f32_to_bf16_bits(v[3]) << 16);
-            *(u32x2_t*)((uint16_t*)p.out + ob + dim) = pk;
+          for (int db = 0; db < NDB; ++db) *(f32x4_t*)((float*)p.out + ob + 16 * db + 4 * q) = own(db) * inv;
+        } else {
+#pragma unroll
+          for (int db = 0; db < NDB; ++db) {
+            const f32x4_t v = own(db) * inv;
+            *(u32x2_t*)((uint16_t*)p.out + ob + 16 * db + 4 * q) = u32x2_t{cvt_pk_bf16(v[0], v[1]), cvt_pk_bf16(v[2], v[3])};
           }
         }
       }
@@ -637,8 +634,7 @@ __global__ __launch_bounds__(64) void flex_combine_kernel(DevParams p) {
     }
   }
   // the piece groups meet: common reference, then the sums (the lanes of group 0 keep them)
-  float mm = m;
-  for (int sh = 32; sh > 0; sh >>= 1) mm = fmaxf(mm, __shfl_xor(mm, sh, 64));
+  const float mm = wave_max(m);
   const float rescale = m == -INFINITY ? 0.f : expf(m - mm);
   z *= rescale;
   acc *= rescale;
@@ -660,8 +656,8 @@ __global__ __launch_bounds__(64) void flex_combine_kernel(DevParams p) {
       *(f32x4_t*)((float*)p.out + base + 4 * d4) = acc;
     } else {
       u32x2_t pk;
-      pk[0] = (uint32_t)f32_to_bf16_bits(acc[0]) | ((uint32_t)f32_to_bf16_bits(acc[1]) << 16);
-      pk[1] = (uint32_t)f32_to_bf16_bits(acc[2]) | ((uint32_t)f32_to_bf16_bits(acc[3]) << 16);
+      pk[0] = cvt_pk_bf16(acc[0], acc[1]);
+      pk[1] = cvt_pk_bf16(acc[2], acc[3]);
       *(u32x2_t*)((uint16_t*)p.out + base + 4 * d4) = pk;
     }
   }

@@ -11,12 +11,6 @@
 
 namespace gla {
 
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
-  return v;
-}
-
 // One query row over keys [j0, j1) by one wave: running maximum m, sum of weights l, weighted values o (element
 // lane + 64 i of the value at o[i]).  NV = ceil(d_v / 64): state elements owned by one lane.
 template <int NV>
@@ -143,9 +137,7 @@ __global__ __launch_bounds__(64) void generic_combine_kernel(DevParams p) {
   // through the ranges one by one).
   if (p.splits <= 64 && p.d_v % 4 == 0) {
     const float ls = lane < p.splits ? p.ws_lse[(int64_t)lane * rows + row] : -INFINITY;
-    float m = ls;
-#pragma unroll
-    for (int sh = 32; sh > 0; sh >>= 1) m = fmaxf(m, __shfl_xor(m, sh, 64));
+    const float m = wave_max(ls);
     const float e = ls != -INFINITY ? expf(ls - m) : 0.f;
     const float z = wave_sum(e);
     // (z == 0: no key in any range; NaN where every range that has keys is NaN)

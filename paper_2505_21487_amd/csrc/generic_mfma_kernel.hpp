@@ -261,8 +261,8 @@ __global__ __launch_bounds__(64 * WR) void generic_mfma_kernel(DevParams p) {
           *(f32x4_t*)((float*)p.out + ob + dim) = v;
         } else {
           u32x2_t pk;
-          pk[0] = (uint32_t)f32_to_bf16_bits(v[0]) | ((uint32_t)f32_to_bf16_bits(v[1]) << 16);
-          pk[1] = (uint32_t)f32_to_bf16_bits(v[2]) | ((uint32_t)f32_to_bf16_bits(v[3]) << 16);
+          pk[0] = cvt_pk_bf16(v[0], v[1]);
+          pk[1] = cvt_pk_bf16(v[2], v[3]);
           *(u32x2_t*)((uint16_t*)p.out + ob + dim) = pk;
         }
       }

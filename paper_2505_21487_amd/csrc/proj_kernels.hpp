@@ -179,8 +179,8 @@ __global__ __launch_bounds__(256) void proj_kernel(ProjParams p) {
           *reinterpret_cast<proj_f32x4_t*>((float*)p.c + off) = v;
         } else {
           uint2 pk;
-          pk.x = (uint32_t)f32_to_bf16_bits(v[0]) | ((uint32_t)f32_to_bf16_bits(v[1]) << 16);
-          pk.y = (uint32_t)f32_to_bf16_bits(v[2]) | ((uint32_t)f32_to_bf16_bits(v[3]) << 16);
+          pk.x = cvt_pk_bf16(v[0], v[1]);
+          pk.y = cvt_pk_bf16(v[2], v[3]);
           *reinterpret_cast<uint2*>((uint16_t*)p.c + off) = pk;
         }
       }
@@ -224,8 +224,8 @@ __global__ __launch_bounds__(256) void proj_reduce_kernel(ProjParams p) {
     *reinterpret_cast<proj_f32x4_t*>((float*)p.c + off) = v;
   } else {
     uint2 pk;
-    pk.x = (uint32_t)f32_to_bf16_bits(v[0]) | ((uint32_t)f32_to_bf16_bits(v[1]) << 16);
-    pk.y = (uint32_t)f32_to_bf16_bits(v[2]) | ((uint32_t)f32_to_bf16_bits(v[3]) << 16);
+    pk.x = cvt_pk_bf16(v[0], v[1]);
+    pk.y = cvt_pk_bf16(v[2], v[3]);
     *reinterpret_cast<uint2*>((uint16_t*)p.c + off) = pk;
   }
 }

@@ -709,25 +709,34 @@ __global__ __launch_bounds__(512) void wide_main_kernel(DevParams p) {
         if (!complete) slot[(size_t)TT::kRows * DV + (wave >> 1) * 32 + col] = lse;
         else if (row_valid && pe == 0) p.lse[((int64_t)cur.b * p.T + t) * p.h_q + h] = lse;
       }
+      // (one loop per kind of result, as in the four-wave kernel)
+      auto quarter = [&](int d, int q4) { return f32x4_t{o[d][4 * q4] * inv, o[d][4 * q4 + 1] * inv, o[d][4 * q4 + 2] * inv, o[d][4 * q4 + 3] * inv}; };
+      if (!complete) {
+        float* const dst = slot + (size_t)(wave * 16) * 256 + le * 4;
+        if (row_valid) {
 #pragma unroll
-      for (int d = 0; d < 4; ++d)
+          for (int d = 0; d < 4; ++d)
 #pragma unroll
-        for (int q4 = 0; q4 < 4; ++q4) {
-          const int dim = pe * 128 + 32 * d + 8 * q4 + 4 * hi;
-          const f32x4_t v = {o[d][4 * q4] * inv, o[d][4 * q4 + 1] * inv, o[d][4 * q4 + 2] * inv, o[d][4 * q4 + 3] * inv};
-          if (!complete) {
-            *(f32x4_t*)(slot + (size_t)((wave * 4 + d) * 4 + q4) * 256 + le * 4) = v;
-          } else if (row_valid) {
-            if (p.out_fp32) {
-              *(f32x4_t*)((float*)p.out + ob + dim) = v;
-            } else {
-              u32x2_t w2;
-              w2[0] = (uint32_t)f32_to_bf16_bits(v[0]) | ((uint32_t)f32_to_bf16_bits(v[1]) << 16);
-              w2[1] = (uint32_t)f32_to_bf16_bits(v[2]) | ((uint32_t)f32_to_bf16_bits(v[3]) << 16);
-              *(u32x2_t*)((uint16_t*)p.out + ob + dim) = w2;
-            }
-          }
+            for (int q4 = 0; q4 < 4; ++q4) *(f32x4_t*)(dst + (d * 4 + q4) * 256) = quarter(d, q4);
         }
+      } else if (p.out_fp32) {
+        float* const dst = (float*)p.out + ob + pe * 128 + 4 * hi;
+        if (row_valid) {
+#pragma unroll
+          for (int d = 0; d < 4; ++d)
+#pragma unroll
+            for (int q4 = 0; q4 < 4; ++q4) *(f32x4_t*)(dst + 32 * d + 8 * q4) = quarter(d, q4);
+        }
+      } else {
+        uint16_t* const dst = (uint16_t*)p.out + ob + pe * 128 + 8 * hi;
+#pragma unroll
+        for (int d = 0; d < 4; ++d)
+#pragma unroll
+          for (int q8 = 0; q8 < 2; ++q8) {
+            const u32x4_t v = join_halves_bf16(quarter(d, 2 * q8), quarter(d, 2 * q8 + 1));
+            if (row_valid) store_b128_align8(dst + 32 * d + 16 * q8, v);
+          }
+      }
     }
     unit_at += cur.tiles_b + cut.setup;
     next_unit(cur);
