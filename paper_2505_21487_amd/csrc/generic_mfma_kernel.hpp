@@ -4,17 +4,18 @@
 // of bf16 are exact in fp32, and each fp32 softmax weight enters the value product as a sum of three bf16 (24
 // significant bits, three MFMAs), never rounded to 16 bits.
 //
-// One workgroup of WR waves takes one (sequence, group, block of 16 * WR query rows, range of tokens); the waves
-// share tiles of 32 tokens in LDS, double-buffered and filled by direct-to-LDS loads, and own 16 query rows each
+// One workgroup takes one (sequence, group, block of 16 * WR query rows, range of tokens).  WS waves share a slab of 16
+// rows: of each tile of 32 * WS tokens every one takes 32, with a softmax of its own, and they meet in LDS at the end
 // (transposed form, S^T = K . Q^T and O^T += V^T . P^T, on 16x16x32 MFMAs; row statistics in the four lanes of a
-// row).  A cache row lies in LDS as its 16-byte chunks [value | RoPE key] or [value | key], rotated by the row
-// number so that reads of one column spread over the banks.  The page ids of a tile's 32 tokens sit in the lanes of
-// one register, fetched a tile ahead.
+// row).  Tiles lie in a ring of two to four stages, filled by direct-to-LDS loads.  A cache row lies in LDS as its 16-byte
+// chunks [value | RoPE key] or [value | key], rotated by the row number so that reads of one column spread over the
+// banks.  The ids of 64 or 128 consecutive pages sit in the lanes of one or two registers.
 //
 // Bound by latency and vector work (address arithmetic with run-time dims, the three-way split).  Two latent heads of
-// 256 dims, 128 heads, 9 sequences of up to 4500 tokens at 128 tokens per page: 1923 us with the scalar kernel, whose
-// waves each read the whole cache for one row, 38 us here (one latent head of 512 dims: 3135 -> 60; four tied states
-// of 128: 374 -> 38).  With one contraction step of operand reads in flight instead of four: 47 us.
+// 256 dims, 128 heads, 9 sequences of up to 4500 tokens at 128 tokens per page: 38.0 us per call with one wave per slab and
+// two stages, 30.8 this way (1923 with the scalar kernel, whose waves each read the whole cache for one row); at two query
+// positions, 2 sequences 32.8 -> 22.8; one latent head of 512 dims, 4 sequences 56.3 -> 39.1; four tied states of 128, 20
+// short sequences 35.9 -> 19.0.
 #pragma once
 
 #include "common.hpp"
@@ -38,12 +39,42 @@ __device__ __forceinline__ int range_tokens(const DevParams& p, int lane, int le
   return ((longest + n - 1) / n + 31) & ~31;
 }
 
+// At most N of this wave's loads still in flight, N known at run time only (the next lower count that has an instruction
+// here: waiting for more than needed is always right).
+__device__ __forceinline__ void wait_vmcnt_at_most(int n) {
+  if (n >= 24) wait_vmcnt<24>();
+  else if (n >= 16) wait_vmcnt<16>();
+  else if (n >= 12) wait_vmcnt<12>();
+  else if (n >= 10) wait_vmcnt<10>();
+  else if (n >= 8) wait_vmcnt<8>();
+  else if (n >= 6) wait_vmcnt<6>();
+  else if (n >= 5) wait_vmcnt<5>();
+  else if (n >= 4) wait_vmcnt<4>();
+  else if (n >= 3) wait_vmcnt<3>();
+  else if (n >= 2) wait_vmcnt<2>();
+  else if (n >= 1) wait_vmcnt<1>();
+  else wait_vmcnt<0>();
+}
+
+// Waves that share a 16-row slab (each takes every WS-th 32 tokens of a tile) and ring stages, by what the LDS holds.
 template <int DVB, int WR, bool SEPK>
-__global__ __launch_bounds__(64 * WR) void generic_mfma_kernel(DevParams p) {
-  constexpr int kMaxChunks = SEPK ? 2 * DVB / 8 : (DVB + 128) / 8;  // chunks per cache row (RoPE keys of up to 128 dims)
-  constexpr int kTile = 32 * kMaxChunks * 16;
+struct GenericTraits {
+  static constexpr int kMaxChunks = SEPK ? 2 * DVB / 8 : (DVB + 128) / 8;  // chunks per cache row (RoPE keys of up to 128 dims)
+  static constexpr int kSub = 32 * kMaxChunks * 16;                         // 32 tokens
+  static constexpr int kMaxWaves = DVB > 256 ? 4 : 8;  // (512 dims: a wave needs more than 256 registers)
+  static constexpr int WS = WR * 4 <= kMaxWaves && kSub * 8 <= 160 * 1024 ? 4 : WR * 2 <= kMaxWaves && kSub * 4 <= 160 * 1024 ? 2 : 1;
+  static constexpr int NST = kSub * WS * 4 <= 160 * 1024 ? 4 : kSub * WS * 3 <= 160 * 1024 ? 3 : 2;
+  static constexpr int kThreads = 64 * WR * WS;
+  static_assert(NST * WS * kSub <= 160 * 1024 && WR * (WS - 1) * 64 * (DVB + 8) * 4 / 4 <= NST * WS * kSub, "LDS capacity");
+};
+
+template <int DVB, int WR, bool SEPK>
+__global__ __launch_bounds__((GenericTraits<DVB, WR, SEPK>::kThreads)) void generic_mfma_kernel(DevParams p) {
+  using GT = GenericTraits<DVB, WR, SEPK>;
+  constexpr int WS = GT::WS, NST = GT::NST, NW = WR * WS, STEP = 32 * WS;
+  constexpr int kTile = WS * GT::kSub;
   constexpr int NDB = DVB / 16, NKN = DVB / 32, NKR = SEPK ? 0 : 4;
-  __shared__ __attribute__((aligned(1024))) unsigned char smem[2 * kTile];
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[NST * kTile];
   const unsigned lds_base = (unsigned)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem;
   const int lane = threadIdx.x & 63, wave = uniform((int)threadIdx.x >> 6);
   const int r16 = lane & 15, q = lane >> 4;
@@ -53,7 +84,8 @@ __global__ __launch_bounds__(64 * WR) void generic_mfma_kernel(DevParams p) {
   const int unit = (int)blockIdx.x / blocks, rb = (int)blockIdx.x - unit * blocks;
   const int b = unit / p.h_c, g = unit - b * p.h_c;
   const int split = blockIdx.y;
-  const int R = (rb * WR + wave) * 16 + r16;
+  const int slab = wave % WR, ws = wave / WR;  // this wave's rows, and its share of a tile's tokens
+  const int R = (rb * WR + slab) * 16 + r16;
   const bool row_valid = R < rows_group;
   const int Rc = row_valid ? R : rows_group - 1;
   const int t = Rc / p.g_q, h = g * p.g_q + (Rc - t * p.g_q);
@@ -99,55 +131,71 @@ __global__ __launch_bounds__(64 * WR) void generic_mfma_kernel(DevParams p) {
   float m = -INFINITY, l = 0.f;
   const float sc2 = p.scale * 1.4426950408889634f;
 
-  // ---- tile loads.  ids / tips: page and slot of token lane % 32 of the tile to fetch (rows past the end of the
-  //      sequence repeat its last token: valid memory, masked and zeroed below)
-  int ids = 0, tips = 0;
-  auto fetch_ids = [&](int tok0) {
-    const int tok = min(tok0 + (lane & 31), L - 1);
-    const int pg = (int)fast_div((unsigned)tok, p.fd_page);
-    tips = tok - pg * p.P;
-    ids = p.page_table[(int64_t)b * p.max_pages + pg];
-  };
-  const int n_slots = 32 * cpr, n_inst = (n_slots + 63) >> 6;
-  auto load_tile = [&](int buf) {
-    for (int i = wave; i < n_inst; i += WR) {
+  // ---- tile loads.  The ids of 64 consecutive pages (128 where a tile can span as many) sit in the lanes of a register
+  //      and are fetched again when a tile leaves them (rows past the end of the sequence repeat its last token: valid
+  //      memory, masked and zeroed below).  The load is complete where it stands: it waits for the tiles in flight, which
+  //      costs pages of one token the depth of the ring.
+  constexpr int NWIN = STEP > 64 ? 2 : 1;
+  int win0 = 0, win1 = 0, win_page = -0x40000000;
+  const int n_slots = STEP * cpr, n_inst = (n_slots + 63) >> 6;
+  const int n_mine = uniform((n_inst - wave + NW - 1) / NW);  // load instructions of this wave per tile
+  auto load_tile = [&](int tok0, int stage) {
+    const int first_page = (int)fast_div((unsigned)tok0, p.fd_page), last_page = (int)fast_div((unsigned)min(tok0 + STEP - 1, L - 1), p.fd_page);
+    if (uniform(last_page) >= uniform(win_page) + 64 * NWIN) {
+      win_page = first_page;
+      const int held = (int)fast_div((unsigned)(L - 1), p.fd_page);
+      const int32_t* row = p.page_table + (int64_t)b * p.max_pages;
+      win0 = load_i32_sync(row + min(first_page + lane, held));
+      if constexpr (NWIN == 2) win1 = load_i32_sync(row + min(first_page + 64 + lane, held));
+    }
+    for (int i = wave; i < n_inst; i += NW) {
       const int n = i * 64 + lane;
-      const int row_i = min((int)fast_div((unsigned)n, p.fd_cpr), 31);
+      const int row_i = min((int)fast_div((unsigned)n, p.fd_cpr), STEP - 1);
       int chunk = n - row_i * cpr - mod_cpr(row_i);
       chunk += chunk < 0 ? cpr : 0;
-      const int64_t page = __builtin_amdgcn_ds_bpermute(row_i << 2, ids);
-      const int64_t tip = __builtin_amdgcn_ds_bpermute(row_i << 2, tips);
+      const int tok = min(tok0 + row_i, L - 1);
+      const int pg = (int)fast_div((unsigned)tok, p.fd_page);
+      const int64_t tip = tok - pg * p.P;
+      int id = __builtin_amdgcn_ds_bpermute((pg - win_page) << 2, win0);
+      if constexpr (NWIN == 2) {
+        const int id1 = __builtin_amdgcn_ds_bpermute((pg - win_page) << 2, win1);  // (lane index modulo 64)
+        id = pg - win_page >= 64 ? id1 : id;
+      }
+      const int64_t page = id;
       const uint16_t* src;
       if (chunk < cv) src = p.state + page * p.st_s[0] + g * p.st_s[1] + tip * p.st_s[2] + chunk * 8;
       else if constexpr (SEPK) src = p.kstate + page * p.k_s[0] + g * p.k_s[1] + tip * p.k_s[2] + (chunk - cv) * 8;
       else src = p.rope + page * p.rp_s[0] + tip * p.rp_s[1] + (chunk - cv) * 8;
-      if (n < n_slots) __builtin_amdgcn_global_load_lds((global_cvoid_t*)src, (lds_void_t*)(smem + buf * kTile + i * 1024), 16, 0, 0);
+      if (n < n_slots) __builtin_amdgcn_global_load_lds((global_cvoid_t*)src, (lds_void_t*)(smem + stage * kTile + i * 1024), 16, 0, 0);
     }
   };
 
-  const int mod_k[2] = {mod_cpr(r16), mod_cpr(16 + r16)};
+  const int row0 = 32 * ws;  // first row of this wave's share of a tile
+  const int mod_k[2] = {mod_cpr(row0 + r16), mod_cpr(row0 + 16 + r16)};
   const int tr_r = r16 >> 2, tr_c = r16 & 3;
-  const int mod_v[2] = {mod_cpr(4 * q + tr_r), mod_cpr(16 + 4 * q + tr_r)};
+  const int mod_v[2] = {mod_cpr(row0 + 4 * q + tr_r), mod_cpr(row0 + 16 + 4 * q + tr_r)};
   const int k0 = SEPK ? cv : 0;  // first chunk of the key (RoPE part apart)
 
   if (j_begin < j_end) {
-    fetch_ids(j_begin);
-    load_tile(0);
-    fetch_ids(min(j_begin + 32, j_end - 1));
-    int buf = 0;
-    for (int j = j_begin; j < j_end; j += 32, buf ^= 1) {
-      wait_vmcnt<0>();  // this wave's part of the tile (and the ids of the next) ...
-      lds_barrier();    // ... and everybody's; the other buffer is free
-      if (j + 32 < j_end) {
-        load_tile(buf ^ 1);
-        fetch_ids(min(j + 64, j_end - 1));
-      }
-      const unsigned base = lds_base + (unsigned)(buf * kTile);
-      if (j + 32 > L) {  // rows past the end may hold anything: 0 x NaN must not leak (uniform over the workgroup)
-        for (int off = (L - j) * cpr * 16 + (int)threadIdx.x * 16; off < n_slots * 16; off += 64 * WR * 16)
+    const int n_tiles = (j_end - j_begin + STEP - 1) / STEP;
+#pragma unroll
+    for (int t = 0; t < NST - 1; ++t)
+      if (t < n_tiles) load_tile(j_begin + t * STEP, t);
+    int stage = 0;
+    for (int tile = 0; tile < n_tiles; ++tile) {
+      const int j = j_begin + tile * STEP;
+      wait_vmcnt_at_most(n_mine * min(n_tiles - 1 - tile, NST - 2));  // this wave's part of the tile ...
+      lds_barrier();  // ... and everybody's; nobody reads the stage of the tile before any more
+      const unsigned base = lds_base + (unsigned)(stage * kTile);
+      const int stage_load = stage == 0 ? NST - 1 : stage - 1;
+      stage = stage == NST - 1 ? 0 : stage + 1;
+      if (tile + NST - 1 < n_tiles) load_tile(j + (NST - 1) * STEP, stage_load);
+      if (j + STEP > L) {  // rows past the end may hold anything: 0 x NaN must not leak (uniform over the workgroup)
+        for (int off = (L - j) * cpr * 16 + (int)threadIdx.x * 16; off < n_slots * 16; off += 64 * NW * 16)
           lds_write_b128<0>(base + (unsigned)off, u32x4_t{0, 0, 0, 0});
         lds_barrier();
       }
+      if (j + row0 >= j_end) continue;  // (the last tile of a range may end before this wave's share)
       // ---- scores of 2 x 16 tokens: S^T[token 16 tb + 4 q + e][row r16]
       f32x4_t s[2] = {f32x4_t{0.f, 0.f, 0.f, 0.f}, f32x4_t{0.f, 0.f, 0.f, 0.f}};
       // (four steps at a time, their eight reads in flight together; a step beyond the key's dims reads its last
@@ -160,8 +208,8 @@ __global__ __launch_bounds__(64 * WR) void generic_mfma_kernel(DevParams p) {
             static_for<0, 4>([&](auto kc) {
               constexpr int ks = decltype(kc)::value;
               const int c = first + min(4 * (k4 + ks) + q, chunks - 1);
-              lds_read_b128<0>(kf[ks][0], base + slot_of(r16, mod_k[0], c));
-              lds_read_b128<0>(kf[ks][1], base + slot_of(16 + r16, mod_k[1], c));
+              lds_read_b128<0>(kf[ks][0], base + slot_of(row0 + r16, mod_k[0], c));
+              lds_read_b128<0>(kf[ks][1], base + slot_of(row0 + 16 + r16, mod_k[1], c));
             });
             static_for<0, 4>([&](auto kc) {
               constexpr int ks = decltype(kc)::value;
@@ -185,12 +233,11 @@ __global__ __launch_bounds__(64 * WR) void generic_mfma_kernel(DevParams p) {
       for (int tb = 0; tb < 2; ++tb)
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          const int tok = j + 16 * tb + 4 * q + e;
+          const int tok = j + row0 + 16 * tb + 4 * q + e;
           visible[4 * tb + e] = tok < n_vis && tok < j_end;
           mx = fmaxf(mx, visible[4 * tb + e] ? s[tb][e] * sc2 : -INFINITY);
         }
-      mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
-      mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+      mx = half_swap_max(row_swap_max(mx));
       const float m_new = fmaxf(m, mx);
       if (__ballot(m_new != m) != 0) {
         const float alpha = m_new != m ? __builtin_amdgcn_exp2f(m - m_new) : 1.f;  // (m = -inf on the first key: 0)
@@ -224,8 +271,8 @@ __global__ __launch_bounds__(64 * WR) void generic_mfma_kernel(DevParams p) {
           static_for<0, 4>([&](auto dc) {
             constexpr int d = decltype(dc)::value;
             const int c = min(2 * (d4 + d) + (tr_c >> 1), cv - 1);  // (blocks past the value's dims: accumulated, never stored)
-            lds_read_tr16_b64<0>(v0[d], base + slot_of(4 * q + tr_r, mod_v[0], c) + (unsigned)((tr_c & 1) * 8));
-            lds_read_tr16_b64<0>(v1[d], base + slot_of(16 + 4 * q + tr_r, mod_v[1], c) + (unsigned)((tr_c & 1) * 8));
+            lds_read_tr16_b64<0>(v0[d], base + slot_of(row0 + 4 * q + tr_r, mod_v[0], c) + (unsigned)((tr_c & 1) * 8));
+            lds_read_tr16_b64<0>(v1[d], base + slot_of(row0 + 16 + 4 * q + tr_r, mod_v[1], c) + (unsigned)((tr_c & 1) * 8));
           });
           static_for<0, 4>([&](auto dc) {
             constexpr int d = decltype(dc)::value;
@@ -244,6 +291,28 @@ __global__ __launch_bounds__(64 * WR) void generic_mfma_kernel(DevParams p) {
 
   l += __shfl_xor(l, 16, 64);
   l += __shfl_xor(l, 32, 64);
+  if constexpr (WS > 1) {  // the waves of a slab meet in the first of them (an empty share has m = -inf and sums of zero)
+    float* const mine = (float*)smem + ((ws - 1) * WR + slab) * 64 * (4 * NDB + 2);
+    lds_barrier();  // (the ring is free)
+    if (ws > 0) {
+      *(float2*)(mine + 64 * 4 * NDB + 2 * lane) = make_float2(m, l);
+#pragma unroll
+      for (int d = 0; d < NDB; ++d) *(f32x4_t*)(mine + d * 256 + lane * 4) = o[d];
+    }
+    lds_barrier();
+    if (ws > 0) return;
+#pragma unroll
+    for (int s2 = 1; s2 < WS; ++s2) {
+      const float* const other = (const float*)smem + ((s2 - 1) * WR + slab) * 64 * (4 * NDB + 2);
+      const float2 ml = *(const float2*)(other + 64 * 4 * NDB + 2 * lane);
+      const float m_new = fmaxf(m, ml.x);
+      const float a = m_new != m ? __builtin_amdgcn_exp2f(m - m_new) : 1.f, c = ml.x == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(ml.x - m_new);
+      l = l * a + ml.y * c;
+#pragma unroll
+      for (int d = 0; d < NDB; ++d) o[d] = o[d] * a + *(const f32x4_t*)(other + d * 256 + lane * 4) * c;
+      m = m_new;
+    }
+  }
   const bool empty = j_begin >= min(j_end, n_vis);  // no visible key in this range
   const float inv = empty ? 0.f : 1.f / l;
   const float lse = empty ? -INFINITY : (m + log2f(l)) * 0.6931471805599453f;
@@ -298,7 +367,7 @@ __global__ __launch_bounds__(64 * WR) void generic_mfma_kernel(DevParams p) {
     asm volatile("" : "+s"(kernarg));
     const DevParams& pk = *(const DevParams*)kernarg;
     for (; odd_rows; odd_rows &= odd_rows - 1) {
-      const int R1 = (rb * WR + wave) * 16 + __ffsll((unsigned long long)odd_rows) - 1;
+      const int R1 = (rb * WR + slab) * 16 + __ffsll((unsigned long long)odd_rows) - 1;
       const int t1 = R1 / pk.g_q, h1 = g * pk.g_q + (R1 - t1 * pk.g_q);
       const int j1 = min(j_end, pk.causal ? L - pk.T + 1 + t1 : L);
       float o1[DVB / 64], m1, l1;

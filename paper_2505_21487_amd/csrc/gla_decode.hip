@@ -142,6 +142,12 @@ int64_t generic_units(const gla_decode_params* p) {
   return std::max<int64_t>(1, (int64_t)p->batch * p->num_groups * (((int64_t)p->num_q_heads / p->num_groups * p->q_len + 63) / 64));
 }
 
+// Workgroups up to which the generic MFMA kernel's ranges may be shorter than 256 tokens (64 at least): two thirds of the
+// compute units.  us per call with a quarter / half / three quarters / all of them / twice as many: MLA shape 4 sequences
+// of 200 to 2500 tokens 59.0 / 39.8 / 36.2 / 33.1 / 33.1, GLA-2 2 x up to 5000 at two positions 28.4 / 23.4 / 23.2 / 21.2 /
+// 21.2, 9 x up to 4500 31.2 up to all and 46.5 with twice as many.
+int64_t small_grid() { return device_cu_count() * 2 / 3; }
+
 // Ranges of the generic route.  The scalar kernel has one wave per row and range: about 4096 of them.
 int scalar_splits(const gla_decode_params* p) {
   const int64_t rows = std::max<int64_t>(1, (int64_t)p->batch * p->q_len * p->num_q_heads);
@@ -159,7 +165,7 @@ int mfma_splits(const gla_decode_params* p) {
   const int64_t rows = std::max<int64_t>(1, (int64_t)p->batch * p->q_len * p->num_q_heads);
   const int64_t units = generic_units(p), tokens = (int64_t)p->max_pages_per_seq * p->page_size;
   int64_t want = (2 * (int64_t)device_cu_count() + units - 1) / units;
-  want = std::min(want, std::max((tokens + 255) / 256, std::min((tokens + 63) / 64, 64 / units)));
+  want = std::min(want, std::max((tokens + 255) / 256, std::min((tokens + 63) / 64, small_grid() / units)));
   want = std::min<int64_t>(want, (64ll << 20) / std::max<int64_t>(1, rows * (p->d_v + 1) * 4));
   return (int)std::max<int64_t>(std::min<int64_t>(want, 64), 1);
 }
@@ -314,15 +320,15 @@ void launch_generic_mfma_waves(int rows_group, int64_t units, int splits, hipStr
   // waves per workgroup (16 rows each): as many as the rows of a group fill, at most four
   const int wr = rows_group <= 16 ? 1 : rows_group <= 32 ? 2 : 4;
   const dim3 grid((unsigned)(units * ((rows_group + 16 * wr - 1) / (16 * wr))), (unsigned)splits);
-  if (wr == 1) hipLaunchKernelGGL((generic_mfma_kernel<DVB, 1, SEPK>), grid, dim3(64), 0, st, d);
-  else if (wr == 2) hipLaunchKernelGGL((generic_mfma_kernel<DVB, 2, SEPK>), grid, dim3(128), 0, st, d);
-  else hipLaunchKernelGGL((generic_mfma_kernel<DVB, 4, SEPK>), grid, dim3(256), 0, st, d);
+  if (wr == 1) hipLaunchKernelGGL((generic_mfma_kernel<DVB, 1, SEPK>), grid, dim3(GenericTraits<DVB, 1, SEPK>::kThreads), 0, st, d);
+  else if (wr == 2) hipLaunchKernelGGL((generic_mfma_kernel<DVB, 2, SEPK>), grid, dim3(GenericTraits<DVB, 2, SEPK>::kThreads), 0, st, d);
+  else hipLaunchKernelGGL((generic_mfma_kernel<DVB, 4, SEPK>), grid, dim3(GenericTraits<DVB, 4, SEPK>::kThreads), 0, st, d);
 }
 
 void launch_generic_mfma(const gla_decode_params* p, DevParams& d, hipStream_t st) {
   const int64_t tokens = (int64_t)p->max_pages_per_seq * p->page_size;
   if (p->num_splits > 0) d.split_tokens = (int32_t)(((tokens + d.splits - 1) / d.splits + 31) / 32 * 32);
-  else d.small_ranges = (int32_t)(64 / generic_units(p));
+  else d.small_ranges = (int32_t)(small_grid() / generic_units(p));
   d.fd_page = make_fastdiv((uint32_t)p->page_size);
   const bool sepk = d.kstate != nullptr;
   d.fd_cpr = make_fastdiv((uint32_t)(p->d_v / 8 + (sepk ? p->d_nope : p->d_rope) / 8));

@@ -56,6 +56,29 @@ def test_generic_mfma(name):
     _close(p, dp, num_splits=splits)
 
 
+RING = {
+    # name: (kind, h_q, h_c, d_v, d_r, T, page): one range over many tiles for every number of waves and stages
+    "dv128_two_slabs_page1": ("gla", 24, 1, 128, 32, 1, 1), "dv96_one_slab_page2": ("gla", 16, 2, 96, 48, 1, 2), "dv128_four_slabs": ("gla", 61, 1, 128, 64, 1, 72),
+    "dv256_four_slabs_page1": ("gla", 128, 2, 256, 64, 1, 1), "dv256_two_slabs_rope128": ("gla", 20, 1, 256, 128, 1, 65), "dv208_five_blocks": ("gla", 70, 1, 208, 24, 4, 96),
+    "dv512_four_slabs": ("gla", 64, 1, 512, 64, 1, 130), "dv464_two_slabs": ("gla", 10, 1, 464, 120, 3, 33), "gta_one_slab": ("gta", 16, 2, 256, 64, 1, 128),
+    "gqa256_four_slabs": ("gqa", 64, 1, 256, 0, 1, 200), "gqa512_two_slabs": ("gqa", 20, 1, 512, 0, 1, 96), "gqa128_one_slab_page3": ("gqa", 9, 1, 128, 0, 1, 3),
+}
+
+
+@pytest.mark.parametrize("name", sorted(RING))
+def test_generic_mfma_ring(name):
+    """A sequence as one range: tiles of 32 to 128 tokens through every stage of the ring, page ids across the 64 or 128 a
+    wave holds, last tiles that end inside or before a wave's 32 tokens; and as ranges of a few tiles."""
+    kind, h_q, h_c, d_v, d_r, T, page = RING[name]
+    lens = [0, 1, 129, 64, 97, 1030, 33]
+    p = make_problem(name, kind=kind, seq_lens=lens, T=T, h_q=h_q, h_c=h_c, d_v=d_v, d_r=d_r, page_size=page, seed=8900 + len(name),
+                     num_pages=sum(n // page + 1 for n in lens) + 9, poison_tail=True, extra_table_cols=1)
+    dp = DeviceProblem(p, poison_unused=True)
+    assert _name(p, dp) == "generic MFMA kernel"
+    for splits in (1, 4):
+        _close(p, dp, num_splits=splits)
+
+
 def _shifted(t, by):
     """The same values in a wider buffer, each row `by` elements in."""
     wide = torch.zeros(*t.shape[:-1], t.shape[-1] + 40, dtype=t.dtype, device=t.device)
