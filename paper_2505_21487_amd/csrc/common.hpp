@@ -61,7 +61,7 @@ struct DevParams {
   // generic kernel: uniform split of every sequence's page range
   int32_t splits, pages_per_split;
   // generic MFMA kernel: the split in tokens or, where the caller left it to the library, 0 and the number of ranges
-  // allowed while the grid is small (range_tokens); divisors (page size, 16-byte chunks of a cache row)
+  // allowed while the grid is small (range_tokens); divisors (page size, 16-byte chunks of a row in LDS)
   int32_t split_tokens, small_ranges;
   FastDiv fd_page, fd_cpr;
   int64_t stream_min_bytes; // second MFMA kernel: a batch with more cache bytes than this is fetched with the streaming hint

@@ -8,14 +8,15 @@
 // rows: of each tile of 32 * WS tokens every one takes 32, with a softmax of its own, and they meet in LDS at the end
 // (transposed form, S^T = K . Q^T and O^T += V^T . P^T, on 16x16x32 MFMAs; row statistics in the four lanes of a
 // row).  Tiles lie in a ring of two to four stages, filled by direct-to-LDS loads.  A cache row lies in LDS as its 16-byte
-// chunks [value | RoPE key] or [value | key], rotated by the row number so that reads of one column spread over the
-// banks.  The ids of 64 or 128 consecutive pages sit in the lanes of one or two registers.
+// chunks [value | RoPE key] or [value | key], in rows of an odd number of chunks, so that reads of one column
+// spread over the banks and an operand's address is the lane's own plus a constant.  The ids of 64 or 128 consecutive pages sit in the lanes of one or two registers.
 //
 // Bound by latency and vector work (address arithmetic with run-time dims, the three-way split).  Two latent heads of
 // 256 dims, 128 heads, 9 sequences of up to 4500 tokens at 128 tokens per page: 38.0 us per call with one wave per slab and
-// two stages, 30.8 this way (1923 with the scalar kernel, whose waves each read the whole cache for one row); at two query
-// positions, 2 sequences 32.8 -> 22.8; one latent head of 512 dims, 4 sequences 56.3 -> 39.1; four tied states of 128, 20
-// short sequences 35.9 -> 19.0.
+// two stages, 30.8 with two and three, 29.1 with rows of an odd number of chunks besides (rotated by the row number
+// before: five instructions more per operand read); 1923 with the scalar kernel, whose waves each read the whole cache
+// for one row.  At two query positions, 2 sequences 32.8 -> 22.7 -> 21.2; one latent head of 512 dims, 4 sequences 56.3 ->
+// 39.1 -> 37.6; four tied states of 128, 20 short sequences 35.9 -> 19.1 -> 18.2.
 #pragma once
 
 #include "common.hpp"
@@ -56,25 +57,24 @@ __device__ __forceinline__ void wait_vmcnt_at_most(int n) {
   else wait_vmcnt<0>();
 }
 
-// Waves that share a 16-row slab (each takes every WS-th 32 tokens of a tile) and ring stages, by what the LDS holds.
+// Waves that share a 16-row slab (each takes every WS-th 32 tokens of a tile) and LDS, for up to four stages.
 template <int DVB, int WR, bool SEPK>
 struct GenericTraits {
-  static constexpr int kMaxChunks = SEPK ? 2 * DVB / 8 : (DVB + 128) / 8;  // chunks per cache row (RoPE keys of up to 128 dims)
-  static constexpr int kSub = 32 * kMaxChunks * 16;                         // 32 tokens
+  static constexpr int kMaxChunks = (SEPK ? 2 * DVB / 8 : (DVB + 128) / 8) | 1;  // 16-byte chunks per row in LDS (RoPE keys of up to 128 dims)
+  static constexpr int kSub = 32 * kMaxChunks * 16;                               // 32 tokens
   static constexpr int kMaxWaves = DVB > 256 ? 4 : 8;  // (512 dims: a wave needs more than 256 registers)
   static constexpr int WS = WR * 4 <= kMaxWaves && kSub * 8 <= 160 * 1024 ? 4 : WR * 2 <= kMaxWaves && kSub * 4 <= 160 * 1024 ? 2 : 1;
-  static constexpr int NST = kSub * WS * 4 <= 160 * 1024 ? 4 : kSub * WS * 3 <= 160 * 1024 ? 3 : 2;
+  static constexpr int kSmem = kSub * WS * 4 <= 160 * 1024 ? kSub * WS * 4 : 160 * 1024;
   static constexpr int kThreads = 64 * WR * WS;
-  static_assert(NST * WS * kSub <= 160 * 1024 && WR * (WS - 1) * 64 * (DVB + 8) * 4 / 4 <= NST * WS * kSub, "LDS capacity");
+  static_assert(2 * WS * kSub <= kSmem && WR * (WS - 1) * 64 * (DVB + 8) <= kSmem, "LDS capacity");
 };
 
 template <int DVB, int WR, bool SEPK>
 __global__ __launch_bounds__((GenericTraits<DVB, WR, SEPK>::kThreads)) void generic_mfma_kernel(DevParams p) {
   using GT = GenericTraits<DVB, WR, SEPK>;
-  constexpr int WS = GT::WS, NST = GT::NST, NW = WR * WS, STEP = 32 * WS;
-  constexpr int kTile = WS * GT::kSub;
+  constexpr int WS = GT::WS, NW = WR * WS, STEP = 32 * WS;
   constexpr int NDB = DVB / 16, NKN = DVB / 32, NKR = SEPK ? 0 : 4;
-  __shared__ __attribute__((aligned(1024))) unsigned char smem[NST * kTile];
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[GT::kSmem];
   const unsigned lds_base = (unsigned)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem;
   const int lane = threadIdx.x & 63, wave = uniform((int)threadIdx.x >> 6);
   const int r16 = lane & 15, q = lane >> 4;
@@ -97,12 +97,11 @@ __global__ __launch_bounds__((GenericTraits<DVB, WR, SEPK>::kThreads)) void gene
   // ---- chunks of a cache row in LDS: value first, then RoPE key or key
   const int cv = p.d_v >> 3, ck = p.d_n >> 3, cr = p.d_r >> 3;
   const int cpr = cv + (SEPK ? ck : cr);
-  auto slot_of = [&](int row_i, int row_mod, int chunk) {  // byte offset of a chunk inside a tile
-    int s = chunk + row_mod;
-    s -= s >= cpr ? cpr : 0;
-    return (unsigned)((row_i * cpr + s) * 16);
-  };
-  auto mod_cpr = [&](int x) { return x - (int)fast_div((unsigned)x, p.fd_cpr) * cpr; };
+  // (an odd number of chunks per row: the rows at one chunk spread over the banks, and every operand address is the lane's
+  // own plus a constant)
+  const int pitch = (cpr | 1) * 16;
+  const int tile_bytes = STEP * pitch;
+  const int nst = min(4, GT::kSmem / tile_bytes);  // ring stages (two at least)
 
   // ---- queries (B operand): dims beyond the real ones are zero, whatever the key operand holds there
   u32x4_t qn[NKN], qr[NKR > 0 ? NKR : 1];
@@ -137,7 +136,7 @@ __global__ __launch_bounds__((GenericTraits<DVB, WR, SEPK>::kThreads)) void gene
   //      costs pages of one token the depth of the ring.
   constexpr int NWIN = STEP > 64 ? 2 : 1;
   int win0 = 0, win1 = 0, win_page = -0x40000000;
-  const int n_slots = STEP * cpr, n_inst = (n_slots + 63) >> 6;
+  const int n_slots = STEP * (cpr | 1), n_inst = (n_slots + 63) >> 6;
   const int n_mine = uniform((n_inst - wave + NW - 1) / NW);  // load instructions of this wave per tile
   auto load_tile = [&](int tok0, int stage) {
     const int first_page = (int)fast_div((unsigned)tok0, p.fd_page), last_page = (int)fast_div((unsigned)min(tok0 + STEP - 1, L - 1), p.fd_page);
@@ -151,8 +150,7 @@ __global__ __launch_bounds__((GenericTraits<DVB, WR, SEPK>::kThreads)) void gene
     for (int i = wave; i < n_inst; i += NW) {
       const int n = i * 64 + lane;
       const int row_i = min((int)fast_div((unsigned)n, p.fd_cpr), STEP - 1);
-      int chunk = n - row_i * cpr - mod_cpr(row_i);
-      chunk += chunk < 0 ? cpr : 0;
+      const int chunk = min(n - row_i * (cpr | 1), cpr - 1);  // (what pads a row repeats its last chunk)
       const int tok = min(tok0 + row_i, L - 1);
       const int pg = (int)fast_div((unsigned)tok, p.fd_page);
       const int64_t tip = tok - pg * p.P;
@@ -166,50 +164,49 @@ __global__ __launch_bounds__((GenericTraits<DVB, WR, SEPK>::kThreads)) void gene
       if (chunk < cv) src = p.state + page * p.st_s[0] + g * p.st_s[1] + tip * p.st_s[2] + chunk * 8;
       else if constexpr (SEPK) src = p.kstate + page * p.k_s[0] + g * p.k_s[1] + tip * p.k_s[2] + (chunk - cv) * 8;
       else src = p.rope + page * p.rp_s[0] + tip * p.rp_s[1] + (chunk - cv) * 8;
-      if (n < n_slots) __builtin_amdgcn_global_load_lds((global_cvoid_t*)src, (lds_void_t*)(smem + stage * kTile + i * 1024), 16, 0, 0);
+      if (n < n_slots) __builtin_amdgcn_global_load_lds((global_cvoid_t*)src, (lds_void_t*)(smem + stage * tile_bytes + i * 1024), 16, 0, 0);
     }
   };
 
   const int row0 = 32 * ws;  // first row of this wave's share of a tile
-  const int mod_k[2] = {mod_cpr(row0 + r16), mod_cpr(row0 + 16 + r16)};
   const int tr_r = r16 >> 2, tr_c = r16 & 3;
-  const int mod_v[2] = {mod_cpr(row0 + 4 * q + tr_r), mod_cpr(row0 + 16 + 4 * q + tr_r)};
-  const int k0 = SEPK ? cv : 0;  // first chunk of the key (RoPE part apart)
+  // operand addresses of this lane in stage 0: key row r16, chunk q of the key (its RoPE part after the value); value row
+  // 4 q + tr_r, half a chunk (transposing reads); 16 rows further on the second token block
+  const unsigned k_at = lds_base + (unsigned)((row0 + r16) * pitch + ((SEPK ? cv : 0) + q) * 16), r_at = lds_base + (unsigned)((row0 + r16) * pitch + (cv + q) * 16);
+  const unsigned v_at = lds_base + (unsigned)((row0 + 4 * q + tr_r) * pitch + tr_c * 8);
+  const unsigned block2 = (unsigned)(16 * pitch);
 
   if (j_begin < j_end) {
     const int n_tiles = (j_end - j_begin + STEP - 1) / STEP;
-#pragma unroll
-    for (int t = 0; t < NST - 1; ++t)
-      if (t < n_tiles) load_tile(j_begin + t * STEP, t);
+    for (int t = 0; t < min(nst - 1, n_tiles); ++t) load_tile(j_begin + t * STEP, t);
     int stage = 0;
     for (int tile = 0; tile < n_tiles; ++tile) {
       const int j = j_begin + tile * STEP;
-      wait_vmcnt_at_most(n_mine * min(n_tiles - 1 - tile, NST - 2));  // this wave's part of the tile ...
+      wait_vmcnt_at_most(n_mine * min(n_tiles - 1 - tile, nst - 2));  // this wave's part of the tile ...
       lds_barrier();  // ... and everybody's; nobody reads the stage of the tile before any more
-      const unsigned base = lds_base + (unsigned)(stage * kTile);
-      const int stage_load = stage == 0 ? NST - 1 : stage - 1;
-      stage = stage == NST - 1 ? 0 : stage + 1;
-      if (tile + NST - 1 < n_tiles) load_tile(j + (NST - 1) * STEP, stage_load);
+      const unsigned off = (unsigned)(stage * tile_bytes);
+      const int stage_load = stage == 0 ? nst - 1 : stage - 1;
+      stage = stage == nst - 1 ? 0 : stage + 1;
+      if (tile + nst - 1 < n_tiles) load_tile(j + (nst - 1) * STEP, stage_load);
       if (j + STEP > L) {  // rows past the end may hold anything: 0 x NaN must not leak (uniform over the workgroup)
-        for (int off = (L - j) * cpr * 16 + (int)threadIdx.x * 16; off < n_slots * 16; off += 64 * NW * 16)
-          lds_write_b128<0>(base + (unsigned)off, u32x4_t{0, 0, 0, 0});
+        for (int z = (L - j) * pitch + (int)threadIdx.x * 16; z < tile_bytes; z += 64 * NW * 16)
+          lds_write_b128<0>(lds_base + off + (unsigned)z, u32x4_t{0, 0, 0, 0});
         lds_barrier();
       }
       if (j + row0 >= j_end) continue;  // (the last tile of a range may end before this wave's share)
       // ---- scores of 2 x 16 tokens: S^T[token 16 tb + 4 q + e][row r16]
       f32x4_t s[2] = {f32x4_t{0.f, 0.f, 0.f, 0.f}, f32x4_t{0.f, 0.f, 0.f, 0.f}};
-      // (four steps at a time, their eight reads in flight together; a step beyond the key's dims reads its last
-      // chunk again, against zeros of the query)
-      auto score_steps = [&](auto nc, const auto& qf, int first, int chunks) {
+      // (four steps at a time, their eight reads in flight together; where the key ends inside them, the lanes beyond its
+      // dims read its last chunk again, against zeros of the query)
+      auto score_steps = [&](auto nc, const auto& qf, unsigned at, int chunks) {
         static_for<0, decltype(nc)::value / 4>([&](auto gc) {
           constexpr int k4 = 4 * decltype(gc)::value;
-          if (4 * k4 < chunks) {
+          auto four = [&](auto back) {  // back(ks): how far this lane's chunk of step ks lies beyond the last one, in bytes
             u32x4_t kf[4][2];
             static_for<0, 4>([&](auto kc) {
               constexpr int ks = decltype(kc)::value;
-              const int c = first + min(4 * (k4 + ks) + q, chunks - 1);
-              lds_read_b128<0>(kf[ks][0], base + slot_of(row0 + r16, mod_k[0], c));
-              lds_read_b128<0>(kf[ks][1], base + slot_of(row0 + 16 + r16, mod_k[1], c));
+              lds_read_b128<(k4 + ks) * 64>(kf[ks][0], at - back(kc));
+              lds_read_b128<(k4 + ks) * 64>(kf[ks][1], at + block2 - back(kc));
             });
             static_for<0, 4>([&](auto kc) {
               constexpr int ks = decltype(kc)::value;
@@ -221,11 +218,14 @@ __global__ __launch_bounds__((GenericTraits<DVB, WR, SEPK>::kThreads)) void gene
                 s[tb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, kf[ks][tb]), __builtin_bit_cast(bf16x8_t, qf[k4 + ks]), s[tb], 0, 0, 0);
               });
             });
-          }
+          };
+          const int n = chunks - 4 * k4;  // chunks from these steps on
+          if (n >= 16) four([&](auto) { return 0u; });
+          else if (n > 0) four([&](auto kc) { return (unsigned)(16 * max(0, 4 * decltype(kc)::value + q + 1 - n)); });
         });
       };
-      score_steps(std::integral_constant<int, NKN>{}, qn, k0, ck);
-      if constexpr (!SEPK) score_steps(std::integral_constant<int, NKR>{}, qr, cv, cr);
+      score_steps(std::integral_constant<int, NKN>{}, qn, k_at + off, ck);
+      if constexpr (!SEPK) score_steps(std::integral_constant<int, NKR>{}, qr, r_at + off, cr);
       // ---- online softmax (base 2), masked by select
       float mx = -INFINITY;
       bool visible[8];
@@ -266,13 +266,13 @@ __global__ __launch_bounds__((GenericTraits<DVB, WR, SEPK>::kThreads)) void gene
       // ---- values
       static_for<0, NDB / 4>([&](auto gc) {
         constexpr int d4 = 4 * decltype(gc)::value;
-        if (2 * d4 < cv) {
+        auto four = [&](auto back) {
           u32x2_t v0[4], v1[4];
+          const unsigned at = v_at + off;
           static_for<0, 4>([&](auto dc) {
             constexpr int d = decltype(dc)::value;
-            const int c = min(2 * (d4 + d) + (tr_c >> 1), cv - 1);  // (blocks past the value's dims: accumulated, never stored)
-            lds_read_tr16_b64<0>(v0[d], base + slot_of(row0 + 4 * q + tr_r, mod_v[0], c) + (unsigned)((tr_c & 1) * 8));
-            lds_read_tr16_b64<0>(v1[d], base + slot_of(row0 + 16 + 4 * q + tr_r, mod_v[1], c) + (unsigned)((tr_c & 1) * 8));
+            lds_read_tr16_b64<(d4 + d) * 32>(v0[d], at - back(dc));
+            lds_read_tr16_b64<(d4 + d) * 32>(v1[d], at + block2 - back(dc));
           });
           static_for<0, 4>([&](auto dc) {
             constexpr int d = decltype(dc)::value;
@@ -284,7 +284,10 @@ __global__ __launch_bounds__((GenericTraits<DVB, WR, SEPK>::kThreads)) void gene
               o[d4 + d] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a4), __builtin_bit_cast(bf16x8_t, b4), o[d4 + d], 0, 0, 0);
             }
           });
-        }
+        };
+        const int n = (cv >> 1) - d4;  // 16-dim blocks from these on (blocks past the value's dims repeat the last one: accumulated, never stored)
+        if (n >= 4) four([&](auto) { return 0u; });
+        else if (n > 0) four([&](auto dc) { return (unsigned)(32 * max(0, decltype(dc)::value + 1 - n)); });
       });
     }
   }

@@ -331,7 +331,7 @@ void launch_generic_mfma(const gla_decode_params* p, DevParams& d, hipStream_t s
   else d.small_ranges = (int32_t)(small_grid() / generic_units(p));
   d.fd_page = make_fastdiv((uint32_t)p->page_size);
   const bool sepk = d.kstate != nullptr;
-  d.fd_cpr = make_fastdiv((uint32_t)(p->d_v / 8 + (sepk ? p->d_nope : p->d_rope) / 8));
+  d.fd_cpr = make_fastdiv((uint32_t)(p->d_v / 8 + (sepk ? p->d_nope : p->d_rope) / 8) | 1u);
   const int rows_group = p->num_q_heads / p->num_groups * p->q_len;
   const int64_t units = (int64_t)p->batch * p->num_groups;
   const int dmax = std::max(p->d_v, p->d_nope);
