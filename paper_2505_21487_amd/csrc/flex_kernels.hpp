@@ -104,10 +104,12 @@ template <int DN, int DR, int DV, bool SEPK, int GPW = 1>
 struct FlexTraits {
   static constexpr int kVB = DV * 2, kKB = DN * 2, kRB = DR * 2;  // row bytes of the value / key / RoPE tiles
   static constexpr int kStage = 32 * (GPW * kVB + (SEPK ? kKB : 0) + kRB);
-  // Ring stages per wave.  Small tiles: three stages in 20 KB, so that two workgroups (two waves per SIMD)
-  // share a compute unit and one wave's LDS and MFMA latencies hide behind the other's work; larger
-  // tiles: as many stages as 40 KB hold, at most six (one workgroup per compute unit).
-  static constexpr int kNST = 3 * kStage <= 20 * 1024 ? 3 : (40 * 1024 / kStage) < 6 ? (40 * 1024 / kStage) : 6;
+  // Ring stages per wave: one tile in use and one on its way (two for tiles of up to 6.7 KB).  The four waves of a
+  // workgroup, one per SIMD, keep the memory busy with that; a deeper ring only delays the first scores, which wait for
+  // the queries and with them for every tile requested before (loads return in order).  us per call with as many stages
+  // as 40 KB hold -> two: GTA-4 d_h 64 48 sequences at one token per page 34.4 -> 32.7, 128 long ones 214.0 -> 212.8, d_h 96
+  // 30 sequences 22.0 -> 21.0, 100 long ones 244.5 -> 242.6.  (Two waves per SIMD: 35.7, 220, 23.3, 250.)
+  static constexpr int kNST = 3 * kStage <= 20 * 1024 ? 3 : 2;
   static constexpr int loads(int rb) { return rb / 32; }  // load instructions (64 lanes x 16 bytes) for 32 rows of rb bytes
   static constexpr int kLPT = GPW * loads(kVB) + (SEPK ? loads(kKB) : 0) + loads(kRB);
   static_assert(GPW == 1 || (GPW == 2 && !SEPK), "two groups per wave: tied / latent states only");

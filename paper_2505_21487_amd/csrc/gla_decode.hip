@@ -111,16 +111,17 @@ bool flex_plan(const gla_decode_params* p, int mode, const KeyCache* kc, bool le
     plan->chunk_tiles = (int)((max_tiles + p->num_splits - 1) / p->num_splits);
     chunks = (bound + plan->chunk_tiles - 1) / plan->chunk_tiles;
   } else {
-    // one wave per SIMD (what is resident at once), chunks of at least eight tiles (by the upper bound):
-    // a wave's start (lengths, page ids, queries, first tiles) costs several tiles' worth of time
+    // one wave per SIMD, chunks of at least four tiles (by the upper bound): a wave's start (lengths, page ids, queries,
+    // first tile) costs several tiles' worth of time.  us per call with eight / five / four / three / two: GTA-4 d_h 64
+    // 100 x 50 to 600 tokens 17.1 / 16.1 / 15.6 / 15.6 / 15.6, 10 sequences 14.5 / 14.0 / 13.9 / 14.6 / 14.6, 1 x 30000 20.0 / 19.4 /
+    // 19.7 / 21.1 / 27.6, d_h 96 3 x 3000 14.3 / 14.3 / 14.3 / 13.7 / 13.4, GQA-4 6 sequences 15.0 / 15.0 / 14.5 / 15.1 / 15.1.
+    // (lean: eight, what a workspace was sized for before)
     plan->chunk_tiles = 0;
     const int64_t waves = device_cu_count();
-    int64_t by_length = bound / 8;
-    // ... but while most of the chip is idle a shorter serial chain pays: chunks of four tiles up to one wave per
-    // compute unit, of two up to half of that.  us per call: GTA-4 d_h 64, batch 1 x 200 12.9 -> 11.0, 4 x 100 to 900
-    // 16.5 -> 12.5; GQA-4 batch 2 x 300 18.1 -> 11.9.
-    if (!lean && p->batch <= kShortChunkBatch)
-      by_length = std::max({by_length, std::min(bound / 4, waves / plan->strands), std::min(bound / 2, waves / 2 / plan->strands)});
+    int64_t by_length = lean ? bound / 8 : bound / 4;
+    // ... but while most of the chip is idle a shorter serial chain pays: chunks of two tiles up to half a wave per compute
+    // unit.  us per call: GTA-4 d_h 64, batch 1 x 200 12.9 -> 11.0; GQA-4 batch 2 x 300 18.1 -> 11.9.
+    if (!lean && p->batch <= kShortChunkBatch) by_length = std::max(by_length, std::min(bound / 2, waves / 2 / plan->strands));
     chunks = std::min<int64_t>((4 * waves + plan->strands - 1) / plan->strands, by_length);
   }
   chunks = std::max<int64_t>(1, chunks);
