@@ -12,9 +12,9 @@
 // a page, a page, two pages ... 32 pages for page sizes 64, 32, 16 ... 1; the
 // address code comes in four forms, see the page modes of the main kernel);
 // a tile is the NG state tiles of its groups plus one RoPE tile.  All tiles of all units, in
-// unit order, form one flat list that is cut into equal chunks, so ragged
-// batches balance by construction and at most two units per chunk are left
-// incomplete.  A chunk is worked on by one workgroup per row block.  A (unit,
+// unit order, form one flat list that is cut into chunks equal in time (cut_list),
+// so ragged batches balance by construction and at most two units per chunk are
+// left incomplete.  A chunk is worked on by one workgroup per row block.  A (unit,
 // row block) that lies inside one chunk is written straight to the output; one
 // that spans chunks leaves one partial (normalised fp32 output + log-sum-exp)
 // per chunk in the workspace, merged by tuned_combine_kernel.
