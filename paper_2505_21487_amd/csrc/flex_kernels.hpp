@@ -10,7 +10,7 @@
 // These shapes have few query rows per group and little arithmetic per cache
 // byte, so the design is the simplest one that streams well: ONE WAVE per piece
 // of work, no cooperation between waves, hence no barriers.  The key tiles of
-// all sequences form one flat list, cut into equal chunks; a wave takes one
+// all sequences form one flat list, cut into chunks equal in time (cut_list); a wave takes one
 // chunk for one (group block, block of 16 query rows) and walks through the
 // sequences its chunk touches, so ragged batches balance by construction.  It
 // moves its tiles of 32 tokens global -> LDS with direct-to-LDS loads of whole
@@ -145,7 +145,7 @@ __global__ __launch_bounds__(256) void flex_main_kernel(DevParams p) {
 
   // ---- this wave's share of the work.  A "strand" is one (group block, block of 16 query rows); every
   //      strand walks the same flat list of key tiles (all tiles of sequence 0, of sequence 1, ...), cut
-  //      into num_chunks equal chunks, one wave per (chunk, strand): ragged batches balance by
+  //      into num_chunks chunks equal in time, one wave per (chunk, strand): ragged batches balance by
   //      construction.  Strands are numbered fastest, group blocks first, so the waves of a workgroup
   //      fetch the SAME shared RoPE-key rows at about the same time (one trip to HBM for all of them).
   const int rows_group = p.g_q * p.T;
