@@ -123,9 +123,11 @@ __global__ __launch_bounds__(64 * NW) void tuned_combine_kernel(DevParams p) {
     f32x4_t acc[NQ];
 #pragma unroll
     for (int c = 0; c < NQ; ++c) acc[c] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-    // everything so far to a reference that is not below it (one rounding in front of the exponential)
+    // (the difference first: it is small where the weight counts, and so is then the error of the exponent)
+    auto weight = [&](float ls, float ref) { return __builtin_amdgcn_exp2f((ls - ref) * kLog2e); };
+    // everything so far to a reference that is not below it
     auto rebase = [&](float m_new) {
-      const float keep = m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(__builtin_fmaf(m, kLog2e, -(m_new * kLog2e)));
+      const float keep = m == -INFINITY ? 0.f : weight(m, m_new);
       z *= keep;
 #pragma unroll
       for (int c = 0; c < NQ; ++c) acc[c] *= keep;
@@ -154,12 +156,11 @@ __global__ __launch_bounds__(64 * NW) void tuned_combine_kernel(DevParams p) {
         for (int u = 0; u < U; ++u) m_new = fmaxf(m_new, ls[u]);
         if (m_new == -INFINITY) continue;
         if (m_new != m) rebase(m_new);
-        const float m2 = m * kLog2e;
 #pragma unroll
         for (int u = 0; u < U; ++u) {
           // a slot marked "no key" may hold anything: its values are dropped, not multiplied by zero
           const bool live = ls[u] != -INFINITY;
-          const float wgt = __builtin_amdgcn_exp2f(__builtin_fmaf(ls[u], kLog2e, -m2));
+          const float wgt = weight(ls[u], m);
           z += wgt;
 #pragma unroll
           for (int c = 0; c < NQ; ++c) acc[c] += wgt * (live ? v[u][c] : f32x4_t{0.f, 0.f, 0.f, 0.f});
@@ -181,11 +182,10 @@ __global__ __launch_bounds__(64 * NW) void tuned_combine_kernel(DevParams p) {
         if (j < kw) m_new = fmaxf(m_new, red_m[wave + j][lane]);
       if (m_new != -INFINITY) {
         if (m_new != m) rebase(m_new);
-        const float m2 = m * kLog2e;
 #pragma unroll
         for (int j = 1; j < NW; ++j) {
           if (j >= kw) continue;
-          const float wgt = __builtin_amdgcn_exp2f(__builtin_fmaf(red_m[wave + j][lane], kLog2e, -m2));  // (no key: 0, as are the sums)
+          const float wgt = weight(red_m[wave + j][lane], m);  // (no key: 0, as are the sums)
           z += wgt * red_z[wave + j][lane];
 #pragma unroll
           for (int c = 0; c < NQ; ++c) acc[c] += wgt * red_a[(wave + j) * NQ + c][lane];
