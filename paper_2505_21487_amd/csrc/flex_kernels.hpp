@@ -158,7 +158,7 @@ __global__ __launch_bounds__(256) void flex_main_kernel(DevParams p) {
   const int rb = (int)((unsigned)strand / HB);
   const int g0 = (strand - rb * (int)HB) * GPW;  // first group of this wave
   const int L_first = lane < p.B ? p.seq_lens[lane] : 0;
-  const ListCut cut = cut_list<32>(p, 1, lane, L_first);
+  const ListCut cut = cut_list<32, 128>(p, 1, lane, L_first, (int)NSTR);
   const int total = cut.tiles;
   const ChunkSpan span0 = locate_chunk<32>(p, 1, cut, chunk, lane, L_first);
   int left = span0.n_tiles;  // tiles of this chunk not yet worked on

@@ -311,9 +311,14 @@ __device__ __forceinline__ int total_tiles(const DevParams& p, int UPB, int lane
 // result of the first is stored, the queries of the second are fetched, its first tiles move the softmax reference.  So
 // every unit holds p.setup_tiles positions in front of its tiles, and chunks are equal in positions: a workgroup with
 // three short sequences gets fewer tiles than one inside a long sequence (before, the median workgroup of a decode of 24
-// ragged sequences ended after 28 us, the last one, with three segments, after 54).  Where all sequences have the same
-// number of tiles and equal chunks in tiles end with them, no chunk crosses anything and the positions are left out.
-// What it gains, and how many positions: kSetupTiles.
+// ragged sequences ended after 28 us, the last one, with three segments, after 54).  What it gains, and how many positions:
+// kSetupTiles.  Without them where no chunk crosses anything:
+//   a list of one unit (but a remainder of one tile is better kept with the rest, without partials: first chunk empty),
+//   sequences all of the same number of tiles, if equal chunks in tiles end with them,
+//   chunks of one tile.  These only while the grid is small, of sequences of about one length, longer than two tiles; else
+//   whole sequences, without partials, are the better cut.  us per call with the positions / without: 8 sequences of 2 to 4
+//   tiles, GLA-2 18.3 / 15.9, 16 heads 16.3 / 14.5, MLA shape 16 heads 16.5 / 14.0, GTA-4 d_h 128 14.7 / 13.3; MLA shape, three
+//   query positions, 2 of 13 and 14 (162 workgroups) 22.0 / 25.3; GLA-2 40 heads, three positions, 48 of 1 to 6 21.0 / 25.7.
 struct ListCut {
   int tiles;     // tiles of the list
   int setup;     // positions in front of a unit's tiles
@@ -321,9 +326,10 @@ struct ListCut {
   int chunk;     // positions per chunk
   int incl0;     // inclusive prefix sums of the tiles (per unit) of the first 64 sequences
 };
-// L_first: lengths of the first 64 sequences.  (Every wave computes the same values.)
-template <int TOK>
-__device__ __forceinline__ ListCut cut_list(const DevParams& p, int UPB, int lane, int L_first) {
+// L_first: lengths of the first 64 sequences; per_chunk: workgroups (waves) that work on one chunk; SMALL: of these, how many
+// there are at most with chunks of one tile cut as they come.  (Every wave computes the same values.)
+template <int TOK, int SMALL>
+__device__ __forceinline__ ListCut cut_list(const DevParams& p, int UPB, int lane, int L_first, int per_chunk) {
   ListCut c;
   const int tl0 = tiles_of<TOK>(L_first);
   c.incl0 = wave_incl_scan(tl0);
@@ -332,6 +338,7 @@ __device__ __forceinline__ ListCut cut_list(const DevParams& p, int UPB, int lan
   int seqs = __popcll(held);
   int same = held ? __builtin_amdgcn_readlane(tl0, __ffsll((long long)held) - 1) : 0;  // tiles of every sequence, 0: they differ
   if (__ballot(tl0 > 0 && tl0 != same)) same = 0;
+  int tl_max = tl0;  // most tiles among this lane's sequences
   for (int base = 64; base < p.B; base += 64) {
     const int idx = base + lane;
     const int tl = idx < p.B ? tiles_of<TOK>(p.seq_lens[idx]) : 0;
@@ -339,6 +346,7 @@ __device__ __forceinline__ ListCut cut_list(const DevParams& p, int UPB, int lan
     held = __ballot(tl > 0);
     if (seqs == 0 && held) same = __builtin_amdgcn_readlane(tl, __ffsll((long long)held) - 1);
     if (__ballot(tl > 0 && tl != same)) same = 0;
+    tl_max = max(tl_max, tl);
     seqs += __popcll(held);
   }
   c.tiles = tiles * UPB;
@@ -347,7 +355,11 @@ __device__ __forceinline__ ListCut cut_list(const DevParams& p, int UPB, int lan
   c.chunk = p.chunk_tiles;
   if (p.chunk_tiles <= 0) {
     c.chunk = (int)fast_div((unsigned)(c.tiles + p.num_chunks - 1), p.fd_chunks);
-    if (p.setup_tiles > 0 && c.chunk > 0 && (same == 0 || (unsigned)same % (unsigned)c.chunk != 0)) {
+    bool none;  // no set-ups
+    if (UPB * seqs == 1) none = c.tiles > c.chunk + 1;
+    else if (same > 0) none = c.chunk > 0 && (unsigned)same % (unsigned)c.chunk == 0;
+    else none = c.chunk == 1 && c.tiles * per_chunk <= SMALL && __ballot(tl_max > 2) != 0 && __ballot(2 * UPB * seqs * tl_max > 5 * c.tiles) == 0;
+    if (p.setup_tiles > 0 && c.chunk > 0 && !none) {
       c.setup = p.setup_tiles;
       c.positions = c.tiles + c.setup * UPB * seqs;
       c.chunk = (int)fast_div((unsigned)(c.positions + p.num_chunks - 1), p.fd_chunks);

@@ -176,7 +176,7 @@ __global__ __launch_bounds__(64 * NG * WPG * KS) void tuned_main_kernel(DevParam
   }
 
   // ---- plan: this workgroup's chunk [c0, c1) of the flat tile list
-  const ListCut cut = cut_list<TOK>(p, UPB, lane, L_first);
+  const ListCut cut = cut_list<TOK, 48>(p, UPB, lane, L_first, MB);
   if (cut.tiles <= 0) return;
   if constexpr (eight_wave_shape(DV, NG, WPG, KS)) {
     if (p.wide_tiles > 0 && cut.tiles >= p.wide_tiles) return;  // the eight-wave kernel, launched next, takes this batch

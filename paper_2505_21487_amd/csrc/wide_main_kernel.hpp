@@ -156,7 +156,7 @@ __global__ __launch_bounds__(512) void wide_main_kernel(DevParams p) {
   if (p.wide_tiles > 0 &&  // (counted as the four-wave kernel counts them: one of the two runs)
       total_tiles<kTok>(p, UPB, lane, wave_incl_scan(tiles_of<kTok>(L_first) * UPB)) < p.wide_tiles)
     return;
-  const ListCut cut = cut_list<TOK>(p, UPB, lane, L_first);
+  const ListCut cut = cut_list<TOK, 0>(p, UPB, lane, L_first, MB);
   if (cut.tiles <= 0) return;
   const ChunkSpan span0 = locate_chunk<TOK>(p, UPB, cut, chunk_id, lane, L_first);
   const int n_tiles = span0.n_tiles;

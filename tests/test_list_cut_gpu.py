@@ -2,8 +2,10 @@
 64 that are counted at once, empty ones first, last and between, chunks that begin in front of a sequence or hold several,
 several units per sequence, equal lengths that end with a chunk and such that do not."""
 import pytest
+import torch
 
 import paper_2505_21487_amd as gla
+from paper_2505_21487_amd.harness import DeviceProblem
 from workloads import make_problem
 
 from gpu_util import check_problem
@@ -35,3 +37,27 @@ def test_cut_list(kernel, lengths):
     p = make_problem(f"{kernel}_{lengths}", kind=kind, seq_lens=lens, T=T, h_q=h, h_c=g, d_v=d_v, **({"d_r": d_r} if d_r else {}), seed=8100 + len(kernel) + len(lengths),
                      num_pages=sum((n + 63) // 64 for n in lens) + 64, poison_tail=True)
     check_problem(p, impl=gla.GLA_IMPL_TUNED, what=f"{kernel} {lengths}")
+
+
+# kind, heads, groups, d_v, RoPE dims, tokens per page, lengths, unused table columns, splits whose chunks are the library's own.  Lists that no chunk
+# boundary has to make allowances for are cut into equal chunks in tiles, as the caller's own number of splits is: one
+# sequence alone (63 tiles over 32 chunks, 7 over 3); chunks of one tile, short sequences of about one length
+EQUAL_TILES = {
+    "gla2_h16_one": ("gla", 16, 2, 256, 64, 64, [2010], 0, 32),
+    "gta4_d64_one": ("gta", 32, 4, 64, 32, 32, [216], 0, 3),
+    "gla2_h16_short": ("gla", 16, 2, 256, 64, 64, [190, 150, 170, 130, 185], 0, 6),
+    "gta4_d64_short": ("gta", 32, 4, 64, 32, 32, [190, 150, 170, 130, 185], 6, 12),
+}
+
+
+@pytest.mark.parametrize("name", sorted(EQUAL_TILES))
+def test_chunks_without_crossings_are_equal_in_tiles(name):
+    """Bit for bit what the same chunks give when the caller asks for them."""
+    kind, h, g, d_v, d_r, page, lens, extra, splits = EQUAL_TILES[name]
+    p = make_problem(name, kind=kind, seq_lens=lens, T=1, h_q=h, h_c=g, d_v=d_v, d_r=d_r, page_size=page, seed=8200 + len(name),
+                     num_pages=sum((n + page - 1) // page for n in lens) + 9, extra_table_cols=extra)
+    dp = DeviceProblem(p, poison_unused=True)
+    fn = gla.gta_decode if kind == "gta" else gla.gla_decode
+    own, asked = (fn(*dp.args(), out_dtype=torch.float32, impl=gla.GLA_IMPL_TUNED, num_splits=n) for n in (0, splits))
+    torch.cuda.synchronize()
+    assert torch.equal(own[0], asked[0]) and torch.equal(own[1], asked[1])
