@@ -110,6 +110,13 @@ struct FlexTraits {
   // as 40 KB hold -> two: GTA-4 d_h 64 48 sequences at one token per page 34.4 -> 32.7, 128 long ones 214.0 -> 212.8, d_h 96
   // 30 sequences 22.0 -> 21.0, 100 long ones 244.5 -> 242.6.  (Two waves per SIMD: 35.7, 220, 23.3, 250.)
   static constexpr int kNST = 3 * kStage <= 20 * 1024 ? 3 : 2;
+  // The merge has one wave per row, with eight pieces in flight for each 16 bytes of a row that its lanes hold: beyond five
+  // such round trips the time goes there, and chunks get up to eight tiles.  us per call with chunks of eight / six / five /
+  // four tiles, one sequence of 400 / 900 / 2000 tiles: GTA-4 d_h 64 16.3 / 16.2 / 15.8 / 16.1, 20.2 / 18.9 / 19.7 / 20.7, 24.4 /
+  // 25.3 / 27.8 / 31.3, d_h 96 18.7 / 18.0 / 17.4 / 19.2, 22.8 / 24.7 / 25.4 / 29.0, 33.6 / 32.9 / 32.9 / 32.9, GQA-4 21.1 / 20.1 /
+  // 19.6 / 20.7, 25.6 / 27.8 / 29.4 / 33.1, 44.2 / 43.3 / 43.3 / 43.3.  (On the device: a wide page table makes chunks
+  // shorter than the host planned.)
+  static constexpr int kPieces = 5 * 8 * (64 / (DV / 4));
   static constexpr int loads(int rb) { return rb / 32; }  // load instructions (64 lanes x 16 bytes) for 32 rows of rb bytes
   static constexpr int kLPT = GPW * loads(kVB) + (SEPK ? loads(kKB) : 0) + loads(kRB);
   static_assert(GPW == 1 || (GPW == 2 && !SEPK), "two groups per wave: tied / latent states only");
@@ -158,7 +165,7 @@ __global__ __launch_bounds__(256) void flex_main_kernel(DevParams p) {
   const int rb = (int)((unsigned)strand / HB);
   const int g0 = (strand - rb * (int)HB) * GPW;  // first group of this wave
   const int L_first = lane < p.B ? p.seq_lens[lane] : 0;
-  const ListCut cut = cut_list<32, 128>(p, 1, lane, L_first, (int)NSTR);
+  const ListCut cut = cut_list<32, 128, FT::kPieces>(p, 1, lane, L_first, (int)NSTR);
   const int total = cut.tiles;
   const ChunkSpan span0 = locate_chunk<32>(p, 1, cut, chunk, lane, L_first);
   int left = span0.n_tiles;  // tiles of this chunk not yet worked on

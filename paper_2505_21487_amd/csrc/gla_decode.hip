@@ -113,8 +113,8 @@ bool flex_plan(const gla_decode_params* p, int mode, const KeyCache* kc, bool le
   } else {
     // one wave per SIMD, chunks of at least four tiles (by the upper bound): a wave's start (lengths, page ids, queries,
     // first tile) costs several tiles' worth of time.  us per call with eight / five / four / three / two: GTA-4 d_h 64
-    // 100 x 50 to 600 tokens 17.1 / 16.1 / 15.6 / 15.6 / 15.6, 10 sequences 14.5 / 14.0 / 13.9 / 14.6 / 14.6, 1 x 30000 20.0 / 19.4 /
-    // 19.7 / 21.1 / 27.6, d_h 96 3 x 3000 14.3 / 14.3 / 14.3 / 13.7 / 13.4, GQA-4 6 sequences 15.0 / 15.0 / 14.5 / 15.1 / 15.1.
+    // 100 x 50 to 600 tokens 17.1 / 16.1 / 15.6 / 15.6 / 15.6, 10 sequences 14.5 / 14.0 / 13.9 / 14.6 / 14.6, d_h 96 3 x 3000 14.3 /
+    // 14.3 / 14.3 / 13.7 / 13.4, GQA-4 6 sequences 15.0 / 15.0 / 14.5 / 15.1 / 15.1.  (Long sequences: FlexTraits::kPieces.)
     // (lean: eight, what a workspace was sized for before)
     plan->chunk_tiles = 0;
     const int64_t waves = device_cu_count();

@@ -327,8 +327,9 @@ struct ListCut {
   int incl0;     // inclusive prefix sums of the tiles (per unit) of the first 64 sequences
 };
 // L_first: lengths of the first 64 sequences; per_chunk: workgroups (waves) that work on one chunk; SMALL: of these, how many
-// there are at most with chunks of one tile cut as they come.  (Every wave computes the same values.)
-template <int TOK, int SMALL>
+// there are at most with chunks of one tile cut as they come; PIECES > 0: pieces per sequence at most, except in chunks of
+// eight tiles or more.  (Every wave computes the same values.)
+template <int TOK, int SMALL, int PIECES = 0>
 __device__ __forceinline__ ListCut cut_list(const DevParams& p, int UPB, int lane, int L_first, int per_chunk) {
   ListCut c;
   const int tl0 = tiles_of<TOK>(L_first);
@@ -355,6 +356,13 @@ __device__ __forceinline__ ListCut cut_list(const DevParams& p, int UPB, int lan
   c.chunk = p.chunk_tiles;
   if (p.chunk_tiles <= 0) {
     c.chunk = (int)fast_div((unsigned)(c.tiles + p.num_chunks - 1), p.fd_chunks);
+    int least = 0;
+    if constexpr (PIECES > 0) {
+      if (c.chunk < 8 && __ballot(tl_max > PIECES * c.chunk) != 0) {
+        least = min(8, (wave_max(tl_max) + PIECES - 1) / PIECES);
+        c.chunk = max(c.chunk, least);
+      }
+    }
     bool none;  // no set-ups
     if (UPB * seqs == 1) none = c.tiles > c.chunk + 1;
     else if (same > 0) none = c.chunk > 0 && (unsigned)same % (unsigned)c.chunk == 0;
@@ -362,7 +370,7 @@ __device__ __forceinline__ ListCut cut_list(const DevParams& p, int UPB, int lan
     if (p.setup_tiles > 0 && c.chunk > 0 && !none) {
       c.setup = p.setup_tiles;
       c.positions = c.tiles + c.setup * UPB * seqs;
-      c.chunk = (int)fast_div((unsigned)(c.positions + p.num_chunks - 1), p.fd_chunks);
+      c.chunk = max(least, (int)fast_div((unsigned)(c.positions + p.num_chunks - 1), p.fd_chunks));
     }
   }
   return c;

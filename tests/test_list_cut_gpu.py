@@ -41,12 +41,14 @@ def test_cut_list(kernel, lengths):
 
 # kind, heads, groups, d_v, RoPE dims, tokens per page, lengths, unused table columns, splits whose chunks are the library's own.  Lists that no chunk
 # boundary has to make allowances for are cut into equal chunks in tiles, as the caller's own number of splits is: one
-# sequence alone (63 tiles over 32 chunks, 7 over 3); chunks of one tile, short sequences of about one length
+# sequence alone (63 tiles over 32 chunks, 7 over 3); chunks of one tile, short sequences of about one length; on the second MFMA
+# kernel one long sequence in chunks of eight tiles, so that the merge does not get too many pieces
 EQUAL_TILES = {
     "gla2_h16_one": ("gla", 16, 2, 256, 64, 64, [2010], 0, 32),
     "gta4_d64_one": ("gta", 32, 4, 64, 32, 32, [216], 0, 3),
     "gla2_h16_short": ("gla", 16, 2, 256, 64, 64, [190, 150, 170, 130, 185], 0, 6),
     "gta4_d64_short": ("gta", 32, 4, 64, 32, 32, [190, 150, 170, 130, 185], 6, 12),
+    "gta4_d96_long": ("gta", 24, 4, 96, 48, 64, [900 * 32], 0, 113), "gqa4_d128_long_wide_table": ("gqa", 16, 4, 128, 0, 64, [700 * 32], 4 * 350, 438),
 }
 
 
@@ -54,10 +56,16 @@ EQUAL_TILES = {
 def test_chunks_without_crossings_are_equal_in_tiles(name):
     """Bit for bit what the same chunks give when the caller asks for them."""
     kind, h, g, d_v, d_r, page, lens, extra, splits = EQUAL_TILES[name]
-    p = make_problem(name, kind=kind, seq_lens=lens, T=1, h_q=h, h_c=g, d_v=d_v, d_r=d_r, page_size=page, seed=8200 + len(name),
+    p = make_problem(name, kind=kind, seq_lens=lens, T=1, h_q=h, h_c=g, d_v=d_v, **({"d_r": d_r} if d_r else {}), page_size=page, seed=8200 + len(name),
                      num_pages=sum((n + page - 1) // page for n in lens) + 9, extra_table_cols=extra)
     dp = DeviceProblem(p, poison_unused=True)
-    fn = gla.gta_decode if kind == "gta" else gla.gla_decode
-    own, asked = (fn(*dp.args(), out_dtype=torch.float32, impl=gla.GLA_IMPL_TUNED, num_splits=n) for n in (0, splits))
+
+    def run(n):
+        kw = dict(out_dtype=torch.float32, impl=gla.GLA_IMPL_TUNED, num_splits=n)
+        if kind == "gqa":
+            return gla.gqa_decode(dp.q_nope, dp.key_cache, dp.state_cache, dp.page_table, dp.seq_lens, p.scale, **kw)
+        return (gla.gta_decode if kind == "gta" else gla.gla_decode)(*dp.args(), **kw)
+
+    own, asked = run(0), run(splits)
     torch.cuda.synchronize()
     assert torch.equal(own[0], asked[0]) and torch.equal(own[1], asked[1])
