@@ -14,6 +14,7 @@
 #include "generic_kernels.hpp"
 #include "generic_mfma_kernel.hpp"
 #include "proj_kernels.hpp"
+#include "proj_plan.hpp"
 #include "tuned_kernels.hpp"
 
 namespace gla {
@@ -484,77 +485,6 @@ int run_noalloc(const gla_decode_params* p, int is_gta) {
 }
 
 // ---- projections around the attention ------------------------------------------
-struct ProjPlan {
-  int mt;          // 32-row blocks of query rows per workgroup (1, 2 or 4)
-  int nt;          // 32-row blocks of output features per wave (1 or 2)
-  int ksplit;      // ranges the input features of a group are cut into
-  int k_per_split;
-  bool direct;     // no partials: the kernel writes the result itself
-  bool stream;     // fetch the weights with the streaming hint
-  size_t part_bytes;
-};
-
-// small: the plan of a call whose workspace is too small for the one it would get otherwise (fewer partials).
-int proj_plan(const gla_proj_params* p, int sum_groups, bool small, ProjPlan* plan) {
-  if (!p || p->rows < 0 || p->groups < 1 || p->n < 1 || p->k < 1) return GLA_ERR_INVALID_ARG;
-  if (p->c_dtype != GLA_OUT_BF16 && p->c_dtype != GLA_OUT_FP32) return GLA_ERR_INVALID_ARG;
-  if ((int64_t)p->rows * p->groups * p->n > (int64_t)0x7fffffff) return GLA_ERR_INVALID_ARG;
-  // what the kernel assumes: whole steps of 64 input features, whole waves of 32 output features, 16-byte loads
-  if (p->k % 64 || p->n % 32) return GLA_ERR_UNSUPPORTED_SHAPE;
-  if (p->a_row_stride % 8 || p->a_group_stride % 8 || p->c_row_stride % 4 || p->c_group_stride % 4)
-    return GLA_ERR_UNSUPPORTED_SHAPE;
-  const int cus = device_cu_count();
-  // Rows per workgroup.  Beyond 64 rows the long sums below take 128, so that up to 128 rows read the weights once
-  // and not twice (100 rows of the benchmark shape: 116.3 -> 76.5 us with the streaming hint, 32 heads 34.9 -> 30.4); in the kernel
-  // for short sums more rows would cost the second workgroup per compute unit.
-  const int mt_long = p->rows <= 32 ? 1 : p->rows <= 64 || small ? 2 : 4;
-  plan->mt = std::min(mt_long, 2);
-  // Long sums (the output projection): 64 output features per wave, i.e. 256 per workgroup, and as many
-  // ranges per group as give one workgroup per compute unit in a single round (its ring of three 40 KB
-  // stages fills the LDS).  Against 32 features per wave that halves the re-reads of the query rows (every
-  // workgroup fetches its range of them: rows x k x 2 bytes per 128 or 256 output features) and needs
-  // fewer partial results (output projection of the benchmark shape: 240 workgroups, 93 -> 74 us).
-  // Taken when such a grid covers at least three quarters of the compute units; ranges of at least 512
-  // features, of ceil(steps / ranges) steps of 64 each, the last one shorter.
-  int ks = 1;
-  plan->nt = 1;
-  plan->k_per_split = p->k;
-  {
-    const int64_t base = (int64_t)((p->n + 255) / 256) * ((p->rows + 32 * mt_long - 1) / (32 * mt_long)) * p->groups;
-    const int64_t want = std::min<int64_t>(std::max(1, p->k / 512), cus / std::max<int64_t>(1, base));
-    if (want >= 1 && base * want * 4 >= (int64_t)cus * 3) {
-      const int steps = p->k / 64, per = (int)((steps + want - 1) / want);
-      plan->nt = 2;
-      plan->mt = mt_long;
-      ks = (steps + per - 1) / per;  // (no empty range)
-      plan->k_per_split = per * 64;
-    }
-  }
-  const int64_t row_tiles = (p->rows + 32 * plan->mt - 1) / (32 * plan->mt);
-  if (plan->nt == 1) {
-    const int64_t tiles = (int64_t)((p->n + 127) / 128) * row_tiles;
-    // Ranges per group: the grid runs in rounds of as many workgroups as there are compute units.  Among
-    // the cuts into ranges of at least 512 features pick the one with the least estimated time: rounds x
-    // (steps per range + a fixed cost per workgroup of about four steps: start-up latency, partial store).
-    double best = 1e30;
-    for (int c = 1; c <= 64 && p->k / c >= 512 && (p->k / c) % 64 == 0; c *= 2) {
-      const int64_t wgs = tiles * p->groups * c;
-      const double t = (double)((wgs + cus - 1) / cus) * (p->k / c / 64 + 4);
-      if (t < best * 0.999) { best = t; ks = c; }
-    }
-    plan->k_per_split = p->k / ks;
-  }
-  plan->ksplit = ks;
-  // Weights read once, by one row tile, that could not stay in the last-level cache for the next step beside anything
-  // else: their lines then do not displace query rows and partials (335 MB 74.6 -> 66.9 us, 671 MB 153.5 -> 134.8, 168 MB
-  // 42.8 -> 38.1).  Smaller ones may still be there (84 MB 19.1 -> 21.2 with the hint), and with two row tiles the second
-  // reader finds less (115.7 -> 130.0).
-  plan->stream = plan->nt == 2 && row_tiles == 1 && (int64_t)p->groups * p->n * p->k * 2 > kLastLevelCacheBytes / 2;
-  plan->direct = ks == 1 && (!sum_groups || p->groups == 1);
-  plan->part_bytes = plan->direct ? 0 : (size_t)p->groups * ks * p->rows * p->n * sizeof(float);
-  return GLA_OK;
-}
-
 template <int MT>
 void launch_proj_long(bool stream, dim3 grid, hipStream_t st, const ProjParams& d) {
   if (stream) hipLaunchKernelGGL((proj_kernel<MT, 2, true>), grid, dim3(256), 0, st, d);
@@ -563,8 +493,9 @@ void launch_proj_long(bool stream, dim3 grid, hipStream_t st, const ProjParams& 
 
 int run_proj(const gla_proj_params* p, int sum_groups) {
   ProjPlan plan;
-  int rc = proj_plan(p, sum_groups, false, &plan);
-  if (rc == GLA_OK && plan.part_bytes > p->workspace_bytes) rc = proj_plan(p, sum_groups, true, &plan);
+  int rc = proj_plan(p, sum_groups, device_cu_count(), 0, &plan);
+  for (int small = 1; small <= 2 && rc == GLA_OK && plan.part_bytes > p->workspace_bytes; ++small)
+    rc = proj_plan(p, sum_groups, device_cu_count(), small, &plan);
   if (rc != GLA_OK) return rc;
   if (p->rows == 0) return GLA_OK;
   if (!p->a || !p->w || !p->c) return GLA_ERR_INVALID_ARG;
@@ -695,9 +626,7 @@ int gla_absorb_query(const gla_proj_params* p) { return gla::run_proj(p, 0); }
 int gla_output_proj(const gla_proj_params* p) { return gla::run_proj(p, 1); }
 
 size_t gla_proj_workspace_size(const gla_proj_params* p, int sum_groups) {
-  gla::ProjPlan plan;
-  if (gla::proj_plan(p, sum_groups, false, &plan) != GLA_OK) return 0;
-  return std::max<size_t>(plan.part_bytes, 256);
+  return gla::proj_workspace(p, sum_groups, gla::device_cu_count());
 }
 
 int gla_decode_select_impl(const gla_decode_params* p, int is_gta) {

@@ -1,0 +1,131 @@
+// Host side of the two projections (proj_kernels.hpp): which kernel a call runs and how its sums are cut.  Needs no GPU
+// headers: the number of compute units is an argument.
+#pragma once
+
+#include <algorithm>
+#include <cstddef>
+#include <cstdint>
+
+#include "../../include/gla_decode.h"
+
+namespace gla {
+
+struct ProjPlan {
+  int mt;          // 32-row blocks of query rows per workgroup (1, 2 or 4)
+  int nt;          // 32-row blocks of output features per wave (1 or 2)
+  int ksplit;      // ranges the input features of a group are cut into
+  int k_per_split;
+  bool direct;     // no partials: the kernel writes the result itself
+  bool stream;     // fetch the weights with the streaming hint
+  size_t part_bytes;
+};
+
+// Weights that the last-level cache cannot hold (256 MB).
+constexpr int64_t kProjCacheBytes = 256ll << 20;
+
+// The cut of the kernel with 64 output features per wave (256 per workgroup) and 32 * mt rows: as many ranges per group as
+// give one workgroup per compute unit in a single round (its ring of three stages of 40 or 48 KB fills the LDS), of at least
+// 512 features, of ceil(steps / ranges) steps of 64 each, the last one shorter.  Against 32 features per wave that halves the
+// re-reads of the query rows (every workgroup fetches its range of them: rows x k x 2 bytes per 128 or 256 output features)
+// and needs fewer partial results (output projection of the benchmark shape: 240 workgroups, 93 -> 74 us).  False where such
+// a grid covers less than three quarters of the compute units.
+inline bool proj_cut_64(const gla_proj_params* p, int mt, int cus, int* ranges, int* per_range) {
+  const int64_t base = (int64_t)((p->n + 255) / 256) * ((p->rows + 32 * mt - 1) / (32 * mt)) * p->groups;
+  const int64_t want = std::min<int64_t>(std::max(1, p->k / 512), cus / std::max<int64_t>(1, base));
+  if (want < 1 || base * want * 4 < (int64_t)cus * 3) return false;
+  const int steps = p->k / 64, per = (int)((steps + want - 1) / want);
+  *ranges = (steps + per - 1) / per;  // (no empty range)
+  *per_range = per * 64;
+  return true;
+}
+
+// small: the plan of a call whose workspace is too small for the one it would get otherwise.  1: no more than 64 rows per
+// workgroup, which takes fewer partials; 2: beyond 64 rows, 32 output features per wave besides.
+inline int proj_plan(const gla_proj_params* p, int sum_groups, int cus, int small, ProjPlan* plan) {
+  if (!p || p->rows < 0 || p->groups < 1 || p->n < 1 || p->k < 1) return GLA_ERR_INVALID_ARG;
+  if (p->c_dtype != GLA_OUT_BF16 && p->c_dtype != GLA_OUT_FP32) return GLA_ERR_INVALID_ARG;
+  if ((int64_t)p->rows * p->groups * p->n > (int64_t)0x7fffffff) return GLA_ERR_INVALID_ARG;
+  // what the kernel assumes: whole steps of 64 input features, whole waves of 32 output features, 16-byte loads
+  if (p->k % 64 || p->n % 32) return GLA_ERR_UNSUPPORTED_SHAPE;
+  if (p->a_row_stride % 8 || p->a_group_stride % 8 || p->c_row_stride % 4 || p->c_group_stride % 4)
+    return GLA_ERR_UNSUPPORTED_SHAPE;
+  const int64_t weights = (int64_t)p->groups * p->n * p->k * 2;
+  const int tiles64 = (p->rows + 63) / 64, tiles128 = (p->rows + 127) / 128;
+  const int mt = p->rows <= 32 ? 1 : 2;
+  int ks = 1, per = p->k;
+  plan->mt = mt;
+  plan->nt = 1;
+  if (p->rows <= 64 || small) {
+    if ((p->rows <= 64 || small < 2) && proj_cut_64(p, mt, cus, &ks, &per)) plan->nt = 2;
+  } else {
+    // More than 64 rows.  128 rows per workgroup halve the passes over the weights (two latent heads x 5120 x 16384, 100
+    // rows: 115 us with 64 rows per workgroup, 72 with 128; 128 heads x 512 x 128, 100 rows: 16.1 -> 12.7), but double the
+    // partials per range and compute what pads the last 128 rows.  Taken
+    //   up to 128 rows, but weights of less than 128 MB only where the number of blocks of 256 features is no multiple of
+    //   eight: else the workgroups of the two 64-row tiles run on one XCD and share the weights through its L2 (2 x 5120 x 4096,
+    //   65 rows: 34.2 -> 28.0, 3 x 1024 x 10752 33.3 -> 29.4; 2 x 2048 x 8192 24.2 -> 27.1, 6144 x 8192 30.2 -> 31.5);
+    //   for sums of one range (and more than 128 output features, else half a workgroup has nothing to do) up to 256 rows,
+    //   where 64 rows would pad about as much (128 heads x 256 x 128: 200 rows 15.3 -> 13.1, 160 rows 11.8 -> 13.1; 32 heads x 512
+    //   x 128: 300 rows 9.0 -> 10.6);
+    //   for longer sums beyond 128 rows in ranges of at least 1280 features where 64 rows would pad about as much, or where the
+    //   weights are as large as the last-level cache (2 x 5120 x 8192: 256 rows 88 -> 73; 1 x 5120 x 4096, ranges of 704: 256 rows
+    //   28.0 -> 31.1, 129 rows 23.8 -> 28.5; 2 x 8192 x 8192: 129 rows 107 -> 92).
+    const bool single = p->k < 1024, as_full = 20 * tiles64 >= 36 * tiles128;  // (nine tenths of the 128-row tiles' halves have rows)
+    int ranges, features;
+    const bool cut4 = proj_cut_64(p, 4, cus, &ranges, &features);
+    bool rows4;
+    if (single) rows4 = as_full && p->rows <= 256 && p->n > 128;
+    else if (p->rows <= 128) rows4 = (p->n + 255) / 256 % 8 != 0 || weights >= kProjCacheBytes / 2;
+    else rows4 = features >= 1280 && (as_full || weights >= kProjCacheBytes);
+    // Else 64 rows with 64 features per wave, but not in short ranges (1 x 2048 x 8192, 65 rows, ranges of 512: 17.8 us, 15.7
+    // with 32 features per wave; 1 x 5120 x 4096, of 704: 22.3, 21.5; 129 rows, of 1024: 23.8, 22.1, 2 x 2048 x 8192, of 1664: 31.8,
+    // 32.4) nor, beyond 128 rows, where 128 rows per workgroup do not fill the chip (4 x 5120 x 8192, 167 rows 126, 117); for sums
+    // of one range only with one block of 256 features per group, up to 128 rows (100 rows of 128 heads x 256 x 128 8.8, 9.3,
+    // of 64 x 512 x 128 9.1, 8.7, 122 rows of 128 x 128 x 192 6.7, 5.7; 64 heads x 256 x 128, 200 rows 8.6, 8.0).
+    if (cut4 && rows4) {
+      plan->mt = 4;
+      plan->nt = 2;
+    } else {
+      const bool rows2 = single ? p->rows <= 128 && p->n > 128 && p->n <= 256 : cut4 || p->rows <= 128;
+      if (rows2 && proj_cut_64(p, 2, cus, &ranges, &features) && (single || features >= (p->rows <= 128 ? 768 : 1152))) plan->nt = 2;
+    }
+    if (plan->nt == 2) {
+      ks = ranges;
+      per = features;
+    }
+  }
+  plan->k_per_split = per;
+  const int64_t row_tiles = (p->rows + 32 * plan->mt - 1) / (32 * plan->mt);
+  if (plan->nt == 1) {
+    const int64_t tiles = (int64_t)((p->n + 127) / 128) * row_tiles;
+    // Ranges per group: the grid runs in rounds of as many workgroups as there are compute units.  Among
+    // the cuts into ranges of at least 512 features pick the one with the least estimated time: rounds x
+    // (steps per range + a fixed cost per workgroup of about four steps: start-up latency, partial store).
+    double best = 1e30;
+    for (int c = 1; c <= 64 && p->k / c >= 512 && (p->k / c) % 64 == 0; c *= 2) {
+      const int64_t wgs = tiles * p->groups * c;
+      const double t = (double)((wgs + cus - 1) / cus) * (p->k / c / 64 + 4);
+      if (t < best * 0.999) { best = t; ks = c; }
+    }
+    plan->k_per_split = p->k / ks;
+  }
+  plan->ksplit = ks;
+  // Weights read once, by one row tile, that would take more than half of the last-level cache and are not there any more
+  // at the next step, after everything else a decode step reads: their lines then do not displace query rows and partials
+  // (335 MB 74.6 -> 66.9 us, 671 MB 153.5 -> 134.8, 201 MB 48.2 -> 45.8, 168 MB 42.4 -> 40.4).  A program that does nothing else
+  // between two calls with the same weights loses by it where the cache can hold them (201 MB 40.7 -> 45.7, 168 MB 37.1 -> 41.7,
+  // 268 MB 55 -> 79).  Smaller ones may still be there (84 MB 19.1 -> 21.2), and with two row tiles the second reader finds
+  // less (115.7 -> 130.0).
+  plan->stream = plan->nt == 2 && row_tiles == 1 && weights > kProjCacheBytes / 2;
+  plan->direct = ks == 1 && (!sum_groups || p->groups == 1);
+  plan->part_bytes = plan->direct ? 0 : (size_t)p->groups * ks * p->rows * p->n * sizeof(float);
+  return GLA_OK;
+}
+
+inline size_t proj_workspace(const gla_proj_params* p, int sum_groups, int cus) {
+  ProjPlan plan;
+  if (proj_plan(p, sum_groups, cus, 0, &plan) != GLA_OK) return 0;
+  return std::max<size_t>(plan.part_bytes, 256);
+}
+
+}  // namespace gla

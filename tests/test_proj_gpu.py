@@ -1,6 +1,8 @@
 """GPU parity of the two projections around the attention (absorbed query,
 grouped output projection) against the CPU oracle, and the whole absorbed block
 raw queries -> absorb -> decode -> output projection end to end."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -28,12 +30,13 @@ def check_projection(c, ref, abs_prod, *, bf16_out, what):
 
 
 @pytest.mark.parametrize("M,G,N,K", [(1, 3, 32, 64), (33, 5, 96, 192), (64, 128, 256, 128), (128, 16, 512, 128), (70, 1, 4096, 1024),
-                                     (64, 8, 1056, 6208)])
+                                     (64, 8, 1056, 6208), (66, 128, 512, 192), (100, 128, 512, 128), (193, 128, 256, 128)])
 def test_absorb_query_against_oracle(M, G, N, K):
     """(64, 128, 256, 128) is the benchmark workload's shape: 64 rows, 128 heads, d_c 256, d_h 128;
     (70, 1, 4096, 1024): one merged weight from a hidden vector, input features cut into ranges;
     (64, 8, 1056, 6208): long sums per group, which take the variant with 64 output features per wave
-    (the last wave's second block of 32 does not exist) and ranges of unequal length."""
+    (the last wave's second block of 32 does not exist) and ranges of unequal length; the last three take up to 128 rows per
+    workgroup: almost two empty blocks of 32, a last one of four rows, a second row tile of 65."""
     g = torch.Generator().manual_seed(700 + M)
     a = torch.randn(M, G, K, generator=g).to(torch.bfloat16)
     w = (torch.randn(G, N, K, generator=g) / K ** 0.5).to(torch.bfloat16)
@@ -70,11 +73,13 @@ def test_output_proj_against_oracle(M, G, N, K):
         check_projection(c.double().cpu().numpy(), ref, abs_prod, bf16_out=dt == torch.bfloat16, what=f"out-proj {M}x{G}x{N}x{K} {dt}")
 
 
-@pytest.mark.parametrize("M,G,N,K", [(65, 2, 1632, 6208), (97, 1, 5120, 16384), (128, 3, 1056, 12352), (129, 2, 2048, 8192)])
+@pytest.mark.parametrize("M,G,N,K", [(65, 2, 1632, 6208), (65, 2, 1792, 8192), (97, 1, 5120, 16384), (128, 3, 1056, 12352), (193, 1, 2560, 16384),
+                                     (129, 2, 2048, 8192)])
 def test_output_proj_of_more_than_64_rows(M, G, N, K):
-    """Long sums take up to 128 rows per workgroup: one row past 64, a last block of one row, full tiles, one row past 128;
-    (97, 1, 5120, 16384) has weights that are fetched with the streaming hint.  A workspace with room for the partials of
-    64 rows per workgroup only is still accepted."""
+    """Long sums take up to 128 rows per workgroup: (65, 2, 1792, 8192) with one row past 64, a last block of one row, full
+    tiles, and a second row tile of 65; (97, 1, 5120, 16384) has weights that are fetched with the streaming hint.  The first
+    and the last stay with 64 rows.  A workspace with room for the partials of 64 rows per workgroup only is still accepted,
+    and is smaller than what 128 rows take."""
     g = torch.Generator().manual_seed(820 + M)
     a = (torch.randn(M, G, K, generator=g) * 0.05).to(torch.bfloat16)
     w = projection_weights(G, N, K, seed=821 + M)
@@ -84,6 +89,10 @@ def test_output_proj_of_more_than_64_rows(M, G, N, K):
     # 64 rows per workgroup: about one workgroup per compute unit over n blocks, row blocks, groups and ranges
     base = (N + 255) // 256 * ((M + 63) // 64) * G
     slices = G * max(1, torch.cuda.get_device_properties(0).multi_processor_count // base)
+    if (M, N) not in ((65, 1632), (129, 2048)):
+        prm = gla.GlaProjParams()
+        prm.rows, prm.groups, prm.n, prm.k = M, G, N, K
+        assert gla.binding.load_library().gla_proj_workspace_size(ctypes.byref(prm), 1) > slices * M * N * 4
     for dt, ws in ((torch.float32, None), (torch.bfloat16, None), (torch.float32, slices * M * N * 4)):
         ws = None if ws is None else torch.empty(ws, dtype=torch.uint8, device="cuda")
         c = gla.gla_output_proj(ad, wd, out_dtype=dt, workspace=ws)
