@@ -61,8 +61,11 @@ struct DevParams {
   // generic kernel: uniform split of every sequence's page range
   int32_t splits, pages_per_split;
   // generic MFMA kernel: the split in tokens or, where the caller left it to the library, 0 and the number of ranges
-  // allowed while the grid is small (range_tokens); divisors (page size, 16-byte chunks of a row in LDS)
-  int32_t split_tokens, small_ranges;
+  // allowed while the grid is small, for sequences of up to 4096 tokens and longer ones (range_tokens); divisors (page size,
+  // 16-byte chunks of a row in LDS)
+  int32_t split_tokens, small_ranges, small_ranges_longer;
+  // ... tiles its LDS holds; workgroups that run side by side, ranges that fill one round of them (range_tokens)
+  int32_t ring_stages, resident, one_round;
   FastDiv fd_page, fd_cpr;
   int64_t stream_min_bytes; // second MFMA kernel: a batch with more cache bytes than this is fetched with the streaming hint
   int32_t flex_rb;          // flex kernel: blocks of 16 query rows per group

@@ -27,16 +27,24 @@ namespace gla {
 
 // Tokens per range, for every sequence the same: the caller's, else the batch's longest sequence in ranges of at least
 // 256 tokens (a partial costs as much as a few tiles: 18 units of up to 4500 tokens take 39 us in 17 ranges, 46 in 28),
-// of at least 64 while the grid is small (2 units of 256 tokens: 19 us in four ranges, 49 in one).  By the lengths
+// of at least 64 while the grid is small (2 units of 256 tokens: 19 us in four ranges, 49 in one).  In no more ranges than
+// run side by side, if they would fill a second round less than the first (one_round, launch_generic_mfma) and the sequences
+// are so much alike that they would run in two: GLA-2 32 x 3000 tokens 70 -> 59 us, MLA shape 16 x 4000 125 -> 104.  By the lengths
 // and not by the page table's row length, which is all the host knows: in a table for the longest context every sequence
 // would lie in its first range (nine sequences of up to 4500 tokens, table for 72000: 213 us, 41 this way).
-// (len: the length of sequence `lane`, loaded ahead)
-__device__ __forceinline__ int range_tokens(const DevParams& p, int lane, int len) {
+// (len: the length of sequence `lane`, loaded ahead; per_seq: workgroups per sequence and range)
+__device__ __forceinline__ int range_tokens(const DevParams& p, int lane, int len, int per_seq) {
   if (p.split_tokens > 0) return p.split_tokens;
   int longest = len;
   for (int i = lane + 64; i < p.B; i += 64) longest = max(longest, p.seq_lens[i]);
   longest = wave_max(max(longest, 1));
-  const int n = max(1, min(p.splits, max((longest + 255) >> 8, min((longest + 63) >> 6, p.small_ranges))));
+  int n = max(1, min(p.splits, max((longest + 255) >> 8, min((longest + 63) >> 6, longest <= 4096 ? p.small_ranges : p.small_ranges_longer))));
+  if (n > p.one_round) {
+    const float inv = (float)n / (float)longest;
+    float held = ceilf((float)max(len, 0) * inv);  // ranges that hold tokens
+    for (int i = lane + 64; i < p.B; i += 64) held += ceilf((float)max(p.seq_lens[i], 0) * inv);
+    if (wave_sum(held) * (float)per_seq > (float)p.resident) n = p.one_round;
+  }
   return ((longest + n - 1) / n + 31) & ~31;
 }
 
@@ -57,24 +65,23 @@ __device__ __forceinline__ void wait_vmcnt_at_most(int n) {
   else wait_vmcnt<0>();
 }
 
-// Waves that share a 16-row slab (each takes every WS-th 32 tokens of a tile) and LDS, for up to four stages.
-template <int DVB, int WR, bool SEPK>
-struct GenericTraits {
-  static constexpr int kMaxChunks = (SEPK ? 2 * DVB / 8 : (DVB + 128) / 8) | 1;  // 16-byte chunks per row in LDS (RoPE keys of up to 128 dims)
-  static constexpr int kSub = 32 * kMaxChunks * 16;                               // 32 tokens
-  static constexpr int kMaxWaves = DVB > 256 ? 4 : 8;  // (512 dims: a wave needs more than 256 registers)
-  static constexpr int WS = WR * 4 <= kMaxWaves && kSub * 8 <= 160 * 1024 ? 4 : WR * 2 <= kMaxWaves && kSub * 4 <= 160 * 1024 ? 2 : 1;
-  static constexpr int kSmem = kSub * WS * 4 <= 160 * 1024 ? kSub * WS * 4 : 160 * 1024;
-  static constexpr int kThreads = 64 * WR * WS;
-  static_assert(2 * WS * kSub <= kSmem && WR * (WS - 1) * 64 * (DVB + 8) <= kSmem, "LDS capacity");
-};
+// Waves that share a 16-row slab (each takes every WS-th 32 tokens of a tile), at most: as many as registers allow (512
+// dims: a wave needs more than 256) and two ring stages leave room for.  Rows of up to dvb dims, RoPE keys of up to 128.
+constexpr int generic_chunks(int dvb, bool sepk) { return (sepk ? 2 * dvb / 8 : (dvb + 128) / 8) | 1; }  // 16-byte chunks per row in LDS
+constexpr int generic_max_waves(int dvb) { return dvb > 256 ? 4 : 8; }
+constexpr int generic_ws(int dvb, int wr, bool sepk) {
+  const int block = 32 * generic_chunks(dvb, sepk) * 16;  // 32 tokens
+  return wr * 4 <= generic_max_waves(dvb) && block * 8 <= 160 * 1024 ? 4 : wr * 2 <= generic_max_waves(dvb) && block * 4 <= 160 * 1024 ? 2 : 1;
+}
+// LDS where the waves of a slab meet
+constexpr int generic_meet_bytes(int dvb, int wr, int ws) { return wr * (ws - 1) * 64 * (dvb + 8); }
 
-template <int DVB, int WR, bool SEPK>
-__global__ __launch_bounds__((GenericTraits<DVB, WR, SEPK>::kThreads)) void generic_mfma_kernel(DevParams p) {
-  using GT = GenericTraits<DVB, WR, SEPK>;
-  constexpr int WS = GT::WS, NW = WR * WS, STEP = 32 * WS;
+template <int DVB, int WR, int WS, bool SEPK>
+__global__ __launch_bounds__(64 * WR * WS) void generic_mfma_kernel(DevParams p) {
+  static_assert(2 * WS * 32 * generic_chunks(DVB, SEPK) * 16 <= 160 * 1024 && generic_meet_bytes(DVB, WR, WS) <= 160 * 1024, "LDS capacity");
+  constexpr int NW = WR * WS, STEP = 32 * WS;
   constexpr int NDB = DVB / 16, NKN = DVB / 32, NKR = SEPK ? 0 : 4;
-  __shared__ __attribute__((aligned(1024))) unsigned char smem[GT::kSmem];
+  extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];  // (ring, then where the waves of a slab meet)
   const unsigned lds_base = (unsigned)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem;
   const int lane = threadIdx.x & 63, wave = uniform((int)threadIdx.x >> 6);
   const int r16 = lane & 15, q = lane >> 4;
@@ -101,7 +108,7 @@ __global__ __launch_bounds__((GenericTraits<DVB, WR, SEPK>::kThreads)) void gene
   // own plus a constant)
   const int pitch = (cpr | 1) * 16;
   const int tile_bytes = STEP * pitch;
-  const int nst = min(4, GT::kSmem / tile_bytes);  // ring stages (two at least)
+  const int nst = p.ring_stages;  // (two at least)
 
   // ---- queries (B operand): dims beyond the real ones are zero, whatever the key operand holds there
   u32x4_t qn[NKN], qr[NKR > 0 ? NKR : 1];
@@ -116,7 +123,7 @@ __global__ __launch_bounds__((GenericTraits<DVB, WR, SEPK>::kThreads)) void gene
     }
   }
   // ---- this range (behind the loads of the queries, which need no lengths)
-  const int span = p.splits == 1 ? 1 << 30 : range_tokens(p, lane, len_lane);
+  const int span = p.splits == 1 ? 1 << 30 : range_tokens(p, lane, len_lane, p.h_c * blocks);
   const int j_begin = (int)min((int64_t)split * span, (int64_t)max(L, 0));
   const int j_end = (int)min((int64_t)j_begin + span, (int64_t)max(L, 0));
   if (p.splits > 1 && j_begin >= j_end) {  // nothing here: the merge needs no values
@@ -136,10 +143,13 @@ __global__ __launch_bounds__((GenericTraits<DVB, WR, SEPK>::kThreads)) void gene
   //      costs pages of one token the depth of the ring.
   constexpr int NWIN = STEP > 64 ? 2 : 1;
   int win0 = 0, win1 = 0, win_page = -0x40000000;
-  const int n_slots = STEP * (cpr | 1), n_inst = (n_slots + 63) >> 6;
-  const int n_mine = uniform((n_inst - wave + NW - 1) / NW);  // load instructions of this wave per tile
+  //      Of the last tile of a range only the 32-token blocks are fetched that hold tokens of it.
+  auto tile_rows = [&](int tok0) { return min(STEP, (j_end - tok0 + 31) & ~31); };
+  auto loads_of = [&](int rows) { return uniform((((rows * (cpr | 1) + 63) >> 6) - wave + NW - 1) / NW); };  // this wave's load instructions
+  const int n_mine = loads_of(STEP);
   auto load_tile = [&](int tok0, int stage) {
-    const int first_page = (int)fast_div((unsigned)tok0, p.fd_page), last_page = (int)fast_div((unsigned)min(tok0 + STEP - 1, L - 1), p.fd_page);
+    const int rows = tile_rows(tok0), n_slots = rows * (cpr | 1), n_inst = (n_slots + 63) >> 6;
+    const int first_page = (int)fast_div((unsigned)tok0, p.fd_page), last_page = (int)fast_div((unsigned)min(tok0 + rows - 1, L - 1), p.fd_page);
     if (uniform(last_page) >= uniform(win_page) + 64 * NWIN) {
       win_page = first_page;
       const int held = (int)fast_div((unsigned)(L - 1), p.fd_page);
@@ -179,17 +189,19 @@ __global__ __launch_bounds__((GenericTraits<DVB, WR, SEPK>::kThreads)) void gene
   if (j_begin < j_end) {
     const int n_tiles = (j_end - j_begin + STEP - 1) / STEP;
     for (int t = 0; t < min(nst - 1, n_tiles); ++t) load_tile(j_begin + t * STEP, t);
+    const int n_last = loads_of(tile_rows(j_begin + (n_tiles - 1) * STEP));
     int stage = 0;
     for (int tile = 0; tile < n_tiles; ++tile) {
       const int j = j_begin + tile * STEP;
-      wait_vmcnt_at_most(n_mine * min(n_tiles - 1 - tile, nst - 2));  // this wave's part of the tile ...
+      const int behind = n_tiles - 1 - tile;
+      wait_vmcnt_at_most(behind > nst - 2 ? n_mine * (nst - 2) : behind > 0 ? n_mine * (behind - 1) + n_last : 0);  // this wave's part of the tile ...
       lds_barrier();  // ... and everybody's; nobody reads the stage of the tile before any more
       const unsigned off = (unsigned)(stage * tile_bytes);
       const int stage_load = stage == 0 ? nst - 1 : stage - 1;
       stage = stage == nst - 1 ? 0 : stage + 1;
       if (tile + nst - 1 < n_tiles) load_tile(j + (nst - 1) * STEP, stage_load);
       if (j + STEP > L) {  // rows past the end may hold anything: 0 x NaN must not leak (uniform over the workgroup)
-        for (int z = (L - j) * pitch + (int)threadIdx.x * 16; z < tile_bytes; z += 64 * NW * 16)
+        for (int z = (L - j) * pitch + (int)threadIdx.x * 16; z < tile_rows(j) * pitch; z += 64 * NW * 16)
           lds_write_b128<0>(lds_base + off + (unsigned)z, u32x4_t{0, 0, 0, 0});
         lds_barrier();
       }

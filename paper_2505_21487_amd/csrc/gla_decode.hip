@@ -144,11 +144,43 @@ int64_t generic_units(const gla_decode_params* p) {
   return std::max<int64_t>(1, (int64_t)p->batch * p->num_groups * (((int64_t)p->num_q_heads / p->num_groups * p->q_len + 63) / 64));
 }
 
-// Workgroups up to which the generic MFMA kernel's ranges may be shorter than 256 tokens (64 at least): two thirds of the
-// compute units.  us per call with a quarter / half / three quarters / all of them / twice as many: MLA shape 4 sequences
-// of 200 to 2500 tokens 59.0 / 39.8 / 36.2 / 33.1 / 33.1, GLA-2 2 x up to 5000 at two positions 28.4 / 23.4 / 23.2 / 21.2 /
-// 21.2, 9 x up to 4500 31.2 up to all and 46.5 with twice as many.
-int64_t small_grid() { return device_cu_count() * 2 / 3; }
+// The generic MFMA kernel's shape for a call.
+struct GenericPlan {
+  int dvb, wr;      // dims and 16-row slabs per workgroup of the instantiation
+  int ws;           // waves per slab
+  bool half;        // half as many as fit: two workgroups and more per compute unit then
+  int tile, meet;   // LDS bytes of a ring stage, and where the waves of a slab meet
+  int per_cu;       // workgroups that a compute unit holds with two stages each (one or two)
+};
+GenericPlan generic_plan(const gla_decode_params* p, bool sepk) {
+  GenericPlan g;
+  const int dmax = std::max(p->d_v, p->d_nope), rows_group = p->num_q_heads / p->num_groups * p->q_len, cus = device_cu_count();
+  g.dvb = dmax <= 128 ? 128 : dmax <= 256 ? 256 : 512;
+  // as many slabs as the rows of a group fill, at most four
+  g.wr = rows_group <= 16 ? 1 : rows_group <= 32 ? 2 : 4;
+  g.ws = generic_ws(g.dvb, g.wr, sepk);
+  // (short sequences that fill the chip as they are have no work for more waves: GTA-4 d_h 128, three positions, 77 x 23 tokens
+  // 12.5 -> 7.4 us, GQA-4 87 x 1 to 52 13.7 -> 9.2; 64 x 4000 149 -> 154)
+  g.half = g.ws > 1 && generic_units(p) >= cus && (int64_t)p->max_pages_per_seq * p->page_size <= 512;
+  if (g.half) g.ws /= 2;
+  const int cpr = p->d_v / 8 + (sepk ? p->d_nope : p->d_rope) / 8;
+  g.tile = 32 * g.ws * (cpr | 1) * 16;
+  g.meet = generic_meet_bytes(g.dvb, g.wr, g.ws);
+  g.per_cu = std::max(2 * g.tile, g.meet) <= 80 * 1024 && 2 * g.wr * g.ws <= generic_max_waves(g.dvb) ? 2 : 1;
+  return g;
+}
+
+// Ranges of fewer than 256 tokens (64 at least) that a sequence may fall into: as many as keep the grid within the compute
+// units; where that would be less than four (a second range then gains little, and merging costs short sequences in a wide
+// table more), or beyond 4096 tokens (longer: ranges of 256 are many already), within two thirds of them.  us per call with two
+// thirds / all: GLA-2 9 x 2500 tokens 29.6 / 26.7, MLA shape 4 of 722 to 1922 36.4 / 33.7; 120 units of 29 tokens in a table for 128
+// 9.9 / 19.1.  With a quarter / half / three quarters / all / twice as many: MLA shape 4 of 200 to 2500 59.0 / 39.8 / 36.2 / 33.1 /
+// 33.1, GLA-2 2 x up to 5000 at two positions 28.4 / 23.4 / 23.2 / 21.2 / 21.2, 9 x up to 4500 31.2 up to all and 46.5 with twice
+// as many.
+int64_t small_ranges(int64_t units, bool longer) {
+  const int64_t cus = device_cu_count();
+  return cus / units >= 4 && !longer ? cus / units : cus * 2 / 3 / units;
+}
 
 // Ranges of the generic route.  The scalar kernel has one wave per row and range: about 4096 of them.
 int scalar_splits(const gla_decode_params* p) {
@@ -167,7 +199,10 @@ int mfma_splits(const gla_decode_params* p) {
   const int64_t rows = std::max<int64_t>(1, (int64_t)p->batch * p->q_len * p->num_q_heads);
   const int64_t units = generic_units(p), tokens = (int64_t)p->max_pages_per_seq * p->page_size;
   int64_t want = (2 * (int64_t)device_cu_count() + units - 1) / units;
-  want = std::min(want, std::max((tokens + 255) / 256, std::min((tokens + 63) / 64, small_grid() / units)));
+  want = std::min(want, std::max((tokens + 255) / 256, std::min((tokens + 63) / 64, small_ranges(units, false))));
+  // (not within one tile, and with many rows not for a second range of 64 tokens, which costs more in the merge: GLA-2 42 x 4
+  // to 59 tokens in a table for 128 20.3 us, 11.7 in one; MLA shape with 16 heads, 75 x 8 to 80, 32 us, 37 in one)
+  if (tokens <= 32 * generic_plan(p, false).ws || (tokens <= 128 && rows > 2048)) want = 1;
   want = std::min<int64_t>(want, (64ll << 20) / std::max<int64_t>(1, rows * (p->d_v + 1) * 4));
   return (int)std::max<int64_t>(std::min<int64_t>(want, 64), 1);
 }
@@ -317,34 +352,46 @@ void fill_dev(const gla_decode_params* p, DevParams* d) {
   d->stream_min_bytes = kLastLevelCacheBytes;
 }
 
-template <int DVB, bool SEPK>
-void launch_generic_mfma_waves(int rows_group, int64_t units, int splits, hipStream_t st, const DevParams& d) {
-  // waves per workgroup (16 rows each): as many as the rows of a group fill, at most four
-  const int wr = rows_group <= 16 ? 1 : rows_group <= 32 ? 2 : 4;
-  const dim3 grid((unsigned)(units * ((rows_group + 16 * wr - 1) / (16 * wr))), (unsigned)splits);
-  if (wr == 1) hipLaunchKernelGGL((generic_mfma_kernel<DVB, 1, SEPK>), grid, dim3(GenericTraits<DVB, 1, SEPK>::kThreads), 0, st, d);
-  else if (wr == 2) hipLaunchKernelGGL((generic_mfma_kernel<DVB, 2, SEPK>), grid, dim3(GenericTraits<DVB, 2, SEPK>::kThreads), 0, st, d);
-  else hipLaunchKernelGGL((generic_mfma_kernel<DVB, 4, SEPK>), grid, dim3(GenericTraits<DVB, 4, SEPK>::kThreads), 0, st, d);
+template <int DVB, int WR, bool SEPK>
+void launch_generic_mfma_waves(const GenericPlan& g, dim3 grid, size_t lds, hipStream_t st, const DevParams& d) {
+  constexpr int WS = generic_ws(DVB, WR, SEPK), HALF = WS > 1 ? WS / 2 : 1;
+  if (g.half) hipLaunchKernelGGL((generic_mfma_kernel<DVB, WR, HALF, SEPK>), grid, dim3(64 * WR * HALF), lds, st, d);
+  else hipLaunchKernelGGL((generic_mfma_kernel<DVB, WR, WS, SEPK>), grid, dim3(64 * WR * WS), lds, st, d);
 }
 
+template <bool SEPK>
 void launch_generic_mfma(const gla_decode_params* p, DevParams& d, hipStream_t st) {
+  const GenericPlan g = generic_plan(p, SEPK);
   const int64_t tokens = (int64_t)p->max_pages_per_seq * p->page_size;
   if (p->num_splits > 0) d.split_tokens = (int32_t)(((tokens + d.splits - 1) / d.splits + 31) / 32 * 32);
-  else d.small_ranges = (int32_t)(small_grid() / generic_units(p));
+  d.small_ranges = (int32_t)small_ranges(generic_units(p), false);
+  d.small_ranges_longer = (int32_t)small_ranges(generic_units(p), true);
+  // One round instead of two (range_tokens): with one workgroup per compute unit, two ranges at least, and less than a tenth
+  // more of the chip busy in two (GQA-4 with 256 dims, 18 x 1353 to 2545 tokens, 72 units: seven ranges 100 us, three 128; 53 x
+  // up to 1061, 212 units: three 117, one 153).
+  const int64_t units = generic_units(p), cus = device_cu_count(), one = cus / units, two = 2 * cus / units;
+  d.resident = (int32_t)cus;
+  d.one_round = g.per_cu == 1 && one >= 2 && 10 * two <= 11 * 2 * one ? (int32_t)one : 1 << 20;
   d.fd_page = make_fastdiv((uint32_t)p->page_size);
-  const bool sepk = d.kstate != nullptr;
-  d.fd_cpr = make_fastdiv((uint32_t)(p->d_v / 8 + (sepk ? p->d_nope : p->d_rope) / 8) | 1u);
+  d.fd_cpr = make_fastdiv((uint32_t)(p->d_v / 8 + (SEPK ? p->d_nope : p->d_rope) / 8) | 1u);
   const int rows_group = p->num_q_heads / p->num_groups * p->q_len;
-  const int64_t units = (int64_t)p->batch * p->num_groups;
-  const int dmax = std::max(p->d_v, p->d_nope);
-  if (sepk) {
-    if (dmax <= 128) launch_generic_mfma_waves<128, true>(rows_group, units, d.splits, st, d);
-    else if (dmax <= 256) launch_generic_mfma_waves<256, true>(rows_group, units, d.splits, st, d);
-    else launch_generic_mfma_waves<512, true>(rows_group, units, d.splits, st, d);
-  } else {
-    if (dmax <= 128) launch_generic_mfma_waves<128, false>(rows_group, units, d.splits, st, d);
-    else if (dmax <= 256) launch_generic_mfma_waves<256, false>(rows_group, units, d.splits, st, d);
-    else launch_generic_mfma_waves<512, false>(rows_group, units, d.splits, st, d);
+  const dim3 grid((unsigned)((int64_t)p->batch * p->num_groups * ((rows_group + 16 * g.wr - 1) / (16 * g.wr))), (unsigned)d.splits);
+  // Ring: as deep as the LDS allows, four stages at most; but where the grid fills the chip and two workgroups fit into a
+  // compute unit, as deep as leaves room for both (MLA shape with 16 heads, one wave per workgroup, 16 x 8000 tokens 178 ->
+  // 106 us, GTA-4 d_h 64 64 x 4000 105 -> 63).  Half the waves: two stages.
+  const bool full = (int64_t)grid.x * grid.y > device_cu_count();
+  d.ring_stages = g.half ? 2 : std::min(4, (full && g.per_cu == 2 ? 80 : 160) * 1024 / g.tile);
+  const size_t lds = (size_t)std::max(d.ring_stages * g.tile, g.meet);
+  switch (g.dvb * 10 + g.wr) {
+    case 1281: launch_generic_mfma_waves<128, 1, SEPK>(g, grid, lds, st, d); break;
+    case 1282: launch_generic_mfma_waves<128, 2, SEPK>(g, grid, lds, st, d); break;
+    case 1284: launch_generic_mfma_waves<128, 4, SEPK>(g, grid, lds, st, d); break;
+    case 2561: launch_generic_mfma_waves<256, 1, SEPK>(g, grid, lds, st, d); break;
+    case 2562: launch_generic_mfma_waves<256, 2, SEPK>(g, grid, lds, st, d); break;
+    case 2564: launch_generic_mfma_waves<256, 4, SEPK>(g, grid, lds, st, d); break;
+    case 5121: launch_generic_mfma_waves<512, 1, SEPK>(g, grid, lds, st, d); break;
+    case 5122: launch_generic_mfma_waves<512, 2, SEPK>(g, grid, lds, st, d); break;
+    default: launch_generic_mfma_waves<512, 4, SEPK>(g, grid, lds, st, d); break;
   }
 }
 
@@ -361,7 +408,8 @@ int launch_generic(const gla_decode_params* p, const KeyCache* kc, bool lean, De
   dim3 grid((unsigned)rows, (unsigned)s), block(64);
   const int nv = (std::max(p->d_v, p->d_nope) + 63) / 64;
   if (ev) (void)hipEventRecord(ev[0], st);
-  if (mfma) launch_generic_mfma(p, d, st);
+  if (mfma && kc) launch_generic_mfma<true>(p, d, st);
+  else if (mfma) launch_generic_mfma<false>(p, d, st);
   else if (nv <= 2) hipLaunchKernelGGL(generic_main_kernel<2>, grid, block, 0, st, d);
   else if (nv <= 4) hipLaunchKernelGGL(generic_main_kernel<4>, grid, block, 0, st, d);
   else if (nv <= 8) hipLaunchKernelGGL(generic_main_kernel<8>, grid, block, 0, st, d);

@@ -38,8 +38,10 @@ CASES = {
 
 
 def _close(p, dp, **kw):
-    out, lse = run_gpu(p, dp=dp, impl=gla.GLA_IMPL_GENERIC, out_dtype=torch.float32, **kw)
-    ref_out, ref_lse = oracle.decode_problem(p)
+    _compare(*run_gpu(p, dp=dp, impl=gla.GLA_IMPL_GENERIC, out_dtype=torch.float32, **kw), *oracle.decode_problem(p))
+
+
+def _compare(out, lse, ref_out, ref_lse):
     none = np.isneginf(ref_lse)
     assert np.array_equal(np.isneginf(lse), none) and (out[none] == 0).all()
     assert np.abs(out - ref_out).max() <= 2e-5
@@ -77,6 +79,32 @@ def test_generic_mfma_ring(name):
     assert _name(p, dp) == "generic MFMA kernel"
     for splits in (1, 4):
         _close(p, dp, num_splits=splits)
+
+
+GRIDS = {
+    # name: (kind, h_q, h_c, d_v, T, page, lengths, unused table columns): automatic ranges on grids that fill the chip.  Short
+    # sequences in short tables (half the waves), ranges that run in one round or in two by the lengths, two workgroups per
+    # compute unit, last tiles that end in every block of 32 tokens
+    "gta_short": ("gta", 16, 4, 64, 1, 33, [1 + (7 * i) % 70 for i in range(66)], 0),
+    "gla256_short": ("gla", 32, 2, 256, 1, 48, [(11 * i) % 97 for i in range(130)], 1), "gqa128_short_three_positions": ("gqa", 8, 4, 128, 3, 3, [3 + (5 * i) % 131 for i in range(64)], 2),
+    "gqa256_short_two_slabs": ("gqa", 12, 2, 256, 4, 128, [4 + (13 * i) % 120 for i in range(128)], 2), "gta128_two_slabs": ("gta", 48, 2, 128, 1, 96, [(9 * i) % 333 for i in range(130)], 0),
+    "gla256_alike": ("gla", 64, 1, 256, 1, 128, [1300] * 61 + [0, 700, 1299], 0), "gla256_one_long": ("gla", 64, 1, 256, 1, 128, [40] * 60 + [0, 1300, 5, 1290], 0),
+    "mla_16_heads": ("gla", 16, 1, 512, 1, 128, [1500, 33, 0, 1217, 640] * 8, 2), "more_than_64_sequences": ("gla", 40, 1, 256, 1, 80, [900] * 70, 0),
+}
+
+
+@pytest.mark.parametrize("name", sorted(GRIDS))
+def test_generic_mfma_full_grids(name):
+    kind, h_q, h_c, d_v, T, page, lens, extra = GRIDS[name]
+    p = make_problem(name, kind=kind, seq_lens=lens, T=T, h_q=h_q, h_c=h_c, d_v=d_v, page_size=page, seed=9100 + len(name),
+                     num_pages=sum(n // page + 1 for n in lens) + 9, poison_tail=True, extra_table_cols=extra)
+    dp = DeviceProblem(p, poison_unused=True)
+    assert _name(p, dp) == "generic MFMA kernel"
+    some = sorted({0, 1, 2, p.B // 3, p.B // 2, p.B - 4, p.B - 3, p.B - 2, p.B - 1})
+    sel = [(b, t, h) for b in (range(p.B) if max(lens) < 400 else some) for t in range(T) for h in range(0, h_q, 5)]
+    out, lse = run_gpu(p, dp=dp, impl=gla.GLA_IMPL_GENERIC, out_dtype=torch.float32)
+    at = tuple(np.asarray(sel).T)
+    _compare(out[at], lse[at], *oracle.decode_problem(p, sel=sel))
 
 
 def _shifted(t, by):
