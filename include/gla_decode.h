@@ -190,7 +190,9 @@ size_t gla_decode_workspace_size(const gla_decode_params* p, int is_gta);
  * GLA_ERR_UNSUPPORTED_SHAPE).  When the input features are cut into ranges
  * (always for gla_output_proj with more than one group) fp32 partial sums go to
  * `workspace` (gla_proj_workspace_size bytes, 256-byte aligned) and are added
- * in a fixed order by a second kernel: results are reproducible bit for bit.
+ * in a fixed order by a second kernel: results are reproducible bit for bit
+ * (a workspace of fewer bytes than that may still do for a cut into fewer
+ * ranges, whose sums are rounded in other places).
  * Nothing is allocated, nothing synchronises. */
 typedef struct gla_proj_params {
   int32_t rows;             /* M = batch * q_len                                              */
@@ -213,7 +215,8 @@ typedef struct gla_proj_params {
 int gla_absorb_query(const gla_proj_params* p);
 int gla_output_proj(const gla_proj_params* p);
 /* Bytes of workspace (host only; pointer fields ignored); sum_groups = 0 for
- * gla_absorb_query, 1 for gla_output_proj.  0 for an invalid parameter set. */
+ * gla_absorb_query, 1 for gla_output_proj.  0 for an invalid parameter set.  The
+ * size for a number of rows serves every smaller one. */
 size_t gla_proj_workspace_size(const gla_proj_params* p, int sum_groups);
 
 /* Which implementation a call would run: GLA_IMPL_GENERIC or GLA_IMPL_TUNED,

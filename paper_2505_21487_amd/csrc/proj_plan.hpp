@@ -122,10 +122,17 @@ inline int proj_plan(const gla_proj_params* p, int sum_groups, int cus, int smal
   return GLA_OK;
 }
 
+// Never less than for fewer rows (a plan depends on the number of blocks of 32 rows only, and its partials grow with the
+// rows), so that a program may size its workspace once, for its largest batch.
 inline size_t proj_workspace(const gla_proj_params* p, int sum_groups, int cus) {
   ProjPlan plan;
   if (proj_plan(p, sum_groups, cus, 0, &plan) != GLA_OK) return 0;
-  return std::max<size_t>(plan.part_bytes, 256);
+  size_t need = std::max<size_t>(plan.part_bytes, 256);
+  if (!sum_groups && p->k < 1024) return need;  // (too short to be cut)
+  gla_proj_params fewer = *p;
+  for (fewer.rows = 32; fewer.rows < p->rows; fewer.rows += 32)
+    if (proj_plan(&fewer, sum_groups, cus, 0, &plan) == GLA_OK) need = std::max(need, plan.part_bytes);
+  return need;
 }
 
 }  // namespace gla

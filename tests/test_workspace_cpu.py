@@ -1,6 +1,8 @@
 """What the host decides from shapes alone.  Workspace sizes: a program may size its workspace once, for its largest
 batch, and keep it as requests come and go.  The eight-wave kernel: taken by the real lengths, not by how long the page
 table's rows are."""
+import ctypes
+
 import pytest
 
 import paper_2505_21487_amd as gla
@@ -77,3 +79,16 @@ def test_kernel_names():
     assert gla.gla_decode_kernel_name(p, 0, [10]) == "scalar kernel"
     p.q_len = 5
     assert gla.gla_decode_kernel_name(p, 0, [10]) == ""
+
+
+@pytest.mark.parametrize("groups,n,k", [(2, 5120, 16384), (1, 5120, 4096), (2, 2048, 8192), (1, 4096, 32768), (3, 1056, 12352), (4, 512, 8192), (2, 96, 1024)])
+@pytest.mark.parametrize("sum_groups", [0, 1])
+def test_more_rows_never_need_less(groups, n, k, sum_groups):
+    """Projections: a workspace sized for the most rows serves every call with fewer."""
+    last = 0
+    for rows in range(1, 700):
+        p = gla.GlaProjParams()
+        p.rows, p.groups, p.n, p.k = rows, groups, n, k
+        need = gla.binding.load_library().gla_proj_workspace_size(ctypes.byref(p), sum_groups)
+        assert need >= last, rows
+        last = need
