@@ -29,7 +29,7 @@ namespace gla {
 // 256 tokens (a partial costs as much as a few tiles: 18 units of up to 4500 tokens take 39 us in 17 ranges, 46 in 28),
 // of at least 64 while the grid is small (2 units of 256 tokens: 19 us in four ranges, 49 in one).  In no more ranges than
 // run side by side, if they would fill a second round less than the first (one_round, launch_generic_mfma) and the sequences
-// are so much alike that they would run in two: GLA-2 32 x 3000 tokens 70 -> 59 us, MLA shape 16 x 4000 125 -> 104.  By the lengths
+// are so much alike that they would run in two: GLA-2 32 x 3000 tokens 70 -> 65 us, MLA shape 16 x 4000 125 -> 104.  By the lengths
 // and not by the page table's row length, which is all the host knows: in a table for the longest context every sequence
 // would lie in its first range (nine sequences of up to 4500 tokens, table for 72000: 213 us, 41 this way).
 // (len: the length of sequence `lane`, loaded ahead; per_seq: workgroups per sequence and range)

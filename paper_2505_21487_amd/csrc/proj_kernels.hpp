@@ -57,7 +57,7 @@ struct ProjParams {
   int32_t sum_groups, c_fp32, direct;
 };
 
-// STREAM: the weights are fetched with the streaming hint (chosen by the host, see run_proj).
+// STREAM: the weights are fetched with the streaming hint (chosen by the host, see proj_plan).
 template <int MT, int NT, bool STREAM>
 __global__ __launch_bounds__(256) void proj_kernel(ProjParams p) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -188,10 +188,11 @@ __global__ __launch_bounds__(256) void proj_kernel(ProjParams p) {
   }
 }
 
-// (Instantiated here, ahead of the reduction: the three kernels of up to 32 rows then lie side by side in memory.  An
-// attention block alternates between them and the decode's two, about 58 KB of code together; spread over the code object
-// as they came, they displaced one another in the 64 KB instruction cache more often: a block of 24 sequences 142.5 us,
-// 141.9 this way, and between 141.4 and 144.2 with other orders of the same kernels.)
+// (Instantiated here, ahead of the reduction: the two kernels that a block of up to 32 rows and with large weights takes then
+// lie side by side with it in memory.  An attention block alternates between them and the decode's two, whose code together
+// nearly fills the 64 KB instruction cache; spread over the code object as they came, they displaced one another more often:
+// a block of 24 sequences 142.5 us, 141.9 this way, and between 141.4 and 144.2 with other orders of the same kernels.  That
+// was with the kernels of then; the same block takes 111 now.)
 template __global__ void proj_kernel<1, 2, true>(ProjParams);
 template __global__ void proj_kernel<1, 1, false>(ProjParams);
 

@@ -17,10 +17,12 @@ namespace gla {
 // 33 MB of partials that a full grid leaves.  So the work of a unit is spread by the length of its list.  A panel is
 // four 32-dim blocks of one wave of the main kernel, 16 blocks of 1 KiB per chunk.  A short list has one workgroup of
 // four waves per panel, each wave taking four blocks over the whole list.  A longer one has up to 16 workgroups per
-// panel ("sets"), each taking its share of the blocks, down to a block for one wave, two or all four; there 16 chunks
-// are in flight per wave.  How many sets a unit has only its list tells, so the workgroups beyond the first belong to
-// windows of merge_span chunks: the k-th window that lies inside a unit's list is its k-th further set, and the windows
-// that are not needed leave.  Their number is that of the chunks over merge_span, however long or short the lists turn out.
+// panel ("sets"), each taking its share of the blocks, down to a block for one wave, two or all four, with
+// four chunks in flight per wave (eight where four waves have one block: 4 to 32 per workgroup; 64 in the one of sixteen
+// waves).  Every unit has 1 << merge_sets_lg sets (more than one in a small grid of long lists).  How many
+// more only its list tells, so the workgroups beyond these belong to windows of merge_span chunks: the k-th window that
+// lies inside a unit's list is its k-th further set, and the windows that are not needed leave.  Their number is that of the
+// chunks over merge_span, however long or short the lists turn out.
 // us per call, against four waves (or, by the mean length, one or sixteen) for every 32-dim block of every unit: GLA-2 15 x
 // 1024 and 1 x 65536 tokens 56.8 -> 41.2, MLA shape 66.1 -> 53.6, GTA-4 10 sequences of up to 6000 20.7 -> 19.1, 1 x 100000
 // 39.1 -> 35.1, GLA-2 1 x 131072 55.4 -> 53.6, 3 x 1000 19.1 -> 17.8, 64 x 8192 122.0 -> 120.6.
