@@ -12,8 +12,8 @@ from gpu_util import check_problem
 
 pytestmark = pytest.mark.gpu
 
-# kind, heads, groups, d_v, RoPE dims, query positions: every kernel that works on a cut list; with 3 positions two units
-# per sequence (groups), with 4 two row blocks too
+# kind, heads, groups, d_v, RoPE dims, query positions: the four-wave kernel (gla2_units: two units per sequence, each of
+# two row blocks; gla4_units: two units) and the second MFMA kernel; the eight-wave kernel below
 KERNELS = {
     "gla2_h16": ("gla", 16, 2, 256, 64, 1), "gla2_units": ("gla", 96, 2, 256, 64, 3), "gla4_units": ("gla", 64, 4, 256, 64, 2),
     "mla": ("gla", 40, 1, 512, 64, 1), "gta4_d128": ("gta", 32, 4, 128, 64, 1), "gta4_d64": ("gta", 32, 4, 64, 32, 1),
@@ -37,6 +37,24 @@ def test_cut_list(kernel, lengths):
     p = make_problem(f"{kernel}_{lengths}", kind=kind, seq_lens=lens, T=T, h_q=h, h_c=g, d_v=d_v, **({"d_r": d_r} if d_r else {}), seed=8100 + len(kernel) + len(lengths),
                      num_pages=sum((n + 63) // 64 for n in lens) + 64, poison_tail=True)
     check_problem(p, impl=gla.GLA_IMPL_TUNED, what=f"{kernel} {lengths}")
+
+
+@pytest.mark.parametrize("shape", ["mla", "gla2"])
+def test_cut_list_of_the_eight_wave_kernel(shape):
+    """The library's own cut, with set-ups: more than 64 sequences, empty ones first, between and around the 64th, many short
+    ones per chunk, long ones over many.  Some rows of every sequence."""
+    lens = [0, 0, 3] + [17, 65, 0, 129] * 14 + [0, 5000, 0, 0, 900, 0, 33] + [1, 64, 40] * 14 + [30000, 0, 21000, 7, 26000, 0]
+    h, d_v, T = (128, 512, 1) if shape == "mla" else (96, 256, 3)
+    if shape == "gla2":
+        lens = lens + [60000]
+    p = make_problem(f"cut_{shape}", seq_lens=lens, T=T, h_q=h, h_c=1 if shape == "mla" else 2, d_v=d_v, page_size=8, seed=8150,
+                     num_pages=sum((n + 7) // 8 for n in lens) + 64, poison_tail=True)
+    dp = DeviceProblem(p, poison_unused=True)
+    out = torch.empty(p.B, T, h, d_v, dtype=torch.float32, device="cuda")
+    prm = gla.make_params(*dp.args()[:6], p.scale, out=out, lse=torch.empty(p.B, T, h, device="cuda"), workspace=None)
+    assert gla.gla_decode_kernel_name(prm, 0, lens) == "eight-wave kernel"
+    sel = [(b, t, i) for b in range(p.B) for t in range(T) for i in range(b % 7, h, 31)]
+    check_problem(p, dp=dp, sel=sel, impl=gla.GLA_IMPL_TUNED, what=f"eight-wave kernel, {shape}")
 
 
 # kind, heads, groups, d_v, RoPE dims, tokens per page, lengths, unused table columns, splits whose chunks are the library's own.  Lists that no chunk
