@@ -350,7 +350,7 @@ def test_many_units_with_very_long_chunk_lists(causal):
 def test_full_size_configs_every_row(index, T):
     """The launch configuration the benchmark times, at the full size of each
     configuration: EVERY output row against the oracle (a few seconds of CPU
-    per configuration on the GPU machine's host cores)."""
+    per configuration on 16 host cores)."""
     p = config(index, T=T)
     check_problem(p, impl=TUNED, what=f"cfg{index} T={T}")
 
