@@ -560,7 +560,6 @@ int run_proj(const gla_proj_params* p, int sum_groups) {
   d.c_row = p->c_row_stride;
   d.c_group = p->c_group_stride;
   d.M = p->rows;
-  d.G = p->groups;
   d.N = p->n;
   d.K = p->k;
   d.ksplit = plan.ksplit;
@@ -570,9 +569,20 @@ int run_proj(const gla_proj_params* p, int sum_groups) {
   d.direct = plan.direct ? 1 : 0;
   hipStream_t st = (hipStream_t)p->stream;
   const int wg_n = 128 * plan.nt;
-  const dim3 grid((unsigned)((p->n + wg_n - 1) / wg_n), (unsigned)((p->rows + 32 * plan.mt - 1) / (32 * plan.mt)),
-                  (unsigned)(p->groups * plan.ksplit));
-  if (grid.y > 65535u || grid.z > 65535u) return GLA_ERR_UNSUPPORTED_SHAPE;
+  const unsigned blocks = (unsigned)((p->n + wg_n - 1) / wg_n), tiles = (unsigned)((p->rows + 32 * plan.mt - 1) / (32 * plan.mt));
+  const unsigned slices = (unsigned)(p->groups * plan.ksplit);
+  if (tiles > 65535u || slices > 65535u) return GLA_ERR_UNSUPPORTED_SHAPE;
+  // Placed by the kernel from 17 rows on (a grid in plain order / placed, us: 2 x 5120 x 4096, 3 rows 17.2 / 18.2, 12 rows 18.2 /
+  // 18.7, 24 rows 19.4 / 19.3, 40 rows 21.9 / 21.2; 1 x 5120 x 16384, 2 rows 30.0 / 30.5, 20 rows 32.6 / 32.4; 64 rows of 128 heads x
+  // 256 x 128 5.6 / 5.1, 200 rows 13.2 / 11.7; output projection of the benchmark 70.2 / 60.7).
+  const bool placed = p->rows > 16 && plan.mt * plan.nt > 1;
+  const dim3 grid = placed ? dim3(blocks * tiles * slices) : dim3(blocks, tiles, slices);
+  d.total = placed ? grid.x : 0;
+  d.tiles = tiles;
+  d.blocks = blocks;
+  d.by_tiles = proj_reciprocal(tiles);
+  d.by_blocks = proj_reciprocal(blocks);
+  d.by_ksplit = proj_reciprocal((uint32_t)plan.ksplit);
   if (plan.nt == 2) {
     if (plan.mt == 1) launch_proj_long<1>(plan.stream, grid, st, d);
     else if (plan.mt == 2) launch_proj_long<2>(plan.stream, grid, st, d);
@@ -584,7 +594,19 @@ int run_proj(const gla_proj_params* p, int sum_groups) {
   if (hipGetLastError() != hipSuccess) return GLA_ERR_LAUNCH;
   if (!plan.direct) {
     const int64_t outs = (int64_t)p->rows * (sum_groups ? 1 : p->groups) * (p->n / 4);
-    hipLaunchKernelGGL(proj_reduce_kernel, dim3((unsigned)((outs + 255) / 256)), dim3(256), 0, st, d);
+    ProjReduceParams q;
+    q.part = d.part;
+    q.c = d.c;
+    q.c_row = d.c_row;
+    q.c_group = sum_groups ? 0 : d.c_group;
+    q.M = d.M;
+    q.N = d.N;
+    q.outs = sum_groups ? 1u : (uint32_t)p->groups;
+    q.slices = sum_groups ? p->groups * plan.ksplit : plan.ksplit;
+    q.c_fp32 = d.c_fp32;
+    q.by_n4 = make_fastdiv((uint32_t)p->n / 4);
+    q.by_outs = make_fastdiv(q.outs);
+    hipLaunchKernelGGL(proj_reduce_kernel, dim3((unsigned)((outs + 255) / 256)), dim3(256), 0, st, q);
     if (hipGetLastError() != hipSuccess) return GLA_ERR_LAUNCH;
   }
   return GLA_OK;

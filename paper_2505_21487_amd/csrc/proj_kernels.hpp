@@ -28,7 +28,7 @@
 //
 // The input features of a group can be cut into KSPLIT ranges (and, for the
 // output projection, the groups themselves are ranges of one long sum): each
-// (group, range) is one grid.z slice that leaves an fp32 partial [m][n] in the
+// (group, range) is one slice that leaves an fp32 partial [m][n] in the
 // workspace, summed by proj_reduce_kernel.  Without a cut the result is
 // written directly.
 #pragma once
@@ -45,6 +45,7 @@ typedef __attribute__((ext_vector_type(8))) __bf16 proj_bf16x8_t;
 typedef __attribute__((ext_vector_type(16))) float proj_f32x16_t;
 typedef __attribute__((ext_vector_type(4))) float proj_f32x4_t;
 
+// (128 bytes with the runtime's share left out: two cache lines that a workgroup waits for first)
 struct ProjParams {
   const uint16_t* a;
   const uint16_t* w;
@@ -52,19 +53,44 @@ struct ProjParams {
   float* part;             // [z][M][N] fp32 partials (z = g * ksplit + s), used when direct == 0
   int64_t a_row, a_group;  // element strides of A
   int64_t c_row, c_group;  // element strides of C
-  int32_t M, G, N, K;
+  int32_t M, N, K;
   int32_t ksplit, k_per_split;
-  int32_t sum_groups, c_fp32, direct;
+  int16_t sum_groups, c_fp32, direct, pad;
+  uint32_t total;                           // > 0: a grid of that many workgroups, placed by the kernel; 0: (blocks, row tiles, slices)
+  uint32_t tiles, blocks;                   // row tiles, blocks of output features
+  uint32_t by_tiles, by_blocks, by_ksplit;  // reciprocals, see proj_div
 };
+static_assert(sizeof(ProjParams) <= 128, "two cache lines");
+
+// n / d for n and d below 2^16 as the upper half of n * m, m = ceil(2^32 / d) (0 for d = 1): exact, since n * (m d - 2^32) < 2^32.
+// Larger grids divide.
+inline uint32_t proj_reciprocal(uint32_t d) { return d > 1 ? (uint32_t)(((1ull << 32) + d - 1) / d) : 0u; }
+__device__ __forceinline__ unsigned proj_div(unsigned n, unsigned d, unsigned m, unsigned total) {
+  if (total >= 65536u) return n / d;
+  return m ? __umulhi(n, m) : n;
+}
 
 // STREAM: the weights are fetched with the streaming hint (chosen by the host, see proj_plan).
 template <int MT, int NT, bool STREAM>
 __global__ __launch_bounds__(256) void proj_kernel(ProjParams p) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int r = lane & 31, h = lane >> 5;
-  const int n0 = blockIdx.x * (128 * NT) + wave * (32 * NT);  // (N is a multiple of 32: a block of 32 output features exists or does not)
-  const int m0 = blockIdx.y * (32 * MT);
-  const int g = (int)blockIdx.z / p.ksplit, ks = (int)blockIdx.z % p.ksplit;
+  // Workgroups are dealt round-robin to the 8 XCDs.  Placed, each XCD gets a contiguous run of the list of (group and range,
+  // block of output features, row tile), the row tile innermost: the row tiles of a block share its weights through one L2,
+  // and of the query rows an XCD fetches the few ranges its run holds, not all of them (64 rows x 32768 features: 1 MB instead
+  // of 4.2).  With few query rows there is nothing to share: see run_proj.
+  constexpr bool kLong = MT * NT > 1;  // (short sums over few rows are over before any of this pays: 5.5 -> 5.8 us)
+  unsigned bx = blockIdx.x, tile = blockIdx.y, bz = blockIdx.z;
+  if (kLong && p.total > 0) {
+    const unsigned total = p.total, xcd = blockIdx.x & 7;
+    const unsigned id = xcd * (total >> 3) + min(xcd, total & 7) + (blockIdx.x >> 3), xz = proj_div(id, p.tiles, p.by_tiles, total);
+    tile = id - xz * p.tiles;
+    bz = proj_div(xz, p.blocks, p.by_blocks, total);
+    bx = xz - bz * p.blocks;
+  }
+  const int n0 = (int)bx * (128 * NT) + wave * (32 * NT);  // (N is a multiple of 32: a block of 32 output features exists or does not)
+  const int m0 = (int)tile * (32 * MT);
+  const int g = (int)(p.by_ksplit ? __umulhi(bz, p.by_ksplit) : bz), ks = (int)bz - g * p.ksplit;  // (fewer than 2^16 slices)
   const int k_begin = ks * p.k_per_split;
   const int k_end = min(p.K, k_begin + p.k_per_split);
 
@@ -118,18 +144,27 @@ __global__ __launch_bounds__(256) void proj_kernel(ProjParams p) {
 
   constexpr int LPS = 4 * NT + MT;  // loads per wave and stage
   static_assert(LPS * (NST - 2) <= 63, "vmcnt range");
-  const int k_last = k_end - 64;
+  // The blocks of output features start at different steps of their range and wrap around.  In step they would all read the
+  // same columns of rows that lie a power of two or so apart, hence through few of the memory channels at a time.  A kernel
+  // that only loads, in this order, with and without the offsets: 335 MB (2 x 5120 x 16384) 50.5 / 53.3 us, 268 MB (2 x 8192 x 8192)
+  // 41.2 / 64.8; this one 60.7 / 67.0 (64 rows) and 46.6 / 76.0 (32 rows), offsets without the placement above 70.2, the
+  // placement without offsets 76.9.
+  const int steps = (k_end - k_begin) / 64, first = kLong ? (int)__umulhi(bx * p.by_blocks, (unsigned)steps) : 0;
+  auto feature = [&](int i) {  // first input feature of step i (steps past the end fetch the last one again)
+    const int j = min(i, steps - 1) + first;
+    return k_begin + 64 * (!kLong || j < steps ? j : j - steps);
+  };
 #pragma unroll
-  for (int st = 0; st < NST - 1; ++st) issue(min(k_begin + 64 * st, k_last), st);  // (steps past the end fetch the last one again)
-  for (int k = k_begin; k < k_end; k += 64 * NST) {
+  for (int st = 0; st < NST - 1; ++st) issue(feature(st), st);
+  for (int i = 0; i < steps; i += NST) {
     static_for<0, NST>([&](auto stc) {
       constexpr int st = decltype(stc)::value;
-      if (k + 64 * st < k_end) {  // (uniform over the workgroup)
+      if (i + st < steps) {  // (uniform over the workgroup)
         // this wave's part of stage st has landed (the NST - 2 stages behind it may be in flight); after the
         // barrier so has everybody's, and everybody is done reading the stage before it, which is loaded next
         wait_vmcnt<LPS * (NST - 2)>();
         bare_barrier();
-        issue(min(k + 64 * (st + NST - 1), k_last), (st + NST - 1) % NST);
+        issue(feature(i + st + NST - 1), (st + NST - 1) % NST);
         u32x4_t wf[NT][4], af[MT][4];
         static_for<0, 4>([&](auto sc) {
           constexpr int s = decltype(sc)::value;
@@ -172,7 +207,7 @@ __global__ __launch_bounds__(256) void proj_kernel(ProjParams p) {
       const int n = n0 + 32 * nt + 8 * q4 + 4 * h;
       const proj_f32x4_t v = {acc[nt][mt][4 * q4], acc[nt][mt][4 * q4 + 1], acc[nt][mt][4 * q4 + 2], acc[nt][mt][4 * q4 + 3]};
       if (!p.direct) {
-        *reinterpret_cast<proj_f32x4_t*>(p.part + ((int64_t)blockIdx.z * p.M + m) * p.N + n) = v;
+        *reinterpret_cast<proj_f32x4_t*>(p.part + ((int64_t)bz * p.M + m) * p.N + n) = v;
       } else {
         const int64_t off = m * p.c_row + (p.sum_groups ? 0 : g * p.c_group) + n;
         if (p.c_fp32) {
@@ -196,31 +231,36 @@ __global__ __launch_bounds__(256) void proj_kernel(ProjParams p) {
 template __global__ void proj_kernel<1, 2, true>(ProjParams);
 template __global__ void proj_kernel<1, 1, false>(ProjParams);
 
-// Sum of the partials of one output: over all grid.z slices (output projection)
-// or over the ksplit slices of each group (absorbed query).  One thread per four
-// consecutive output features, slices added in index order (deterministic).
-__global__ __launch_bounds__(256) void proj_reduce_kernel(ProjParams p) {
-  const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int n4 = p.N / 4;
-  const int outs = p.sum_groups ? 1 : p.G;
-  if (idx >= (int64_t)p.M * outs * n4) return;
-  const int n = (int)(idx % n4) * 4;
-  const int g = (int)((idx / n4) % outs);
-  const int m = (int)(idx / ((int64_t)n4 * outs));
-  const int z0 = p.sum_groups ? 0 : g * p.ksplit, z1 = p.sum_groups ? p.G * p.ksplit : (g + 1) * p.ksplit;
+// Sum of the partials of one output: over all slices (output projection) or over the ksplit slices of each group (absorbed
+// query).  One thread per four consecutive output features, slices added in index order (deterministic).
+struct ProjReduceParams {
+  const float* part;
+  void* c;
+  int64_t c_row, c_group;
+  int32_t M, N, slices;  // slices per result
+  int32_t c_fp32;
+  FastDiv by_n4, by_outs;  // N / 4; results (groups) per query row
+  uint32_t outs;
+};
+__global__ __launch_bounds__(256) void proj_reduce_kernel(ProjReduceParams p) {
+  // (rows x groups x output features are less than 2^31: see proj_plan)
+  const unsigned idx = blockIdx.x * blockDim.x + threadIdx.x;
+  const unsigned n4 = (unsigned)p.N / 4, q = fast_div(idx, p.by_n4), mu = fast_div(q, p.by_outs);
+  if (mu >= (unsigned)p.M) return;
+  const int n = (int)(idx - q * n4) * 4, g = (int)(q - mu * p.outs), m = (int)mu;
   proj_f32x4_t v = {0.f, 0.f, 0.f, 0.f};
-  const float* src = p.part + ((int64_t)z0 * p.M + m) * p.N + n;
+  const float* src = p.part + ((int64_t)g * p.slices * p.M + m) * p.N + n;
   const int64_t step = (int64_t)p.M * p.N;
-  int z = z0;
-  for (; z + 4 <= z1; z += 4, src += 4 * step) {  // four slices in flight, added in index order
+  int z = 0;
+  for (; z + 4 <= p.slices; z += 4, src += 4 * step) {  // four slices in flight, added in index order
     const proj_f32x4_t a0 = *reinterpret_cast<const proj_f32x4_t*>(src);
     const proj_f32x4_t a1 = *reinterpret_cast<const proj_f32x4_t*>(src + step);
     const proj_f32x4_t a2 = *reinterpret_cast<const proj_f32x4_t*>(src + 2 * step);
     const proj_f32x4_t a3 = *reinterpret_cast<const proj_f32x4_t*>(src + 3 * step);
     v = (((v + a0) + a1) + a2) + a3;
   }
-  for (; z < z1; ++z, src += step) v += *reinterpret_cast<const proj_f32x4_t*>(src);
-  const int64_t off = m * p.c_row + (p.sum_groups ? 0 : g * p.c_group) + n;
+  for (; z < p.slices; ++z, src += step) v += *reinterpret_cast<const proj_f32x4_t*>(src);
+  const int64_t off = m * p.c_row + g * p.c_group + n;
   if (p.c_fp32) {
     *reinterpret_cast<proj_f32x4_t*>((float*)p.c + off) = v;
   } else {
