@@ -42,3 +42,32 @@ def test_absorb_query(M, G, N, K):
     ref = oracle.project(bf16_bits(a), bf16_bits(w), sum_groups=False)
     abs_prod = np.einsum("mgk,gnk->mgn", np.abs(a.double().numpy()), np.abs(w.double().numpy()))
     check_projection(c, ref, abs_prod, bf16_out=False, what=f"absorb {M}x{G}x{N}x{K}")
+
+
+def test_on_the_current_stream():
+    """On a stream of its own, behind work that takes a while, and captured: the input is what that stream has made of it."""
+    gen = torch.Generator(device="cuda").manual_seed(860)
+    a = torch.randn(24, 16, 128, generator=gen, device="cuda", dtype=torch.bfloat16)
+    w = torch.randn(16, 256, 128, generator=gen, device="cuda", dtype=torch.bfloat16)
+    want = gla.gla_absorb_query(a, w)
+    other, ws = torch.zeros_like(a), torch.empty(256, dtype=torch.uint8, device="cuda")
+    got = torch.empty_like(want)
+    big = torch.randn(4096, 4096, device="cuda")
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        for _ in range(4):
+            big = big @ big * 1e-4
+        other.copy_(a)
+        gla.gla_absorb_query(other, w, out=got, workspace=ws)
+    side.synchronize()
+    assert torch.equal(got, want)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        gla.gla_absorb_query(other, w, out=got, workspace=ws)
+    for scale in (1.0, 2.0):  # (a power of two: exact)
+        other.copy_(a * scale)
+        got.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(got.float(), want.float() * scale)
