@@ -184,6 +184,18 @@ __device__ __forceinline__ void load_window(int cond, const int32_t* row, int o0
         : "memory", "scc");
 }
 
+// Direct-to-LDS load of 16 bytes per lane from a uniform base and a 32-bit offset per lane: IMM bytes past both addresses.
+// SET: sets m0, the LDS address; the loads that follow with the same dst leave it (a kernel with these has nothing else that
+// writes m0 in between: other loads to LDS are assembly too).  The compiler's builtin takes a 64-bit address per lane, which
+// costs an addition per load.  STREAM: with the streaming hint.
+template <int IMM, bool SET, bool STREAM>
+__device__ __forceinline__ void load_lds_b128(const unsigned char* base, unsigned off, const unsigned char* dst) {
+  // (a wait state between m0 and the load that uses it)
+  if constexpr (SET) asm volatile("s_mov_b32 m0, %0\n\ts_nop 0" ::"s"((unsigned)(uintptr_t)(lds_void_t*)dst) : "memory");
+  if constexpr (STREAM) asm volatile("global_load_lds_dwordx4 %0, %1 offset:%2 nt" ::"v"(off), "s"(base), "n"(IMM) : "memory");
+  else asm volatile("global_load_lds_dwordx4 %0, %1 offset:%2" ::"v"(off), "s"(base), "n"(IMM) : "memory");
+}
+
 // A 32-bit global load that is complete when the statement ends.  Used for the
 // rare bookkeeping reads inside the tile loop (page ids, next sequence length):
 // being opaque to the compiler's memory-counter tracking, it cannot make the

@@ -234,9 +234,6 @@ __global__ __launch_bounds__(64 * NG * WPG * KS) void tuned_main_kernel(DevParam
   unsigned char* const lds_rope_w = smem + TT::kRopeBase + wave * (RLW * 1024);
 
   uint64_t pre_goff = (uint64_t)pre.ub * NG * st_group_bytes;  // byte offset of the cursor's group block in a page
-  const unsigned char* pre_sp = nullptr;  // state / RoPE page of the prefetch cursor
-  const unsigned char* pre_rp = nullptr;
-  bool pre_page_valid = false;
   // addresses of the tile being issued (this wave's share)
   const unsigned char* dma_s[NSGW] = {};
   const unsigned char* dma_r[RLW] = {};
@@ -284,20 +281,76 @@ __global__ __launch_bounds__(64 * NG * WPG * KS) void tuned_main_kernel(DevParam
   // chunk has been issued the previous tile's addresses are kept: the loads
   // then re-read lines that are still in L2 into a stage nobody reads, which
   // keeps the steady-state loop free of branches around the load instructions.
-  // The preparation is scalar work (a few dozen instructions).  It is cut in
+  // The preparation is scalar work (some thirty instructions).  It is cut in
   // three pieces so that the tile loop can place them between value MFMAs
   // instead of running them in one stretch with the matrix pipe idle.
-  bool prep_active = false, prep_need_page = false;
-  unsigned prep_page_idx = 0, prep_tip = 0;
-  auto dma_prepare_0 = [&](int stage) {  // where to, and are page ids needed
+  bool prep_active = false;
+  unsigned prep_page_idx = 0;
+  // Pages of 16 tokens and more: the tiles ahead form runs inside one unit whose page ids the lanes of pt_vec hold; what
+  // depends on unit and page table is done where a run begins, what is left per tile is a page id and its product with the
+  // page's bytes for every load group (some 100 instructions per tile fewer in the code than working it all out each time, 40
+  // of them executed; what bounds the kernel on many rows is a wave's issue).  us per call with that and with it in runs, and
+  // with loads of 32-bit offsets (load_lds_b128): GLA-2 two query positions 37 ragged sequences, pages of 16, 98.6 / 94.9; 64 x
+  // 8192 119.2 / 116.7; MLA shape 15 x 1024 and 1 x 65536 53.8 / 52.8, three positions 40 x 500 to 3000, pages of 32, 110 / 103.
+  // Behind the chunk's last tile the cursor stands still.
+  int run_left = 0, run_step = 1;                      // tiles left in the run; 0 once the chunk has been requested
+  const unsigned char* run_s = nullptr;                // state cache + the unit's group + this wave's first row
+  int run_last_page = 0;                               // last page the sequence holds
+  uint32_t run_page_s[NSGW] = {}, run_page_r[RLW] = {};  // page ids of the tile's load groups
+  auto begin_run = [&]() __attribute__((always_inline)) {
+    if (issued >= n_tiles) {
+      if (run_step) --pre.j;  // (the last tile again)
+      run_step = 0;
+      run_left = 0x7fffffff;
+      return;
+    }
+    if (pre.j == pre.tiles_b) {
+      pre.j = 0;
+      if (++pre.ub == UPB) {
+        pre.ub = 0;
+        do {
+          ++pre.b;
+          pre.L = pre.b < p.B ? uniform(load_i32_sync(p.seq_lens + pre.b)) : 0;
+          pre.tiles_b = tiles_of<TOK>(pre.L);
+        } while (pre.b < p.B && pre.tiles_b == 0);
+      }
+    }
+    run_s = state_w + (uint64_t)pre.ub * NG * st_group_bytes + wpos * (SLW * 1024);
+    run_last_page = (pre.L - 1) >> lgP;
+    const int first = (pre.j * TOK) >> lgP, last = (pre.j * TOK + TOK - 1) >> lgP;
+    if (pre.b != pt_b || first < pt_base || last >= pt_base + 64) {
+      pt_b = pre.b;
+      pt_base = first;
+      pt_vec = load_i32_sync(p.page_table + (int64_t)pre.b * p.max_pages + min(first + lane, p.max_pages - 1));
+    }
+    run_left = min(min(pre.tiles_b - pre.j, n_tiles - issued), (int)(((unsigned)(pt_base + 64) << lgP) / TOK) - pre.j);
+  };
+  auto dma_prepare_0 = [&](int stage) {  // where to, and from which pages
     dma_ls = lds_state_w + stage * STB;
     dma_lr = lds_rope_w + stage * RTB;
+    if constexpr (!kLane) {
+      if (__builtin_expect(run_left == 0, 0)) begin_run();
+      --run_left;
+      prep_active = run_step != 0;
+      const int tok0 = pre.j * TOK;
+      if constexpr (PM == 0) {
+        run_page_s[0] = run_page_r[0] = (uint32_t)__builtin_amdgcn_readlane(pt_vec, (tok0 >> 6) - pt_base);
+      } else {
+        // One page per load group.  Rows past the end of the sequence may lie in a page the table does not hold: they are
+        // fetched from the sequence's last page instead (any finite-or-not data will do, those rows are masked and zeroed),
+        // never through an unused table entry.
+#pragma unroll
+        for (int gi = 0; gi < NSGW; ++gi)
+          run_page_s[gi] = (uint32_t)__builtin_amdgcn_readlane(pt_vec, min((tok0 + (wpos * SLW + 4 * gi) * RPL) >> lgP, run_last_page) - pt_base);
+#pragma unroll
+        for (int ir = 0; ir < RLW; ++ir)
+          run_page_r[ir] = (uint32_t)__builtin_amdgcn_readlane(pt_vec, min((tok0 + (wave * RLW + ir) * 8) >> lgP, run_last_page) - pt_base);
+      }
+      return;
+    }
     prep_active = issued < n_tiles;
     const unsigned tok0 = (unsigned)pre.j * TOK;
-    prep_page_idx = tok0 >> lgP;                    // first page of the tile
-    prep_tip = (tok0 & ((1u << lgP) - 1)) / TOK;  // tile within the page (pages of 64)
-    prep_need_page = prep_active && (lgP < 6 || prep_tip == 0 || !pre_page_valid);
-    const int last_idx = (int)((tok0 + TOK - 1) >> lgP);
+    prep_page_idx = tok0 >> lgP;  // first page of the tile
     if constexpr (kRegWin) {
       // fetch0 / fetch1: request window id0 / id1 into the first / second set of registers
       int fetch0 = 0, fetch1 = 0, id0 = 0, id1 = 0, last_page = 0;
@@ -361,22 +414,34 @@ __global__ __launch_bounds__(64 * NG * WPG * KS) void tuned_main_kernel(DevParam
           win_fetch(win_sel ^ 1, pre.b, nxt, last_page);
         }
       }
-    } else if (prep_need_page && (pre.b != pt_b || (int)prep_page_idx < pt_base || last_idx >= pt_base + 64)) {
-      pt_b = pre.b;
-      pt_base = (int)prep_page_idx;
-      const int idx = min((int)prep_page_idx + lane, p.max_pages - 1);
-      pt_vec = load_i32_sync(p.page_table + (int64_t)pre.b * p.max_pages + idx);
     }
   };
-  auto dma_prepare_1 = [&]() {  // pages of 64: page id -> page base addresses (kept for the page's second tile)
-    if (prep_need_page && lgP == 6) {
-      const uint32_t page = (uint32_t)__builtin_amdgcn_readlane(pt_vec, (int)prep_page_idx - pt_base);
-      pre_sp = state_w + ((uint64_t)page * st_page_bytes + pre_goff);
-      pre_rp = rope_w + (uint64_t)page * rp_page_bytes;
-      pre_page_valid = true;
+  auto dma_prepare_1 = [&]() {  // pages of 16 tokens and more: base address of every load group of the state
+    if constexpr (!kLane) {
+      const unsigned pmask = (1u << lgP) - 1;
+#pragma unroll
+      for (int gi = 0; gi < NSGW; ++gi) {
+        if constexpr (PM == 0) {
+          dma_s[gi] = gi == 0 ? run_s + ((uint64_t)run_page_s[0] * st_page_bytes + (unsigned)(pre.j & 1) * (unsigned)STB) : dma_s[0] + 4096 * gi;
+        } else {  // (run_s points past the rows of the wave's loads before: a multiple of GROWS rows)
+          const unsigned row = (unsigned)(wpos * SLW + 4 * gi) * RPL, tok = (unsigned)pre.j * TOK + row;
+          dma_s[gi] = run_s + ((uint64_t)run_page_s[gi] * st_page_bytes + (uint64_t)(tok & pmask) * ROWB) - wpos * (SLW * 1024);
+        }
+      }
     }
   };
-  auto dma_prepare_2 = [&]() {  // base address of every load group; advance the prefetch cursor
+  auto dma_prepare_2 = [&]() {  // ... of the RoPE keys, and the cursor moves on; smaller pages: a page id per lane and load
+    if constexpr (!kLane) {
+      const unsigned pmask = (1u << lgP) - 1;
+#pragma unroll
+      for (int ir = 0; ir < RLW; ++ir) {
+        const unsigned tok = (unsigned)pre.j * TOK + (unsigned)(wave * RLW + ir) * 8;
+        dma_r[ir] = rope_w + ((uint64_t)run_page_r[PM == 0 ? 0 : ir] * rp_page_bytes + (uint64_t)((tok & pmask) * rrb));
+      }
+      pre.j += run_step;
+      issued += run_step;
+      return;
+    }
     if (!prep_active) return;
     if constexpr (kRegWin) {
       const unsigned tok0 = (unsigned)pre.j * TOK;
@@ -430,37 +495,10 @@ __global__ __launch_bounds__(64 * NG * WPG * KS) void tuned_main_kernel(DevParam
       }
       dma_goff = pre_goff;
       dma_pmask = (1u << lgP) - 1;
-    } else if (lgP == 6) {
-#pragma unroll
-      for (int gi = 0; gi < NSGW; ++gi) dma_s[gi] = pre_sp + prep_tip * STB + (wpos * SLW + 4 * gi) * 1024;
-#pragma unroll
-      for (int ir = 0; ir < RLW; ++ir) dma_r[ir] = pre_rp + (prep_tip * TOK + (wave * RLW + ir) * 8) * rrb;
-    } else {
-      // Smaller pages: one page lookup per load group.  Rows past the end of the
-      // sequence may lie in a page the table does not hold: they are fetched from
-      // the sequence's last page instead (any finite-or-not data will do, those
-      // rows are masked and zeroed), never through an unused table entry.
-      const unsigned tok0 = (unsigned)pre.j * TOK, pmask = (1u << lgP) - 1;
-      const int last_page = (pre.L - 1) >> lgP;
-#pragma unroll
-      for (int gi = 0; gi < NSGW; ++gi) {
-        const unsigned tok = tok0 + (unsigned)(wpos * SLW + 4 * gi) * RPL;
-        const int pi = min((int)(tok >> lgP), last_page);
-        const uint32_t page = (uint32_t)__builtin_amdgcn_readlane(pt_vec, pi - pt_base);
-        dma_s[gi] = state_w + ((uint64_t)page * st_page_bytes + pre_goff + (uint64_t)(tok & pmask) * ROWB);
-      }
-#pragma unroll
-      for (int ir = 0; ir < RLW; ++ir) {
-        const unsigned tok = tok0 + (unsigned)(wave * RLW + ir) * 8;
-        const int pi = min((int)(tok >> lgP), last_page);
-        const uint32_t page = (uint32_t)__builtin_amdgcn_readlane(pt_vec, pi - pt_base);
-        dma_r[ir] = rope_w + ((uint64_t)page * rp_page_bytes + (uint64_t)(tok & pmask) * rrb);
-      }
     }
     ++issued;
     if (++pre.j == pre.tiles_b) {
       pre.j = 0;
-      pre_page_valid = false;
       if (++pre.ub == UPB) {
         pre.ub = 0;
         do {
@@ -516,10 +554,10 @@ __global__ __launch_bounds__(64 * NG * WPG * KS) void tuned_main_kernel(DevParam
       }
     } else if constexpr (i < SLW) {
       const unsigned voff = s_lane_w ^ ((unsigned)swz16(i * RPL) << 4);
-      tile_dma(std::integral_constant<int, (i % 4) * 1024>{}, dma_s[i / 4] + voff, dma_ls + (i / 4) * 4096);
+      load_lds_b128<(i % 4) * 1024, i % 4 == 0, STREAM>(dma_s[i / 4], voff, dma_ls + (i / 4) * 4096);
     } else {
       constexpr int ir = i - SLW;
-      rope_dma(std::integral_constant<int, 0>{}, dma_r[ir] + r_voff[ir & 1], dma_lr + ir * 1024);
+      load_lds_b128<0, true, false>(dma_r[ir], r_voff[ir & 1], dma_lr + ir * 1024);
     }
   };
 
@@ -1197,6 +1235,7 @@ __global__ __launch_bounds__(64 * NG * WPG * KS) void tuned_main_kernel(DevParam
     cur.j = seg_j0 + seg_n - 1;
     advance<TOK>(p, UPB, cur);
   }
+  wait_vmcnt<0>();  // (tiles fetched again past the end of the chunk: let them land before the wave leaves)
 }
 
 }  // namespace gla
