@@ -86,6 +86,23 @@ struct DevParams {
   int32_t wide_tiles;       // > 0: the eight-wave kernel runs if the list has that many tiles of 32 tokens, else the four-wave one
 };
 
+// The kernel's parameters into the scalar cache, all lines at once.  Left to itself a kernel loads them where it needs them,
+// and waits for one line after the other: the four-wave kernel for three before its first memory access and two more before
+// its first tile.  us per call without / with (there and in its merge): GLA-2 16 heads 1 x 256 tokens 12.8 / 12.0, 1 x 2048
+// 16.4 / 16.1, 1 x 131072 50.7 / 50.2; GTA-4 d_h 128 8 x 2000 16.3 / 15.7.  Nothing in the eight-wave and the second MFMA kernel
+// (32.7 / 32.6), and a loss in the generic one (29.3 / 30.1).
+__device__ __forceinline__ void fetch_params() {
+  static_assert(sizeof(DevParams) > 448 && sizeof(DevParams) <= 512, "eight lines of 64 bytes");
+  const auto args = __builtin_amdgcn_kernarg_segment_ptr();
+  int t0, t1, t2, t3, t4, t5, t6, t7;
+  asm volatile(
+      "s_load_dword %0, %8, 0x0\n\ts_load_dword %1, %8, 0x40\n\ts_load_dword %2, %8, 0x80\n\ts_load_dword %3, %8, 0xc0\n\t"
+      "s_load_dword %4, %8, 0x100\n\ts_load_dword %5, %8, 0x140\n\ts_load_dword %6, %8, 0x180\n\ts_load_dword %7, %8, 0x1c0\n\t"
+      "s_waitcnt lgkmcnt(0)"
+      : "=&s"(t0), "=&s"(t1), "=&s"(t2), "=&s"(t3), "=&s"(t4), "=&s"(t5), "=&s"(t6), "=&s"(t7)
+      : "s"(args));
+}
+
 // Over the 64 lanes with data-parallel-primitive moves (no LDS round trips): shifts by 1, 2, 4, 8 inside each row of 16
 // lanes, then the last lane of row 0 / 2 into row 1 / 3 and lane 31 into the upper half.  A lane that receives nothing
 // combines with `none`.

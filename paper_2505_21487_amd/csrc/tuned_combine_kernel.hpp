@@ -40,6 +40,7 @@ __global__ __launch_bounds__(64 * NW) void tuned_combine_kernel(DevParams p) {
   static_assert(NW == 4 || NW == 16, "waves per workgroup");
   __shared__ float red_m[NW][64], red_z[NW][64];
   __shared__ f32x4_t red_a[16][64];
+  fetch_params();
   const int lane = threadIdx.x & 63, wave = uniform((int)threadIdx.x >> 6);
   const int col = lane & 31, hi = lane >> 5;
   const int MB = p.mb;
