@@ -160,9 +160,9 @@ __global__ __launch_bounds__(256) void flex_main_kernel(DevParams p) {
   const unsigned NSTR = HB * (unsigned)p.flex_rb;        // strands
   const unsigned unit = blockIdx.x * 4u + (unsigned)wave;  // (the host keeps the number of waves below 2^31)
   if (unit >= NSTR * (unsigned)p.num_chunks) return;
-  const int chunk = (int)(unit / NSTR);
+  const int chunk = (int)fast_div(unit, p.fd_mb);  // / NSTR
   const int strand = (int)(unit - (unsigned)chunk * NSTR);
-  const int rb = (int)((unsigned)strand / HB);
+  const int rb = (int)fast_div((unsigned)strand, p.fd_upb_mb);  // / HB
   const int g0 = (strand - rb * (int)HB) * GPW;  // first group of this wave
   const int L_first = lane < p.B ? p.seq_lens[lane] : 0;
   const ListCut cut = cut_list<32, 128, FT::kPieces>(p, 1, lane, L_first, (int)NSTR);
@@ -179,7 +179,7 @@ __global__ __launch_bounds__(256) void flex_main_kernel(DevParams p) {
   const int R = GPW == 2 ? (r16 & 7) : rb * 16 + r16;      // row within the group
   const bool row_valid = R < rows_group;
   const int Rc = row_valid ? R : rows_group - 1;
-  const int t = Rc / p.g_q;
+  const int t = (int)fast_div((unsigned)Rc, p.fd_gq);
   const int h = (g0 + jg) * p.g_q + (Rc - t * p.g_q);
 
   // ---- tile loads.  A tile of 32 rows of LPR 16-byte chunks is 32 * LPR consecutive LDS slots, 64 per
@@ -274,7 +274,7 @@ __global__ __launch_bounds__(256) void flex_main_kernel(DevParams p) {
     auto row_at = [&](int row, int64_t page_stride, int dims) -> int64_t {
       const int t = ln_tok0 + row;
       const int e = min(t >> lgP, ln_last);
-      const int64_t id = __builtin_amdgcn_ds_bpermute((e & 63) << 2, pt_vec);
+      const int64_t id = (uint32_t)__builtin_amdgcn_ds_bpermute((e & 63) << 2, pt_vec);  // (unsigned: one 32-bit product fewer)
       return id * page_stride + (int64_t)(t & ((1 << lgP) - 1)) * dims;
     };
     auto loads = [&](auto hint) {
@@ -572,24 +572,30 @@ __global__ __launch_bounds__(256) void flex_main_kernel(DevParams p) {
 // Merge of the pieces of the rows whose sequence was cut between chunks: one wave per output row.
 // Rows of sequences that one chunk held entirely were written by the main kernel; empty sequences
 // are filled here (out = 0, lse = -inf).
-template <int GPW>
+// Nothing but start-up and one or two round trips for short lists: a row's sequence, position, head and group come from
+// host-made reciprocals and the row's width is the instantiation's (seven integer divisions, one after the other, before the
+// first piece's address otherwise).  us per call, with the three divisions at the main kernel's start, before -> after: GTA-4 d_h
+// 64 8 sequences of 100 to 2000 tokens 12.05 -> 11.3, 48 of 300 to 20000 at one token per page 32.6 -> 31.7, d_h 96 30 of
+// 300 to 8000 18.5 -> 17.7, GQA-4 d_h 128 24 of 500 to 4000 27.5 -> 26.9.
+template <int DV, int GPW>
 __global__ __launch_bounds__(64) void flex_combine_kernel(DevParams p) {
   const int row = blockIdx.x;
   const int lane = threadIdx.x;
-  const int h = row % p.h_q;
-  const int t = (row / p.h_q) % p.T;
-  const int b = row / (p.h_q * p.T);
+  const int bt = (int)fast_div((unsigned)row, p.fd_tiles_full);  // / h_q
+  const int h = row - bt * p.h_q;
+  const int b = (int)fast_div((unsigned)bt, p.fd_units_full);  // / T
+  const int t = bt - b * p.T;
   const int64_t base = b * p.out_s[0] + t * p.out_s[1] + h * p.out_s[2];
   const int L = p.seq_lens[b];
   if (L <= 0) {
     if (lane == 0) p.lse[row] = -INFINITY;
-    for (int d = lane; d < p.d_v; d += 64) {
+    for (int d = lane; d < DV; d += 64) {
       if (p.out_fp32) ((float*)p.out)[base + d] = 0.f;
       else ((uint16_t*)p.out)[base + d] = 0;
     }
     return;
   }
-  const int g = h / p.g_q;
+  const int g = (int)fast_div((unsigned)h, p.fd_gq);
   const int lr = t * p.g_q + (h - g * p.g_q);  // row within the group
   const int HB = p.h_c / GPW, NSTR = HB * p.flex_rb;
   const int strand = GPW == 2 ? g / 2 : (lr / 16) * HB + g;
@@ -606,7 +612,7 @@ __global__ __launch_bounds__(64) void flex_combine_kernel(DevParams p) {
   // time behind two passes over the log-sum-exps: GTA-4 d_h 64, 48 sequences of 300 to 20000 tokens 38.5 -> 33.9 us,
   // one sequence of 131072 80.1 -> 38.4; GQA-4 d_h 128, 24 sequences 55.2 -> 49.2; equal lists of two or three pieces
   // unchanged.
-  const int nd4 = p.d_v / 4, pgs = 64 / nd4;
+  constexpr int nd4 = DV / 4, pgs = 64 / nd4;
   const int pg = lane / nd4, d4 = lane - pg * nd4;
   constexpr int kFly = 8;
   f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
@@ -619,7 +625,7 @@ __global__ __launch_bounds__(64) void flex_combine_kernel(DevParams p) {
       for (int u = 0; u < kFly; ++u) {  // (past the last piece: the last one again, with weight zero)
         const int64_t sl = slot_of(min(c + u * pgs, c_last));
         ls[u] = p.ws_lse[sl];
-        v[u] = *(const f32x4_t*)(p.ws_out + sl * p.d_v + 4 * d4);
+        v[u] = *(const f32x4_t*)(p.ws_out + sl * DV + 4 * d4);
       }
       float m_new = m;
 #pragma unroll

@@ -269,9 +269,17 @@ int check_pointers(const gla_decode_params* p) {
 }
 
 template <int DN, int DR, int DV, bool SEPK, int GPW>
-void launch_flex_main(bool lane, dim3 grid, dim3 block, hipStream_t st, const DevParams& d) {
-  if (lane) hipLaunchKernelGGL((flex_main_kernel<DN, DR, DV, SEPK, GPW, true>), grid, block, 0, st, d);
-  else hipLaunchKernelGGL((flex_main_kernel<DN, DR, DV, SEPK, GPW, false>), grid, block, 0, st, d);
+int launch_flex_kernels(bool lane, dim3 grid, dim3 rows, hipStream_t st, hipEvent_t* ev, const DevParams& d) {
+  if (ev) (void)hipEventRecord(ev[0], st);
+  if (lane) hipLaunchKernelGGL((flex_main_kernel<DN, DR, DV, SEPK, GPW, true>), grid, dim3(256), 0, st, d);
+  else hipLaunchKernelGGL((flex_main_kernel<DN, DR, DV, SEPK, GPW, false>), grid, dim3(256), 0, st, d);
+  if (hipGetLastError() != hipSuccess) return GLA_ERR_LAUNCH;
+  if (ev) (void)hipEventRecord(ev[1], st);
+  // (always: it also fills the rows of empty sequences, which no chunk holds)
+  hipLaunchKernelGGL((flex_combine_kernel<DV, GPW>), rows, dim3(64), 0, st, d);
+  if (hipGetLastError() != hipSuccess) return GLA_ERR_LAUNCH;
+  if (ev) (void)hipEventRecord(ev[2], st);
+  return GLA_OK;
 }
 
 int launch_flex(const gla_decode_params* p, const FlexPlan& plan, DevParams& d, hipStream_t st, hipEvent_t* ev) {
@@ -280,6 +288,12 @@ int launch_flex(const gla_decode_params* p, const FlexPlan& plan, DevParams& d, 
   d.flex_rb = plan.rb;
   d.setup_tiles = setup_tiles(kSetupTilesFlex, plan.list_bound);
   d.fd_chunks = make_fastdiv((uint32_t)plan.chunks);
+  // what its kernels divide a row's or a wave's number by
+  d.fd_mb = make_fastdiv((uint32_t)plan.strands);
+  d.fd_upb_mb = make_fastdiv((uint32_t)(p->num_groups / plan.gpw));
+  d.fd_gq = make_fastdiv((uint32_t)(p->num_q_heads / p->num_groups));
+  d.fd_tiles_full = make_fastdiv((uint32_t)p->num_q_heads);
+  d.fd_units_full = make_fastdiv((uint32_t)p->q_len);
   int lg = 0;
   while ((1 << lg) < p->page_size) ++lg;
   d.lg_page = lg;
@@ -293,29 +307,17 @@ int launch_flex(const gla_decode_params* p, const FlexPlan& plan, DevParams& d, 
     d.flex_rng = (int32_t*)w;
   }
   const int64_t waves = (int64_t)plan.chunks * plan.strands;
-  const dim3 grid((unsigned)((waves + 3) / 4)), block(256);
-  if (ev) (void)hipEventRecord(ev[0], st);
+  const dim3 grid((unsigned)((waves + 3) / 4)), merge((unsigned)rows);
   switch (plan.id) {
-    case 0: launch_flex_main<128, 0, 128, true, 1>(plan.lane, grid, block, st, d); break;
-    case 1: launch_flex_main<64, 0, 64, true, 1>(plan.lane, grid, block, st, d); break;
+    case 0: return launch_flex_kernels<128, 0, 128, true, 1>(plan.lane, grid, merge, st, ev, d);
+    case 1: return launch_flex_kernels<64, 0, 64, true, 1>(plan.lane, grid, merge, st, ev, d);
     case 2:
-      if (plan.gpw == 2) launch_flex_main<32, 32, 64, false, 2>(plan.lane, grid, block, st, d);
-      else launch_flex_main<32, 32, 64, false, 1>(plan.lane, grid, block, st, d);
-      break;
-    case 3: launch_flex_main<48, 48, 96, false, 1>(plan.lane, grid, block, st, d); break;
-    case 4: launch_flex_main<128, 32, 128, false, 1>(plan.lane, grid, block, st, d); break;
+      return plan.gpw == 2 ? launch_flex_kernels<32, 32, 64, false, 2>(plan.lane, grid, merge, st, ev, d)
+                           : launch_flex_kernels<32, 32, 64, false, 1>(plan.lane, grid, merge, st, ev, d);
+    case 3: return launch_flex_kernels<48, 48, 96, false, 1>(plan.lane, grid, merge, st, ev, d);
+    case 4: return launch_flex_kernels<128, 32, 128, false, 1>(plan.lane, grid, merge, st, ev, d);
     default: return GLA_ERR_UNSUPPORTED_SHAPE;
   }
-  if (hipGetLastError() != hipSuccess) return GLA_ERR_LAUNCH;
-  if (ev) (void)hipEventRecord(ev[1], st);
-  // (always: it also fills the rows of empty sequences, which no chunk holds)
-  if (plan.gpw == 2)
-    hipLaunchKernelGGL(flex_combine_kernel<2>, dim3((unsigned)rows), dim3(64), 0, st, d);
-  else
-    hipLaunchKernelGGL(flex_combine_kernel<1>, dim3((unsigned)rows), dim3(64), 0, st, d);
-  if (hipGetLastError() != hipSuccess) return GLA_ERR_LAUNCH;
-  if (ev) (void)hipEventRecord(ev[2], st);
-  return GLA_OK;
 }
 
 void fill_dev(const gla_decode_params* p, DevParams* d) {
