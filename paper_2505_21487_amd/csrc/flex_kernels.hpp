@@ -576,7 +576,7 @@ __global__ __launch_bounds__(256) void flex_main_kernel(DevParams p) {
 // host-made reciprocals and the row's width is the instantiation's (seven integer divisions, one after the other, before the
 // first piece's address otherwise).  us per call, with the three divisions at the main kernel's start, before -> after: GTA-4 d_h
 // 64 8 sequences of 100 to 2000 tokens 12.05 -> 11.3, 48 of 300 to 20000 at one token per page 32.6 -> 31.7, d_h 96 30 of
-// 300 to 8000 18.5 -> 17.7, GQA-4 d_h 128 24 of 500 to 4000 27.5 -> 26.9.
+// 300 to 8000 18.5 -> 17.7, GQA-4 d_h 128 24 of 500 to 4000 27.5 -> 26.9 (and 11.05, 31.3, 17.4 and 26.4 with the next).
 template <int DV, int GPW>
 __global__ __launch_bounds__(64) void flex_combine_kernel(DevParams p) {
   const int row = blockIdx.x;
@@ -586,7 +586,17 @@ __global__ __launch_bounds__(64) void flex_combine_kernel(DevParams p) {
   const int b = (int)fast_div((unsigned)bt, p.fd_units_full);  // / T
   const int t = bt - b * p.T;
   const int64_t base = b * p.out_s[0] + t * p.out_s[1] + h * p.out_s[2];
-  const int L = p.seq_lens[b];
+  const int g = (int)fast_div((unsigned)h, p.fd_gq);
+  const int lr = t * p.g_q + (h - g * p.g_q);  // row within the group
+  const int HB = p.h_c / GPW, NSTR = HB * p.flex_rb;
+  const int strand = GPW == 2 ? g / 2 : (lr / 16) * HB + g;
+  const int r16 = GPW == 2 ? (g % 2) * 8 + lr : lr % 16;
+  const int32_t* rng = p.flex_rng + ((int64_t)b * NSTR + strand) * 2;
+  // the range (garbage for an empty sequence) and the length in one round trip: without the tie the range's load stays behind
+  // the test of the length (GTA-4 d_h 64, 8 sequences of 100 to 2000 tokens, 11.3 -> 11.05 us)
+  const int rng0 = rng[0], rng1 = rng[1];
+  int L = p.seq_lens[b];
+  asm volatile("" : "+s"(L) : "s"(rng0), "s"(rng1));
   if (L <= 0) {
     if (lane == 0) p.lse[row] = -INFINITY;
     for (int d = lane; d < DV; d += 64) {
@@ -595,13 +605,7 @@ __global__ __launch_bounds__(64) void flex_combine_kernel(DevParams p) {
     }
     return;
   }
-  const int g = (int)fast_div((unsigned)h, p.fd_gq);
-  const int lr = t * p.g_q + (h - g * p.g_q);  // row within the group
-  const int HB = p.h_c / GPW, NSTR = HB * p.flex_rb;
-  const int strand = GPW == 2 ? g / 2 : (lr / 16) * HB + g;
-  const int r16 = GPW == 2 ? (g % 2) * 8 + lr : lr % 16;
-  const int32_t* rng = p.flex_rng + ((int64_t)b * NSTR + strand) * 2;
-  const int c_first = rng[0] >> 1, slot_first = rng[0] & 1, c_last = rng[1];
+  const int c_first = rng0 >> 1, slot_first = rng0 & 1, c_last = rng1;
   if (c_first == c_last) return;  // one chunk held the whole sequence: written by the main kernel
   auto slot_of = [&](int c) -> int64_t {
     return (((int64_t)c * NSTR + strand) * 2 + (c == c_first ? slot_first : 0)) * 16 + r16;
