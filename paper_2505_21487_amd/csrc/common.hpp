@@ -101,6 +101,7 @@ __device__ __forceinline__ void fetch_params() {
       "s_waitcnt lgkmcnt(0)"
       : "=&s"(t0), "=&s"(t1), "=&s"(t2), "=&s"(t3), "=&s"(t4), "=&s"(t5), "=&s"(t6), "=&s"(t7)
       : "s"(args));
+  asm volatile("" ::"s"(t0), "s"(t1), "s"(t2), "s"(t3), "s"(t4), "s"(t5), "s"(t6), "s"(t7));  // (none of them unused; no instruction)
 }
 
 // Over the 64 lanes with data-parallel-primitive moves (no LDS round trips): shifts by 1, 2, 4, 8 inside each row of 16
