@@ -1,7 +1,7 @@
 """Build step: compiles the HIP sources into the C-ABI shared library, in-tree.
 
     python -m paper_2505_21487_amd.build            # build the library
-    python -m paper_2505_21487_amd.build --check    # code-generation check (see check_register_windows)
+    python -m paper_2505_21487_amd.build --check    # code-generation checks (check_register_windows, check_uniform_loads)
 """
 from __future__ import annotations
 
@@ -107,8 +107,98 @@ def check_register_windows(verbose: bool = True) -> list:
     return found
 
 
+def device_code(lib: str = LIB) -> str:
+    """Disassembly of the built library's device code object."""
+    llvm = os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "llvm", "bin")
+    with tempfile.TemporaryDirectory() as tmp:
+        fat, obj = os.path.join(tmp, "fat"), os.path.join(tmp, "gfx950.o")
+        subprocess.check_call([os.path.join(llvm, "llvm-objcopy"), "--dump-section", ".hip_fatbin=" + fat, lib, os.devnull])
+        subprocess.check_call([os.path.join(llvm, "clang-offload-bundler"), "--unbundle", "--type=o", "--input=" + fat,
+                               "--targets=hipv4-amdgcn-amd-amdhsa--gfx950", "--output=" + obj])
+        return subprocess.check_output([os.path.join(llvm, "llvm-objdump"), "-d", "--no-show-raw-insn", obj], text=True)
+
+
+# tuned_main_kernel<DV, DN, DR, NG, WPG, KS, TOK, STAGES, PM, STREAM> in page modes 0 and 1
+_UNIFORM_LOADS = re.compile(r"tuned_main_kernelI(?:Li\d+E){8}Li[01]E")
+
+
+def _sgprs(operand: str) -> set:
+    """Scalar registers of an operand (vcc: 106 and 107)."""
+    m = re.match(r"s\[(\d+):(\d+)\]|s(\d+)\b", operand)
+    if m:
+        return {int(m.group(3))} if m.group(3) else set(range(int(m.group(1)), int(m.group(2)) + 1))
+    return {"vcc": {106, 107}, "vcc_lo": {106}, "vcc_hi": {107}}.get(operand.split(" ")[0], set())
+
+
+def check_uniform_loads(text: str) -> list:
+    """Checks, in a disassembly, what the compiler does not see of direct-to-LDS loads written in assembly with a scalar base.
+
+    In every kernel: a vector-memory instruction reads a scalar base at the earliest five wait states after a vector
+    instruction wrote it, on every path to it.  In the kernels whose tile loads are assembly: m0 is written by nothing but
+    "s_mov_b32 m0" with a wait state behind it, used by no load but those, and a load with an offset follows the one 1024 bytes
+    before it with m0 untouched.  Returns one description per kernel of the second kind; raises on a violation."""
+    found = []
+    for fn in re.split(r"\n(?=[0-9a-f]+ <)", text):
+        head = re.match(r"\s*([0-9a-f]+) <(\S+)>:", fn)
+        if not head or "s_endpgm" not in fn:
+            continue
+        base, name = int(head.group(1), 16), head.group(2)
+        ops, at, jumps = [], {}, {}
+        for line in fn.split("\n")[1:]:
+            m = re.match(r"\s+(\S+)\s*(.*?)\s*// ([0-9A-F]+):(.*)", line)
+            if not m:
+                continue
+            at[int(m.group(3), 16)] = len(ops)
+            target = re.search(r"<\S+?(?:\+0x([0-9a-f]+))?>", m.group(4)) if m.group(1).startswith(("s_cbranch", "s_branch")) else None
+            if target:
+                jumps.setdefault(base + int(target.group(1) or "0", 16), []).append(len(ops))
+            ops.append((m.group(1), [x.strip() for x in m.group(2).split(",")]))
+        into = {at[a]: src for a, src in jumps.items()}
+
+        def before(i):  # the instructions that may run directly ahead of the i-th
+            prev = [] if i == 0 or ops[i - 1][0] in ("s_branch", "s_endpgm") else [i - 1]
+            return prev + into.get(i, [])
+
+        for i, (op, args) in enumerate(ops):
+            if not op.startswith(("global_", "buffer_", "scratch_")):
+                continue
+            regs = set().union(*[_sgprs(a) for a in args])
+            todo, seen = [(j, 0) for j in before(i)] if regs else [], set()
+            while todo:
+                j, states = todo.pop()
+                if states >= 5 or (j, states) in seen:
+                    continue
+                seen.add((j, states))
+                o, a = ops[j]
+                # (a scalar result is the first operand or, of carries, products with one and scaled divisions, the second)
+                vector = re.match(r"v(\d|\[)", a[0])
+                second = re.match(r"v_(add_co|addc_co|sub_co|subb_co|subrev_co|subbrev_co|div_scale|mad_[iu]64)", o)
+                if o.startswith("v_") and regs & (_sgprs(a[1]) if vector and second else _sgprs(a[0])):
+                    raise RuntimeError(f"{name}: {op} {', '.join(args)} reads a base written {states} wait states before by {o} {', '.join(a)}")
+                todo += [(k, states + (int(a[0], 0) + 1 if o == "s_nop" else 1)) for k in before(j)]
+
+        if not _UNIFORM_LOADS.search(name):
+            continue
+        offset, loads = None, 0  # offset: of the last load since m0 was written; -1024 right behind that
+        for i, (op, args) in enumerate(ops):
+            if "_lds_" in op:
+                m = re.match(r"s\[\d+:\d+\](?: offset:(\d+))?", args[-1])
+                if not op.startswith("global_load_lds") or not m or offset is None or int(m.group(1) or 0) != offset + 1024:
+                    raise RuntimeError(f"{name}: {op} {', '.join(args)} is not one of the tile loads, or not behind the write of m0 meant for it")
+                offset, loads = offset + 1024, loads + 1
+            elif any(re.search(r"\bm0\b", a) for a in args):
+                if op != "s_mov_b32" or args[0] != "m0" or ops[i + 1][0] != "s_nop":
+                    raise RuntimeError(f"{name}: m0 in {op} {', '.join(args)}")
+                offset = -1024
+            elif op.startswith(("s_sendmsg", "s_movrel", "v_movrel", "ds_gws", "v_interp")) or "addtid" in op:
+                raise RuntimeError(f"{name}: {op} uses m0")
+        found.append(f"{name}: {loads} tile loads")
+    return found
+
+
 if __name__ == "__main__":
     if sys.argv[1:] == ["--check"]:
         check_register_windows()
+        print("\n".join(check_uniform_loads(device_code())))
     else:
         build(extra_flags=sys.argv[1:])

@@ -185,9 +185,12 @@ __device__ __forceinline__ void load_window(int cond, const int32_t* row, int o0
 }
 
 // Direct-to-LDS load of 16 bytes per lane from a uniform base and a 32-bit offset per lane: IMM bytes past both addresses.
-// SET: sets m0, the LDS address; the loads that follow with the same dst leave it (a kernel with these has nothing else that
-// writes m0 in between: other loads to LDS are assembly too).  The compiler's builtin takes a 64-bit address per lane, which
-// costs an addition per load.  STREAM: with the streaming hint.
+// SET: sets m0, the LDS address; the loads that follow with the same dst leave it.  The compiler's builtin takes a 64-bit
+// address per lane, which costs an addition per load.  STREAM: with the streaming hint.
+// Two things the compiler does not know of these statements, and which the build's check of the library's code holds for every
+// kernel that has them (check_uniform_loads in build.py): nothing else writes or uses m0 there, and no vector instruction (a
+// register reload, a readfirstlane) writes the base within the five wait states before a load.  (A clobber of m0 cannot be
+// stated: the compiler reserves the register and warns.)
 template <int IMM, bool SET, bool STREAM>
 __device__ __forceinline__ void load_lds_b128(const unsigned char* base, unsigned off, const unsigned char* dst) {
   // (a wait state between m0 and the load that uses it)

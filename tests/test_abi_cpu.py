@@ -203,6 +203,45 @@ def test_register_page_windows_keep_their_registers():
     assert len(found) == 2
 
 
+# a kernel as the disassembler prints it; the loop's back edge leads to the load
+LOADS = """0000000000001000 <_ZN3gla17tuned_main_kernelILi256ELi256ELi64ELi2ELi2ELi1ELi32ELi4ELi0ELb0EEEvNS_9DevParamsE>:
+\t{early}                          // 000000001000: 00000000
+\ts_mov_b32 m0, s8                 // 000000001004: 00000000
+\ts_nop 0                          // 000000001008: 00000000
+\t{middle}                         // 00000000100C: 00000000
+\tglobal_load_lds_dwordx4 v1, s[4:5] // 000000001010: 00000000 00000000
+\tv_add_u32_e32 v3, s4, v2          // 000000001018: 00000000
+\tglobal_load_lds_dwordx4 v1, s[4:5] offset:{second} nt // 00000000101C: 00000000 00000000
+\t{late}                           // 000000001024: 00000000
+\ts_nop 0                          // 000000001028: 00000000
+\ts_cbranch_scc1 65527             // 00000000102C: BF85FFF7 <_ZN3gla17tuned_main_kernelILi256ELi256ELi64ELi2ELi2ELi1ELi32ELi4ELi0ELb0EEEvNS_9DevParamsE+0x{target}>
+\ts_endpgm                         // 000000001030: 00000000"""
+SOUND = dict(early="v_readfirstlane_b32 s9, v0", middle="s_nop 0", second=1024, late="v_readlane_b32 s6, v0, 3", target="4")
+
+
+@pytest.mark.parametrize("change", [
+    dict(early="v_readfirstlane_b32 s5, v0"), dict(middle="v_readlane_b32 s4, v0, 3"), dict(middle="v_cmp_eq_u32_e64 s[4:5], v0, v1"),
+    dict(late="v_readlane_b32 s4, v0, 3", target="10"),  # (around the loop: two wait states)
+    dict(middle="v_add_co_u32_e64 v4, s[4:5], v0, v1"), dict(second=2048), dict(second=0), dict(middle="s_add_i32 m0, s8, 4"),
+    dict(middle="s_mov_b32 m0, s9"), dict(middle="global_load_lds_dwordx4 v[2:3], off"), dict(middle="ds_gws_init v0")])
+def test_check_of_uniform_loads_finds(change):
+    from paper_2505_21487_amd import build
+
+    for sound in (SOUND, dict(SOUND, early="s_mov_b32 s4, s6"), dict(SOUND, late="v_readlane_b32 s4, v0, 3", middle="s_nop 4")):
+        assert len(build.check_uniform_loads(LOADS.format(**sound))) == 1
+    with pytest.raises(RuntimeError):
+        build.check_uniform_loads(LOADS.format(**dict(SOUND, **change)))
+
+
+def test_uniform_loads_of_the_library():
+    """Tile loads with a scalar base are assembly statements that rely on m0 staying as it is and on wait states the compiler
+    does not place for them: the built library's code is checked for both, in each of the 52 kernels that have such loads."""
+    from paper_2505_21487_amd import build
+
+    gla.load_library()
+    assert len(build.check_uniform_loads(build.device_code())) == 52
+
+
 def test_bench_refuses_more_than_one_gpu():
     """One GPU only: `bench.py --gpus N` with N above 1 (or a WORLD_SIZE above 1) exits with a message that says
     so, before anything touches a GPU."""
