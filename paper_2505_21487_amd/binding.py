@@ -301,11 +301,12 @@ def _proj(sum_groups: bool, a: torch.Tensor, w: torch.Tensor, *, out=None, out_d
     p = GlaProjParams(M, G, N, K, a.data_ptr(), a_row, a_group, w.data_ptr(), out.data_ptr(), out.stride(0),
                       0 if sum_groups else out.stride(1), _OUT_CODE[out.dtype])
     ref = ctypes.byref(p)
-    if workspace is None:
+    if workspace is None or not a.is_cuda:  # (not on a GPU: the shape is judged first, the stream refuses the rest)
         need = int(lib.gla_proj_workspace_size(ref, int(sum_groups)))
         if need == 0:
             raise GlaError(GLA_ERR_UNSUPPORTED_SHAPE)
-        workspace = torch.empty(need, dtype=torch.uint8, device=dev)
+        if workspace is None:
+            workspace = torch.empty(need, dtype=torch.uint8, device=dev)
     p.workspace, p.workspace_bytes = workspace.data_ptr(), workspace.numel() * workspace.element_size()
     p.stream = _stream_of(dev)
     run = lib.gla_output_proj if sum_groups else lib.gla_absorb_query

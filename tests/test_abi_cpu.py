@@ -6,6 +6,7 @@ import os
 import re
 
 import pytest
+import torch
 
 import paper_2505_21487_amd as gla
 from paper_2505_21487_amd import accounting
@@ -102,6 +103,15 @@ def test_page_sizes_the_tuned_kernel_takes(page_size, tuned):
         want = gla.GLA_IMPL_TUNED if tuned else gla.GLA_IMPL_GENERIC
         assert gla.gla_decode_select_impl(p, is_gta) == want
         assert gla.gla_decode_workspace_size(p, is_gta) > 0
+
+
+def test_projections_judge_the_shape_first_with_or_without_a_workspace():
+    a, w = torch.zeros(4, 2, 64, dtype=torch.bfloat16), torch.zeros(2, 30, 64, dtype=torch.bfloat16)  # n % 32 != 0
+    for workspace in (None, torch.empty(1 << 16, dtype=torch.uint8)):
+        for run in (gla.gla_absorb_query, gla.gla_output_proj):
+            with pytest.raises(gla.GlaError) as e:
+                run(a, w, workspace=workspace)
+            assert e.value.status == gla.GLA_ERR_UNSUPPORTED_SHAPE
 
 
 def test_empty_batch_is_ok():
