@@ -577,8 +577,10 @@ int run_proj(const gla_proj_params* p, int sum_groups) {
   // Placed by the kernel from 17 rows on (a grid in plain order / placed, us: 2 x 5120 x 4096, 3 rows 17.2 / 18.2, 12 rows 18.2 /
   // 18.7, 24 rows 19.4 / 19.3, 40 rows 21.9 / 21.2; 1 x 5120 x 16384, 2 rows 30.0 / 30.5, 20 rows 32.6 / 32.4; 64 rows of 128 heads x
   // 256 x 128 5.6 / 5.1, 200 rows 13.2 / 11.7; output projection of the benchmark 70.2 / 60.7).
-  // (A launch holds fewer than 2^32 threads per dimension: a list of 2^24 workgroups and more keeps its three.)
-  const bool placed = p->rows > 16 && plan.mt * plan.nt > 1 && (uint64_t)blocks * tiles * slices < (1u << 24);
+  // (One dimension of a launch holds fewer than 2^24 workgroups of 256 threads.  The list is shorter: at most 2^31 results, at
+  // least some 33 rows x 32 features each, make 2^21 workgroups per range, and proj_plan cuts the sums of no more than 1000 rounds
+  // of workgroups, into 64 ranges at most.)
+  const bool placed = p->rows > 16 && plan.mt * plan.nt > 1;
   const dim3 grid = placed ? dim3(blocks * tiles * slices) : dim3(blocks, tiles, slices);
   d.total = placed ? grid.x : 0;
   d.tiles = tiles;

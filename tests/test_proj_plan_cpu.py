@@ -1,7 +1,9 @@
 """Which projection kernel a call runs and how its sums are cut, from shapes alone (256 compute units): the host code is
 compiled by itself."""
 import ctypes
+import math
 import os
+import random
 import subprocess
 
 import pytest
@@ -82,3 +84,22 @@ def test_ranges_cover_the_sum(lib):
                     q = plan(lib, rows, groups, n, k, sum_groups, small)
                     assert (q["ranges"] - 1) * q["features"] < k <= q["ranges"] * q["features"] and q["features"] % 64 == 0
                     assert small == 0 or q["mt"] <= 2
+
+
+def test_a_list_of_workgroups_fits_one_dimension_of_a_launch(lib):
+    """The projections' grids have one dimension: fewer than 2^32 threads, 2^24 workgroups.  Sums of 2^30 features and more
+    than 2^20 rows or output features are no calls anyone makes, but the plan takes them."""
+    rng = random.Random(5)
+    longest = 0
+    for i in range(60000):
+        rows = min(17 + int(2 ** rng.uniform(0, 20)), 64 * 65535)
+        n, k = 32 * int(2 ** rng.uniform(0, 20)), 64 * int(2 ** rng.uniform(0, 24))
+        most = min(0x7fffffff // (rows * n), 65535)
+        if most < 1:
+            continue
+        groups = most if i % 2 else int(2 ** rng.uniform(0, math.log2(most)))
+        q = plan(lib, rows, groups, n, k, i % 3 % 2)
+        blocks, tiles, slices = -(-n // (128 * q["nt"])), -(-rows // (32 * q["mt"])), groups * q["ranges"]
+        if q["mt"] * q["nt"] > 1 and tiles <= 65535 and slices <= 65535:
+            longest = max(longest, blocks * tiles * slices)
+    assert 2 ** 20 < longest < 2 ** 24, longest
