@@ -13,10 +13,25 @@ from test_proj_gpu import check_projection
 pytestmark = pytest.mark.gpu
 
 
-# (rows, groups, output features, input features): 41 blocks or fewer of features, grids that do not divide by eight, ranges of
-# fewer steps than the ring has stages and of an odd number of them, a last block of 32 features
-@pytest.mark.parametrize("M", [16, 17, 65])
-@pytest.mark.parametrize("G,N,K", [(1, 10400, 3136), (3, 1312, 6208), (2, 4128, 1600)])
+# What a call's plan makes of it at 256 compute units, held on the CPU in test_proj_plan_cpu.py.
+# (rows, groups, output features, input features) -> 32-row and 32-feature blocks, ranges, steps of a range and of the last one
+OUTPUT_PROJ = {
+    # few blocks of features, grids that do not divide by eight, ranges of an odd number of steps, a last block of 32 features
+    (16, 1, 10400, 3136): (1, 2, 6, 9, 4), (17, 1, 10400, 3136): (1, 2, 6, 9, 4), (65, 1, 10400, 3136): (4, 2, 6, 9, 4),
+    (16, 3, 1312, 6208): (1, 2, 11, 9, 7), (17, 3, 1312, 6208): (1, 2, 11, 9, 7), (65, 3, 1312, 6208): (4, 2, 11, 9, 7),
+    # the variant without either (one block of 32 rows and features) beside the one with both
+    (16, 2, 4128, 1600): (1, 1, 1, 25, 25), (17, 2, 4128, 1600): (1, 1, 1, 25, 25), (65, 2, 4128, 1600): (2, 1, 1, 25, 25),
+    # a last range of fewer steps than the ring has stages (three with 64 features per wave)
+    (16, 3, 1088, 6976): (1, 2, 13, 9, 1), (17, 3, 832, 9280): (1, 2, 17, 9, 1), (33, 3, 1312, 5824): (2, 2, 11, 9, 1),
+    (65, 2, 1088, 8512): (2, 2, 12, 12, 1), (100, 2, 1152, 8576): (2, 2, 12, 12, 2), (100, 3, 1056, 6976): (4, 2, 13, 9, 1),
+}
+ABSORB = {
+    (33, 77, 160, 64): (2, 1, 1, 1, 1), (65, 13, 544, 192): (2, 1, 1, 3, 3), (17, 21, 288, 2048): (1, 1, 4, 8, 8),
+    (33, 77, 160, 128): (2, 1, 1, 2, 2), (66, 33000, 32, 64): (2, 1, 1, 1, 1), (34, 33000, 160, 128): (2, 1, 1, 2, 2),
+}
+
+
+@pytest.mark.parametrize("M,G,N,K", sorted(OUTPUT_PROJ))
 def test_output_proj(M, G, N, K):
     g = torch.Generator().manual_seed(840 + M + G)
     a = (torch.randn(M, G, K, generator=g) * 0.05).to(torch.bfloat16)
@@ -28,16 +43,18 @@ def test_output_proj(M, G, N, K):
     check_projection(c.double().cpu().numpy(), ref, abs_prod, bf16_out=False, what=f"out-proj {M}x{G}x{N}x{K}")
 
 
-@pytest.mark.parametrize("M,G,N,K", [(33, 77, 160, 64), (65, 13, 544, 192), (17, 21, 288, 2048), (66, 33000, 32, 64)])
+@pytest.mark.parametrize("M,G,N,K", sorted(ABSORB))
 def test_absorb_query(M, G, N, K):
-    """The last has more than 2^16 workgroups."""
+    """(33, 77, 160, 128): two steps, the second block starts at the second.  33000 groups: more than 2^16 workgroups, with one
+    block of features and with two, where the kernel divides by both."""
     gen = torch.Generator(device="cuda").manual_seed(850 + M)
     a = torch.randn(M, G, K, generator=gen, device="cuda", dtype=torch.bfloat16)
     w = (torch.randn(G, N, K, generator=gen, device="cuda", dtype=torch.bfloat16) / K ** 0.5).to(torch.bfloat16)
-    c = gla.gla_absorb_query(a, w, out_dtype=torch.float32)
+    c = torch.full((M, G, N), float("nan"), device="cuda")  # (a result that no workgroup wrote shows)
+    gla.gla_absorb_query(a, w, out=c)
     torch.cuda.synchronize()
     assert bool(torch.isfinite(c).all())
-    some = sorted({0, 1, G // 3, G // 2, G - 2, G - 1})
+    some = sorted({0, 1, G // 3, G // 2, G - 2, G - 1, *range(0, G, max(1, G // 50))})
     a, w, c = a[:, some].cpu(), w[some].cpu(), c[:, some].double().cpu().numpy()
     ref = oracle.project(bf16_bits(a), bf16_bits(w), sum_groups=False)
     abs_prod = np.einsum("mgk,gnk->mgn", np.abs(a.double().numpy()), np.abs(w.double().numpy()))

@@ -10,6 +10,8 @@ import pytest
 
 from paper_2505_21487_amd.binding import GlaProjParams
 
+from test_proj_placement_gpu import ABSORB as PLACED_ABSORB, OUTPUT_PROJ
+
 CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2505_21487_amd", "csrc")
 SOURCE = r"""
 #include "proj_plan.hpp"
@@ -103,3 +105,11 @@ def test_a_list_of_workgroups_fits_one_dimension_of_a_launch(lib):
         if q["mt"] * q["nt"] > 1 and tiles <= 65535 and slices <= 65535:
             longest = max(longest, blocks * tiles * slices)
     assert 2 ** 20 < longest < 2 ** 24, longest
+
+
+@pytest.mark.parametrize("sum_groups,cases", [(1, OUTPUT_PROJ), (0, PLACED_ABSORB)])
+def test_the_placement_tests_reach_what_they_are_for(lib, sum_groups, cases):
+    for shape, (mt, nt, ranges, steps, last) in cases.items():
+        q = plan(lib, *shape, sum_groups)
+        assert (q["mt"], q["nt"], q["ranges"], q["features"] // 64) == (mt, nt, ranges, steps), (shape, q)
+        assert shape[3] // 64 - (ranges - 1) * steps == last, shape
