@@ -70,7 +70,7 @@ struct DevParams {
   int64_t stream_min_bytes; // second MFMA kernel: a batch with more cache bytes than this is fetched with the streaming hint
   int32_t flex_rb;          // flex kernel: blocks of 16 query rows per group
   int32_t* flex_rng;        // flex kernel: per (sequence, strand) the first chunk holding a piece of it (x 2 + its slot) and the last
-  // tuned kernel: flat partition of all key tiles of the batch into chunks
+  // four-wave, eight-wave and second MFMA kernel: flat partition of all key tiles of the batch into chunks
   int32_t num_chunks;       // chunks of the tile list (the main kernel runs one workgroup per chunk and row block)
   int32_t chunk_tiles;      // > 0: fixed tiles per chunk; 0: ceil(total / num_chunks)
   int32_t setup_tiles;      // chunks derived on the device: tiles' worth of time that a chunk's step into another unit costs (cut_list)
@@ -81,7 +81,15 @@ struct DevParams {
   int32_t xcd_map;          // 1: grid is a multiple of 8 * mb, chunks are laid out per XCD
   int32_t tiles_full;       // tiles of a sequence that fills its page-table row
   int32_t chunk_guess;      // chunk length if every sequence did
-  FastDiv fd_mb, fd_chunks, fd_gq, fd_tiles_full, fd_units_full, fd_upb_mb;
+  // Divisors.  Chunks and query heads per group for every kernel with a tile list; the others share their places: one name for the
+  // four- and eight-wave kernels, one for the second MFMA kernel (what it divides the number of a wave or of a result row by).
+  // Code that both run, cut_list and the rest of tuned_device.hpp, reads neither.  (Places of their own among the generic
+  // kernels' fields, two cache lines away, cost the second MFMA kernel 0.2 us: 31.07 -> 31.32.)
+  union { FastDiv fd_mb, fd_strands; };
+  FastDiv fd_chunks, fd_gq;
+  union { FastDiv fd_tiles_full, fd_heads; };
+  union { FastDiv fd_units_full, fd_q_len; };
+  union { FastDiv fd_upb_mb, fd_group_blocks; };
   int32_t merge_sets_lg, merge_span, merge_windows;  // merge kernel: log2(sets of every unit), chunks per window, windows (tuned_combine_kernel)
   int32_t wide_tiles;       // > 0: the eight-wave kernel runs if the list has that many tiles of 32 tokens, else the four-wave one
 };

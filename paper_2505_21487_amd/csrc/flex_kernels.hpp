@@ -160,9 +160,9 @@ __global__ __launch_bounds__(256) void flex_main_kernel(DevParams p) {
   const unsigned NSTR = HB * (unsigned)p.flex_rb;        // strands
   const unsigned unit = blockIdx.x * 4u + (unsigned)wave;  // (the host keeps the number of waves below 2^31)
   if (unit >= NSTR * (unsigned)p.num_chunks) return;
-  const int chunk = (int)fast_div(unit, p.fd_mb);  // / NSTR
+  const int chunk = (int)fast_div(unit, p.fd_strands);
   const int strand = (int)(unit - (unsigned)chunk * NSTR);
-  const int rb = (int)fast_div((unsigned)strand, p.fd_upb_mb);  // / HB
+  const int rb = (int)fast_div((unsigned)strand, p.fd_group_blocks);
   const int g0 = (strand - rb * (int)HB) * GPW;  // first group of this wave
   const int L_first = lane < p.B ? p.seq_lens[lane] : 0;
   const ListCut cut = cut_list<32, 128, FT::kPieces>(p, 1, lane, L_first, (int)NSTR);
@@ -581,9 +581,9 @@ template <int DV, int GPW>
 __global__ __launch_bounds__(64) void flex_combine_kernel(DevParams p) {
   const int row = blockIdx.x;
   const int lane = threadIdx.x;
-  const int bt = (int)fast_div((unsigned)row, p.fd_tiles_full);  // / h_q
+  const int bt = (int)fast_div((unsigned)row, p.fd_heads);
   const int h = row - bt * p.h_q;
-  const int b = (int)fast_div((unsigned)bt, p.fd_units_full);  // / T
+  const int b = (int)fast_div((unsigned)bt, p.fd_q_len);
   const int t = bt - b * p.T;
   const int64_t base = b * p.out_s[0] + t * p.out_s[1] + h * p.out_s[2];
   const int g = (int)fast_div((unsigned)h, p.fd_gq);

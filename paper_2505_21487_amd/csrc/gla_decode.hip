@@ -288,12 +288,11 @@ int launch_flex(const gla_decode_params* p, const FlexPlan& plan, DevParams& d, 
   d.flex_rb = plan.rb;
   d.setup_tiles = setup_tiles(kSetupTilesFlex, plan.list_bound);
   d.fd_chunks = make_fastdiv((uint32_t)plan.chunks);
-  // what its kernels divide a row's or a wave's number by
-  d.fd_mb = make_fastdiv((uint32_t)plan.strands);
-  d.fd_upb_mb = make_fastdiv((uint32_t)(p->num_groups / plan.gpw));
+  d.fd_strands = make_fastdiv((uint32_t)plan.strands);
+  d.fd_group_blocks = make_fastdiv((uint32_t)(p->num_groups / plan.gpw));
+  d.fd_heads = make_fastdiv((uint32_t)p->num_q_heads);
+  d.fd_q_len = make_fastdiv((uint32_t)p->q_len);
   d.fd_gq = make_fastdiv((uint32_t)(p->num_q_heads / p->num_groups));
-  d.fd_tiles_full = make_fastdiv((uint32_t)p->num_q_heads);
-  d.fd_units_full = make_fastdiv((uint32_t)p->q_len);
   int lg = 0;
   while ((1 << lg) < p->page_size) ++lg;
   d.lg_page = lg;
