@@ -573,20 +573,17 @@ int run_proj(const gla_proj_params* p, int sum_groups) {
   const unsigned blocks = (unsigned)((p->n + wg_n - 1) / wg_n), tiles = (unsigned)((p->rows + 32 * plan.mt - 1) / (32 * plan.mt));
   const unsigned slices = (unsigned)(p->groups * plan.ksplit);
   if (tiles > 65535u || slices > 65535u) return GLA_ERR_UNSUPPORTED_SHAPE;
-  // Placed by the kernel from 17 rows on (a grid in plain order / placed, us: 2 x 5120 x 4096, 3 rows 17.2 / 18.2, 12 rows 18.2 /
-  // 18.7, 24 rows 19.4 / 19.3, 40 rows 21.9 / 21.2; 1 x 5120 x 16384, 2 rows 30.0 / 30.5, 20 rows 32.6 / 32.4; 64 rows of 128 heads x
-  // 256 x 128 5.6 / 5.1, 200 rows 13.2 / 11.7; output projection of the benchmark 70.2 / 60.7).
   // (One dimension of a launch holds fewer than 2^24 workgroups of 256 threads.  The list is shorter: at most 2^31 results, at
   // least some 33 rows x 32 features each, make 2^21 workgroups per range, and proj_plan cuts the sums of no more than 1000 rounds
   // of workgroups, into 64 ranges at most.)
-  const bool placed = p->rows > 16 && plan.mt * plan.nt > 1;
-  const dim3 grid = placed ? dim3(blocks * tiles * slices) : dim3(blocks, tiles, slices);
-  d.total = placed ? grid.x : 0;
+  const dim3 grid = plan.placed ? dim3(blocks * tiles * slices) : dim3(blocks, tiles, slices);
+  d.total = plan.placed ? grid.x : 0;
   d.tiles = tiles;
   d.blocks = blocks;
   d.by_tiles = proj_reciprocal(tiles);
   d.by_blocks = proj_reciprocal(blocks);
   d.by_ksplit = proj_reciprocal((uint32_t)plan.ksplit);
+  d.start = plan.rotated ? d.by_blocks : 0;
   if (plan.nt == 2) {
     if (plan.mt == 1) launch_proj_long<1>(plan.stream, grid, st, d);
     else if (plan.mt == 2) launch_proj_long<2>(plan.stream, grid, st, d);

@@ -45,7 +45,7 @@ typedef __attribute__((ext_vector_type(8))) __bf16 proj_bf16x8_t;
 typedef __attribute__((ext_vector_type(16))) float proj_f32x16_t;
 typedef __attribute__((ext_vector_type(4))) float proj_f32x4_t;
 
-// (128 bytes with the runtime's share left out: two cache lines that a workgroup waits for first)
+// (124 bytes, the runtime's share left out: two cache lines that a workgroup waits for first)
 struct ProjParams {
   const uint16_t* a;
   const uint16_t* w;
@@ -59,6 +59,7 @@ struct ProjParams {
   uint32_t total;                           // > 0: a grid of that many workgroups, placed by the kernel; 0: (blocks, row tiles, slices)
   uint32_t tiles, blocks;                   // row tiles, blocks of output features
   uint32_t by_tiles, by_blocks, by_ksplit;  // reciprocals, see proj_div
+  uint32_t start;                           // blocks start at different steps: the reciprocal of their number; else 0
 };
 static_assert(sizeof(ProjParams) <= 128, "two cache lines");
 
@@ -78,10 +79,15 @@ __global__ __launch_bounds__(256) void proj_kernel(ProjParams p) {
   // Workgroups are dealt round-robin to the 8 XCDs.  Placed, each XCD gets a contiguous run of the list of (group and range,
   // block of output features, row tile), the row tile innermost: the row tiles of a block share its weights through one L2,
   // and of the query rows an XCD fetches the few ranges its run holds, not all of them (64 rows x 32768 features: 1 MB instead
-  // of 4.2).  With few query rows there is nothing to share: see run_proj.
-  constexpr bool kLong = MT * NT > 1;  // (short sums over few rows are over before any of this pays: 5.5 -> 5.8 us)
+  // of 4.2).  Which calls are placed: see proj_plan.
+  constexpr bool kPlaced = MT * NT > 1;  // (one block of 32 rows and features has neither this nor the start offsets below)
+  // All parameters in one round trip.  The compiler would ask for those behind the placement's branch only there (128 heads x 512
+  // x 128, one row 5.99 -> 5.86 us).  Nothing to gain where there is no branch, nor with 128 rows.
+  if constexpr (kPlaced && MT < 4)
+    asm volatile("" ::"s"(p.a), "s"(p.w), "s"(p.a_row), "s"(p.a_group), "s"(p.M), "s"(p.N), "s"(p.K), "s"(p.ksplit), "s"(p.k_per_split),
+                 "s"(p.total), "s"(p.tiles), "s"(p.blocks), "s"(p.by_tiles), "s"(p.by_blocks), "s"(p.by_ksplit), "s"(p.start));
   unsigned bx = blockIdx.x, tile = blockIdx.y, bz = blockIdx.z;
-  if (kLong && p.total > 0) {
+  if (kPlaced && p.total > 0) {
     const unsigned total = p.total, xcd = blockIdx.x & 7;
     const unsigned id = xcd * (total >> 3) + min(xcd, total & 7) + (blockIdx.x >> 3), xz = proj_div(id, p.tiles, p.by_tiles, total);
     tile = id - xz * p.tiles;
@@ -144,15 +150,14 @@ __global__ __launch_bounds__(256) void proj_kernel(ProjParams p) {
 
   constexpr int LPS = 4 * NT + MT;  // loads per wave and stage
   static_assert(LPS * (NST - 2) <= 63, "vmcnt range");
-  // The blocks of output features start at different steps of their range and wrap around.  In step they would all read the
-  // same columns of rows that lie a power of two or so apart, hence through few of the memory channels at a time.  A kernel
-  // that only loads, in this order, with and without the offsets: 335 MB (2 x 5120 x 16384) 50.5 / 53.3 us, 268 MB (2 x 8192 x 8192)
-  // 41.2 / 64.8; this one 60.7 / 67.0 (64 rows) and 46.6 / 76.0 (32 rows), offsets without the placement above 70.2, the
-  // placement without offsets 76.9.
-  const int steps = (k_end - k_begin) / 64, first = kLong ? (int)__umulhi(bx * p.by_blocks, (unsigned)steps) : 0;
+  // The blocks of output features may start at different steps of their range and wrap around (which calls do: see proj_plan).
+  // In step they would all read the same columns of rows that lie a power of two or so apart, hence through few of the memory
+  // channels at a time.  A kernel that only loads, in this order, with and without the offsets: 335 MB (2 x 5120 x 16384) 50.5 /
+  // 53.3 us, 268 MB (2 x 8192 x 8192) 41.2 / 64.8; this one on the first, 64 rows, placed 60.7 / 73.5.
+  const int steps = (k_end - k_begin) >> 6, first = kPlaced ? (int)__umulhi(bx * p.start, (unsigned)steps) : 0;
   auto feature = [&](int i) {  // first input feature of step i (steps past the end fetch the last one again)
     const int j = min(i, steps - 1) + first;
-    return k_begin + 64 * (!kLong || j < steps ? j : j - steps);
+    return k_begin + 64 * (!kPlaced || j < steps ? j : j - steps);
   };
 #pragma unroll
   for (int st = 0; st < NST - 1; ++st) issue(feature(st), st);
@@ -227,7 +232,7 @@ __global__ __launch_bounds__(256) void proj_kernel(ProjParams p) {
 // lie side by side with it in memory.  An attention block alternates between them and the decode's two, whose code together
 // nearly fills the 64 KB instruction cache; spread over the code object as they came, they displaced one another more often:
 // a block of 24 sequences 142.5 us, 141.9 this way, and between 141.4 and 144.2 with other orders of the same kernels.  That
-// was with the kernels of then; the same block takes 111 now.)
+// was with the kernels of then; the same block takes 105 now.)
 template __global__ void proj_kernel<1, 2, true>(ProjParams);
 template __global__ void proj_kernel<1, 1, false>(ProjParams);
 

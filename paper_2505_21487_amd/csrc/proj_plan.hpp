@@ -17,6 +17,8 @@ struct ProjPlan {
   int k_per_split;
   bool direct;     // no partials: the kernel writes the result itself
   bool stream;     // fetch the weights with the streaming hint
+  bool placed;     // workgroups are placed on the XCDs, each with a contiguous run of (range, block of features, row tile)
+  bool rotated;    // blocks of features start at different steps of their range
   size_t part_bytes;
 };
 
@@ -117,6 +119,45 @@ inline int proj_plan(const gla_proj_params* p, int sum_groups, int cus, int smal
   // 268 MB 55 -> 79).  Smaller ones may still be there (84 MB 19.1 -> 21.2), and with two row tiles the second reader finds
   // less (115.7 -> 130.0).
   plan->stream = plan->nt == 2 && row_tiles == 1 && weights > kProjCacheBytes / 2;
+  // Placement and start offsets (what they are for: proj_kernel).  us in plain order / this way, weights not in the caches:
+  //   64 features per wave, ranges of 512 features and more: placed (64 rows of 2 x 5120 x 16384 70.1 / 60.7, both with offsets,
+  //   of 16 x 2048 x 1024 24.7 / 23.8; 128 rows of 8 x 4096 x 2048 46.2 / 41.6), up to 16 rows only with many groups (8 x 4096 x
+  //   2048, 1 row 30.4 / 28.2; 16 x 2048 x 1024 17.9 / 17.6; 1 x 16384 x 1536, 16 rows 14.8 / 15.1, 4 x 5120 x 8192 56.5 / 58.4).
+  //   Offsets where rows of weights lie more than 2 KB apart (32 rows of 2 x 8192 x 8192 77 / 48, of 128 x 512 x 2048 70 / 48,
+  //   1 row of 1 x 5120 x 16384 33.4 / 30.0).  Closer rows of a block cover the channels by themselves (16 x 4096 x 512, 1 row
+  //   15.3 / 15.9; 8 x 4096 x 1024, 65 rows 21.9 / 23.2), but at 2 KB large weights still gain (64 x 1024 x 1024, 134 MB, 1 row
+  //   27.5 / 26.5).  Groups start alike: many of them with long rows are better off as they are (17 rows of 32 x 1024 x 8192 122 / 148,
+  //   of 32 x 2048 x 8192 169 / 231; not of 64 x 1024 x 4096 134 / 94, nor of 16 x 2048 x 8192 122 / 93).
+  //   32 features per wave, and short ranges: two workgroups share a compute unit at different steps, and long lists run in
+  //   rounds.  Weights of more than the last-level cache with rows more than 2 KB apart: as above (64 rows of 1 x 128256 x 8192 474 / 364,
+  //   of 32 x 8192 x 2048 250 / 212; the other way 16 x 7168 x 7168 331 / 343).  (One block of 32 rows and features has neither: offsets
+  //   alone would gain where rows lie a multiple of 4 KB apart, 1 x 128256 x 8192, 1 row 464 / 403, and cost short sums 2 %.)
+  //   Else beyond 64 rows, where the workgroups in between two row tiles of a block read more weights than the L2s hold (32 MB:
+  //   129 rows of 1 x 128256 x 1024 132 / 94; 300 rows of 8 x 5120 x 2048, 21 MB 92.7 / 97.9), or where few blocks put a block's
+  //   row tiles on different XCDs (128 heads x 256 x 128, 65 rows 8.5 / 7.0; 32 x 256 x 128, 129 rows 4.85 / 4.6; 128 x 256 x 1024,
+  //   256 rows 58 / 36), but not in short sums of few groups or on part of the chip (16 x 512 x 128, 129 rows 4.47 / 4.60, 200
+  //   rows 4.78 / 4.93).  With eight blocks and more they mostly share one anyway, and the writes suffer (32 x 7168 x 64, 65 rows 24.9 /
+  //   28.9; 4 x 1024 x 2048, 256 rows 14.3 / 16.3; 16 x 5120 x 128, 200 rows 23.4 / 24.4; the other way 1 x 4096 x 2048, 256 rows 15.8 /
+  //   14.2, 32 x 1536 x 192 21.0 / 18.6).
+  //   33 to 64 rows: one round of workgroups with long ranges (1 x 1024 x 16384, 64 rows 15.7 / 14.2; 2 x 16384 x 512 11.9 / 11.6),
+  //   not short sums (128 x 256 x 128, 64 rows 5.37 / 5.55), few weights (2 x 4096 x 1024 9.2 / 9.5) nor several rounds (8 x
+  //   5120 x 2048 39.6 / 42.9).
+  const int64_t blocks = (p->n + 128 * plan->nt - 1) / (128 * plan->nt), slices = (int64_t)p->groups * ks, list = blocks * row_tiles * slices;
+  const int64_t l2s = 32ll << 20;
+  if (plan->nt == 2 && plan->k_per_split >= 512) {
+    const bool alike = p->groups >= 32 && p->k >= 8192 && weights >= 2 * kProjCacheBytes;
+    plan->placed = !alike && (p->rows > 16 || p->groups >= 8);
+    plan->rotated = !alike && (p->k > 1024 || (p->k == 1024 && weights >= kProjCacheBytes / 2));
+  } else {
+    const bool large = p->k > 1024 && weights >= kProjCacheBytes;
+    if (p->rows <= 32) plan->placed = false;
+    else if (large) plan->placed = true;
+    else if (p->rows <= 64) plan->placed = plan->k_per_split >= 512 && weights >= l2s && list >= cus && list <= 2 * cus;
+    else
+      plan->placed = (row_tiles > 1 && (int64_t)p->n * plan->k_per_split * 2 >= l2s) ||
+                     (blocks < 8 && (plan->k_per_split >= 512 || (slices >= 32 && 4 * list >= 3 * cus)));
+    plan->rotated = large && plan->placed;
+  }
   plan->direct = ks == 1 && (!sum_groups || p->groups == 1);
   plan->part_bytes = plan->direct ? 0 : (size_t)p->groups * ks * p->rows * p->n * sizeof(float);
   return GLA_OK;

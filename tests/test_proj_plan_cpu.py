@@ -1,6 +1,7 @@
 """Which projection kernel a call runs and how its sums are cut, from shapes alone (256 compute units): the host code is
 compiled by itself."""
 import ctypes
+import itertools
 import math
 import os
 import random
@@ -15,11 +16,12 @@ from test_proj_placement_gpu import ABSORB as PLACED_ABSORB, OUTPUT_PROJ
 CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2505_21487_amd", "csrc")
 SOURCE = r"""
 #include "proj_plan.hpp"
-extern "C" int plan(const gla_proj_params* p, int sum_groups, int small, int64_t out[6]) {
+extern "C" int plan(const gla_proj_params* p, int sum_groups, int small, int64_t out[8]) {
   gla::ProjPlan q;
   const int rc = gla::proj_plan(p, sum_groups, 256, small, &q);
   if (rc != GLA_OK) return rc;
   out[0] = q.mt; out[1] = q.nt; out[2] = q.ksplit; out[3] = q.k_per_split; out[4] = q.direct; out[5] = (int64_t)q.part_bytes;
+  out[6] = q.placed; out[7] = q.rotated;
   return 0;
 }
 """
@@ -37,9 +39,9 @@ def plan(lib, rows, groups, n, k, sum_groups, small=0):
     p = GlaProjParams()
     p.rows, p.groups, p.n, p.k = rows, groups, n, k
     p.a_row_stride, p.a_group_stride, p.c_row_stride, p.c_group_stride = groups * k, k, groups * n, n
-    out = (ctypes.c_int64 * 6)()
+    out = (ctypes.c_int64 * 8)()
     assert lib.plan(ctypes.byref(p), sum_groups, small, out) == 0
-    return dict(zip(("mt", "nt", "ranges", "features", "direct", "bytes"), out))
+    return dict(zip(("mt", "nt", "ranges", "features", "direct", "bytes", "placed", "rotated"), out))
 
 
 def rows_computed(q, rows):
@@ -78,6 +80,44 @@ def test_the_faster_kernel(lib, shape):
     assert (q["mt"], q["nt"]) == FASTER[shape], q
 
 
+# ... -> (placed on the XCDs, blocks of features start at different steps): the faster order of those measured
+ORDER = {
+    # 64 features per wave, long ranges; rows of weights that lie close together
+    (64, 2, 5120, 16384, 1): (1, 1), (128, 2, 5120, 8192, 1): (1, 1), (32, 2, 8192, 8192, 1): (1, 1), (16, 1, 5120, 16384, 1): (0, 1),
+    (1, 8, 4096, 2048, 0): (1, 1), (16, 1, 16384, 1536, 0): (0, 1), (1, 64, 1024, 1024, 0): (1, 1), (1, 16, 4096, 512, 0): (1, 0),
+    (65, 8, 4096, 1024, 1): (1, 0), (17, 64, 1024, 4096, 0): (1, 1), (17, 32, 2048, 8192, 0): (0, 0), (1, 4, 5120, 8192, 1): (0, 1),
+    # 32 features per wave and short ranges: more weights than the last-level cache holds
+    (64, 1, 128256, 8192, 1): (1, 1), (64, 32, 8192, 2048, 0): (1, 1), (300, 2, 20480, 8192, 1): (1, 1), (1, 1, 128256, 8192, 1): (0, 0),
+    (32, 16, 7168, 7168, 0): (0, 0), (64, 16, 8192, 1024, 0): (0, 0),
+    # ... than the L2s do between two row tiles
+    (129, 1, 128256, 1024, 1): (1, 0), (300, 2, 28672, 1536, 1): (1, 0), (300, 8, 5120, 2048, 0): (0, 0), (65, 64, 16384, 64, 0): (0, 0),
+    # ... one row tile, few blocks of features, many, too few workgroups
+    (64, 128, 256, 128, 0): (0, 0), (32, 128, 512, 128, 0): (0, 0), (65, 128, 256, 128, 0): (1, 0), (256, 128, 256, 1024, 0): (1, 0),
+    (65, 32, 7168, 64, 0): (0, 0), (256, 4, 1024, 2048, 1): (0, 0), (200, 128, 1536, 64, 0): (0, 0), (200, 16, 5120, 128, 0): (0, 0),
+    (200, 16, 512, 128, 0): (0, 0), (129, 32, 256, 128, 0): (1, 0), (128, 32, 256, 128, 0): (0, 0), (129, 64, 128, 1024, 0): (1, 0),
+    # ... one round of long ranges, few weights, several rounds
+    (64, 1, 1024, 16384, 1): (1, 0), (33, 64, 256, 1024, 0): (1, 0), (64, 2, 4096, 1024, 1): (0, 0), (33, 8, 5120, 2048, 0): (0, 0),
+}
+
+
+@pytest.mark.parametrize("shape", sorted(ORDER))
+def test_the_faster_order(lib, shape):
+    q = plan(lib, *shape)
+    assert (q["placed"], q["rotated"]) == ORDER[shape], q
+
+
+def test_the_kernel_of_one_block_has_the_plain_order(lib):
+    """proj_kernel<1, 1> has neither the placement nor the offsets."""
+    found = 0
+    for rows, groups, n, k in itertools.product((1, 16, 17, 32, 33, 64, 65, 129), (1, 2, 8, 32, 128), (32, 160, 512, 2048, 16384), (64, 192, 512, 1024, 2048, 16384)):
+        for sum_groups, small in itertools.product((0, 1), (0, 1, 2)):
+            q = plan(lib, rows, groups, n, k, sum_groups, small)
+            if (q["mt"], q["nt"]) == (1, 1):
+                found += 1
+                assert (q["placed"], q["rotated"]) == (0, 0), (rows, groups, n, k, sum_groups, small)
+    assert found > 100
+
+
 def test_ranges_cover_the_sum(lib):
     for rows in (1, 33, 65, 100, 129, 200, 300, 500):
         for groups, n, k in ((1, 32, 64), (2, 5120, 16384), (1, 5120, 4160), (3, 1056, 12352), (4, 4096, 8192), (1, 96, 65536), (128, 512, 128)):
@@ -109,7 +149,8 @@ def test_a_list_of_workgroups_fits_one_dimension_of_a_launch(lib):
 
 @pytest.mark.parametrize("sum_groups,cases", [(1, OUTPUT_PROJ), (0, PLACED_ABSORB)])
 def test_the_placement_tests_reach_what_they_are_for(lib, sum_groups, cases):
-    for shape, (mt, nt, ranges, steps, last) in cases.items():
+    for shape, (mt, nt, ranges, steps, last, placed, rotated) in cases.items():
         q = plan(lib, *shape, sum_groups)
         assert (q["mt"], q["nt"], q["ranges"], q["features"] // 64) == (mt, nt, ranges, steps), (shape, q)
         assert shape[3] // 64 - (ranges - 1) * steps == last, shape
+        assert (q["placed"], q["rotated"]) == (placed, rotated), (shape, q)
