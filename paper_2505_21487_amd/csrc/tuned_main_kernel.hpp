@@ -279,12 +279,13 @@ __global__ __launch_bounds__(64 * NG * WPG * KS) void tuned_main_kernel(DevParam
   };
 
   // Prepare the loads of the next tile into `stage`.  Once every tile of the
-  // chunk has been issued the previous tile's addresses are kept: the loads
+  // chunk has been issued the last tile's addresses stay (pages of 16 tokens
+  // and more: the cursor stands still and they are worked out again): the loads
   // then re-read lines that are still in L2 into a stage nobody reads, which
   // keeps the steady-state loop free of branches around the load instructions.
-  // The preparation is scalar work (some thirty instructions).  It is cut in
-  // three pieces so that the tile loop can place them between value MFMAs
-  // instead of running them in one stretch with the matrix pipe idle.
+  // The preparation is scalar work.  It is cut in three pieces so that the tile
+  // loop can place them between value MFMAs instead of running them in one
+  // stretch with the matrix pipe idle.
   bool prep_active = false;
   unsigned prep_page_idx = 0;
   // Pages of 16 tokens and more: the tiles ahead form runs inside one unit whose page ids the lanes of pt_vec hold; what
@@ -293,7 +294,6 @@ __global__ __launch_bounds__(64 * NG * WPG * KS) void tuned_main_kernel(DevParam
   // of them executed; what bounds the kernel on many rows is a wave's issue).  us per call with that and with it in runs, and
   // with loads of 32-bit offsets (load_lds_b128): GLA-2 two query positions 37 ragged sequences, pages of 16, 98.6 / 94.9; 64 x
   // 8192 119.2 / 116.7; MLA shape 15 x 1024 and 1 x 65536 53.8 / 52.8, three positions 40 x 500 to 3000, pages of 32, 110 / 103.
-  // Behind the chunk's last tile the cursor stands still.
   int run_left = 0, run_step = 1;                      // tiles left in the run; 0 once the chunk has been requested
   const unsigned char* run_s = nullptr;                // state cache + the unit's group + this wave's first row
   int run_last_page = 0;                               // last page the sequence holds
@@ -523,16 +523,11 @@ __global__ __launch_bounds__(64 * NG * WPG * KS) void tuned_main_kernel(DevParam
   // cacheable, since the next decode step reads it again.  (A compile-time choice: a branch on every
   // load cost the issue-bound variants 1-3 %.)
   // (the RoPE-key tile, a ninth of the bytes and the part that group blocks of a sequence share, stays cacheable)
-  auto rope_dma = [&](auto immc, const unsigned char* src, unsigned char* dst) {
-    constexpr int imm = decltype(immc)::value;
-    __builtin_amdgcn_global_load_lds((global_cvoid_t*)src, (lds_void_t*)dst, 16, imm, 0);
+  auto rope_dma = [&](const unsigned char* src, unsigned char* dst) {
+    __builtin_amdgcn_global_load_lds((global_cvoid_t*)src, (lds_void_t*)dst, 16, 0, 0);
   };
-  auto tile_dma = [&](auto immc, const unsigned char* src, unsigned char* dst) {
-    constexpr int imm = decltype(immc)::value;
-    if constexpr (STREAM)
-      __builtin_amdgcn_global_load_lds((global_cvoid_t*)src, (lds_void_t*)dst, 16, imm, 2);
-    else
-      __builtin_amdgcn_global_load_lds((global_cvoid_t*)src, (lds_void_t*)dst, 16, imm, 0);
+  auto tile_dma = [&](const unsigned char* src, unsigned char* dst) {
+    __builtin_amdgcn_global_load_lds((global_cvoid_t*)src, (lds_void_t*)dst, 16, 0, STREAM ? 2 : 0);
   };
   // i-th of this wave's LPW loads of the prepared tile
   auto dma_load = [&](auto ic) {
@@ -545,13 +540,13 @@ __global__ __launch_bounds__(64 * NG * WPG * KS) void tuned_main_kernel(DevParam
         const unsigned rho = (unsigned)((wpos * SLW + i) * RPL + s_rl);
         const unsigned off = (rho & dma_pmask) * ROWB + (voff & (ROWB - 1));
         const unsigned char* src = state_w + ((uint64_t)(uint32_t)pg_s[i] * st_page_bytes + dma_goff + off);
-        tile_dma(std::integral_constant<int, 0>{}, src, dma_ls + i * 1024);
+        tile_dma(src, dma_ls + i * 1024);
       } else {
         constexpr int ir = i - SLW;
         const unsigned rho = (unsigned)((wave * RLW + ir) * 8 + r_rl);
         const unsigned off = (rho & dma_pmask) * rrb + (r_voff[ir & 1] - (unsigned)r_rl * rrb);
         const unsigned char* src = rope_w + ((uint64_t)(uint32_t)pg_r[ir] * rp_page_bytes + off);
-        rope_dma(std::integral_constant<int, 0>{}, src, dma_lr + ir * 1024);
+        rope_dma(src, dma_lr + ir * 1024);
       }
     } else if constexpr (i < SLW) {
       const unsigned voff = s_lane_w ^ ((unsigned)swz16(i * RPL) << 4);
