@@ -61,17 +61,19 @@ inline int proj_plan(const gla_proj_params* p, int sum_groups, int cus, int smal
     if ((p->rows <= 64 || small < 2) && proj_cut_64(p, mt, cus, &ks, &per)) plan->nt = 2;
   } else {
     // More than 64 rows.  128 rows per workgroup halve the passes over the weights (two latent heads x 5120 x 16384, 100
-    // rows: 115 us with 64 rows per workgroup, 72 with 128; 128 heads x 512 x 128, 100 rows: 16.1 -> 12.7), but double the
-    // partials per range and compute what pads the last 128 rows.  Taken
+    // rows: 83 us with 64 rows per workgroup, 73 with 128), but double the partials per range and compute what pads the last 128 rows.
+    // The lines were drawn with workgroups in plain order.  us in the present one, the other way / the way taken (some have
+    // moved: where the first figure is the smaller one the line now lies on the wrong side of the shape).  128 rows are taken
     //   up to 128 rows, but weights of less than 128 MB only where the number of blocks of 256 features is no multiple of
-    //   eight: else the workgroups of the two 64-row tiles run on one XCD and share the weights through its L2 (2 x 5120 x 4096,
-    //   65 rows: 34.2 -> 28.0, 3 x 1024 x 10752 33.3 -> 29.4; 2 x 2048 x 8192 24.2 -> 27.1, 6144 x 8192 30.2 -> 31.5);
+    //   eight.  (Else the workgroups of the two 64-row tiles of a block met on one XCD and shared the weights through its L2; placed,
+    //   they do with any number.)  2 x 2048 x 8192, 100 rows 27.4 / 23.7, 6144 x 8192 32.5 / 31.1; but 2 x 5120 x 4096 28.2 / 30.3, 3 x
+    //   1024 x 10752 25.9 / 30.0.  2 x 8192 x 8192, 100 rows 64.4 / 59.3;
     //   for sums of one range (and more than 128 output features, else half a workgroup has nothing to do) up to 256 rows,
-    //   where 64 rows would pad about as much (128 heads x 256 x 128: 200 rows 15.3 -> 13.1, 160 rows 11.8 -> 13.1; 32 heads x 512
-    //   x 128: 300 rows 9.0 -> 10.6);
+    //   where 64 rows would pad about as much (128 heads x 256 x 128: 200 rows 11.7 / 11.7, 160 rows 10.9 / 9.5; 128 x 512 x 128, 100
+    //   rows 12.5 / 12.3; 32 x 512 x 128, 300 rows 10.3 / 9.4);
     //   for longer sums beyond 128 rows in ranges of at least 1280 features where 64 rows would pad about as much, or where the
-    //   weights are as large as the last-level cache (2 x 5120 x 8192: 256 rows 88 -> 73; 1 x 5120 x 4096, ranges of 704: 256 rows
-    //   28.0 -> 31.1, 129 rows 23.8 -> 28.5; 2 x 8192 x 8192: 129 rows 107 -> 92).
+    //   weights are as large as the last-level cache (2 x 5120 x 8192: 256 rows 85 / 66, but 300 rows 85 / 98; 1 x 5120 x 4096,
+    //   ranges of 704: 256 rows 29.5 / 27.1, 129 rows 26.2 / 21.3; 2 x 8192 x 8192: 129 rows 97.7 / 86.9).
     const bool single = p->k < 1024, as_full = 20 * tiles64 >= 36 * tiles128;  // (nine tenths of the 128-row tiles' halves have rows)
     int ranges, features;
     const bool cut4 = proj_cut_64(p, 4, cus, &ranges, &features);
@@ -79,11 +81,11 @@ inline int proj_plan(const gla_proj_params* p, int sum_groups, int cus, int smal
     if (single) rows4 = as_full && p->rows <= 256 && p->n > 128;
     else if (p->rows <= 128) rows4 = (p->n + 255) / 256 % 8 != 0 || weights >= kProjCacheBytes / 2;
     else rows4 = features >= 1280 && (as_full || weights >= kProjCacheBytes);
-    // Else 64 rows with 64 features per wave, but not in short ranges (1 x 2048 x 8192, 65 rows, ranges of 512: 17.8 us, 15.7
-    // with 32 features per wave; 1 x 5120 x 4096, of 704: 22.3, 21.5; 129 rows, of 1024: 23.8, 22.1, 2 x 2048 x 8192, of 1664: 31.8,
-    // 32.4) nor, beyond 128 rows, where 128 rows per workgroup do not fill the chip (4 x 5120 x 8192, 167 rows 126, 117); for sums
-    // of one range only with one block of 256 features per group, up to 128 rows (100 rows of 128 heads x 256 x 128 8.8, 9.3,
-    // of 64 x 512 x 128 9.1, 8.7, 122 rows of 128 x 128 x 192 6.7, 5.7; 64 heads x 256 x 128, 200 rows 8.6, 8.0).
+    // Else 64 rows with 64 features per wave, but not in short ranges (1 x 2048 x 8192, 65 rows, ranges of 512: 16.0 / 14.2; 1 x
+    // 5120 x 4096, of 704: 18.4 / 20.8; 129 rows, of 1024: 21.4 / 21.3; 2 x 2048 x 8192, of 1664: 31.0 / 28.9) nor, beyond 128
+    // rows, where 128 rows per workgroup do not fill the chip (4 x 5120 x 8192, 167 rows 107 / 112); for sums of one range only with
+    // one block of 256 features per group, up to 128 rows (100 rows of 128 heads x 256 x 128 7.15 / 7.5, of 64 x 512 x 128 7.5 / 7.15,
+    // 122 rows of 128 x 128 x 192 6.7 / 5.6; 64 heads x 256 x 128, 200 rows 7.5 / 7.05).
     if (cut4 && rows4) {
       plan->mt = 4;
       plan->nt = 2;
@@ -114,10 +116,10 @@ inline int proj_plan(const gla_proj_params* p, int sum_groups, int cus, int smal
   plan->ksplit = ks;
   // Weights read once, by one row tile, that would take more than half of the last-level cache and are not there any more
   // at the next step, after everything else a decode step reads: their lines then do not displace query rows and partials
-  // (335 MB 74.6 -> 66.9 us, 671 MB 153.5 -> 134.8, 201 MB 48.2 -> 45.8, 168 MB 42.4 -> 40.4).  A program that does nothing else
-  // between two calls with the same weights loses by it where the cache can hold them (201 MB 40.7 -> 45.7, 168 MB 37.1 -> 41.7,
-  // 268 MB 55 -> 79).  Smaller ones may still be there (84 MB 19.1 -> 21.2), and with two row tiles the second reader finds
-  // less (115.7 -> 130.0).
+  // (64 rows, without / with the hint: 335 MB 66.7 / 60.7 us, 671 MB 125 / 108, 168 to 268 MB +-1.5 %; 16 rows: 168 MB 34.2 / 32.3, 199 MB
+  // 39.5 / 37.3, 268 MB 50.1 / 46.9).  A program that does nothing else between two calls with the same weights loses by it where
+  // the cache can hold them (64 rows: 199 MB 39.6 / 44.5, 168 MB 37.1 / 39.0, 268 MB 50.5 / 52.5; 16 rows gain also then).
+  // Smaller ones may still be there (84 MB 24.8 / 27.7).  With two row tiles it hardly matters (335 MB, 129 rows 108.9 / 108.6).
   plan->stream = plan->nt == 2 && row_tiles == 1 && weights > kProjCacheBytes / 2;
   // Placement and start offsets (what they are for: proj_kernel).  us in plain order / this way, weights not in the caches:
   //   64 features per wave, ranges of 512 features and more: placed (64 rows of 2 x 5120 x 16384 70.1 / 60.7, both with offsets,
@@ -142,7 +144,8 @@ inline int proj_plan(const gla_proj_params* p, int sum_groups, int cus, int smal
   //   33 to 64 rows: one round of workgroups with long ranges (1 x 1024 x 16384, 64 rows 15.7 / 14.2; 2 x 16384 x 512 11.9 / 11.6),
   //   not short sums (128 x 256 x 128, 64 rows 5.37 / 5.55), few weights (2 x 4096 x 1024 9.2 / 9.5) nor several rounds (8 x
   //   5120 x 2048 39.6 / 42.9).
-  const int64_t blocks = (p->n + 128 * plan->nt - 1) / (128 * plan->nt), slices = (int64_t)p->groups * ks, list = blocks * row_tiles * slices;
+  const int64_t blocks = (p->n + 128 * plan->nt - 1) / (128 * plan->nt), slices = (int64_t)p->groups * ks;
+  const int64_t list = blocks * row_tiles * slices;
   const int64_t l2s = 32ll << 20;
   if (plan->nt == 2 && plan->k_per_split >= 512) {
     const bool alike = p->groups >= 32 && p->k >= 8192 && weights >= 2 * kProjCacheBytes;
