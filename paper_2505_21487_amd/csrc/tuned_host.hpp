@@ -69,8 +69,8 @@ constexpr int kShortChunkBatch = 8;
 // launched.  It wins where the matrix pipe sets the pace and chunks are long; it starts a chunk and a sequence more slowly
 // (twice the tokens per tile, queries loaded by twice the waves).  What counts is therefore the real number of tiles per
 // chunk t and of sequences' parts per chunk, 1 + u, which only the device knows: both kernels are launched, both count,
-// and the one that is not meant leaves (0.1 to 1 us per call).  Measured, four waves -> eight waves, us per call, tiles of
-// 64 tokens (t, u):
+// and the one that is not meant leaves (0.1 to 1 us per call).  Measured when the line was drawn, four waves -> eight waves, us per
+// call, tiles of 64 tokens (t, u):
 //   512 dims, 128 rows, pages of 64: (63, 1) 206 -> 185, (75, 2.3) 269 -> 259, (32, 1) 118 -> 108, (31, 0.1) 116 -> 115,
 //     (16, 0) 65 -> 63, (16, 0.1) 73 -> 76, (64, 4) 243 -> 245, (16, 4) 104 -> 120, (32, 8) 207 -> 225, (4, 0) 35 -> 39
 //   ... pages of 1: (16, 0.5) 91 -> 71, (16, 1) 79 -> 66, (8, 0.5) 53 -> 51, (4, 1) 35 -> 35, (16, 8) 190 -> 187
@@ -78,6 +78,12 @@ constexpr int kShortChunkBatch = 8;
 //     (63, 1) 176 -> 171, (63, 0.5) 178 -> 184, (31, 0.3) 103 -> 110, (64, 2) 185 -> 186, (117, 4.7) 369 -> 381
 //   ... pages of 1: (32, 1) 108 -> 96, (32, 2) 123 -> 114, (31, 0.3) 116 -> 112, (16, 0.3) 75 -> 78, (16, 8) 178 -> 183
 // With 128 rows and 256 dims (no second row block to share the tiles with) it loses, 117 -> 123.
+// That was before the four-wave kernel's tiles came in runs, and with sequences of equal length.  Now, pages of 64: 512 dims (16, 0)
+// 75 -> 81, (40, 0) 155 -> 156, (64, 0) 217 -> 207, (24, 0.5) 91 -> 101, (38, 0.5) 135 -> 155, (60, 0.5) 208 -> 199, (32, 1) 120 -> 118,
+// (54, 2.3) 212 -> 234, (136, 2.3) 452 -> 456, (216, 2.3) 684 -> 669; ragged (62, 0.5) 213 -> 223, (99, 0.5) 320 -> 313, (49, 1) 181 ->
+// 196, (121, 1) 392 -> 392; 256 dims (80, 0) 214 -> 216, (201, 0) 489 -> 479, (82, 0.1) 213 -> 227, (206, 0.1) 504 -> 489, (90, 0.5) 232
+// -> 234, (225, 0.5) 543 -> 529, (160, 1) 391 -> 387; ragged (165, 1) 416 -> 433, (372, 0.1) 889 -> 871.  The line below is right for
+// long chunks but about half as high as it should be: batches up to twice above it lose up to 15 % (512 dims) and 7 % (256 dims).
 inline int wide_tiles_of(const gla_decode_params* p, const TunedPlan& plan) {
   if (!eight_wave_shape(p->d_v, plan.ng, plan.wpg, plan.ks) || (p->d_v == 256 && plan.mb == 1)) return 0;
   const bool small_pages = p->page_size < 16;
