@@ -107,15 +107,15 @@ def check_register_windows(verbose: bool = True) -> list:
     return found
 
 
-def device_code(lib: str = LIB) -> str:
-    """Disassembly of the built library's device code object."""
+def device_code(lib: str = LIB, tool=("llvm-objdump", "-d", "--no-show-raw-insn")) -> str:
+    """Disassembly of the built library's device code object, or what another tool prints of it."""
     llvm = os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "llvm", "bin")
     with tempfile.TemporaryDirectory() as tmp:
         fat, obj = os.path.join(tmp, "fat"), os.path.join(tmp, "gfx950.o")
         subprocess.check_call([os.path.join(llvm, "llvm-objcopy"), "--dump-section", ".hip_fatbin=" + fat, lib, os.devnull])
         subprocess.check_call([os.path.join(llvm, "clang-offload-bundler"), "--unbundle", "--type=o", "--input=" + fat,
                                "--targets=hipv4-amdgcn-amd-amdhsa--gfx950", "--output=" + obj])
-        return subprocess.check_output([os.path.join(llvm, "llvm-objdump"), "-d", "--no-show-raw-insn", obj], text=True)
+        return subprocess.check_output([os.path.join(llvm, tool[0]), *tool[1:], obj], text=True)
 
 
 # tuned_main_kernel<DV, DN, DR, NG, WPG, KS, TOK, STAGES, PM, STREAM> in page modes 0 and 1

@@ -583,7 +583,7 @@ int run_proj(const gla_proj_params* p, int sum_groups) {
   d.by_tiles = proj_reciprocal(tiles);
   d.by_blocks = proj_reciprocal(blocks);
   d.by_ksplit = proj_reciprocal((uint32_t)plan.ksplit);
-  d.start = plan.rotated ? d.by_blocks : 0;
+  d.rotated = plan.rotated ? 1 : 0;
   if (plan.nt == 2) {
     if (plan.mt == 1) launch_proj_long<1>(plan.stream, grid, st, d);
     else if (plan.mt == 2) launch_proj_long<2>(plan.stream, grid, st, d);

@@ -45,7 +45,8 @@ typedef __attribute__((ext_vector_type(8))) __bf16 proj_bf16x8_t;
 typedef __attribute__((ext_vector_type(16))) float proj_f32x16_t;
 typedef __attribute__((ext_vector_type(4))) float proj_f32x4_t;
 
-// (124 bytes, the runtime's share left out: two cache lines that a workgroup waits for first)
+// No more than 112 bytes: a launch with a larger parameter block takes the host longer (an empty kernel, launched again and again:
+// 56 to 112 bytes 2.9 to 3.0 us per launch, 120 bytes and more 3.7 to 3.9).
 struct ProjParams {
   const uint16_t* a;
   const uint16_t* w;
@@ -55,13 +56,13 @@ struct ProjParams {
   int64_t c_row, c_group;  // element strides of C
   int32_t M, N, K;
   int32_t ksplit, k_per_split;
-  int16_t sum_groups, c_fp32, direct, pad;
+  uint8_t sum_groups, c_fp32, direct;
+  uint8_t rotated;                          // blocks of features start at different steps
   uint32_t total;                           // > 0: a grid of that many workgroups, placed by the kernel; 0: (blocks, row tiles, slices)
   uint32_t tiles, blocks;                   // row tiles, blocks of output features
   uint32_t by_tiles, by_blocks, by_ksplit;  // reciprocals, see proj_div
-  uint32_t start;                           // blocks start at different steps: the reciprocal of their number; else 0
 };
-static_assert(sizeof(ProjParams) <= 128, "two cache lines");
+static_assert(sizeof(ProjParams) <= 112, "larger parameter blocks are slower to launch");
 
 // n / d for n and d below 2^16 as the upper half of n * m, m = ceil(2^32 / d) (0 for d = 1): exact, since n * (m d - 2^32) < 2^32.
 // Larger grids divide.
@@ -85,7 +86,7 @@ __global__ __launch_bounds__(256) void proj_kernel(ProjParams p) {
   // x 128, one row 5.99 -> 5.86 us).  Nothing to gain where there is no branch, nor with 128 rows.
   if constexpr (kPlaced && MT < 4)
     asm volatile("" ::"s"(p.a), "s"(p.w), "s"(p.a_row), "s"(p.a_group), "s"(p.M), "s"(p.N), "s"(p.K), "s"(p.ksplit), "s"(p.k_per_split),
-                 "s"(p.total), "s"(p.tiles), "s"(p.blocks), "s"(p.by_tiles), "s"(p.by_blocks), "s"(p.by_ksplit), "s"(p.start));
+                 "s"(p.total), "s"(p.tiles), "s"(p.blocks), "s"(p.by_tiles), "s"(p.by_blocks), "s"(p.by_ksplit), "s"((int)p.rotated));
   unsigned bx = blockIdx.x, tile = blockIdx.y, bz = blockIdx.z;
   if (kPlaced && p.total > 0) {
     const unsigned total = p.total, xcd = blockIdx.x & 7;
@@ -154,7 +155,7 @@ __global__ __launch_bounds__(256) void proj_kernel(ProjParams p) {
   // In step they would all read the same columns of rows that lie a power of two or so apart, hence through few of the memory
   // channels at a time.  A kernel that only loads, in this order, with and without the offsets: 335 MB (2 x 5120 x 16384) 50.5 /
   // 53.3 us, 268 MB (2 x 8192 x 8192) 41.2 / 64.8; this one on the first, 64 rows, placed 60.7 / 73.5.
-  const int steps = (k_end - k_begin) >> 6, first = kPlaced ? (int)__umulhi(bx * p.start, (unsigned)steps) : 0;
+  const int steps = (k_end - k_begin) >> 6, first = kPlaced && p.rotated ? (int)__umulhi(bx * p.by_blocks, (unsigned)steps) : 0;
   auto feature = [&](int i) {  // first input feature of step i (steps past the end fetch the last one again)
     const int j = min(i, steps - 1) + first;
     return k_begin + 64 * (!kPlaced || j < steps ? j : j - steps);

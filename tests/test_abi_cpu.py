@@ -252,6 +252,16 @@ def test_uniform_loads_of_the_library():
     assert len(build.check_uniform_loads(build.device_code())) == 52
 
 
+def test_parameter_blocks_of_the_projections_stay_small():
+    """A launch with more than 112 bytes of parameters takes the host up to a microsecond longer, a quarter of the smallest calls."""
+    from paper_2505_21487_amd import build
+
+    gla.load_library()
+    kernels = build.device_code(tool=("llvm-readelf", "--notes")).split("- .agpr_count:")[1:]
+    sizes = [int(re.search(r"\.kernarg_segment_size: +(\d+)", k).group(1)) for k in kernels if re.search(r"\.name: +\S*proj_kernel", k)]
+    assert len(sizes) == 8 and max(sizes) <= 112, sizes
+
+
 def test_bench_refuses_more_than_one_gpu():
     """One GPU only: `bench.py --gpus N` with N above 1 (or a WORLD_SIZE above 1) exits with a message that says
     so, before anything touches a GPU."""
