@@ -290,8 +290,8 @@ __global__ __launch_bounds__(64 * NG * WPG * KS) void tuned_main_kernel(DevParam
   unsigned prep_page_idx = 0;
   // Pages of 16 tokens and more: the tiles ahead form runs inside one unit whose page ids the lanes of pt_vec hold; what
   // depends on unit and page table is done where a run begins, what is left per tile is a page id and its product with the
-  // page's bytes for every load group (some 100 instructions per tile fewer in the code than working it all out each time, 40
-  // of them executed; what bounds the kernel on many rows is a wave's issue).  us per call with that and with it in runs, and
+  // page's bytes for every load group (some 100 instructions per tile fewer in the code than working it all out each time; executed,
+  // 30 fewer with pages of 16, 19 with 64; what bounds the kernel on many rows is a wave's issue).  us per call with that and with it in runs, and
   // with loads of 32-bit offsets (load_lds_b128): GLA-2 two query positions 37 ragged sequences, pages of 16, 98.6 / 94.9; 64 x
   // 8192 119.2 / 116.7; MLA shape 15 x 1024 and 1 x 65536 53.8 / 52.8, three positions 40 x 500 to 3000, pages of 32, 110 / 103.
   int run_left = 0, run_step = 1;                      // tiles left in the run; 0 once the chunk has been requested
